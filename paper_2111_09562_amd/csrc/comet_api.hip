@@ -75,6 +75,7 @@ struct comet_ctx {
     uint32_t *rec_stage = nullptr;   // row-walking quantise kernel: staging area of every run's outlier records
     uint32_t *run_count = nullptr;   //   and per run: record count, non-zero inputs, verbatim records
     uint64_t max_runs = 0;
+    uint64_t stage_bytes = 0;        // size of rec_stage, which also holds the band sums of a decompression
     uint64_t *enc = nullptr;
     BookScratch book{};
     DecodeTables tables{};
@@ -173,6 +174,39 @@ bool recon_geometry(comet_shape s, ReconGeometry *g) {
     }
     g->lds = (size_t)g->tile_rows * g->pitch * 4u + (g->use_carry ? (size_t)s.w * 4u : 0u);
     return g->lds <= 96u * 1024u;
+}
+
+// Reconstruction in bands (k_band_*): columns per lane, rows per band, segments per row, bands per plane, units, and
+// the offsets of the three arrays of sums inside their workspace of `bytes` bytes.
+struct BandGeom { uint32_t vec, R, segs, bands; uint64_t n_units, off_row, off_unit, bytes; };
+// About 2^19 * 64 elements or more: bands of 64 rows; smaller tensors: fewer rows, so that there are enough units to
+// fill the chip (a unit has 128 columns at most; 2^19 / 128 = 4096 units, four per SIMD).
+BandGeom band_geometry(comet_shape s, uint64_t n, uint32_t vec) {
+    BandGeom g{};
+    g.vec = vec;
+    const uint32_t seg_w = (uint32_t)kWave * vec;
+    g.segs = (s.w + seg_w - 1u) / seg_w;
+    uint64_t R = n >> 19;
+    if (R < kBandRowsMin) R = kBandRowsMin;
+    if (R > kBandRowsMax) R = kBandRowsMax;
+    g.bands = (uint32_t)((s.h + R - 1u) / R);
+    g.R = (s.h + g.bands - 1u) / g.bands;
+    g.bands = (s.h + g.R - 1u) / g.R;
+    const uint64_t pb = (uint64_t)s.n * s.c * g.bands;
+    g.n_units = pb * g.segs;
+    g.off_row = g.bands > 1u ? align_up(4ull * pb * s.w, 256) : 0u;           // (one band per plane: no column sums)
+    g.off_unit = g.off_row + (g.segs > 1u ? align_up(4ull * g.n_units * g.R, 256) : 0u);
+    g.bytes = g.off_unit + align_up(4ull * g.n_units, 256);
+    return g;
+}
+constexpr uint32_t kBandMinW = 128;     // narrower planes leave lanes of a unit idle (and a workgroup of k_decode_scan shares a plane)
+// What the sums of any tensor of up to n elements take, planes of at least kBandMinW columns: a column sum per
+// R / 2 or more elements (R: rows per band as above; 8n / R is below 4.7 MB until R reaches its limit of 64), a row sum
+// per 43 (129 columns, one per lane, three segments) times three halves (the rows of a plane's bands are at most half
+// as many again as its own), a unit sum per row sum at the most.
+constexpr uint64_t band_bytes_max(uint64_t n) {
+    const uint64_t col = n < (8ull << 20) ? n : (n / 8u > (8ull << 20) ? n / 8u : (8ull << 20));
+    return col + 4u * (n / 32u + n / 128u) + 4u * (n / 40u) + 8192u;
 }
 
 int fused_opt_in();          // k_decode_scan: opt in to its dynamic LDS size (defined with the decompression)
@@ -453,7 +487,9 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     if ((e = hipMalloc((void **)&c->enc, 8ull * kMaxBins)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     if ((e = hipMalloc((void **)&c->stats, 8ull * (kStatsPartialMax + 1u))) != hipSuccess) return fail(COMET_ERR_NOMEM);
     c->max_runs = (uint64_t)c->num_cu * 4u * kQuantRunsPerSimd + 8u;
-    if ((e = hipMalloc((void **)&c->rec_stage, c->max_runs * kQuantRecRun * 8ull)) != hipSuccess) return fail(COMET_ERR_NOMEM);
+    c->stage_bytes = c->max_runs * kQuantRecRun * 8ull;
+    if (c->stage_bytes < band_bytes_max(max_elems)) c->stage_bytes = band_bytes_max(max_elems);
+    if ((e = hipMalloc((void **)&c->rec_stage, c->stage_bytes)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     // (a fourth array of one entry per run: the words of every run of the single-pass compression)
     if ((e = hipMalloc((void **)&c->run_count, 4ull * c->max_runs * 4ull)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     {
@@ -657,6 +693,8 @@ struct DecompWs {
     DecodeTables tables;
     int16_t *resid;            // one int16 per element, max_elems of them
     uint64_t max_elems;
+    uint8_t *band;             // sums of the reconstruction in bands
+    uint64_t band_bytes;
     int num_cu;
     uint32_t chunk_syms;       // chunk size the launch geometry is estimated with
     comet_ctx *prof;           // per-kernel timing, or null
@@ -666,6 +704,7 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
 DecompWs ctx_ws(comet_ctx *ctx) {
     DecompWs ws{};
     ws.state = ctx->state; ws.tables = ctx->tables; ws.resid = reinterpret_cast<int16_t *>(ctx->codes);
+    ws.band = reinterpret_cast<uint8_t *>(ctx->rec_stage); ws.band_bytes = ctx->stage_bytes;
     ws.max_elems = ctx->max_elems; ws.num_cu = ctx->num_cu; ws.chunk_syms = ctx->chunk_syms; ws.prof = ctx; ws.dev_status = nullptr;
     return ws;
 }
@@ -742,6 +781,50 @@ FusedGeom fused_geometry(int num_cu, comet_shape s) {
     return f;
 }
 
+// Huffman decode of a whole container into int16 residuals.
+void launch_decode_chunks(const DecompWs &ws, const DsArgs &d, hipStream_t st) {
+    // groups of 64 chunks, one per wavefront at a time; the same number of groups for every
+    // wavefront of a grid that is resident at once (estimated with the context's chunk size)
+    const uint64_t groups = (d.n + (uint64_t)ws.chunk_syms * kWave - 1) / ((uint64_t)ws.chunk_syms * kWave);
+    const uint64_t resident = (uint64_t)ws.num_cu * 4u * kDsWaves;
+    const uint64_t per_wave = (groups + resident - 1) / resident;
+    const uint64_t waves = (groups + per_wave - 1) / per_wave;
+    const uint32_t grid = (uint32_t)((waves + kDsWaves - 1) / kDsWaves);
+    TimedScope ts(ws.prof, st, COMET_KERNEL_DECODE);
+    hipLaunchKernelGGL(k_decode_chunks, dim3(grid), dim3(kDsBlock), (size_t)kDsWaves * kDsStageWords * 4u, st, d);
+}
+
+// Planes of at most 512 columns: is the reconstruction in bands quicker than the kernels with a plane per wavefront or
+// workgroup?  Those take as long as their longest serial chain (or as the elements take, for many planes); the bands
+// have no chain, and move more bytes.  Estimates in us from measurements (old kernel / bands):
+//   k_decode_scan, a plane per wavefront (10 us a strip of 4032 elements, 20 with one column per lane):
+//     4 planes of 512 x 512 672 / 48, 64 721 / 91, 1024 848 / 991; 256 planes of 257 x 257 361 / 99, 1024 452 / 340, 4096 757 / 1260
+//   k_decode_scan, a plane's strips dealt to the sixteen wavefronts of a workgroup (20 us a round):
+//     8 planes of 3000 x 256 265 / 84, 32 of 256 x 256 45 / 51, 512 of them 75 / 127
+//   k_scan_store (a plane per wavefront, 0.25 us a row and 0.06 more per 64 lanes of it; 1.3 us per million elements,
+//   2 if a row takes more than 128 lanes), chunks of 128 symbols:
+//     16 planes of 224 x 224 107 / 52, 4096 of them 664 / 767, 1024 of 512 x 512 1086 / 955, 4096 of 257 x 257 973 / 1227
+bool band_pays(int num_cu, comet_shape s, uint64_t n, bool chunk64, uint32_t vec) {
+    const uint64_t planes = (uint64_t)s.n * s.c, P = (uint64_t)s.h * s.w;
+    const uint32_t lpr = s.w / vec;
+    const double mega = (double)n * 1e-6;
+    if (!chunk64) {                                          // (the decoding itself is the same kernel on both sides)
+        const double row = 0.25 + 0.06 * (double)((lpr + 63u) / 64u);
+        const uint64_t waves = (uint64_t)num_cu * 32u;
+        const double chain = row * (double)s.h * (double)((planes + waves - 1u) / waves);
+        const double flow = (lpr <= 128u ? 1.3 : 2.0) * mega;
+        return 30.0 + (vec == 2u ? 1.7 : 2.6) * mega < (chain > flow ? chain : flow);
+    }
+    const double bands = 45.0 + (vec == 2u ? 3.6 : 4.5) * mega;
+    const uint64_t strip = 4032u / s.w * s.w, strips = (P + strip - 1u) / strip;
+    if (lpr <= 128u) {
+        const uint64_t seg_planes = (planes + (uint64_t)num_cu - 1u) / (uint64_t)num_cu;
+        return bands < 20.0 * (double)((seg_planes * strips + (uint64_t)kFuWaves - 1u) / (uint64_t)kFuWaves);
+    }
+    const uint64_t waves = (uint64_t)num_cu * kFuWaves;
+    return bands < (vec == 2u ? 10.0 : 20.0) * (double)(strips * ((planes + waves - 1u) / waves));
+}
+
 int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, comet_shape s, void *stream, void *dev_out, int out_type) {
     uint64_t n;
     if (!dev_in || !dev_out || !shape_elems(s, &n) || s.w > kMaxW || ((uintptr_t)dev_in & 15u)) return COMET_ERR_INVALID;
@@ -757,18 +840,22 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
     const uint32_t vec = ((s.w & 1u) == 0u && ((uintptr_t)dev_out & (2u * out_elem - 1u)) == 0u) ? 2u : 1u;
     const uint32_t lpr = s.w / vec;
     const uint32_t ppi = lpr <= 16u ? 4u * (16u / lpr) : (lpr <= 32u ? 2u : 1u);
+    // (buffer offsets: a strip of whole rows, or the planes side by side in a wavefront, stays below 2^28 elements)
     const bool fast_path = s.w <= kDsMaxW && (uint64_t)ppi * s.h * s.w < (1ull << 28);
+    const BandGeom bg = band_geometry(s, n, vec);
+    const bool bands = s.w >= kBandMinW && bg.bytes <= ws.band_bytes && bg.n_units < (1ull << 31) &&
+                       (!fast_path || band_pays(ws.num_cu, s, n, ws.chunk_syms == 64u, vec));
     if (out_type != 0 && !fast_path) return COMET_ERR_INVALID;       // 16-bit outputs: planes of at most kDsMaxW columns
     // Chunks of 64 symbols (what the caller's context compresses with tells what to expect) go through the
     // single fused kernel; it leaves a container with another chunk size alone, and the kernels launched
     // behind it, which take any chunk size, leave one with 64 alone.
-    const bool fused = fast_path && ws.chunk_syms == 64u;
+    const bool fused = fast_path && !bands && ws.chunk_syms == 64u;
     {
         TablesArgs t{};
         t.len = in + kHeaderBytes; t.nbins = 0; t.t = ws.tables; t.ctl = &ws.state->ctl;
         t.hdr = reinterpret_cast<const Header *>(in);
         t.expect.N = s.n; t.expect.C = s.c; t.expect.H = s.h; t.expect.W = s.w; t.bytes = bytes;
-        t.compact_only = fast_path ? 1u : 0u;
+        t.compact_only = (fast_path || bands) ? 1u : 0u;
         t.general_unless_chunk64 = (fused && out_type == 0) ? 1u : 0u;   // the kernel behind k_decode_scan reads the general table
         // the only kernel of a decompression that raises status bits: it clears the call's control block itself
         // and latches what it raises, so the call needs neither a fill before nor a kernel after
@@ -813,6 +900,36 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
         const uint32_t cap = (uint32_t)ws.num_cu * 4u;
         if (grid > cap) grid = cap;
         hipLaunchKernelGGL(k_reconstruct<0>, dim3(grid), dim3(kDecBlock), g.lds, st, a);
+    } else if (bands) {
+        DsArgs d{};
+        d.container = in; d.t = ws.tables; d.n = n; d.planes = s.n * s.c; d.H = s.h; d.W = s.w;
+        d.resid = ws.resid; d.out = dev_out; d.ctl = &ws.state->ctl;
+        launch_decode_chunks(ws, d, st);
+        HIP_TRY(hipGetLastError());
+        BandArgs a{};
+        a.container = in; a.planes = s.n * s.c; a.H = s.h; a.W = s.w; a.R = bg.R;
+        a.divSegs = make_fastdiv(bg.segs); a.divBands = make_fastdiv(bg.bands); a.n_units = (uint32_t)bg.n_units;
+        a.resid = ws.resid;
+        a.col_sums = reinterpret_cast<int32_t *>(ws.band); a.row_sums = reinterpret_cast<int32_t *>(ws.band + bg.off_row);
+        a.unit_sums = reinterpret_cast<int32_t *>(ws.band + bg.off_unit);
+        a.out = dev_out; a.ctl = &ws.state->ctl;
+        const dim3 rec_grid((uint32_t)ws.num_cu), grid((uint32_t)((bg.n_units + kBandBlock / kWave - 1u) / (kBandBlock / kWave))), block(kBandBlock);
+        TimedScope ts(ws.prof, st, COMET_KERNEL_RECONSTRUCT);
+        hipLaunchKernelGGL(k_band_patch, rec_grid, block, 0, st, a);
+        if (bg.bands > 1u || bg.segs > 1u) {
+            if (vec == 2u) hipLaunchKernelGGL(k_band_sums<2>, grid, block, 0, st, a);
+            else hipLaunchKernelGGL(k_band_sums<1>, grid, block, 0, st, a);
+        }
+#define COMET_LAUNCH_BAND(OUT)                                                              \
+        do {                                                                                \
+            if (vec == 2u) hipLaunchKernelGGL((k_band_store<2, OUT>), grid, block, 0, st, a); \
+            else hipLaunchKernelGGL((k_band_store<1, OUT>), grid, block, 0, st, a);         \
+            hipLaunchKernelGGL(k_band_verbatim<OUT>, rec_grid, block, 0, st, a);            \
+        } while (0)
+        if (out_type == COMET_F16) COMET_LAUNCH_BAND(1);
+        else if (out_type == COMET_BF16) COMET_LAUNCH_BAND(2);
+        else COMET_LAUNCH_BAND(0);
+#undef COMET_LAUNCH_BAND
     } else if (fast_path) {
         // Huffman decode into int16 residuals (the code buffer of the context doubles as
         // the work buffer), then scans and stores
@@ -820,17 +937,7 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
         d.skip_chunk64 = fused ? 1u : 0u;
         d.container = in; d.t = ws.tables; d.n = n; d.planes = s.n * s.c; d.H = s.h; d.W = s.w; d.divW = make_fastdiv(s.w); d.divL = make_fastdiv(lpr);
         d.resid = ws.resid; d.out = dev_out; d.ctl = &ws.state->ctl;
-        {
-            // groups of 64 chunks, one per wavefront at a time; the same number of groups for every
-            // wavefront of a grid that is resident at once (estimated with the context's chunk size)
-            const uint64_t groups = (n + (uint64_t)ws.chunk_syms * kWave - 1) / ((uint64_t)ws.chunk_syms * kWave);
-            const uint64_t resident = (uint64_t)ws.num_cu * 4u * kDsWaves;
-            const uint64_t per_wave = (groups + resident - 1) / resident;
-            const uint64_t waves = (groups + per_wave - 1) / per_wave;
-            const uint32_t grid = (uint32_t)((waves + kDsWaves - 1) / kDsWaves);
-            TimedScope ts(ws.prof, st, COMET_KERNEL_DECODE);
-            hipLaunchKernelGGL(k_decode_chunks, dim3(grid), dim3(kDsBlock), (size_t)kDsWaves * kDsStageWords * 4u, st, d);
-        }
+        launch_decode_chunks(ws, d, st);
         HIP_TRY(hipGetLastError());
         // small planes: a unit of work is a group of whole planes, `passes` times the planes that sit side by
         // side in a wavefront: about kScanStripElems elements, fewer if that leaves the chip short of wavefronts
@@ -903,7 +1010,8 @@ constexpr size_t kSsLut16 = kSsLut + 4 * kLutSize;
 constexpr size_t kSsSub16 = kSsLut16 + 2 * kLut16Size;
 constexpr size_t kSsSorted = kSsSub16 + 2 * kSubEntries;
 constexpr size_t kSsResid = (kSsSorted + 2 * (size_t)kMaxBins + 255) / 256 * 256;
-constexpr size_t kSsBytes = kSsResid + 2 * (size_t)kStaticMaxElems + 256;
+constexpr size_t kSsBand = (kSsResid + 2 * (size_t)kStaticMaxElems + 256 + 255) / 256 * 256;
+constexpr size_t kSsBytes = kSsBand + (size_t)band_bytes_max(kStaticMaxElems);
 static_assert(sizeof(DevState) <= kSsLimit && kSsMeta % 16 == 0 && kSsLut % 16 == 0, "scratch layout");
 constexpr int kStaticMaxDevices = 64;
 struct StaticDev { void *ptr; int num_cu; };
@@ -964,6 +1072,7 @@ int comet_decompress_static(const void *dev_in, uint64_t bytes, comet_shape s, v
     ws.tables.sub16 = reinterpret_cast<uint16_t *>(base + kSsSub16);
     ws.tables.sorted = reinterpret_cast<uint16_t *>(base + kSsSorted);
     ws.resid = reinterpret_cast<int16_t *>(base + kSsResid);
+    ws.band = base + kSsBand; ws.band_bytes = kSsBytes - kSsBand;
     ws.max_elems = kStaticMaxElems; ws.num_cu = sd.num_cu; ws.chunk_syms = COMET_DEFAULT_CHUNK_SYMS;
     ws.prof = nullptr; ws.dev_status = dev_status;
     // Nothing in the array has to start at zero: the tables kernel clears the control block and stores

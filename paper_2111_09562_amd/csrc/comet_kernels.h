@@ -270,6 +270,29 @@ __global__ void k_decode_chunks(DsArgs a);
 // VEC: adjacent columns per lane (2: even W, output aligned to two elements); the lane mapping follows W / VEC
 template <int NSEG, int MODE, int OUT = 0, int VEC = 1> __global__ void k_scan_store(DsArgs a);
 
+// ---- reconstruct from the residuals of k_decode_chunks, planes cut into bands of rows and segments of columns -------
+constexpr int kBandBlock = 256;                       // four wavefronts, each on a unit of its own
+constexpr uint32_t kBandRowsMin = 8u, kBandRowsMax = 64u;   // rows of a unit (the upper limit: one lane per row)
+
+struct BandArgs {
+    const uint8_t *container;
+    uint32_t planes, H, W;
+    uint32_t R;                // rows per band (the last band of a plane may have fewer)
+    FastDiv divSegs;           // segments of 64 lanes per row (one or two columns per lane)
+    FastDiv divBands;          // bands per plane
+    uint32_t n_units;          // planes * bands * segments; segments of a band are neighbours, bands of a plane as well
+    int16_t *resid;            // work buffer: one int16 residual per element
+    int32_t *col_sums;         // [planes * bands][W]
+    int32_t *row_sums;         // [n_units][R]
+    int32_t *unit_sums;        // [n_units]
+    void *out;
+    Control *ctl;
+};
+__global__ void k_band_patch(BandArgs a);
+template <int VEC> __global__ void k_band_sums(BandArgs a);
+template <int VEC, int OUT> __global__ void k_band_store(BandArgs a);
+template <int OUT> __global__ void k_band_verbatim(BandArgs a);
+
 // ---- decode + reconstruct in one kernel (planes up to 512 columns, chunks of 64 symbols) ----------
 constexpr int kFuWaves = 16;                          // wavefronts per workgroup, each working on its own; one workgroup per CU
 constexpr int kFuBlock = kFuWaves * kWave;
