@@ -636,6 +636,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
 
     BookArgs b{};
     b.hist = hist; b.given_len = dev_len; b.nbins = nbins; b.len_out = out + proto.off_len; b.code_out = nullptr; b.enc = ctx->enc;
+    b.narrow = n < 0x7fffffffull ? 1u : 0u;
     b.scratch = ctx->book; b.ctl = &ctx->state->ctl; b.hdr = reinterpret_cast<Header *>(out); b.proto = proto; b.capacity = capacity;
     uint32_t *rec = reinterpret_cast<uint32_t *>(out + proto.off_outlier);
     const uint64_t rec_cap = (capacity - proto.off_outlier) / 8u;

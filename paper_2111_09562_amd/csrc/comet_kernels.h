@@ -95,6 +95,7 @@ struct BookArgs {
     uint64_t *enc;             // u64[nbins]: (code << 6) | len, 0 for unused symbols
     BookScratch scratch;
     uint32_t presorted;        // scratch.keys holds the leaves in (frequency, symbol) order (k_book_sort_tiles, k_book_merge) if more than kBookLdsSyms symbols occur
+    uint32_t narrow;           // all frequencies together are below 2^31 - 1 (a container's header only; a stage call looks for itself)
     Control *ctl;
     // container finalisation (null header = stage call)
     Header *hdr;

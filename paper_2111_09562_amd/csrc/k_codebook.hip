@@ -38,27 +38,110 @@ __device__ void bitonic_sort(uint64_t *keys, uint32_t n2) {
     }
 }
 
-// Ascending bitonic sort of one key per lane over the first n2 (power of two,
-// <= blockDim) lanes of the workgroup; keys stay in registers, partners closer
-// than a wavefront are reached by shuffles, the others through LDS.
-__device__ inline uint64_t bitonic_sort_regs(uint64_t key, uint64_t *s_x, uint32_t n2) {
-    const uint32_t i = threadIdx.x;
-    for (uint32_t k = 2; k <= n2; k <<= 1) {
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            uint64_t other;
-            if (j < (uint32_t)kWave) other = __shfl_xor(key, (int)j, kWave);
-            else {
-                s_x[i] = key;
-                __syncthreads();
-                other = s_x[i ^ j];
-                __syncthreads();
-            }
-            const bool keep_min = ((i & k) == 0) == ((i & j) == 0);
-            const uint64_t lo = key < other ? key : other, hi = key < other ? other : key;
-            key = keep_min ? lo : hi;
+// Value of lane (mine ^ J) of the wavefront, by data-parallel primitives (no LDS access): quad permutes, row
+// rotation, and for 16 and 32 the row and half swaps, whose two results are the values of both partners.
+template <int J> __device__ inline uint32_t lane_xor(uint32_t v) {
+    if (J == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);      // quad_perm:[1,0,3,2]
+    if (J == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);      // quad_perm:[2,3,0,1]
+    if (J == 4) {                                                                                   // ^3, then ^7
+        const int t = __builtin_amdgcn_update_dpp(0, (int)v, 0x1B, 0xf, 0xf, true);                 // quad_perm:[3,2,1,0]
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, t, 0x141, 0xf, 0xf, true);                  // row_half_mirror
+    }
+    if (J == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true);     // row_ror:8
+    if (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (lane_id() & 16) ? r[0] : r[1];
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (lane_id() & 32) ? r[0] : r[1];
+}
+template <int J> __device__ inline uint64_t lane_xor(uint64_t v) {
+    return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
+}
+// One comparison of a sorting network with the partner J lanes away.
+template <int J> __device__ inline uint64_t compare_exchange(uint64_t v, bool keep_min) {
+    const uint64_t o = lane_xor<J>(v);
+    return (v < o) == keep_min ? v : o;
+}
+// (32 bits: minimum, maximum and a selection by a mask that does not change, nothing through the scalar unit)
+template <int J> __device__ inline uint32_t compare_exchange(uint32_t v, bool keep_min) {
+    const uint32_t o = lane_xor<J>(v);
+    const uint32_t lo = v < o ? v : o, hi = v < o ? o : v;
+    return keep_min ? lo : hi;
+}
+// The lanes' values (a bitonic sequence) in ascending order, or descending.
+template <typename T> __device__ inline T wave_merge(T v, uint32_t lane, bool ascending) {
+    v = compare_exchange<32>(v, ((lane & 32u) == 0u) == ascending);
+    v = compare_exchange<16>(v, ((lane & 16u) == 0u) == ascending);
+    v = compare_exchange<8>(v, ((lane & 8u) == 0u) == ascending);
+    v = compare_exchange<4>(v, ((lane & 4u) == 0u) == ascending);
+    v = compare_exchange<2>(v, ((lane & 2u) == 0u) == ascending);
+    v = compare_exchange<1>(v, ((lane & 1u) == 0u) == ascending);
+    return v;
+}
+
+// Ascending bitonic sort by the whole workgroup of kBookBlock threads: thread i holds the keys i and, NK == 2,
+// i + kBookBlock of the first n2 (a power of two, at least a wavefront).  Partners closer than a wavefront exchange by
+// data-parallel primitives, the others through LDS (s_x: 2 * NK * kBookBlock keys, two buffers in turn, so that an
+// exchange needs one barrier).  512 keys: 2.6 us; with shuffles through the LDS unit and two barriers 7.2.
+template <int NK>
+__device__ inline void block_sort(uint64_t (&key)[NK], uint64_t *s_x, uint32_t n2) {
+    const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1);
+    const bool mine = (tid & ~(uint32_t)(kWave - 1)) < n2;           // my wavefront holds keys (NK == 2: both or none)
+    if (mine) {
+#pragma unroll
+        for (int v = 0; v < NK; ++v) {
+            uint64_t k = key[v];
+            const uint32_t i = lane;
+            k = compare_exchange<1>(k, ((i & 2u) == 0u) == ((i & 1u) == 0u));
+            k = compare_exchange<2>(k, ((i & 4u) == 0u) == ((i & 2u) == 0u));
+            k = compare_exchange<1>(k, ((i & 4u) == 0u) == ((i & 1u) == 0u));
+            k = compare_exchange<4>(k, ((i & 8u) == 0u) == ((i & 4u) == 0u));
+            k = compare_exchange<2>(k, ((i & 8u) == 0u) == ((i & 2u) == 0u));
+            k = compare_exchange<1>(k, ((i & 8u) == 0u) == ((i & 1u) == 0u));
+            k = compare_exchange<8>(k, ((i & 16u) == 0u) == ((i & 8u) == 0u));
+            k = compare_exchange<4>(k, ((i & 16u) == 0u) == ((i & 4u) == 0u));
+            k = compare_exchange<2>(k, ((i & 16u) == 0u) == ((i & 2u) == 0u));
+            k = compare_exchange<1>(k, ((i & 16u) == 0u) == ((i & 1u) == 0u));
+            k = compare_exchange<16>(k, ((i & 32u) == 0u) == ((i & 16u) == 0u));
+            k = compare_exchange<8>(k, ((i & 32u) == 0u) == ((i & 8u) == 0u));
+            k = compare_exchange<4>(k, ((i & 32u) == 0u) == ((i & 4u) == 0u));
+            k = compare_exchange<2>(k, ((i & 32u) == 0u) == ((i & 2u) == 0u));
+            k = compare_exchange<1>(k, ((i & 32u) == 0u) == ((i & 1u) == 0u));
+            key[v] = wave_merge(k, lane, n2 == (uint32_t)kWave || (tid & (uint32_t)kWave) == 0u);
         }
     }
-    return key;
+    uint32_t flip = 0;
+    for (uint32_t k = 2u * kWave; k <= n2; k <<= 1) {
+        for (uint32_t j = k >> 1; j >= (uint32_t)kWave; j >>= 1) {
+            if (NK == 2 && j == (uint32_t)kBookBlock) {              // (k == 2 * kBookBlock: ascending throughout)
+                const uint64_t x = key[0], y = key[NK - 1];
+                key[0] = x < y ? x : y;
+                key[NK - 1] = x < y ? y : x;
+                continue;
+            }
+            uint64_t *buf = s_x + flip * (uint32_t)(NK * kBookBlock);
+            flip ^= 1u;
+            if (mine) {
+#pragma unroll
+                for (int v = 0; v < NK; ++v) buf[v * kBookBlock + tid] = key[v];
+            }
+            __syncthreads();
+            if (mine) {
+#pragma unroll
+                for (int v = 0; v < NK; ++v) {
+                    const uint32_t i = v * (uint32_t)kBookBlock + tid;
+                    const uint64_t o = buf[i ^ j];
+                    const bool keep_min = ((i & k) == 0u) == ((i & j) == 0u);
+                    key[v] = (key[v] < o) == keep_min ? key[v] : o;
+                }
+            }
+        }
+        if (mine) {
+#pragma unroll
+            for (int v = 0; v < NK; ++v) key[v] = wave_merge(key[v], lane, ((v * (uint32_t)kBookBlock + tid) & k) == 0u);
+        }
+    }
 }
 
 // arr[begin, end) is non-decreasing in (arr[i] >> shift); number of entries <= t
@@ -269,6 +352,8 @@ __device__ inline void huffman_rounds(const uint64_t *keys, uint64_t *iw, uint32
 }
 
 __device__ inline uint64_t lane_value64(uint64_t v, uint32_t src) { return lane_value64_any(v, src); }
+__device__ inline uint64_t lane_value(uint64_t v, uint32_t src) { return lane_value64_any(v, src); }
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t src) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)src); }
 
 // The same rounds for arrays in LDS, by the whole workgroup.  The first wavefront runs the rounds of
 // at most 64 items alone and in registers: lane l holds the l-th waiting leaf and the l-th waiting
@@ -375,113 +460,207 @@ __device__ inline void huffman_rounds_lds(const uint64_t *keys, uint64_t *iw, ui
     }
 }
 
-// Everything between the histogram and the tables, on storage that is either LDS
-// (LDS == true: the pointers are the workgroup's own __shared__ arrays, so the
-// compiler emits ds_* instructions) or global scratch for large alphabets.
-// l_keys .. l_ip: the workgroup's LDS arrays of kBookLdsSyms entries (the same pointers as keys .. int_parent when LDS).
-template <bool LDS>
-__device__ inline void codebook_body(const BookArgs &a, uint32_t m, uint64_t *keys, uint64_t *iw, uint32_t *leaf_parent,
-                                     uint32_t *int_parent, uint64_t *l_keys, uint64_t *l_iw, uint32_t *l_lp, uint32_t *l_ip,
-                                     uint64_t *s_x, uint32_t *s_part, uint32_t *s_cnt,
-                                     uint64_t *s_first, uint32_t *s_findex, uint32_t *s_maxlen, uint32_t *s_wc) {
+// The merge rounds of an alphabet that fits LDS, by one wavefront.  A round looks at the 64 lightest waiting items: lane
+// l holds the l-th waiting leaf and the (63 - l)-th waiting node, and the smaller of the two values is one of the 64
+// lightest (a bitonic sequence), which six compare-exchange steps put into merged order.  A key is (weight, node after
+// leaf): of equal keys the one earlier in its queue comes first whatever the network does with them, because only its
+// kind is read off the key and its place in its queue is the number of items of that kind in front of it.  With t the
+// sum of the two lightest, the items of weight <= t, or the first 64 of them, are the next steps of the sequential
+// construction (a node created now weighs t at least); an odd one out waits.
+// W: 32-bit keys as long as all weights together stay below 2^31 - 1, else 64-bit ones.
+// leafw: the leaves' keys in order, 64 keys of all ones behind the last; nodew: all ones on entry.  About 0.2 us a round
+// (0.8 with the merged order from a loop over the shorter queue and the weights added up atomically).
+// parent: of leaf i at i, of node i at kBookLdsSyms + i, of nobody at 2 * kBookLdsSyms + 0 .. 63; every lane writes in every
+// round, those that merge nothing to a place of their own (switching the execution mask costs more).
+template <typename W>
+__device__ inline void huffman_rounds_wave(const W *leafw, W *nodew, uint16_t *parent, uint32_t m, uint32_t lane) {
+    uint32_t li = 0, ii = 0, ni = 0;
+    const uint32_t nobody = 2u * kBookLdsSyms + lane;
+    while (ni + 1u < m) {
+        const W a = leafw[li + lane], b = nodew[ii + (uint32_t)kWave - 1u - lane];
+        const W key = wave_merge<W>(a < b ? a : b, lane, true);
+        const W two = (lane_value(key, 0) | (W)1u) + (lane_value(key, 1) & ~(W)1u);        // (key of a node that weighs both)
+        const uint32_t cnt = (uint32_t)__popcll(wave_ballot(key <= two)) & ~1u;
+        const bool taken = lane < cnt, node = (key & (W)1u) != 0u;
+        const uint64_t nodes = wave_ballot(node) & (cnt < (uint32_t)kWave ? (1ull << cnt) - 1ull : ~0ull);
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(nodes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nodes, 0u));
+        const uint32_t nn = (uint32_t)__popcll(nodes), up = ni + (lane >> 1);
+        const W other = lane_xor<1>(key);
+        // (lanes that make no node write all ones where nodes to come are all ones already)
+        nodew[(taken && (lane & 1u) == 0u) ? up : kBookLdsSyms] = (taken && (lane & 1u) == 0u) ? (key | (W)1u) + (other & ~(W)1u) : ~(W)0;
+        parent[taken ? (node ? kBookLdsSyms + ii + before : li + lane - before) : nobody] = (uint16_t)up;
+        __builtin_amdgcn_wave_barrier();                     // (a wavefront's LDS accesses happen in order: nothing to wait for)
+        li += cnt - nn; ii += nn; ni += cnt >> 1;
+    }
+}
+
+// LDS of k_codebook: one piece, used in turn for what follows.
+constexpr uint32_t kBookPad = kBookLdsSyms + (uint32_t)kWave;
+struct BookLds {
+    // by construction: sort exchange (two buffers of 2 * kBookBlock keys), then the leaves' and the nodes' keys
+    union {
+        uint64_t exchange[4 * kBookBlock];
+        struct { uint64_t leafw[kBookPad], nodew[kBookPad]; } q;
+        struct { uint16_t sym[kBookBySymbolMax]; uint8_t depth[kBookBySymbolMax]; } given;      // code book reuse: up to kBookBySymbolMax symbols
+        struct { uint64_t keys[kBookLdsSyms], iw[kBookLdsSyms]; } large;                        // construction in global memory, its last rounds
+    } u;
+    union {
+        struct { uint16_t parent[2 * kBookLdsSyms + kWave], order[kBookLdsSyms]; } t;
+        struct { uint32_t lp[kBookLdsSyms], ip[kBookLdsSyms]; } large;
+        uint32_t wc[(kBookBlock / kWave) * 64 + 65];         // canonical order: symbols per (wavefront, length), and per length so far
+    } v;
+    uint16_t sym[kBookLdsSyms];       // the symbols that occur, ascending
+    uint8_t depth[kBookLdsSyms];      // their code lengths
+    uint32_t cnt[65];                 // symbols per length
+    uint64_t first[65];
+    uint32_t findex[65];
+    uint32_t part[kBookBlock / kWave];
+    uint32_t word[4];
+};
+static_assert(sizeof(BookLds) <= 64u * 1024u, "static LDS");
+
+// Canonical codes of the symbols sym[0, m) (ascending) from their lengths: the code of a symbol is the first code of its
+// length plus the number of smaller symbols of the same length (per wavefront the lanes of one length are found with a
+// ballot per length that occurs, then a prefix over the wavefronts in front).  sym == nullptr: every symbol of the
+// alphabet (m of them), length 0 if it does not occur.
+__device__ inline void book_codes(const BookArgs &a, const uint16_t *syms, const uint8_t *depths, uint32_t m, const uint64_t *first, uint32_t *s_wc) {
+    const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1), wave = tid / (uint32_t)kWave;
+    constexpr uint32_t kWaves = kBookBlock / kWave;
+    uint32_t *s_run = s_wc + kWaves * 64u;                   // symbols per length in front of the current 1024 symbols
+    for (uint32_t i = tid; i < 65u; i += kBookBlock) s_run[i] = 0;
+    for (uint32_t base = 0; base < m; base += kBookBlock) {
+        for (uint32_t i = tid; i < kWaves * 64u; i += kBookBlock) s_wc[i] = 0;
+        __syncthreads();
+        const uint32_t at = base + tid;
+        const uint32_t L = (at < m) ? depths[at] : 0u;
+        uint32_t in_wave = 0;
+        uint64_t todo = wave_ballot(L != 0u);
+        while (todo) {                                       // one step per length that occurs in the wavefront
+            const uint32_t Lc = (uint32_t)__builtin_amdgcn_readlane((int)L, __builtin_ctzll(todo));
+            const uint64_t same = wave_ballot(L == Lc);
+            if (L == Lc) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            if (lane == 0) s_wc[wave * 64u + (Lc & 63u)] = (uint32_t)__popcll(same);
+            todo &= ~same;
+        }
+        __syncthreads();
+        if (L) {
+            uint32_t before = s_run[L & 63u];
+            for (uint32_t w = 0; w < wave; ++w) before += s_wc[w * 64u + (L & 63u)];
+            const uint64_t code = first[L] + before + in_wave;
+            const uint32_t sym = syms ? syms[at] : at;
+            a.len_out[sym] = (uint8_t)L;
+            a.enc[sym] = (code << 6) | (uint64_t)(L & 63u);
+            if (a.code_out) a.code_out[sym] = code;
+        }
+        if (base + kBookBlock >= m) break;
+        __syncthreads();
+        if (tid < 64u) {
+            uint32_t add = 0;
+            for (uint32_t w = 0; w < kWaves; ++w) add += s_wc[w * 64u + tid];
+            s_run[tid] += add;
+        }
+        __syncthreads();                                     // the counts are cleared for the next 1024 symbols
+    }
+}
+
+// First codes per length from the counts s.cnt; a table that is no complete prefix code raises a status bit.
+__device__ inline void book_first_codes(const BookArgs &a, BookLds &s, uint32_t m, bool given) {
+    if (threadIdx.x < (uint32_t)kWave) {
+        uint32_t mx = 0, mn;
+        const bool ok = (m == 0 && !given) || (m != 0 && canonical_first_codes_wave(s.cnt, m, s.first, s.findex, &mx, &mn));
+        if (threadIdx.x == 0) {
+            s.word[2] = mx;
+            if (!ok) atomicOr(&a.ctl->status, given ? (uint32_t)ST_CODEBOOK : (uint32_t)ST_INTERNAL);   // a given table must be a complete code
+        }
+    }
+    __syncthreads();
+}
+
+// The code lengths (s.depth, s.cnt) of m <= kBookLdsSyms symbols: thread i holds the i-th and, n_keys == 2, the
+// (i + kBookBlock)-th (frequency, place in s.sym) key in order; all ones behind the last.
+template <typename W>
+__device__ inline void book_tree(BookLds &s, uint32_t m, const uint64_t (&key)[2], uint32_t n_keys) {
+    const uint32_t tid = threadIdx.x;
+    // ---- leaves in order, waiting; no nodes yet ----
+    W *leafw = reinterpret_cast<W *>(s.u.q.leafw), *nodew = reinterpret_cast<W *>(s.u.q.nodew);
+    __syncthreads();                                         // the exchange buffers of the sort are free
+#pragma unroll
+    for (uint32_t v = 0; v < 2; ++v) {
+        const uint32_t i = tid + v * kBookBlock;
+        const bool on = i < m;
+        if (on) s.v.t.order[i] = (uint16_t)(key[v] & 0xffffu);
+        if (v < n_keys && i < m + (uint32_t)kWave) leafw[i] = on ? (W)((key[v] >> 16) << 1) : ~(W)0;
+    }
+    for (uint32_t i = n_keys * kBookBlock + tid; i < m + (uint32_t)kWave; i += kBookBlock) leafw[i] = ~(W)0;
+    for (uint32_t i = tid; i < m + (uint32_t)kWave; i += kBookBlock) nodew[i] = ~(W)0;
+    __syncthreads();
+    if (tid < (uint32_t)kWave) huffman_rounds_wave<W>(leafw, nodew, s.v.t.parent, m, tid);
+    __syncthreads();
+    // ---- depth of every leaf: walk to the root (node m - 2) ----
+    for (uint32_t i = tid; i < m; i += kBookBlock) {
+        uint32_t depth = 1;
+        if (m >= 2) {
+            const uint16_t *node_parent = s.v.t.parent + kBookLdsSyms;
+            for (uint32_t p = s.v.t.parent[i]; p != m - 2u && depth < 64u; p = node_parent[p]) ++depth;
+        }
+        s.depth[s.v.t.order[i]] = (uint8_t)depth;
+        atomicAdd(&s.cnt[depth], 1u);
+    }
+    __syncthreads();
+}
+
+// More symbols than fit LDS, built from the histogram in global memory; keys[0, m): the leaves in order if presorted.
+__device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     const uint32_t tid = threadIdx.x;
     const uint32_t nbins = a.nbins;
-    // ---- 1. compact the active symbols into sort keys (frequency << 16 | symbol) ----
-    // (code book reuse: the given length takes the place of the frequency, so the keys are already
-    // those of step 5 and steps 2-4 are skipped)
-    const bool given = a.given_len != nullptr;
-    // presorted: the sort kernels have left the leaves in order in keys[0, m) (large alphabets built from a histogram)
-    const bool presorted = !LDS && !given && a.presorted != 0u;
-    if (presorted) {
-        for (uint32_t s = tid; s < nbins; s += kBookBlock)
-            if (a.hist[s] == 0u) {
-                a.len_out[s] = 0;
-                a.enc[s] = 0;
-                if (a.code_out) a.code_out[s] = 0;
-            }
-    } else {
-        uint32_t done = 0;
-        for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-            const uint32_t s = base + tid;
-            const uint32_t f = (s < nbins) ? (given ? (uint32_t)a.given_len[s] : a.hist[s]) : 0u;
+    uint64_t *keys = a.scratch.keys, *iw = a.scratch.iw;
+    uint32_t *leaf_parent = a.scratch.leaf_parent, *int_parent = a.scratch.int_parent;
+    // ---- 1. the symbols that occur as sort keys (frequency << 16 | symbol), unless the sort kernels have done that ----
+    uint32_t done = 0;
+    for (uint32_t base = 0; base < nbins; base += kBookBlock) {
+        const uint32_t sy = base + tid;
+        const uint32_t f = (sy < nbins) ? a.hist[sy] : 0u;
+        if (!a.presorted) {
             uint32_t tot;
-            const uint32_t pos = block_excl_scan<uint32_t, kBookBlock / kWave>(f ? 1u : 0u, s_part, tot);
-            if (f) keys[done + pos] = ((uint64_t)f << 16) | s;
-            else if (s < nbins) {           // unused symbol: length 0 everywhere
-                a.len_out[s] = 0;
-                a.enc[s] = 0;
-                if (a.code_out) a.code_out[s] = 0;
-            }
+            const uint32_t pos = block_excl_scan<uint32_t, kBookBlock / kWave>(f ? 1u : 0u, s.part, tot);
+            if (f) keys[done + pos] = ((uint64_t)f << 16) | sy;
             done += tot;
         }
+        if (!f && sy < nbins) {             // unused symbol: length 0 everywhere
+            a.len_out[sy] = 0;
+            a.enc[sy] = 0;
+            if (a.code_out) a.code_out[sy] = 0;
+        }
     }
-    const uint32_t m2 = next_pow2(m > 1 ? m : 2);
-    if (!presorted) for (uint32_t i = m + tid; i < m2; i += kBookBlock) keys[i] = ~0ull;
+    const uint32_t m2 = next_pow2(m);
+    if (!a.presorted) for (uint32_t i = m + tid; i < m2; i += kBookBlock) keys[i] = ~0ull;
     for (uint32_t i = tid; i < m; i += kBookBlock) iw[i] = 0;
     __syncthreads();
-
-    const bool reg_sort = LDS && m2 <= (uint32_t)kBookBlock;
-    // Canonical order without a second sort: the lengths are scattered into a by-symbol table (in the
-    // sort's exchange buffer, free after step 2) and the symbols are then visited in increasing order.
-    // The by-symbol table of an alphabet built in global memory is the length table itself (a sort of
-    // that many keys by one workgroup would cost more than visiting every symbol).
-    const bool by_symbol = !LDS || nbins <= (uint32_t)kBookBySymbolMax;
-    uint8_t *s_depth = LDS ? reinterpret_cast<uint8_t *>(s_x) : a.len_out;
-    if (given) {
-        // lengths per symbol are known: count them; a length the container cannot hold spoils the count
-        // of length 64, which the completeness test below then rejects
-        if (by_symbol && LDS) {
-            for (uint32_t i = tid; i < nbins; i += kBookBlock) s_depth[i] = 0;
-            __syncthreads();
-        }
-        for (uint32_t i = tid; i < m; i += kBookBlock) {
-            const uint32_t depth = (uint32_t)(keys[i] >> 16);
-            atomicAdd(&s_cnt[depth > 57 ? 64 : depth], 1u);
-            atomicMax(s_maxlen, depth);
-            if (by_symbol) s_depth[(uint32_t)(keys[i] & 0xffffu)] = (uint8_t)(depth > 57 ? 64 : depth);
-        }
-        __syncthreads();
-    } else {
     // ---- 2. leaves in (frequency, symbol) order ----
-    if (reg_sort) {
-        uint64_t key = tid < m2 ? keys[tid] : ~0ull;
-        key = bitonic_sort_regs(key, s_x, m2);
-        if (tid < m2) keys[tid] = key;
-        __syncthreads();
-    } else if (!presorted) {
-        bitonic_sort(keys, m2);
-    }
-
+    if (!a.presorted) bitonic_sort(keys, m2);
     // ---- 3. two-queue merge in rounds ----
-    if (m >= 2) {
-        if (LDS) {
-            huffman_rounds_lds(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, s_part);
-        } else {
-            // The first rounds merge thousands of light leaves each: in global memory, by everybody.  Most
-            // rounds come later, with few items each: once the L leaves and N nodes that wait make at most
-            // kBookLdsSyms / 2 items, they move to LDS (L + 2N - 1 nodes at the end, which fit), the rounds
-            // are finished there, and the parents go back with the offset of the first node moved.
-            uint32_t li, ii, ni;
-            huffman_rounds<false>(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, [] { __syncthreads(); },
-                                  kBookLdsSyms / 2u, li, ii, ni);
-            const uint32_t L = m - li, N = ni - ii;
-            if (L + N > 1u) {
-                for (uint32_t j = tid; j < L; j += kBookBlock) l_keys[j] = keys[li + j];
-                for (uint32_t k = tid; k < kBookLdsSyms; k += kBookBlock) l_iw[k] = k < N ? iw[ii + k] : 0ull;
-                __syncthreads();
-                huffman_rounds_lds(l_keys, l_iw, l_lp, l_ip, L, tid, (uint32_t)kBookBlock, s_part, N);
-                __syncthreads();
-                for (uint32_t j = tid; j < L; j += kBookBlock) leaf_parent[li + j] = ii + l_lp[j];
-                for (uint32_t k = tid; k + 1u < L + 2u * N - 1u; k += kBookBlock) int_parent[ii + k] = ii + l_ip[k];   // (the last node is the root)
-            }
+    {
+        // The first rounds merge thousands of light leaves each: in global memory, by everybody.  Most
+        // rounds come later, with few items each: once the L leaves and N nodes that wait make at most
+        // kBookLdsSyms / 2 items, they move to LDS (L + 2N - 1 nodes at the end, which fit), the rounds
+        // are finished there, and the parents go back with the offset of the first node moved.
+        uint32_t li, ii, ni;
+        huffman_rounds<false>(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, [] { __syncthreads(); },
+                              kBookLdsSyms / 2u, li, ii, ni);
+        const uint32_t L = m - li, N = ni - ii;
+        if (L + N > 1u) {
+            uint64_t *l_keys = s.u.large.keys, *l_iw = s.u.large.iw;
+            uint32_t *l_lp = s.v.large.lp, *l_ip = s.v.large.ip;
+            for (uint32_t j = tid; j < L; j += kBookBlock) l_keys[j] = keys[li + j];
+            for (uint32_t k = tid; k < kBookLdsSyms; k += kBookBlock) l_iw[k] = k < N ? iw[ii + k] : 0ull;
+            __syncthreads();
+            huffman_rounds_lds(l_keys, l_iw, l_lp, l_ip, L, tid, (uint32_t)kBookBlock, s.part, N);
+            __syncthreads();
+            for (uint32_t j = tid; j < L; j += kBookBlock) leaf_parent[li + j] = ii + l_lp[j];
+            for (uint32_t k = tid; k + 1u < L + 2u * N - 1u; k += kBookBlock) int_parent[ii + k] = ii + l_ip[k];   // (the last node is the root)
         }
     }
     __syncthreads();
-
-    if (by_symbol && LDS) {
-        for (uint32_t i = tid; i < nbins; i += kBookBlock) s_depth[i] = 0;
-        __syncthreads();
-    }
     // ---- 4. depth of every leaf: walk to the root (node m-2) ----
     // (four leaves per thread at a time: a walk is a chain of dependent loads, in global memory for a large
     // alphabet, and four chains wait side by side)
@@ -512,85 +691,14 @@ __device__ inline void codebook_body(const BookArgs &a, uint32_t m, uint64_t *ke
             const uint32_t i = i0 + k * kBookBlock;
             if (i < m) {
                 const uint32_t sym = (uint32_t)(keys[i] & 0xffffu);
-                keys[i] = ((uint64_t)depth[k] << 16) | sym;     // re-keyed for the canonical order
-                atomicAdd(&s_cnt[depth[k] > 64 ? 64 : depth[k]], 1u);
-                atomicMax(s_maxlen, depth[k]);
-                if (by_symbol) s_depth[sym] = (uint8_t)(depth[k] > 64 ? 64 : depth[k]);
+                atomicAdd(&s.cnt[depth[k] > 64 ? 64 : depth[k]], 1u);
+                a.len_out[sym] = (uint8_t)(depth[k] > 64 ? 64 : depth[k]);    // (the canonical order is counted by symbol)
             }
         }
     }
     __syncthreads();
-    }   // !given
-
-    // ---- 5. canonical order (length, symbol) ----
-    if (!by_symbol) {
-        if (reg_sort) {
-            uint64_t key = tid < m2 ? keys[tid] : ~0ull;
-            key = bitonic_sort_regs(key, s_x, m2);
-            if (tid < m2) keys[tid] = key;
-            __syncthreads();
-        } else {
-            bitonic_sort(keys, m2);
-        }
-    }
-    bool ok = true;
-    if (tid < (uint32_t)kWave) {
-        uint32_t mx, mn;
-        ok = (m == 0 && !given) || (m != 0 && canonical_first_codes_wave(s_cnt, m, s_first, s_findex, &mx, &mn));
-        if (!ok && tid == 0) atomicOr(&a.ctl->status, given ? (uint32_t)ST_CODEBOOK : (uint32_t)ST_INTERNAL);   // a given table must be a complete code
-    }
-    ok = __syncthreads_and(ok ? 1 : 0) != 0;
-
-    // ---- 6. codes and tables ----
-    if (!by_symbol) {
-        for (uint32_t p = tid; p < m; p += kBookBlock) {
-            const uint32_t L = (uint32_t)(keys[p] >> 16);
-            const uint32_t sym = (uint32_t)(keys[p] & 0xffffu);
-            const uint64_t code = s_first[L > 64 ? 64 : L] + (p - s_findex[L > 64 ? 64 : L]);
-            a.len_out[sym] = (uint8_t)L;
-            a.enc[sym] = (code << 6) | (uint64_t)(L & 63u);
-            if (a.code_out) a.code_out[sym] = code;
-        }
-        return;
-    }
-    // The symbols in increasing order: the code of a symbol is the first code of its length plus the
-    // number of smaller symbols of the same length (per wavefront the lanes of one length are found
-    // with a ballot per length that occurs, then a prefix over the wavefronts in front).
-    const uint32_t lane = tid & (uint32_t)(kWave - 1), wave = tid / (uint32_t)kWave;
-    constexpr uint32_t kWaves = kBookBlock / kWave;
-    uint32_t *s_run = s_wc + kWaves * 64u;                   // symbols per length in front of the current 1024 symbols
-    for (uint32_t i = tid; i < 65u; i += kBookBlock) s_run[i] = 0;
-    for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-        for (uint32_t i = tid; i < kWaves * 64u; i += kBookBlock) s_wc[i] = 0;
-        __syncthreads();
-        const uint32_t sym = base + tid;
-        const uint32_t L = (sym < nbins) ? s_depth[sym] : 0u;
-        uint32_t in_wave = 0;
-        uint64_t todo = wave_ballot(L != 0u);
-        while (todo) {                                       // one step per length that occurs in the wavefront
-            const uint32_t Lc = (uint32_t)__builtin_amdgcn_readlane((int)L, __builtin_ctzll(todo));
-            const uint64_t same = wave_ballot(L == Lc);
-            if (L == Lc) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-            if (lane == 0) s_wc[wave * 64u + (Lc & 63u)] = (uint32_t)__popcll(same);
-            todo &= ~same;
-        }
-        __syncthreads();
-        if (L) {
-            uint32_t before = s_run[L & 63u];
-            for (uint32_t w = 0; w < wave; ++w) before += s_wc[w * 64u + (L & 63u)];
-            const uint64_t code = s_first[L] + before + in_wave;
-            a.len_out[sym] = (uint8_t)L;
-            a.enc[sym] = (code << 6) | (uint64_t)(L & 63u);
-            if (a.code_out) a.code_out[sym] = code;
-        }
-        __syncthreads();
-        if (tid < 64u) {
-            uint32_t add = 0;
-            for (uint32_t w = 0; w < kWaves; ++w) add += s_wc[w * 64u + tid];
-            s_run[tid] += add;
-        }
-        __syncthreads();                                     // the counts are cleared for the next 1024 symbols
-    }
+    book_first_codes(a, s, m, false);
+    book_codes(a, nullptr, a.len_out, nbins, s.first, s.v.wc);
 }
 
 // ---------------------------------------------------------------------------
@@ -603,14 +711,14 @@ __device__ inline void codebook_body(const BookArgs &a, uint32_t m, uint64_t *ke
 // occurring symbols fit LDS are built there from the histogram: the merges then have nothing to do.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(const uint32_t *hist, uint32_t nbins, uint64_t *keys, Control *ctl) {
-    __shared__ uint64_t s_x[kBookBlock];
+    __shared__ uint64_t s_x[2 * kBookBlock];
     const uint32_t s = blockIdx.x * (uint32_t)kBookBlock + threadIdx.x;
     const uint32_t f = s < nbins ? hist[s] : 0u;
     const uint32_t cnt = (uint32_t)__syncthreads_count(f != 0u);
     if (threadIdx.x == 0 && cnt) atomicAdd(&ctl->n_active, cnt);
-    uint64_t key = f ? (((uint64_t)f << 16) | s) : ((1ull << 63) | s);
-    key = bitonic_sort_regs(key, s_x, (uint32_t)kBookBlock);
-    keys[s] = key;
+    uint64_t key[1] = {f ? (((uint64_t)f << 16) | s) : ((1ull << 63) | s)};
+    block_sort<1>(key, s_x, (uint32_t)kBookBlock);
+    keys[s] = key[0];
 }
 
 __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl) {
@@ -631,57 +739,144 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     // One workgroup on the critical path of its stream, often next to the streaming kernels of
     // other streams: its wavefronts go first whenever they are ready to issue.
     __builtin_amdgcn_s_setprio(3);
-    __shared__ uint64_t s_keys[kBookLdsSyms];
-    __shared__ uint64_t s_iw[kBookLdsSyms];
-    __shared__ uint32_t s_lp[kBookLdsSyms];
-    __shared__ uint32_t s_ip[kBookLdsSyms];
-    __shared__ uint64_t s_x[kBookBlock];
-    __shared__ uint32_t s_part[kBookBlock / kWave];
-    __shared__ uint32_t s_cnt[65];
-    __shared__ uint64_t s_first[65];
-    __shared__ uint32_t s_findex[65];
-    __shared__ uint32_t s_maxlen;
-    __shared__ uint32_t s_wc[(kBookBlock / kWave) * 64 + 65];      // canonical order: symbols per (wavefront, length), and per length so far
-
-    const uint32_t tid = threadIdx.x;
+    __shared__ BookLds s;
+    const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     const uint32_t nbins = a.nbins;
-    if (tid < 65) s_cnt[tid] = 0;
-    if (tid == 0) s_maxlen = 0;
+    const bool given = a.given_len != nullptr;
+    // (what the header takes from the control block: asked for now, needed last)
+    const uint64_t n_rec = a.ctl->n_rec, n_vrec = a.ctl->n_vrec, nnz = a.ctl->nnz;
+    if (tid < 65) s.cnt[tid] = 0;
+    if (tid < 4) s.word[tid] = 0;
+    __syncthreads();
 
-    uint32_t m = 0;
-    // (and: does every symbol that occurs, but for the escape symbol, lie in the part of the encode table that the
-    // encoders keep in LDS?)
+    // ---- 1. the symbols that occur.  A wavefront looks at consecutive symbols, kGroup x 64 at a time (their loads in
+    // flight together); counted first, then listed, so that the list is in order of the symbols.  (And: does every
+    // symbol that occurs, but for the escape symbol, lie in the part of the encode table that the encoders keep in
+    // LDS?)  Code book reuse: the given length takes the place of the frequency. ----
     const uint32_t win_n = nbins < kEncTableMax ? nbins : kEncTableMax, win_lo = (nbins - win_n) / 2u;
     const uint32_t lenw_n = enc_len_window(nbins), lenw_lo = (nbins - lenw_n) / 2u;
-    int outside = 0;
-    for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-        const uint32_t s = base + tid;
-        const bool occurs = (s < nbins) && (a.given_len ? a.given_len[s] != 0 : a.hist[s] != 0u);
-        m += __syncthreads_count(occurs);
-        outside |= (occurs && s != 0u && s - win_lo >= win_n) ? 1 : 0;
-        outside |= (occurs && s != 0u && s - lenw_lo >= lenw_n) ? 2 : 0;
+    constexpr uint32_t kGroup = 8;
+    const uint32_t iters = (nbins + (uint32_t)kBookBlock - 1u) / (uint32_t)kBookBlock;      // steps of 64 symbols per wavefront
+    const uint32_t s0 = wave * iters * (uint32_t)kWave;
+    uint32_t f[kGroup];
+    auto fetch = [&](uint32_t g) {
+#pragma unroll
+        for (uint32_t j = 0; j < kGroup; ++j) {
+            const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
+            f[j] = (g + j < iters && sy < nbins) ? (given ? (uint32_t)a.given_len[sy] : a.hist[sy]) : 0u;
+        }
+    };
+    uint32_t mine = 0;
+    {
+        bool out1 = false, out2 = false;
+        for (uint32_t g = 0; g < iters; g += kGroup) {
+            fetch(g);
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) {
+                const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
+                mine += (uint32_t)__popcll(wave_ballot(f[j] != 0u));
+                out1 = out1 || (f[j] != 0u && sy != 0u && sy - win_lo >= win_n);
+                out2 = out2 || (f[j] != 0u && sy != 0u && sy - lenw_lo >= lenw_n);
+            }
+        }
+        const uint32_t outside = (wave_ballot(out1) ? 1u : 0u) | (wave_ballot(out2) ? 2u : 0u);
+        if (lane == 0) {
+            s.part[wave] = mine;
+            if (outside) atomicOr(&s.word[0], outside);
+        }
     }
-    outside = (__syncthreads_or(outside & 1) ? 1 : 0) | (__syncthreads_or(outside & 2) ? 2 : 0);
-    if (m <= kBookLdsSyms)
-        codebook_body<true>(a, m, s_keys, s_iw, s_lp, s_ip, s_keys, s_iw, s_lp, s_ip, s_x, s_part, s_cnt, s_first, s_findex, &s_maxlen, s_wc);
-    else
-        codebook_body<false>(a, m, a.scratch.keys, a.scratch.iw, a.scratch.leaf_parent, a.scratch.int_parent, s_keys, s_iw, s_lp, s_ip,
-                             s_x, s_part, s_cnt, s_first, s_findex, &s_maxlen, s_wc);
+    __syncthreads();
+    uint32_t m = 0, at = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kBookBlock / kWave; ++w) {
+        const uint32_t c = s.part[w];
+        at += w < wave ? c : 0u;
+        m += c;
+    }
+    const uint32_t outside = s.word[0];
+
+    if (given || m <= kBookLdsSyms) {
+        uint16_t *syms = given ? s.u.given.sym : s.sym;
+        uint8_t *depths = given ? s.u.given.depth : s.depth;
+        for (uint32_t g = 0; g < iters; g += kGroup) {
+            if (iters > kGroup) fetch(g);                    // (else they are still there)
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) {
+                const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
+                const uint64_t mask = wave_ballot(f[j] != 0u);
+                const uint32_t pos = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (f[j] != 0u) {
+                    syms[pos] = (uint16_t)sy;
+                    if (given) depths[pos] = (uint8_t)(f[j] > 57u ? 64u : f[j]);      // (64: a length the container cannot hold; refused below)
+                    else s.u.exchange[pos] = ((uint64_t)f[j] << 16) | pos;
+                } else if (g + j < iters && sy < nbins) {    // unused symbol: length 0 everywhere
+                    a.len_out[sy] = 0;
+                    a.enc[sy] = 0;
+                    if (a.code_out) a.code_out[sy] = 0;
+                }
+                at += (uint32_t)__popcll(mask);
+            }
+        }
+        if (given) {
+            __syncthreads();
+            for (uint32_t i = tid; i < m; i += kBookBlock) atomicAdd(&s.cnt[depths[i]], 1u);
+            __syncthreads();
+        } else {
+            // ---- 2. leaves in (frequency, symbol) order, 3. the tree, 4. depths ----
+            uint32_t n2 = next_pow2(m);
+            n2 = n2 < (uint32_t)kWave ? (uint32_t)kWave : n2;
+            for (uint32_t i = m + tid; i < n2; i += kBookBlock) s.u.exchange[i] = ~0ull;
+            // (keys of 32 bits if all frequencies together allow it; a container's do but for the largest possible tensor)
+            bool narrow = a.narrow != 0u;
+            if (!a.hdr) {
+                __syncthreads();
+                uint64_t total = 0, sum = 0;
+                for (uint32_t i = tid; i < m; i += kBookBlock) sum += s.u.exchange[i] >> 16;
+                sum = wave_sum<uint64_t>(sum);
+                uint64_t *part64 = reinterpret_cast<uint64_t *>(s.v.wc);
+                if (lane == 0) part64[wave] = sum;
+                __syncthreads();
+                for (uint32_t w = 0; w < kBookBlock / kWave; ++w) total += part64[w];
+                narrow = total < 0x7fffffffull;
+            }
+            __syncthreads();
+            uint64_t key[2] = {tid < n2 ? s.u.exchange[tid] : ~0ull, 0ull};
+            if (n2 <= (uint32_t)kBookBlock) {
+                __syncthreads();                             // (the keys are read before the exchange overwrites them)
+                uint64_t k1[1] = {key[0]};
+                block_sort<1>(k1, s.u.exchange, n2);
+                key[0] = k1[0];
+            } else {
+                key[1] = s.u.exchange[kBookBlock + tid];
+                __syncthreads();
+                block_sort<2>(key, s.u.exchange, n2);
+            }
+            const uint32_t n_keys = n2 <= (uint32_t)kBookBlock ? 1u : 2u;
+            if (narrow) book_tree<uint32_t>(s, m, key, n_keys);
+            else book_tree<uint64_t>(s, m, key, n_keys);
+        }
+        // ---- 5. canonical codes ----
+        book_first_codes(a, s, m, given);
+        book_codes(a, syms, depths, m, s.first, s.v.wc);
+    } else {
+        book_large(a, s, m);
+    }
 
     // ---- 7. container layout ----
     if (tid == 0) {
         a.ctl->n_active = m;
-        a.ctl->max_len = s_maxlen;
+        a.ctl->max_len = s.word[2];
         a.ctl->enc_in_window = (outside & 1) ? 0u : 1u;
         a.ctl->len_in_window = (outside & 2) ? 0u : 1u;
         if (a.hdr) {
             Header h = a.proto;
             h.n_active = m;
-            h.max_len = s_maxlen;
-            h.n_rec = (uint32_t)a.ctl->n_rec;
-            h.n_vrec = (uint32_t)a.ctl->n_vrec;
-            h.nnz = a.ctl->nnz;
-            h.off_payload = align16(h.off_outlier + 8ull * a.ctl->n_rec);
+            h.max_len = s.word[2];
+            h.n_rec = (uint32_t)n_rec;
+            h.n_vrec = (uint32_t)n_vrec;
+            h.nnz = nnz;
+            h.off_payload = align16(h.off_outlier + 8ull * n_rec);
             h.payload_words = 0;
             h.total_bytes = 0;
             h.status = 1;                      // overwritten by the encode kernel's last workgroup
@@ -693,7 +888,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
             for (uint64_t o = h.off_len + nbins; o < h.off_chunk; ++o) base[o] = 0;
             for (uint64_t o = h.off_chunk + 4ull * h.n_chunks; o < h.off_outlier; ++o) base[o] = 0;
             if (h.off_payload <= a.capacity)
-                for (uint64_t o = h.off_outlier + 8ull * a.ctl->n_rec; o < h.off_payload; ++o) base[o] = 0;
+                for (uint64_t o = h.off_outlier + 8ull * n_rec; o < h.off_payload; ++o) base[o] = 0;
         }
     }
 }

@@ -1,0 +1,47 @@
+"""Code lengths and canonical codes of alphabets at the edges of the code book kernel: the sort's sizes (one and two
+keys per thread), the 64 lightest items a merge round looks at, ties of leaves with nodes, and the largest total of
+frequencies its 32-bit keys take (2^31 - 2).  Bit-exact against the CPU oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _hist(kind, m, rng):
+    if kind == "flat":
+        return np.full(m, 7, np.uint64)
+    if kind == "doubling":                                # a node weighs what the next leaf weighs, over and over
+        return np.minimum(2 ** (np.arange(m) % 24), 2 ** 20).astype(np.uint64)
+    if kind == "steps":                                   # many equal leaves beside equal nodes
+        return (1 + np.arange(m) // 37).astype(np.uint64)
+    if kind == "geometric":
+        return np.maximum(1, (1e6 * 0.93 ** np.abs(np.arange(m) - m // 2)).astype(np.uint64))
+    return rng.integers(1, 2 ** 14, m).astype(np.uint64)
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 62, 63, 64, 65, 66, 128, 129, 512, 513, 1023, 1024, 1025, 1500, 2047, 2048])
+@pytest.mark.parametrize("nbins", [2048, 4096, 65536])
+def test_edges(oracle, m, nbins):
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(m * 7 + nbins)
+    ctx = comet.Context(max_elems=4096, max_nbins=65536)
+    lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+    codes = torch.empty(nbins, dtype=torch.int64, device="cuda")
+    for kind in ("flat", "doubling", "steps", "geometric", "random"):
+        w = _hist(kind, m, rng)
+        totals = [None]
+        if kind == "random":
+            totals += [2 ** 31 - 2, 2 ** 31 - 1]          # the last total of 32-bit keys, the first of 64-bit ones
+        for total in totals:
+            f = w.copy()
+            if total is not None:
+                f[int(np.argmax(f))] += total - int(f.sum())
+            h = np.zeros(nbins, np.uint32)
+            h[np.sort(rng.choice(nbins, m, replace=False))] = f
+            want = oracle.code_lengths(h)
+            ctx.comet_stage_codebook(torch.from_numpy(h.view(np.int32)).cuda(), nbins, lens, codes)
+            ctx.comet_sync()
+            assert np.array_equal(lens.cpu().numpy(), want), (kind, total)
+            assert np.array_equal(codes.cpu().numpy().view(np.uint64), oracle.canonical_codes(want)), (kind, total)
+    ctx.close()
