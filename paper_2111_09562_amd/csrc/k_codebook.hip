@@ -897,33 +897,56 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
 // Decode tables from a length table.  Also checks a container header against
 // the shape the caller passed; any inconsistency latches ST_FORMAT, which makes
 // the reconstruct kernel do nothing.
+// A chain of latencies on every decompression's critical path: the lengths are asked for while one thread still
+// checks the header; a wavefront keeps its counts per length in a register (lane L: length L), so that counting and
+// ordering need three barriers whatever the alphabet; a table entry finds its length by comparison with the first
+// twelve limits and its symbol by arithmetic, and the second level, whose prefixes are the end of the first one with
+// sizes that never decrease, is laid out in closed form.  1024 bins: 6.1 us instead of 12.7 (binary searches over
+// the limits, a scan over the prefixes), 4096 bins: 8 instead of 18, 65536 bins: 45 instead of 111.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     __builtin_amdgcn_s_setprio(3);                  // as k_codebook: a single workgroup others wait for
+    constexpr uint32_t kWaves = kBookBlock / kWave;
     __shared__ uint32_t s_cnt[65];
     __shared__ uint64_t s_first[65];
     __shared__ uint64_t s_limit[65];
     __shared__ uint32_t s_findex[65];
-    __shared__ uint32_t s_ok, s_maxlen, s_nbins, s_chunk;
-    __shared__ uint16_t s_sorted[kBookBlock * 2];                   // symbols in canonical order (alphabets up to this size)
-    __shared__ uint32_t s_wc[(kBookBlock / kWave) * 64];            // symbols per (wavefront, length) of the current 1024 symbols
-    __shared__ uint32_t s_run[65];                                  // symbols per length in front of them
-    __shared__ uint32_t s_scan[kBookBlock / kWave];
-    __shared__ uint16_t s_ent[kLut16Size];                          // first level of the compact table
-    __shared__ uint16_t s_owner[kSubEntries];                       // second level: the prefix every entry belongs to
+    __shared__ uint32_t s_lim18[20];                                // limits of the lengths up to 18, of codes left-aligned in 18 bits
+    __shared__ uint32_t s_off[20];                                  // place in canonical order minus first code, of those lengths
+    __shared__ uint32_t s_ok, s_maxlen, s_m;
+    __shared__ uint16_t s_sorted[kLut16MaxBins];                    // symbols in canonical order (the first ones, of a larger alphabet)
+    __shared__ uint32_t s_wc[kWaves][64];                           // symbols per (wavefront, length), then those of the wavefronts in front
 
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     if (a.reset_ctl && tid < sizeof(Control) / 4u) reinterpret_cast<uint32_t *>(a.ctl)[tid] = 0u;   // before the first barrier: nothing has raised a bit yet
     auto raise_format = [&]() {                     // thread 0 only
         atomicOr(&a.ctl->status, (uint32_t)ST_FORMAT);
         if (a.latched) atomicOr(a.latched, (uint32_t)ST_FORMAT);
         if (a.status_out) *a.status_out = -3;
     };
+    const uint32_t nbins = a.hdr ? a.hdr->nbins : a.nbins;
+    const uint32_t chunk = a.hdr ? a.hdr->chunk_syms : 64u;
+    const bool readable = nbins <= 65536u && (!a.hdr || a.bytes >= (uint64_t)kHeaderBytes + nbins);
+
+    // ---- the lengths, 64 consecutive symbols of a wavefront's own range at a time, kGroup of those in flight ----
+    // (few, and the next ones asked for before these are worked on: unrolled further, the code that every launch
+    // fetches anew cost more than it saved)
+    constexpr uint32_t kGroup = 4;
+    const uint32_t iters = readable ? (nbins + (uint32_t)kBookBlock - 1u) / (uint32_t)kBookBlock : 0u;
+    const uint32_t s0 = wave * iters * (uint32_t)kWave;
+    uint32_t len[kGroup], ahead[kGroup];
+    auto fetch = [&](uint32_t g, uint32_t (&to)[kGroup]) {
+#pragma unroll
+        for (uint32_t j = 0; j < kGroup; ++j) {
+            const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
+            to[j] = (g + j < iters && sy < nbins) ? (uint32_t)a.len[sy] : 0u;
+        }
+    };
+    fetch(0, len);
     if (tid == 0) {
         if (a.status_out) *a.status_out = 0;
-        uint32_t ok = 1;
-        s_nbins = a.nbins;
-        s_chunk = 64u;
+        uint32_t ok = readable ? 1u : 0u;
         if (a.hdr) {
             const Header h = *a.hdr;
             const Header &e = a.expect;
@@ -932,9 +955,7 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
             if (h.magic != kMagic || (h.version != 1u && h.version != 2u) || h.status != 0u) ok = 0;
             if (h.N != e.N || h.C != e.C || h.H != e.H || h.W != e.W) ok = 0;
             if (h.nbins < 4u || h.nbins > 65536u || (h.nbins & 1u)) ok = 0;
-            s_nbins = h.nbins;
             if (h.chunk_syms == 0) ok = 0;
-            s_chunk = h.chunk_syms;
             const float eb = __uint_as_float(h.eb_bits);
             if (!(eb >= 0x1p-100f && eb <= 0x1p100f)) ok = 0;
             if (__float_as_uint(2.0f * eb) != h.ebx2_bits) ok = 0;
@@ -950,32 +971,53 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
         }
         s_ok = ok;
     }
-    if (tid < 65) s_cnt[tid] = 0;
-    __syncthreads();
-    if (!s_ok) {
-        if (tid == 0) raise_format();
-        return;
-    }
-    const uint32_t nbins = s_nbins;
 
-    // ---- symbols per length ----
-    uint32_t m = 0;
+    // ---- symbols per length: lane L of a wavefront counts its symbols of length L ----
+    // (one step per length that occurs among 64 symbols; f(length, lanes that have it))
+    auto each_length = [&](uint32_t L, auto f) {
+        uint64_t todo = wave_ballot(L != 0u);
+        while (todo) {
+            const uint32_t Lc = (uint32_t)__builtin_amdgcn_readlane((int)L, __builtin_ctzll(todo));
+            const uint64_t same = wave_ballot(L == Lc);
+            f(Lc, same);
+            todo &= ~same;
+        }
+    };
+    uint32_t mine = 0;
     bool bad = false;
-    for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-        const uint32_t s = base + tid;
-        const uint32_t L = (s < nbins) ? a.len[s] : 0u;
-        if (L > 57u) bad = true;
-        if (L) atomicAdd(&s_cnt[L > 64u ? 64u : L], 1u);
-        m += __syncthreads_count(L != 0u);
+    for (uint32_t g = 0; g < iters; g += kGroup) {
+        if (g + kGroup < iters) fetch(g + kGroup, ahead);
+#pragma unroll
+        for (uint32_t j = 0; j < kGroup; ++j) {
+            if (g + j >= iters) continue;                    // (uniform)
+            bad = bad || len[j] > 57u;
+            each_length(len[j] > 57u ? 0u : len[j], [&](uint32_t Lc, uint64_t same) { mine += lane == Lc ? (uint32_t)__popcll(same) : 0u; });
+        }
+        if (g + kGroup < iters) {
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) len[j] = ahead[j];
+        }
     }
-    if (__syncthreads_or(bad ? 1 : 0) || m == 0) {
+    s_wc[wave][lane] = mine;
+    bad = __syncthreads_or(bad ? 1 : 0) != 0;
+    if (!s_ok || bad) {
         if (tid == 0) raise_format();
         return;
     }
     if (tid < (uint32_t)kWave) {
+        uint32_t run = 0;
+        for (uint32_t w = 0; w < kWaves; ++w) {
+            const uint32_t c = s_wc[w][lane];
+            s_wc[w][lane] = run;
+            run += c;
+        }
+        s_cnt[lane] = run;
+        if (lane == 0) s_cnt[64] = 0;
+        const uint32_t m = (uint32_t)wave_sum<uint32_t>(run);
+        wave_lds_fence();
         uint32_t mx, mn;
-        const bool ok = canonical_first_codes_wave(s_cnt, m, s_first, s_findex, &mx, &mn);
-        if (tid == 0) { s_maxlen = mx; s_ok = ok ? 1u : 0u; }
+        const bool ok = m != 0u && canonical_first_codes_wave(s_cnt, m, s_first, s_findex, &mx, &mn);
+        if (tid == 0) { s_maxlen = mx; s_m = m; s_ok = ok ? 1u : 0u; }
         if (ok) {
             wave_lds_fence();                                // the first codes of the other lengths
             const uint32_t L = tid ? tid : 64u;              // one length per lane
@@ -984,6 +1026,10 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
             if (L < mx) lim = (s_first[L] + s_cnt[L]) << (64u - L);
             else lim = ~0ull;
             s_limit[L] = lim;
+            if (L < 20u) {
+                s_lim18[L] = L < mx ? (uint32_t)(lim >> 46) : 1u << 18;
+                s_off[L] = s_findex[L] - (uint32_t)s_first[L];
+            }
             a.t.limit[L] = lim;
             a.t.first_code[L] = s_first[L];
             a.t.first_index[L] = s_findex[L];
@@ -998,88 +1044,72 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
         if (tid == 0) raise_format();
         return;
     }
-    // ---- canonical order: by length, then by symbol.  The symbols are visited in increasing order,
-    // so the place of a symbol is the first index of its length plus the number of smaller symbols of
-    // the same length: a counting sort (per wavefront the lanes of one length are found with a ballot
-    // per length that occurs, then a prefix over the wavefronts in front). ----
-    const bool small = m <= (uint32_t)kBookBlock * 2u;
-    uint16_t *sorted = small ? s_sorted : a.t.sorted;
+    const uint32_t m = s_m, mx = s_maxlen;
+    // ---- canonical order: by length, then by symbol.  The symbols are visited in increasing order, so the place of a
+    // symbol is the first index of its length plus the number of smaller symbols of the same length (lane L: the next
+    // place for length L among my wavefront's symbols) ----
     {
-        const uint32_t lane = tid & (uint32_t)(kWave - 1), wave = tid / (uint32_t)kWave;
-        constexpr uint32_t kWaves = kBookBlock / kWave;
-        for (uint32_t i = tid; i < 65u; i += kBookBlock) s_run[i] = 0;
-        for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-            for (uint32_t i = tid; i < kWaves * 64u; i += kBookBlock) s_wc[i] = 0;
-            __syncthreads();
-            const uint32_t s = base + tid;
-            const uint32_t L = (s < nbins) ? a.len[s] : 0u;  // 1 .. 57 here
-            uint32_t in_wave = 0;
-            uint64_t todo = wave_ballot(L != 0u);
-            while (todo) {                                   // one step per length that occurs in the wavefront
-                const uint32_t Lc = (uint32_t)__builtin_amdgcn_readlane((int)L, __builtin_ctzll(todo));
-                const uint64_t same = wave_ballot(L == Lc);
-                if (L == Lc) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-                if (lane == 0) s_wc[wave * 64u + Lc] = (uint32_t)__popcll(same);
-                todo &= ~same;
+        if (iters > kGroup) fetch(0, len);                   // (else they are still there)
+        uint32_t next = lane ? s_findex[lane] + s_wc[wave][lane] : 0u;
+        for (uint32_t g = 0; g < iters; g += kGroup) {
+            if (g + kGroup < iters) fetch(g + kGroup, ahead);
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) {
+                if (g + j >= iters) continue;
+                const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
+                uint32_t pos = 0;
+                each_length(len[j], [&](uint32_t Lc, uint64_t same) {
+                    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)next, (int)Lc);
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+                    pos = len[j] == Lc ? at + rank : pos;
+                    next += lane == Lc ? (uint32_t)__popcll(same) : 0u;
+                });
+                if (len[j]) {
+                    a.t.sorted[pos] = (uint16_t)sy;
+                    if (pos < kLut16MaxBins) s_sorted[pos] = (uint16_t)sy;
+                }
             }
-            __syncthreads();
-            if (L) {
-                uint32_t before = s_run[L];
-                for (uint32_t w = 0; w < wave; ++w) before += s_wc[w * 64u + L];
-                sorted[s_findex[L] + before + in_wave] = (uint16_t)s;
+            if (g + kGroup < iters) {
+#pragma unroll
+                for (uint32_t j = 0; j < kGroup; ++j) len[j] = ahead[j];
             }
-            __syncthreads();
-            if (tid < 64u && tid) {                          // symbols of each length so far
-                uint32_t add = 0;
-                for (uint32_t w = 0; w < kWaves; ++w) add += s_wc[w * 64u + tid];
-                s_run[tid] += add;
-            }
-            __syncthreads();                                 // the counts are cleared for the next 1024 symbols
         }
     }
-    if (small) {
-        for (uint32_t p = tid; p < m; p += kBookBlock) a.t.sorted[p] = sorted[p];
-    }
+    __syncthreads();
 
-    // look-up table on the next kLutBits bits; entries carry the residual, not the symbol
-    const uint32_t mx = s_maxlen;
-    // Length of the code a left-aligned bit pattern v starts with, searched in [lo, hi]: the smallest L with
-    // v below the upper bound of the codes of length L (the bounds do not decrease with L, and the longest
-    // length closes the code space); 0 if the code is longer than hi.  A handful of LDS reads.
-    auto code_length = [&](uint64_t v, uint32_t lo, uint32_t hi) -> uint32_t {
-        if (hi > mx) hi = mx;
-        if (lo > hi) return 0u;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (mid >= mx || v < s_limit[mid]) hi = mid; else lo = mid + 1u;
-        }
-        return (lo >= mx || v < s_limit[lo]) && s_cnt[lo] ? lo : 0u;
-    };
+    // ---- look-up tables; entries carry the residual, not the symbol ----
+    // Length of the code that the bits v, left-aligned in 18, start with, if it is one of lo .. hi bits (else hi + 1): one
+    // more than the number of limits it reaches.  lim[i]: the limit of length lo + i.
     const int32_t radius = (int32_t)(nbins / 2u);
     const bool compact = nbins <= kLut16MaxBins;
-    const bool skip_general = compact && a.compact_only && !(a.general_unless_chunk64 && s_chunk != 64u);
-    for (uint32_t e = tid; e < (skip_general ? 0u : kLutSize); e += kBookBlock) {
-        const uint64_t v = (uint64_t)e << (64 - kLutBits);
-        uint32_t entry = 0;
-        {
-            const uint32_t L = code_length(v, 1u, (uint32_t)kLutBits);
-            if (L) {
-                uint64_t off = (v >> (64u - L)) - s_first[L];
-                if (off >= s_cnt[L]) off = s_cnt[L] - 1u;      // only reachable with an invalid stream
-                const uint32_t sym = sorted[s_findex[L] + off];
-                const int32_t d = sym ? (int32_t)sym - radius : -32768;
-                entry = ((uint32_t)d << 8) | L;
+    const bool skip_general = compact && a.compact_only && !(a.general_unless_chunk64 && chunk != 64u);
+    auto symbol_of = [&](uint32_t v18, uint32_t L) -> uint32_t {
+        const uint32_t idx = s_off[L] + (v18 >> (18u - L));
+        return s_sorted[idx < m ? idx : m - 1u];             // (beyond: a code of a single symbol, the bit pattern that is no code)
+    };
+    if (!skip_general) {
+        uint32_t lim[kLutBits];
+#pragma unroll
+        for (int i = 0; i < kLutBits; ++i) lim[i] = s_lim18[i + 1];
+        for (uint32_t e = tid; e < kLutSize; e += kBookBlock) {
+            const uint32_t v18 = e << (18 - kLutBits);
+            uint32_t L = 1;
+#pragma unroll
+            for (int i = 0; i < kLutBits; ++i) L += v18 >= lim[i] ? 1u : 0u;
+            uint32_t entry;
+            if (L <= (uint32_t)kLutBits) {
+                const uint32_t sym = symbol_of(v18, L);
+                entry = ((uint32_t)(sym ? (int32_t)sym - radius : -32768) << 8) | L;
+            } else {
+                // no code of at most kLutBits bits starts here: length byte 0, and in the residual field the
+                // shortest length a code with this prefix can have (where the decoder's search starts)
+                const uint64_t v = (uint64_t)e << (64 - kLutBits);
+                while (L < mx && v >= s_limit[L]) ++L;
+                entry = L << 8;
             }
+            a.t.lut[e] = entry;
+            if (!compact) reinterpret_cast<uint32_t *>(a.t.lut16)[e] = entry;    // the chunk decoders load their table from one place
         }
-        if (entry == 0) {
-            // no code of at most kLutBits bits starts here: length byte 0, and in the residual field the
-            // shortest length a code with this prefix can have (where the decoder's search starts)
-            uint32_t L = code_length(v, (uint32_t)kLutBits + 1u, mx);
-            if (L == 0u) L = mx;
-            entry = L << 8;
-        }
-        a.t.lut[e] = entry;
-        if (!compact) reinterpret_cast<uint32_t *>(a.t.lut16)[e] = entry;    // the chunk decoders load their table from one place
     }
     // The compact table on the next kLut16Bits bits, for alphabets whose residuals fit 12 signed bits, and
     // its second level.  A prefix of kLut16Bits bits under which longer codes lie gets a sub-table indexed by
@@ -1087,72 +1117,56 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     // (residual << 4) | (length - kLut16Bits), or 0 for a code that is longer still.  The first-level entry of
     // such a prefix is ((offset / 2) << 2 | width code) << 4 with a zero length; offset 0 is never given out,
     // so an all-zero entry means "no sub-table" (the sub-tables filled their array: search by length).
+    // Canonical codes grow in length with their value: the prefixes with longer codes are e0, e0 + 1, ... to the end,
+    // and the first of them have nothing beyond 13 bits, the next nothing beyond 14, then 16: four classes in a row.
     if (compact) {
         constexpr uint32_t kPer = kLut16Size / kBookBlock;          // consecutive first-level entries per thread
-        uint32_t ent[kPer], kbits[kPer], need = 0;
-        for (uint32_t j = 0; j < kPer; ++j) {
-            const uint32_t e = tid * kPer + j;
-            const uint64_t v = (uint64_t)e << (64 - kLut16Bits);
-            uint32_t entry = 0;
-            {
-                const uint32_t L = code_length(v, 1u, (uint32_t)kLut16Bits);
-                if (L) {
-                    uint64_t off = (v >> (64u - L)) - s_first[L];
-                    if (off >= s_cnt[L]) off = s_cnt[L] - 1u;      // only reachable with an invalid stream
-                    const uint32_t sym = sorted[s_findex[L] + off];
-                    const int32_t d = sym ? (int32_t)sym - radius : kLut16Escape;
-                    entry = (((uint32_t)d & 0xfffu) << 4) | L;
+        static_assert(kPer == 4u && kLut16Bits == 12, "packed stores, classes");
+        auto prefixes_within = [&](uint32_t L) -> uint32_t { return s_lim18[L] >> 6; };     // whose codes all have at most L bits
+        const uint32_t e0 = prefixes_within(12), e1 = prefixes_within(13), e2 = prefixes_within(14), e3 = prefixes_within(16);
+        const uint32_t o1 = 2u, o2 = o1 + 2u * (e1 - e0), o3 = o2 + 4u * (e2 - e1), o4 = o3 + 16u * (e3 - e2), end = o4 + 64u * (kLut16Size - e3);
+        {
+            uint32_t lim[kLut16Bits];
+#pragma unroll
+            for (int i = 0; i < kLut16Bits; ++i) lim[i] = s_lim18[i + 1];
+            uint32_t ent[kPer];
+#pragma unroll
+            for (uint32_t j = 0; j < kPer; ++j) {
+                const uint32_t e = tid * kPer + j, v18 = e << 6;
+                uint32_t L = 1;
+#pragma unroll
+                for (int i = 0; i < kLut16Bits; ++i) L += v18 >= lim[i] ? 1u : 0u;
+                if (L <= (uint32_t)kLut16Bits) {
+                    const uint32_t sym = symbol_of(v18, L);
+                    ent[j] = (((uint32_t)(sym ? (int32_t)sym - radius : kLut16Escape) & 0xfffu) << 4) | L;
+                } else {
+                    const uint32_t k = e < e1 ? 0u : (e < e2 ? 1u : (e < e3 ? 2u : 3u));                 // class
+                    const uint32_t kb = (0x6421u >> (k * 4u)) & 0xfu;
+                    const uint32_t at = (k == 0u ? o1 - (e0 << 1) : (k == 1u ? o2 - (e1 << 2) : (k == 2u ? o3 - (e2 << 4) : o4 - (e3 << 6)))) + (e << kb);
+                    ent[j] = at + (1u << kb) <= kSubEntries ? (((at >> 1) << 2) | k) << 4 : 0u;
                 }
             }
-            ent[j] = entry;
-            kbits[j] = 0;
-            if (entry == 0) {
-                // the longest code under this prefix is the one its last bit pattern belongs to
-                const uint64_t v_hi = v | ((1ull << (64 - kLut16Bits)) - 1ull);
-                uint32_t L = code_length(v_hi, (uint32_t)kLut16Bits + 1u, mx);
-                if (L == 0u) L = mx;
-                const uint32_t k = L - (uint32_t)kLut16Bits;
-                kbits[j] = k <= 1u ? 1u : (k <= 2u ? 2u : (k <= 4u ? 4u : 6u));
-                need += 1u << kbits[j];
-            }
+            reinterpret_cast<uint2 *>(a.t.lut16)[tid] = make_uint2(ent[0] | (ent[1] << 16), ent[2] | (ent[3] << 16));
         }
-        uint32_t total;
-        uint32_t at = 2u + block_excl_scan<uint32_t, kBookBlock / kWave>(need, s_scan, total);
-        // first-level entries; every sub-table entry learns which prefix it belongs to
-        for (uint32_t j = 0; j < kPer; ++j) {
-            const uint32_t e = tid * kPer + j;
-            if (kbits[j]) {
-                const uint32_t kb = kbits[j], size = 1u << kb;
-                if (at + size <= kSubEntries) {
-                    const uint32_t kcode = kb == 1u ? 0u : (kb == 2u ? 1u : (kb == 4u ? 2u : 3u));
-                    ent[j] = (((at >> 1) << 2) | kcode) << 4;
-                    for (uint32_t i = 0; i < size; ++i) s_owner[at + i] = (uint16_t)e;
-                }
-                at += size;
-            }
-            s_ent[e] = (uint16_t)ent[j];
-            a.t.lut16[e] = (uint16_t)ent[j];
-        }
-        __syncthreads();
         // the sub-table entries, one thread each
-        const uint32_t used = (2u + total < kSubEntries) ? 2u + total : kSubEntries;
+        uint32_t lim[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) lim[i] = s_lim18[13 + i];
+        const uint32_t used = end < kSubEntries ? end : kSubEntries;
         for (uint32_t x = tid; x < used; x += kBookBlock) {
             uint32_t entry = 0;
             if (x >= 2u) {
-                const uint32_t e = s_owner[x] & (kLut16Size - 1u);      // (an entry past the last sub-table that fitted holds anything)
-                const uint32_t pe = s_ent[e];
-                const uint32_t kb = (0x6421u >> (((pe >> 4) & 3u) * 4u)) & 0xfu;
-                const uint32_t first = (pe >> 6) << 1;
-                if (pe != 0u && (pe & 0xfu) == 0u && x >= first && x - first < (1u << kb)) {       // (always, for an entry inside an allocated sub-table)
-                    const uint64_t v = ((uint64_t)e << (64 - kLut16Bits)) | ((uint64_t)(x - first) << (64 - kLut16Bits - kb));
-                    const uint32_t L = code_length(v, (uint32_t)kLut16Bits + 1u, (uint32_t)kLut16Bits + kb);
-                    if (L) {
-                        uint64_t off = (v >> (64u - L)) - s_first[L];
-                        if (off >= s_cnt[L]) off = s_cnt[L] - 1u;  // only reachable with an invalid stream
-                        const uint32_t sym = sorted[s_findex[L] + off];
-                        const int32_t d = sym ? (int32_t)sym - radius : kLut16Escape;
-                        entry = (((uint32_t)d & 0xfffu) << 4) | (L - (uint32_t)kLut16Bits);
-                    }
+                const uint32_t k = x < o2 ? 0u : (x < o3 ? 1u : (x < o4 ? 2u : 3u));
+                const uint32_t kb = (0x6421u >> (k * 4u)) & 0xfu;
+                const uint32_t rel = x - (k == 0u ? o1 : (k == 1u ? o2 : (k == 2u ? o3 : o4)));
+                const uint32_t first = k == 0u ? e0 : (k == 1u ? e1 : (k == 2u ? e2 : e3));
+                const uint32_t v18 = ((first << kb) + rel) << (6u - kb);
+                uint32_t L = 13;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) L += v18 >= lim[i] ? 1u : 0u;
+                if (L <= (uint32_t)kLut16Bits + kb) {
+                    const uint32_t sym = symbol_of(v18, L);
+                    entry = (((uint32_t)(sym ? (int32_t)sym - radius : kLut16Escape) & 0xfffu) << 4) | (L - (uint32_t)kLut16Bits);
                 }
             }
             a.t.sub16[x] = (uint16_t)entry;
