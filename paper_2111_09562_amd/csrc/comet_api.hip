@@ -259,7 +259,21 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         a.hist_copies = hist_copies(nbins);
         a.hist_shift = a.win_n <= 2048u ? 2u : 0u;            // four copies while they fit 32 KB
         const bool full = a.win_n == nbins;
-        const size_t lds = (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u + (full ? 0u : (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u);
+        const size_t lds = full ? (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u : 0u;
+        // (an alphabet larger than the window: the codes are counted from memory, behind the sweep)
+        auto count_codes = [&]() {
+            if (full || reuse_len) return;
+            CodeHistArgs h{};
+            h.codes = codes; h.n = n; h.nbins = nbins; h.radius = nbins / 2u;
+            h.win_n = nbins < kCodeHistWindow ? nbins : kCodeHistWindow;
+            h.win_lo = (nbins - h.win_n) / 2u;
+            h.parts = hist_parts; h.copies = a.hist_copies;
+            // one workgroup per compute unit, with at least 8192 codes (clearing and adding up its bins costs as much as those)
+            uint64_t wg = (n + 8191u) / 8192u;
+            if (wg > (uint64_t)ctx->num_cu) wg = (uint64_t)ctx->num_cu;
+            const size_t lds_h = ((size_t)h.win_n + 4u * kCodeHistHot + kCodeHistBlock) * 4u;
+            hipLaunchKernelGGL(k_code_hist, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
+        };
 #define COMET_LAUNCH_QR_IN(VEC, NSEG, MULTI, IN)                                                                       \
         do {                                                                                                           \
             {                                                                                                          \
@@ -267,6 +281,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
                 if (full) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, true, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);   \
                 else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, false, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);       \
             }                                                                                                          \
+            count_codes();                                                                                             \
             TimedScope ts(ctx, st, COMET_KERNEL_GATHER);                                                               \
             hipLaunchKernelGGL((k_gather_records<VEC, NSEG, MULTI, false, IN>), dim3(grid), dim3(kQuantBlock), 0, st, a); \
         } while (0)
@@ -424,14 +439,13 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
         }
         // a few wavefronts per SIMD, but runs of at least 2048 elements (every run re-reads one row)
         // All runs should be resident at once: a run that has to wait for a place makes the launch take two rounds.
-        // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (the
-        // histogram window of a large alphabet leaves room for three; the encoder's ring and tables of the single-pass
+        // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (a
+        // histogram window of 8192 bins leaves room for three; the encoder's ring and tables of the single-pass
         // compression for four).
         uint32_t runs_per_simd = chunk_align ? kQuantRunsPerSimdSingle : kQuantRunsPerSimd;
         if (!chunk_align) {
-            const uint32_t win_n = nbins < kHistWindowMax ? nbins : kHistWindowMax;
-            const size_t lds = (((size_t)win_n << (win_n <= 2048u ? 2u : 0u)) + kQuantBlock) * 4u + kQuantStaticLds +
-                               (win_n < nbins ? (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u : 0u);
+            const size_t window = nbins <= kHistWindowMax ? (((size_t)nbins << (nbins <= 2048u ? 2u : 0u)) + kQuantBlock) * 4u : 0u;
+            const size_t lds = window + kQuantStaticLds;
             const uint32_t fit = (uint32_t)(kLdsPerCu / lds);
             if (fit < runs_per_simd) runs_per_simd = fit ? fit : 1u;
         }
@@ -528,6 +542,9 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     if ((e = hipFuncSetAttribute((const void *)k_reconstruct<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
         return fail(hip_fail(e, "hipFuncSetAttribute(k_reconstruct<1>)"));
     if (fused_opt_in() != COMET_OK) return fail(COMET_ERR_HIP);
+    if ((e = hipFuncSetAttribute((const void *)k_code_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
+        return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->occ_quant, k_quantize<true>, kQuantBlock, 4096 + kQuantRecLds * 8) != hipSuccess || c->occ_quant < 1) c->occ_quant = 4;
     (void)rc;
     *out = c;

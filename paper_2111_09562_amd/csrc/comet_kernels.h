@@ -8,7 +8,7 @@ namespace comet {
 // ---- quantise (prequantise + Lorenzo + codes + histogram + records) ----------
 constexpr int kQuantBlock = 256;
 constexpr int kQuantTile = 4096;           // elements per tile: 256 lanes x 4 iterations x float4
-constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup
+constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup (row-walking kernel: larger alphabets are counted by k_code_hist)
 
 struct QuantArgs {
     const void *x;             // fp32; the row-walking kernels also take IEEE half or bfloat16 (template parameter IN)
@@ -53,20 +53,33 @@ constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane of the row-walking ker
 constexpr uint32_t kQuantRecRun = 768;    // outlier records staged per run (one run of rows per wavefront)
 constexpr uint32_t kQuantRecLds2 = 256;   // records a wavefront buffers in LDS before it writes them to the staging area in bulk
 constexpr uint32_t kQuantRunsPerSimd = 5; // runs the launch aims at, per SIMD
-constexpr uint32_t kQuantOowList = 512;   // codes outside the LDS histogram window a wavefront lists before it adds them to the global histogram
 constexpr uint32_t kQuantStaticLds = 8448; // static LDS of k_quantize_rows (the record buffers of its four wavefronts and a few words), rounded up
 constexpr uint32_t kLdsPerCu = 160u * 1024u;
 constexpr uint32_t kQuantRunsPerSimdSingle = 4;   //   ... of the single-pass compression (all of them resident at once)
 constexpr uint32_t kQuantHistCopiesMax = 32;        // partial histograms the workgroups spread their flushes over
 constexpr uint32_t kQuantHistPartsWords = 8u * 65536u;    // all copies together have at most this many entries (2 MB: eight copies of the largest alphabet)
 // VEC adjacent columns per lane (2 needs an even W and 8-byte aligned input), NSEG segments of 64 lanes per row,
-// MULTI: several rows per step
+// MULTI: several rows per step; FULLWIN: the histogram is made here (every bin is in the LDS window), else by k_code_hist from the codes
 // REUSE: code book reuse: escapes follow the given length table, no histogram (FULLWIN is then true and unused)
 // IN: element type of x (0 fp32, 1 IEEE half, 2 bfloat16; 16-bit inputs are widened exactly as they are loaded;
 // VEC = 2 then needs 4-byte aligned input)
 template <int VEC, int NSEG, bool MULTI, bool FULLWIN, bool REUSE = false, int IN = 0> __global__ void k_quantize_rows(QuantArgs a);
 template <int VEC, int NSEG, bool MULTI, bool REUSE = false, int IN = 0> __global__ void k_gather_records(QuantArgs a);
 constexpr uint32_t kQuantReuseMaxBins = 8192;   // largest alphabet whose length table the REUSE kernels keep in LDS
+
+// ---- histogram of the codes of a large alphabet ----------------------------------
+constexpr int kCodeHistBlock = 1024;
+constexpr uint32_t kCodeHistWindow = 32768;   // bins counted in LDS at most (128 KB: one workgroup per compute unit)
+constexpr uint32_t kCodeHistHot = 1024;       // innermost bins with four counters each
+struct CodeHistArgs {
+    const uint16_t *codes;     // 8-byte aligned (its 16-byte loads need four)
+    uint64_t n;
+    uint32_t nbins, radius;
+    uint32_t win_lo, win_n;    // bins counted in LDS
+    uint32_t *parts;           // `copies` partial histograms of nbins entries
+    uint32_t copies;
+};
+__global__ void k_code_hist(CodeHistArgs a);
 
 // ---- statistics ---------------------------------------------------------------
 constexpr int kStatsBlock = 256;

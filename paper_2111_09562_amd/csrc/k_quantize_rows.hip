@@ -80,10 +80,7 @@ template <int IN> __device__ inline float load_elem(const void *x, size_t i) {
 
 struct SweepCounts {
     uint32_t nnz_lane = 0;      // per lane: non-zero inputs
-    uint32_t oow = 0;           // wavefront-uniform: codes outside the LDS window (counted in the global histogram)
     uint32_t vrec = 0;          // wavefront-uniform: verbatim records
-    uint16_t *oow_list = nullptr;   // LDS, kQuantOowList entries of this wavefront: such codes on their way to the global histogram
-    uint32_t oow_held = 0;      // wavefront-uniform: entries of the list in use
 };
 
 // One sweep of a wavefront over rows [row_lo, row_hi).  PASS 0: everything (codes, histogram,
@@ -92,7 +89,7 @@ struct SweepCounts {
 // VEC: adjacent columns per lane (1, or 2 for even W: one 8-byte load, one packed code store and
 // one cross-lane shift per pair); NSEG: segments of 64 lanes per row (1, 2, 4, 8); MULTI: a row
 // takes at most 32 lanes, K rows per step (NSEG == 1); FULLWIN: every histogram bin is in the LDS
-// window.
+// window, and the codes are counted here (else k_code_hist does that).
 // REUSE: code book reuse.  s_len (LDS, u8[nbins]) holds the code lengths the caller brought; a code
 // whose length is 0 becomes an escape, there is no histogram, and an escape that the table has no
 // code word for raises ST_CODEBOOK.  In PASS 0 the codes go to the ring of `enc` in LDS and are encoded
@@ -215,15 +212,6 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
         cur += buffered;
         buffered = 0;
     };
-    auto flush_oow = [&]() {                                     // the listed codes -> global histogram
-        wave_lds_fence();
-        // (into the workgroup's partial histogram: the codes just outside the window are few and frequent, and all
-        // workgroups adding to one copy of them queue up on a handful of cache lines)
-        uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
-        for (uint32_t i = lane; i < cnt.oow_held; i += kWave) atomicAdd(&part[cnt.oow_list[i]], 1u);
-        wave_lds_fence();
-        cnt.oow_held = 0;
-    };
     uint16_t *ring_w = (PASS == 0 && REUSE) ? const_cast<uint16_t *>(enc->ring) : nullptr;
     // REUSE: does the given table have a code word for this code?  From the length table; the single-pass sweep with
     // the whole encode table in LDS reads that instead (an entry is 0 for a symbol without a code word), which saves
@@ -307,31 +295,13 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                     sm[v] = wave_ballot(susp[v]) & vmask;
                     any_rec |= em[v] | sm[v];
                     if (PASS == 0) cnt.nnz_lane += (x[v] != 0.0f) ? 1u : 0u;   // lanes without an element hold 0
-                    if (PASS == 0 && !REUSE) {
+                    if (PASS == 0 && !REUSE && FULLWIN) {
                         // Histogram: no divergent branch (switching the execution mask costs more than the
                         // atomic).  Lanes that count nothing add to a word of their own; the centre bin is
                         // not counted here, it is what is left of the workgroup's elements.  The window is
                         // replicated: lanes that meet in one bin mostly use different copies.
                         const bool count = valid && code[v] != (uint32_t)radius;
-                        if (FULLWIN) {
-                            atomicAdd(&s_hist[count ? (code[v] << a.hist_shift) + hist_sub : hist_dummy], 1u);
-                        } else {
-                            const uint32_t bin = code[v] - a.win_lo;
-                            const bool inwin = bin < a.win_n;
-                            atomicAdd(&s_hist[(count && inwin) ? (bin << a.hist_shift) + hist_sub : hist_dummy], 1u);
-                            // A code outside the window goes to a list in LDS and from there, in bulk, to the global
-                            // histogram: an atomic on global memory in this loop would make every step wait for all
-                            // loads in flight.
-                            const uint64_t om = wave_ballot(count && !inwin);
-                            if (om != 0ull) {                   // uniform
-                                const uint32_t n_new = (uint32_t)__popcll(om);
-                                if (cnt.oow_held + n_new > kQuantOowList) flush_oow();
-                                if (count && !inwin)
-                                    cnt.oow_list[cnt.oow_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u))] = (uint16_t)code[v];
-                                cnt.oow_held += n_new;
-                                cnt.oow += n_new;
-                            }
-                        }
+                        atomicAdd(&s_hist[count ? (code[v] << a.hist_shift) + hist_sub : hist_dummy], 1u);
                     }
                 }
                 if (PASS == 0 && REUSE) {
@@ -417,7 +387,6 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
     }
     drain(n_el, true);
     flush_records();
-    if (PASS == 0 && !REUSE && !FULLWIN && cnt.oow_held) flush_oow();
     return cur;
 }
 
@@ -465,7 +434,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
             for (uint32_t i = tid; i < a.nbins; i += kQuantBlock) s_len[i] = a.reuse_len[i];
         for (uint32_t i = tid; i <= a.enc_n; i += kQuantBlock) s_tbl[i] = (i < a.enc_n) ? a.enc[a.enc_lo + i] : 0ull;
         for (uint32_t i = lane; i < kEncRunBufWords; i += kWave) s_asm[i] = 0;
-    } else {
+    } else if (FULLWIN) {
         for (uint32_t i = tid; i < (a.win_n << a.hist_shift); i += kQuantBlock) s_hist[i] = 0;
     }
     __syncthreads();
@@ -474,8 +443,6 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     uint32_t row_lo, row_hi;
     run_rows(a, run, &row_lo, &row_hi);
     SweepCounts cnt;
-    // (a window that does not hold every bin: behind it and the threads' dummy words, a list per wavefront)
-    if (!REUSE && !FULLWIN) cnt.oow_list = reinterpret_cast<uint16_t *>(s_hist + (a.win_n << a.hist_shift) + kQuantBlock) + wave * kQuantOowList;
     uint32_t my_records = 0;
     RunEncoder enc;
     TableView<FULLWIN> tbl{s_tbl, a.enc, a.enc_lo, a.enc_n, a.nbins};
@@ -516,14 +483,14 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         for (int w = 0; w < kWaves; ++w) t += s_tot[w][tid];
         a.run_count[gridDim.x * kWaves + tid * gridDim.x + blockIdx.x] = t;   // three arrays of one entry per workgroup
     }
-    if (REUSE) return;                              // no histogram (uniform: every thread has passed the barrier above)
+    if (REUSE || !FULLWIN) return;                  // no histogram (uniform: every thread has passed the barrier above)
     uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
-    uint64_t counted = (FULLWIN || lane != 0u) ? 0ull : (uint64_t)cnt.oow;
+    uint64_t counted = 0;
     for (uint32_t i = tid; i < a.win_n; i += kQuantBlock) {
         uint32_t v = 0;
         for (uint32_t k = 0; k < (1u << a.hist_shift); ++k) v += s_hist[(i << a.hist_shift) + k];
         counted += v;
-        if (v) atomicAdd(&part[a.win_lo + i], v);
+        if (v) atomicAdd(&part[i], v);
     }
     uint64_t total;
     (void)block_excl_scan<uint64_t, kWaves>(counted, s_part64, total);
@@ -554,10 +521,9 @@ __global__ __launch_bounds__(kQuantBlock) void k_gather_records(QuantArgs a) {
         for (uint32_t i = tid; i < a.nbins; i += kQuantBlock) s_len[i] = a.reuse_len[i];
         __syncthreads();
     }
-    // histogram: one thread per bin adds up the partial histograms (codes outside the LDS window of
-    // the quantise kernel were counted in hist directly)
+    // histogram: one thread per bin adds up the partial histograms
     for (uint32_t b = blockIdx.x * kQuantBlock + tid; !REUSE && b < a.nbins; b += gridDim.x * kQuantBlock) {
-        uint32_t v = a.hist[b];                                             // (codes outside the LDS window)
+        uint32_t v = 0;
         uint32_t p[kQuantHistCopiesMax];                                    // every copy in flight at once: one round trip
 #pragma unroll
         for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) p[j] = (j < a.hist_copies) ? a.hist_parts[(size_t)j * a.nbins + b] : 0u;
