@@ -521,6 +521,7 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
         const uint64_t o_sub16 = o; o += 2ull * kSubEntries;
         const uint64_t o_meta = o; o += 64;
         const uint64_t o_sorted = o; o += 2ull * kMaxBins;
+        const uint64_t o_resid = o; o += 2ull * kMaxBins;
         uint8_t *blob = nullptr;
         if ((e = hipMalloc((void **)&blob, align_up(o, 256))) != hipSuccess) return fail(COMET_ERR_NOMEM);
         c->tables_blob = blob;
@@ -529,6 +530,7 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
         c->tables.limit = (uint64_t *)(blob + o_limit); c->tables.first_code = (uint64_t *)(blob + o_first);
         c->tables.first_index = (uint32_t *)(blob + o_findex); c->tables.lut = (uint32_t *)(blob + o_lut);
         c->tables.meta = (uint32_t *)(blob + o_meta); c->tables.sorted = (uint16_t *)(blob + o_sorted);
+        c->tables.resid = (uint16_t *)(blob + o_resid);
         c->tables.lut16 = (uint16_t *)(blob + o_lut16);
         c->tables.sub16 = (uint16_t *)(blob + o_sub16);
     }
@@ -1027,7 +1029,8 @@ constexpr size_t kSsLut = kSsMeta + 64;
 constexpr size_t kSsLut16 = kSsLut + 4 * kLutSize;
 constexpr size_t kSsSub16 = kSsLut16 + 2 * kLut16Size;
 constexpr size_t kSsSorted = kSsSub16 + 2 * kSubEntries;
-constexpr size_t kSsResid = (kSsSorted + 2 * (size_t)kMaxBins + 255) / 256 * 256;
+constexpr size_t kSsSymResid = kSsSorted + 2 * (size_t)kMaxBins;
+constexpr size_t kSsResid = (kSsSymResid + 2 * (size_t)kMaxBins + 255) / 256 * 256;
 constexpr size_t kSsBand = (kSsResid + 2 * (size_t)kStaticMaxElems + 256 + 255) / 256 * 256;
 constexpr size_t kSsBytes = kSsBand + (size_t)band_bytes_max(kStaticMaxElems);
 static_assert(sizeof(DevState) <= kSsLimit && kSsMeta % 16 == 0 && kSsLut % 16 == 0, "scratch layout");
@@ -1089,6 +1092,7 @@ int comet_decompress_static(const void *dev_in, uint64_t bytes, comet_shape s, v
     ws.tables.lut16 = reinterpret_cast<uint16_t *>(base + kSsLut16);
     ws.tables.sub16 = reinterpret_cast<uint16_t *>(base + kSsSub16);
     ws.tables.sorted = reinterpret_cast<uint16_t *>(base + kSsSorted);
+    ws.tables.resid = reinterpret_cast<uint16_t *>(base + kSsSymResid);
     ws.resid = reinterpret_cast<int16_t *>(base + kSsResid);
     ws.band = base + kSsBand; ws.band_bytes = kSsBytes - kSsBand;
     ws.max_elems = kStaticMaxElems; ws.num_cu = sd.num_cu; ws.chunk_syms = COMET_DEFAULT_CHUNK_SYMS;

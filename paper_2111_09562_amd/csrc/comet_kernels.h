@@ -182,6 +182,10 @@ constexpr int kLut16Bits = 12;
 constexpr uint32_t kLut16Size = 1u << kLut16Bits;
 constexpr uint32_t kLut16MaxBins = 4096;
 constexpr int32_t kLut16Escape = -2048;    // residual value that stands for the escape symbol in the compact table
+constexpr int kLenBits = 13;
+constexpr uint32_t kLenMixed = 0x80u;
+constexpr uint32_t kLenFast = 32u;         // longest code of a length table entry without the mark
+static_assert((1u << kLenBits) == 2u * kLut16Size && 4u * kLutSize == 2u * kLut16Size, "the tables the chunk decoders load are of one size");
 constexpr uint32_t kSubEntries = 2048;     // second level of the compact table: entries of all sub-tables together
 
 struct DecodeTables {          // all in the workspace (global memory)
@@ -191,13 +195,17 @@ struct DecodeTables {          // all in the workspace (global memory)
     uint64_t *limit;           // [65]: left-aligned exclusive upper bound of the codes of each length
     uint64_t *first_code;      // [65]
     uint32_t *first_index;     // [65]: position of the first symbol of each length in `sorted`
-    uint16_t *lut16;           // (if the alphabet is too large for the compact table: a copy of `lut`, so that the chunk decoders
-                               // always load from here; meta[4] tells which it is)
+    uint16_t *lut16;           // (if the alphabet is too large for the compact table: the length table instead, of the same size, so that
+                               // the chunk decoders always load from here; meta[4] tells which it is.  One byte per prefix of kLenBits
+                               // bits: the length of the codes under it if they are all as long, at most 32 bits; else kLenMixed plus
+                               // the shortest length)
                                // kLut16Size entries: (residual << 4) | length, residual in 12 signed bits (kLut16Escape for
                                // the escape symbol); length 0 = longer code: the upper 12 bits are (offset / 2) << 2 | width
                                // code of the prefix's sub-table in sub16 (width 1, 2, 4, 6 bits), all zero if it has none
-    uint16_t *sub16;           // kSubEntries entries: (residual << 4) | (length - kLut16Bits), 0 = longer still
+    uint16_t *sub16;           // (too large an alphabet: the first kSubEntries entries of `resid`)
+                               // kSubEntries entries: (residual << 4) | (length - kLut16Bits), 0 = longer still
     uint16_t *sorted;          // symbols in canonical (length, symbol) order
+    uint16_t *resid;           // (too large an alphabet) their residuals, int16, -32768 for the escape symbol; 65536 entries
     uint32_t *meta;            // [0] max_len, [1] n_active, [2] min_len, [3] radius, [4] 1 if lut16 is valid
 };
 
@@ -261,7 +269,7 @@ constexpr int kDsBlock = kDsWaves * kWave;
 constexpr uint32_t kDsStageWords = 1536u;             // decode: Huffman words of 64 chunks per wavefront (LDS)
 constexpr uint32_t kDsStageBatch = 8u;                // decode: loads in flight per lane while those words are fetched
 constexpr uint32_t kDsMaxW = 512u;
-constexpr uint32_t kDsTailEntries = 1024u;            // decode: residuals of long codes kept in LDS
+constexpr uint32_t kDsTailEntries = 1024u;            // decode, compact table: residuals of long codes kept in LDS
 constexpr uint32_t kScanListWords = 1024u;            // scan: escape list of a strip per wavefront (pairs) (LDS)
 constexpr uint32_t kScanStripElems = 4096u;           // scan: elements per strip (unit of the escape list)
 

@@ -1066,6 +1066,11 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
                 });
                 if (len[j]) {
                     a.t.sorted[pos] = (uint16_t)sy;
+                    if (nbins > kLut16MaxBins) {
+                        const uint16_t r = (uint16_t)(sy ? (int32_t)sy - (int32_t)(nbins / 2u) : -32768);
+                        a.t.resid[pos] = r;
+                        if (pos < kSubEntries) a.t.sub16[pos] = r;
+                    }
                     if (pos < kLut16MaxBins) s_sorted[pos] = (uint16_t)sy;
                 }
             }
@@ -1082,7 +1087,7 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     // more than the number of limits it reaches.  lim[i]: the limit of length lo + i.
     const int32_t radius = (int32_t)(nbins / 2u);
     const bool compact = nbins <= kLut16MaxBins;
-    const bool skip_general = compact && a.compact_only && !(a.general_unless_chunk64 && chunk != 64u);
+    const bool skip_general = a.compact_only && !(a.general_unless_chunk64 && chunk != 64u);
     auto symbol_of = [&](uint32_t v18, uint32_t L) -> uint32_t {
         const uint32_t idx = s_off[L] + (v18 >> (18u - L));
         return s_sorted[idx < m ? idx : m - 1u];             // (beyond: a code of a single symbol, the bit pattern that is no code)
@@ -1108,8 +1113,25 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
                 entry = L << 8;
             }
             a.t.lut[e] = entry;
-            if (!compact) reinterpret_cast<uint32_t *>(a.t.lut16)[e] = entry;    // the chunk decoders load their table from one place
         }
+    }
+    // Larger alphabets: the length table.  Canonical codes grow in length with their value, so nearly every prefix of
+    // kLenBits bits has codes of one length under it, also where they are longer than the prefix: all but those in
+    // which one length ends and the next begins.  A thread's prefixes are consecutive: the length only ever grows.
+    if (!compact) {
+        constexpr uint32_t kPer = (1u << kLenBits) / kBookBlock;
+        static_assert(kPer == 8u, "one 8-byte store per thread");
+        uint64_t packed = 0;
+        uint32_t L = 1;
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; ++j) {
+            const uint64_t v = (uint64_t)(tid * kPer + j) << (64 - kLenBits), v_last = v | (~0ull >> kLenBits);
+            while (L < mx && v >= s_limit[L]) ++L;
+            const uint32_t shortest = L;
+            while (L < mx && v_last >= s_limit[L]) ++L;
+            packed |= (uint64_t)((L == shortest && L <= kLenFast) ? L : (kLenMixed | shortest)) << (8u * j);
+        }
+        reinterpret_cast<uint64_t *>(a.t.lut16)[tid] = packed;
     }
     // The compact table on the next kLut16Bits bits, for alphabets whose residuals fit 12 signed bits, and
     // its second level.  A prefix of kLut16Bits bits under which longer codes lie gets a sub-table indexed by

@@ -7,9 +7,14 @@
 //     decodes one chunk per lane: two words of the stream and a bit position per
 //     lane, one word of look-ahead from LDS so that no load sits on the critical
 //     path, and a look-up table whose entries already hold the residual (code -
-//     radius): 12 bits and 16-bit entries for alphabets up to 4096 bins, else 11
-//     bits and 32-bit entries (8 KB of LDS either way).  Symbols are decoded in
-//     pairs (one refill per pair); codes longer than the table take a
+//     radius), on 12 bits, for alphabets up to 4096 bins.  Larger ones have a table of
+//     lengths alone on 13 bits (8 KB of LDS either way): a canonical code's
+//     place in the order of the codes follows from its bits and its length by arithmetic, and
+//     the residuals at those places are looked up behind the chain of the decoding, many at a time.
+//     (Before, such an alphabet's codes were mostly longer than its table of 11 bits, and each was searched
+//     by length and looked up in global memory inside the chain: 128 x 64 x 224 x 224 with 65536 bins
+//     1500 us instead of 950, 64 x 256 x 56 x 56 with 16384 bins in bfloat16 239 instead of 141.)
+//     Symbols are decoded in pairs (one refill per pair); codes longer than the table take a
 //     wavefront-uniform slow path that starts its search at the length the table
 //     entry gives.  32 residuals are collected in registers and leave as int16
 //     in four back-to-back 16-byte stores.  The kernel needs about 9 KB of LDS per
@@ -46,11 +51,13 @@ namespace {
 typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
 
 struct DsTables {
-    const uint32_t *lut;        // LDS: the 11-bit table (u32 entries) or the compact 12-bit one (u16 entries)
+    const uint32_t *lut;        // LDS: the compact 12-bit table (u16 entries) or the 13-bit table of lengths (bytes)
+    const uint32_t *off;        // LDS, table of lengths: place of the first code of every length up to kLenFast minus that code
+    const uint16_t *resid;      // global, table of lengths: residuals in canonical order
     const uint64_t *limit, *first;
     const uint32_t *findex;
     const uint16_t *sorted;     // global: symbols in canonical order
-    const uint16_t *sub;        // LDS: second level of the compact table (sub-tables of the prefixes with longer codes), or null
+    const uint16_t *sub;        // LDS: second level of the compact table (sub-tables of the prefixes with longer codes); table of lengths: the first residuals
     const int16_t *tail;        // LDS: residuals of the canonical indices [tail0, tail0 + tail_n), i.e. of the long codes
     uint32_t tail0, tail_n;
     uint32_t max_len, n_active;
@@ -73,6 +80,16 @@ __device__ inline int32_t decode_long(uint64_t win, uint32_t start, uint32_t lut
     return sym ? (int32_t)sym - t.radius : t.escape;
 }
 
+// The same for the table of lengths: place in canonical order of the code that starts win.
+__device__ inline uint32_t place_long(uint64_t win, uint32_t start, const DsTables &t, uint32_t *len_out) {
+    uint32_t L = start;
+    while (L < t.max_len && win >= t.limit[L]) ++L;
+    if (L > 57u) L = 57u;
+    const uint64_t idx = t.findex[L] + ((win >> (64u - L)) - t.first[L]);
+    *len_out = L;
+    return idx < t.n_active ? (uint32_t)idx : t.n_active - 1u;   // (beyond: corrupt stream only)
+}
+
 // Bit reader of one lane: two words of the stream plus a bit position inside the
 // first one, and one word of look-ahead so that no load sits on the critical
 // path.  Words are read from words[min(i, last)].  Everything is branch-free
@@ -81,13 +98,13 @@ __device__ inline int32_t decode_long(uint64_t win, uint32_t start, uint32_t lut
 // the second word's first), so that the next 32 bits of the stream are always one
 // funnel shift of the two words, `alignbit(hi, lo, 32 - pos)`, whose shift count
 // the hardware takes modulo 32.
-// C16: the compact table (12 bits, u16 entries (residual << 4) | length), else the
-// general one (11 bits, u32 entries (residual << 8) | length).
+// C16: the compact table (12 bits, u16 entries (residual << 4) | length), symbols come
+// out as residuals; else the table of lengths, and symbols come out as places in canonical order.
 // STAGED: the words lie in the wavefront's LDS region, where a read past the last word is harmless (it stays inside
 // the workgroup's LDS or returns nothing) and needs no clamp.
 template <bool C16, bool STAGED = false>
 struct BitBuf {
-    static constexpr int kBits = C16 ? kLut16Bits : kLutBits;
+    static constexpr int kBits = C16 ? kLut16Bits : kLenBits;
     const uint32_t *words;
     uint32_t last;
     uint32_t hi, lo, nw;        // the word being consumed, the next one, the one after (look-ahead)
@@ -101,19 +118,29 @@ struct BitBuf {
     }
     static __device__ inline uint32_t look(const DsTables &t, uint64_t window) {
         const uint32_t idx = (uint32_t)(window >> (64 - kBits));
-        return C16 ? (uint32_t)reinterpret_cast<const uint16_t *>(t.lut)[idx] : t.lut[idx];
+        return C16 ? (uint32_t)reinterpret_cast<const uint16_t *>(t.lut)[idx] : (uint32_t)reinterpret_cast<const uint8_t *>(t.lut)[idx];
     }
     static __device__ inline uint32_t look32(const DsTables &t, uint32_t window) {       // window: the next 32 bits
         const uint32_t idx = window >> (32 - kBits);
-        return C16 ? (uint32_t)reinterpret_cast<const uint16_t *>(t.lut)[idx] : t.lut[idx];
+        return C16 ? (uint32_t)reinterpret_cast<const uint16_t *>(t.lut)[idx] : (uint32_t)reinterpret_cast<const uint8_t *>(t.lut)[idx];
     }
-    static __device__ inline uint32_t len_of(uint32_t e) { return C16 ? (e & 0xfu) : (e & 0xffu); }
-    static __device__ inline int32_t resid_of(uint32_t e) { return C16 ? ((int32_t)(e << 16) >> 20) : ((int32_t)e >> 8); }
-    static __device__ inline uint32_t hint_of(uint32_t e) { return C16 ? (e >> 4) : (e >> 8); }
+    static __device__ inline uint32_t len_of(uint32_t e) { return e & 0xfu; }
+    static __device__ inline int32_t resid_of(uint32_t e) { return (int32_t)(e << 16) >> 20; }
     __device__ inline void advance() { hi = lo; lo = nw; ++wp; nw = word(wp); }
 
     __device__ inline int32_t next(const DsTables &t) {
         const uint64_t both = (((uint64_t)hi << 32) | lo) << pos;          // the next 64 - pos bits, left-aligned
+        if constexpr (!C16) {
+            uint32_t L;
+            const uint32_t place = place_long(both | ((uint64_t)nw >> (32u - pos)), look(t, both) & (kLenMixed - 1u), t, &L);
+            if (pos + L >= 64u) {                // the code runs into the look-ahead word: move one word on here
+                advance();
+                pos -= 32u;
+            }
+            pos += L;
+            if (pos > 32u) { advance(); pos -= 32u; }
+            return (int32_t)place;
+        }
         const uint32_t e = look(t, both);
         uint32_t L = len_of(e);
         int32_t d = resid_of(e);
@@ -123,7 +150,7 @@ struct BitBuf {
                 // second level: the prefix's sub-table on the next 1, 2, 4 or 6 bits; what is longer still
                 // (or has no sub-table) is searched by length
                 const bool found = second_level(t, e, win, L, d);
-                if (!found) d = decode_long(win, C16 ? 0u : hint_of(e), (uint32_t)kBits, t, &L);
+                if (!found) d = decode_long(win, 0u, (uint32_t)kBits, t, &L);
                 if (pos + L >= 64u) {            // the code runs into the look-ahead word: move one word on here
                     advance();
                     pos -= 32u;                  // (modulo 2^32; the sum below is in range again)
@@ -145,7 +172,7 @@ struct BitBuf {
     // code's first bit).  False if the prefix has no sub-table or the code is longer than its sub-table covers.
     static __device__ inline bool second_level(const DsTables &t, uint32_t e, uint64_t win, uint32_t &L, int32_t &d) {
         const uint32_t h = e >> 4;
-        if (!C16 || h == 0u) return false;
+        if (h == 0u) return false;
         const uint32_t kb = (0x6421u >> ((h & 3u) * 4u)) & 0xfu;
         const uint32_t e2 = t.sub[((h >> 2) << 1) + (uint32_t)((win << kBits) >> (64u - kb))];
         if ((e2 & 0xfu) == 0u) return false;
@@ -162,8 +189,31 @@ struct BitBuf {
     // kBits long, so 32 - kBits >= kBits of them are still there), and the words move on at most once per
     // pair.  One wavefront-uniform test per pair: if either code of any lane is longer than the table the
     // pair is finished by pair_with_long_codes.
+    // (The table of lengths: both codes have to lie in those 32 bits, which the sum of the two entries says; a marked one
+    // is above 32 by itself.)
     __device__ inline uint32_t next_pair(const DsTables &t) {
         const uint32_t top = __builtin_amdgcn_alignbit(hi, lo, 32u - pos);
+        if constexpr (!C16) {
+            const uint32_t l0 = look32(t, top);
+            const uint32_t top1 = top << (l0 & 31u);
+            const uint32_t l1 = look32(t, top1);
+            if (__builtin_expect(wave_ballot(l0 + l1 > 32u) != 0ull, 0)) {
+                const uint32_t i0 = (uint32_t)next(t);
+                return ((uint32_t)next(t) << 16) | i0;
+            }
+            const uint32_t p2 = pos + l0 + l1;
+            const bool need = p2 > 32u;
+            hi = need ? lo : hi;
+            lo = need ? nw : lo;
+            pos = need ? p2 - 32u : p2;
+            wp += need ? 1u : 0u;
+            nw = word(wp);
+            uint32_t i0 = (top >> (32u - l0)) + t.off[l0], i1 = (top1 >> (32u - l1)) + t.off[l1];
+            const uint32_t i_max = t.n_active - 1u;              // (beyond: corrupt stream only)
+            i0 = i0 < i_max ? i0 : i_max;
+            i1 = i1 < i_max ? i1 : i_max;
+            return (i1 << 16) | i0;
+        }
         const uint32_t e0 = look32(t, top);
         const uint32_t e1 = look32(t, top << len_of(e0));
         if (__builtin_expect(wave_ballot(len_of(e0) == 0u || len_of(e1) == 0u) != 0ull, 0)) return pair_with_long_codes(t, e0);
@@ -174,14 +224,11 @@ struct BitBuf {
         pos = need ? p2 - 32u : p2;
         wp += need ? 1u : 0u;
         nw = word(wp);
-        if (C16) {
-            // the two entries side by side, then both residuals moved down over their lengths at once
-            typedef short s16x2 __attribute__((ext_vector_type(2)));
-            s16x2 two = __builtin_bit_cast(s16x2, __builtin_amdgcn_perm(e1, e0, 0x05040100u));
-            two >>= (short)4;
-            return __builtin_bit_cast(uint32_t, two);
-        }
-        return __builtin_amdgcn_perm(e1, e0, 0x06050201u);      // bytes 1, 2 of each entry: the two residuals
+        // the two entries side by side, then both residuals moved down over their lengths at once
+        typedef short s16x2 __attribute__((ext_vector_type(2)));
+        s16x2 two = __builtin_bit_cast(s16x2, __builtin_amdgcn_perm(e1, e0, 0x05040100u));
+        two >>= (short)4;
+        return __builtin_bit_cast(uint32_t, two);
     }
     // The same pair when some lane has a code longer than the table.  Such a code is resolved through the
     // second level (the lanes concerned only): up to 18 bits, so the second look-up still finds its bits in the
@@ -216,6 +263,28 @@ struct BitBuf {
     }
 };
 
+// Table of lengths: the residuals at the N * 2 places in canonical order that p[0 .. N) holds, in their place.  The first
+// ones, of the shortest codes, are in LDS; the lanes that need others load them (with an offset out of range where they do not).
+template <int N>
+__device__ inline void residuals_at(uint32_t (&p)[N], const DsTables &t) {
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(t.resid, 2u * 65536u);
+    uint32_t lds[2 * N], far[2 * N];
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) {
+        const uint32_t at = (i & 1) ? p[i / 2] >> 16 : p[i / 2] & 0xffffu;
+        lds[i] = t.sub[at & (kSubEntries - 1u)];
+        far[i] = 0;
+        if (t.n_active > kSubEntries)                        // (uniform)
+            far[i] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, at < kSubEntries ? 0x7ffffffe : (int)(at * 2u), 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t a = (p[i] & 0xffffu) < kSubEntries ? lds[2 * i] : far[2 * i];
+        const uint32_t b = (p[i] >> 16) < kSubEntries ? lds[2 * i + 1] : far[2 * i + 1];
+        p[i] = a | (b << 16);
+    }
+}
+
 // Decode the first `nsym` symbols of one chunk into dst[0 .. nsym) (int16).  Chunk sizes that are a
 // multiple of 32 (dst is then 64-byte aligned) collect 32 residuals in registers and write a whole
 // 64-byte sector with four back-to-back 16-byte stores: every lane keeps a line of its own open, far
@@ -232,6 +301,7 @@ __device__ inline void decode_chunk(const uint32_t *words, uint32_t last, uint32
             uint32_t pk[16];                 // indexed by a wavefront-uniform counter: stays in registers
 #pragma unroll 4
             for (int j = 0; j < 16; ++j) pk[j] = bb.next_pair(t);
+            if (!C16) residuals_at(pk, t);
 #pragma unroll
             for (int j = 0; j < 4; ++j) dst16[k32 * 4u + j] = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
         }
@@ -242,11 +312,16 @@ __device__ inline void decode_chunk(const uint32_t *words, uint32_t last, uint32
             uint32_t pk[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) pk[j] = bb.next_pair(t);
+            if (!C16) residuals_at(pk, t);
             dst16[k8] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         }
         k = nsym & ~7u;
     }
-    for (; k < nsym; ++k) dst[k] = (int16_t)bb.next(t);     // chunk sizes that are no multiple of eight; the tensor's last chunk
+    for (; k < nsym; ++k) {                                 // chunk sizes that are no multiple of eight; the tensor's last chunk
+        uint32_t one[1] = {(uint32_t)bb.next(t)};
+        if (!C16) residuals_at(one, t);
+        dst[k] = (int16_t)one[0];
+    }
 }
 
 // first record index in [lo, hi) whose key is >= target (65-ary search by one wavefront)
@@ -273,6 +348,7 @@ __global__ __launch_bounds__(kDsBlock) void k_decode_chunks(DsArgs a) {
     __shared__ uint64_t s_limit[65];
     __shared__ uint64_t s_first[65];
     __shared__ uint32_t s_findex[65];
+    __shared__ uint32_t s_off[kLenFast + 1u];
     __shared__ int16_t s_tail[kDsTailEntries];
     __shared__ uint32_t s_sub[kSubEntries / 2u];
 
@@ -293,20 +369,20 @@ __global__ __launch_bounds__(kDsBlock) void k_decode_chunks(DsArgs a) {
 
     const bool c16 = a.t.meta[4] != 0u;                     // the compact table exists: use it
     {
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.t.lut16);     // the compact table, or a copy of the general one: kLutSize dwords
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.t.lut16);     // the compact table, or that of the lengths: kLutSize dwords
         for (uint32_t i = tid; i < kLutSize; i += kDsBlock) s_lut[i] = src[i];
     }
     for (uint32_t i = tid; i < 65u; i += kDsBlock) { s_limit[i] = a.t.limit[i]; s_first[i] = a.t.first_code[i]; s_findex[i] = a.t.first_index[i]; }
-    if (c16) for (uint32_t i = tid; i < kSubEntries / 2u; i += kDsBlock) s_sub[i] = reinterpret_cast<const uint32_t *>(a.t.sub16)[i];
+    for (uint32_t i = tid; i <= kLenFast; i += kDsBlock) s_off[i] = a.t.first_index[i] - (uint32_t)a.t.first_code[i];
+    for (uint32_t i = tid; i < kSubEntries / 2u; i += kDsBlock) s_sub[i] = reinterpret_cast<const uint32_t *>(a.t.sub16)[i];
     DsTables t;
-    t.sub = reinterpret_cast<const uint16_t *>(s_sub);
+    t.sub = reinterpret_cast<const uint16_t *>(s_sub); t.off = s_off; t.resid = a.t.resid;
     t.lut = s_lut; t.limit = s_limit; t.first = s_first; t.findex = s_findex; t.sorted = a.t.sorted;
     t.max_len = a.t.meta[0]; t.n_active = a.t.meta[1]; t.radius = (int32_t)(hdr->nbins / 2u);
     // residuals of the symbols whose codes are longer than the look-up table, in canonical order
     t.tail = s_tail;
-    const uint32_t lut_bits = c16 ? (uint32_t)kLut16Bits : (uint32_t)kLutBits;
     t.escape = c16 ? kLut16Escape : kEscape;
-    t.tail0 = (t.max_len > lut_bits) ? a.t.first_index[lut_bits + 1u] : t.n_active;
+    t.tail0 = (c16 && t.max_len > (uint32_t)kLut16Bits) ? a.t.first_index[kLut16Bits + 1] : t.n_active;
     t.tail_n = t.n_active - t.tail0 < kDsTailEntries ? t.n_active - t.tail0 : kDsTailEntries;
     for (uint32_t i = tid; i < t.tail_n; i += kDsBlock) {
         const uint32_t sym = a.t.sorted[t.tail0 + i];
@@ -701,6 +777,7 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
     __shared__ uint64_t s_limit[65];
     __shared__ uint64_t s_first[65];
     __shared__ uint32_t s_findex[65];
+    __shared__ uint32_t s_off[kLenFast + 1u];
     __shared__ int32_t s_carry[COOP ? kFuWaves : 1][COOP ? CW : 1];   // column sums a strip hands to the next one
     __shared__ uint32_t s_ready[kFuWaves], s_acked[kFuWaves];               // strip number + 1 of the slot's content / of its last reader
     __shared__ uint32_t s_cnt[(MODE != 2) ? kFuWaves : 1][64];                // MODE 0 / 1: escapes per slot of lanes
@@ -724,23 +801,28 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
     const float ebx2 = __uint_as_float(hdr->ebx2_bits);
 
     // ---- decode tables into LDS (every load independent of the others: one round trip) ----
-    const bool c16 = a.t.meta[4] != 0u;
+    const bool compact = a.t.meta[4] != 0u;
     {
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.t.lut16);     // the compact table, or a copy of the general one
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.t.lut16);     // the compact table, or that of the lengths
         for (uint32_t i = tid; i < kLutSize; i += kFuBlock) s_lut[i] = src[i];
         for (uint32_t i = tid; i < kSubEntries / 2u; i += kFuBlock) s_sub[i] = reinterpret_cast<const uint32_t *>(a.t.sub16)[i];
     }
     for (uint32_t i = tid; i < 65u; i += kFuBlock) { s_limit[i] = a.t.limit[i]; s_first[i] = a.t.first_code[i]; s_findex[i] = a.t.first_index[i]; }
+    if (tid <= kLenFast) s_off[tid] = a.t.first_index[tid] - (uint32_t)a.t.first_code[tid];
     if (tid < (uint32_t)kFuWaves) { s_ready[tid] = 0u; s_acked[tid] = 0u; }
     DsTables t;
-    t.lut = s_lut; t.sub = reinterpret_cast<const uint16_t *>(s_sub);
+    t.lut = s_lut; t.sub = reinterpret_cast<const uint16_t *>(s_sub); t.off = s_off; t.resid = a.t.resid;
     t.limit = s_limit; t.first = s_first; t.findex = s_findex; t.sorted = a.t.sorted;
     t.max_len = a.t.meta[0]; t.n_active = a.t.meta[1]; t.radius = (int32_t)(hdr->nbins / 2u);
     t.tail = nullptr; t.tail0 = 0; t.tail_n = 0;            // what neither table level resolves is rare: symbols from global memory
-    t.escape = c16 ? kLut16Escape : kEscape;
-    const int32_t esc_marker = t.escape;
     __syncthreads();
 
+    // Everything else, once per kind of table (the same for every thread): with both kinds in one loop their registers do
+    // not fit together, and the spills cost a third of the small alphabets' time.
+    auto work = [&](auto c16_tag) __attribute__((always_inline)) {
+    constexpr bool c16 = decltype(c16_tag)::value;
+    constexpr int32_t esc_marker = c16 ? kLut16Escape : kEscape;   // what stands for an escaped residual
+    t.escape = esc_marker;
     uint32_t *strip = s_dyn_ds + wave * kFuRegionWords;
     int32_t *esc = reinterpret_cast<int32_t *>(strip + kFuStripWords);
 
@@ -915,14 +997,15 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
             // a loop over four groups of four pairs (a vector of 16 words indexed by a wavefront-uniform
             // counter stays in registers; an array would be placed in scratch memory) ----
             u32x16_t pa = {}, pb = {};
+            bool no_words = false;
             {
                 const uint32_t last = n_words ? n_words - 1u : 0u;
                 uint32_t w0 = (my_off < w_begin) ? 0u : my_off - w_begin;
                 w0 = w0 < last ? w0 : last;
                 // (one call per address space of the words, so that the reader's loads are LDS or global
                 // instructions, not generic ones)
-                auto run = [&](auto c16_tag, auto staged_tag, auto wsrc) {
-                    BitBuf<decltype(c16_tag)::value, decltype(staged_tag)::value> bb;
+                auto run = [&](auto staged_tag, auto wsrc) {
+                    BitBuf<c16, decltype(staged_tag)::value> bb;
                     bb.open(wsrc, last, w0);
 #pragma nounroll
                     for (uint32_t j4 = 0; j4 < 4u; ++j4) {
@@ -936,12 +1019,7 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
                     }
                 };
                 if (c < c1 && n_words) {
-                    if (all_staged) {
-                        if (c16) run(std::true_type{}, std::true_type{}, strip); else run(std::false_type{}, std::true_type{}, strip);
-                    } else {
-                        const uint32_t *gsrc = payload + w_begin;
-                        if (c16) run(std::true_type{}, std::false_type{}, gsrc); else run(std::false_type{}, std::false_type{}, gsrc);
-                    }
+                    if (all_staged) run(std::true_type{}, strip); else run(std::false_type{}, payload + w_begin);
                 }
                 // Container version 2: a chunk without words is residual 0 throughout.  Its lane has read
                 // the words of the chunk behind it (or past the end of the strip's, which is harmless) with
@@ -949,7 +1027,8 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
                 if (zero_chunks && n_words) {
                     const uint32_t next_off = (uint32_t)__shfl_down((int)my_off, 1, kWave);
                     const uint32_t w_last = w_begin + n_words;
-                    if (((c + 1u < c1) ? next_off : w_last) <= my_off) { pa = u32x16_t{}; pb = u32x16_t{}; }
+                    no_words = ((c + 1u < c1) ? next_off : w_last) <= my_off;
+                    if (no_words) { pa = u32x16_t{}; pb = u32x16_t{}; }
                 }
             }
             wave_lds_fence();
@@ -978,6 +1057,24 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
                     row[i] = make_uint4(pa[4 * i], pa[4 * i + 1], pa[4 * i + 2], pa[4 * i + 3]);
                     row[4 + i] = make_uint4(pb[4 * i], pb[4 * i + 1], pb[4 * i + 2], pb[4 * i + 3]);
                 }
+            }
+
+            // Table of lengths: places in canonical order -> residuals, in place (from LDS: the registers above and the
+            // look-ups in flight do not fit the register file together).
+            if (!c16 && n_words) {
+                wave_lds_fence();
+#pragma nounroll
+                for (uint32_t i0 = 0; i0 < kFuStripWords; i0 += 4u * kWave) {
+                    uint32_t pk[4];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4u; ++i) pk[i] = strip[i0 + i * kWave + lane];
+                    residuals_at(pk, t);
+#pragma unroll
+                    for (uint32_t i = 0; i < 4u; ++i) strip[i0 + i * kWave + lane] = pk[i];
+                }
+                if (no_words)                                 // (no places, but residual 0 throughout)
+                    for (uint32_t i = 0; i < 8u; ++i) reinterpret_cast<uint4 *>(strip + lane * 32u)[i] = make_uint4(0u, 0u, 0u, 0u);
+                wave_lds_fence();
             }
 
             // ---- the strip's escaped residuals: their values compacted into LDS in element order; each also goes,
@@ -1363,8 +1460,7 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
                 }
             };
             if (n_esc == 0u) scan_rows(std::integral_constant<int, 0>{});
-            else if (c16) scan_rows(std::integral_constant<int, 1>{});
-            else scan_rows(std::integral_constant<int, 2>{});
+            else scan_rows(std::integral_constant<int, c16 ? 1 : 2>{});
 
             // ---- verbatim values overwrite what was just stored ----
             if (has_verbatim) {
@@ -1388,6 +1484,8 @@ __global__ __launch_bounds__(kFuBlock) void k_decode_scan(FuArgs a) {
             j += NWG;
         }
     }
+    };
+    if (compact) work(std::true_type{}); else work(std::false_type{});
 }
 
 // One translation unit per output type (COMET_DEC_OUT: 0 fp32, 1 IEEE half, 2 bfloat16) instantiates the
