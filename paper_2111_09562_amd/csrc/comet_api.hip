@@ -351,7 +351,7 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
         while (tiles * (uint32_t)kBookBlock < b.nbins) tiles <<= 1;
         const uint32_t total = tiles * (uint32_t)kBookBlock;          // <= kMaxBins: what the scratch arrays hold
         uint64_t *src = b.scratch.keys, *dst = b.scratch.iw;
-        hipLaunchKernelGGL(k_book_sort_tiles, dim3(tiles), dim3(kBookBlock), 0, st, b.hist, b.nbins, src, b.ctl);
+        hipLaunchKernelGGL(k_book_sort_tiles, dim3(tiles), dim3(kBookBlock), 0, st, b);
         for (uint32_t run = (uint32_t)kBookBlock; run < total; run <<= 1) {
             hipLaunchKernelGGL(k_book_merge, dim3(total / (uint32_t)kBookMergeBlock), dim3(kBookMergeBlock), 0, st, src, dst, run, b.ctl);
             uint64_t *t = src; src = dst; dst = t;
@@ -360,6 +360,10 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
         b.presorted = 1u;
     }
     hipLaunchKernelGGL(k_codebook, dim3(1), dim3(kBookBlock), 0, st, b);
+    if (b.presorted) {                                       // (they leave an alphabet whose occurring symbols fit LDS alone)
+        hipLaunchKernelGGL(k_book_depths, dim3((b.nbins + kBookDepthBlock - 1u) / kBookDepthBlock), dim3(kBookDepthBlock), 0, st, b);
+        hipLaunchKernelGGL(k_book_codes, dim3((b.nbins + kBookBlock - 1u) / kBookBlock), dim3(kBookBlock), 0, st, b);
+    }
     HIP_TRY(hipGetLastError());
     return COMET_OK;
 }
@@ -522,6 +526,7 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
         const uint64_t o_meta = o; o += 64;
         const uint64_t o_sorted = o; o += 2ull * kMaxBins;
         const uint64_t o_resid = o; o += 2ull * kMaxBins;
+        const uint64_t o_tcnt = o; o += 4ull * (kMaxBins / kBookBlock) * kBookLens;
         uint8_t *blob = nullptr;
         if ((e = hipMalloc((void **)&blob, align_up(o, 256))) != hipSuccess) return fail(COMET_ERR_NOMEM);
         c->tables_blob = blob;
@@ -531,6 +536,7 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
         c->tables.first_index = (uint32_t *)(blob + o_findex); c->tables.lut = (uint32_t *)(blob + o_lut);
         c->tables.meta = (uint32_t *)(blob + o_meta); c->tables.sorted = (uint16_t *)(blob + o_sorted);
         c->tables.resid = (uint16_t *)(blob + o_resid);
+        c->book.tile_cnt = (uint32_t *)(blob + o_tcnt);
         c->tables.lut16 = (uint16_t *)(blob + o_lut16);
         c->tables.sub16 = (uint16_t *)(blob + o_sub16);
     }

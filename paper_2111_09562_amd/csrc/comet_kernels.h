@@ -97,7 +97,9 @@ struct BookScratch {                        // global scratch for large alphabet
     uint64_t *iw;          // internal-node weights
     uint32_t *leaf_parent;
     uint32_t *int_parent;
+    uint32_t *tile_cnt;    // [tile of kBookBlock symbols][kBookLens]: symbols per length (alphabets above kBookBySymbolMax)
 };
+constexpr uint32_t kBookLens = 65u;        // lengths 0 .. 64 (64 stands for every length the container cannot hold)
 
 struct BookArgs {
     const uint32_t *hist;
@@ -117,7 +119,10 @@ struct BookArgs {
 };
 __global__ void k_codebook(BookArgs a);
 constexpr int kBookMergeBlock = 256;
-__global__ void k_book_sort_tiles(const uint32_t *hist, uint32_t nbins, uint64_t *keys, Control *ctl);
+constexpr int kBookDepthBlock = 256;
+__global__ void k_book_sort_tiles(BookArgs a);
+__global__ void k_book_depths(BookArgs a);
+__global__ void k_book_codes(BookArgs a);
 __global__ void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl);
 
 // ---- encode -------------------------------------------------------------------

@@ -616,20 +616,20 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     uint64_t *keys = a.scratch.keys, *iw = a.scratch.iw;
     uint32_t *leaf_parent = a.scratch.leaf_parent, *int_parent = a.scratch.int_parent;
     // ---- 1. the symbols that occur as sort keys (frequency << 16 | symbol), unless the sort kernels have done that ----
-    uint32_t done = 0;
-    for (uint32_t base = 0; base < nbins; base += kBookBlock) {
-        const uint32_t sy = base + tid;
-        const uint32_t f = (sy < nbins) ? a.hist[sy] : 0u;
-        if (!a.presorted) {
+    if (!a.presorted) {
+        uint32_t done = 0;
+        for (uint32_t base = 0; base < nbins; base += kBookBlock) {
+            const uint32_t sy = base + tid;
+            const uint32_t f = (sy < nbins) ? a.hist[sy] : 0u;
             uint32_t tot;
             const uint32_t pos = block_excl_scan<uint32_t, kBookBlock / kWave>(f ? 1u : 0u, s.part, tot);
             if (f) keys[done + pos] = ((uint64_t)f << 16) | sy;
             done += tot;
-        }
-        if (!f && sy < nbins) {             // unused symbol: length 0 everywhere
-            a.len_out[sy] = 0;
-            a.enc[sy] = 0;
-            if (a.code_out) a.code_out[sy] = 0;
+            if (!f && sy < nbins) {             // unused symbol: length 0 everywhere
+                a.len_out[sy] = 0;
+                a.enc[sy] = 0;
+                if (a.code_out) a.code_out[sy] = 0;
+            }
         }
     }
     const uint32_t m2 = next_pow2(m);
@@ -661,6 +661,7 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
         }
     }
     __syncthreads();
+    if (a.presorted) return;                                 // the rest by whole grids: k_book_depths, k_book_codes
     // ---- 4. depth of every leaf: walk to the root (node m-2) ----
     // (four leaves per thread at a time: a walk is a chain of dependent loads, in global memory for a large
     // alphabet, and four chains wait side by side)
@@ -701,6 +702,32 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     book_codes(a, nullptr, a.len_out, nbins, s.first, s.v.wc);
 }
 
+// The container's header and the padding between its sections, once the code book is known (one thread).
+__device__ inline void book_finish(const BookArgs &a, uint32_t m, uint32_t max_len, uint64_t n_rec, uint64_t n_vrec, uint64_t nnz) {
+    a.ctl->max_len = max_len;
+    if (a.hdr) {
+        Header h = a.proto;
+        h.n_active = m;
+        h.max_len = max_len;
+        h.n_rec = (uint32_t)n_rec;
+        h.n_vrec = (uint32_t)n_vrec;
+        h.nnz = nnz;
+        h.off_payload = align16(h.off_outlier + 8ull * n_rec);
+        h.payload_words = 0;
+        h.total_bytes = 0;
+        h.status = 1;                      // overwritten by the encode kernel's last workgroup
+        a.ctl->off_payload = h.off_payload;
+        if (h.off_payload > a.capacity) atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
+        *a.hdr = h;
+        // zero the padding between sections
+        uint8_t *base = reinterpret_cast<uint8_t *>(a.hdr);
+        for (uint64_t o = h.off_len + a.nbins; o < h.off_chunk; ++o) base[o] = 0;
+        for (uint64_t o = h.off_chunk + 4ull * h.n_chunks; o < h.off_outlier; ++o) base[o] = 0;
+        if (h.off_payload <= a.capacity)
+            for (uint64_t o = h.off_outlier + 8ull * n_rec; o < h.off_payload; ++o) base[o] = 0;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Leaves of a large alphabet in (frequency, symbol) order.  One key per symbol: (frequency, symbol), or
 // a key above all of those for a symbol that does not occur (each its own, so that no two keys are
@@ -710,15 +737,21 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
 // number of smaller keys in the other one (binary search); one key per thread.  Alphabets whose
 // occurring symbols fit LDS are built there from the histogram: the merges then have nothing to do.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(const uint32_t *hist, uint32_t nbins, uint64_t *keys, Control *ctl) {
+__global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
     __shared__ uint64_t s_x[2 * kBookBlock];
     const uint32_t s = blockIdx.x * (uint32_t)kBookBlock + threadIdx.x;
-    const uint32_t f = s < nbins ? hist[s] : 0u;
+    const uint32_t f = s < a.nbins ? a.hist[s] : 0u;
+    if (!f && s < a.nbins) {                        // unused symbol: length 0 everywhere
+        a.len_out[s] = 0;
+        a.enc[s] = 0;
+        if (a.code_out) a.code_out[s] = 0;
+    }
+    if (threadIdx.x < kBookLens) a.scratch.tile_cnt[blockIdx.x * kBookLens + threadIdx.x] = 0;
     const uint32_t cnt = (uint32_t)__syncthreads_count(f != 0u);
-    if (threadIdx.x == 0 && cnt) atomicAdd(&ctl->n_active, cnt);
+    if (threadIdx.x == 0 && cnt) atomicAdd(&a.ctl->n_active, cnt);
     uint64_t key[1] = {f ? (((uint64_t)f << 16) | s) : ((1ull << 63) | s)};
     block_sort<1>(key, s_x, (uint32_t)kBookBlock);
-    keys[s] = key[0];
+    a.scratch.keys[s] = key[0];
 }
 
 __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl) {
@@ -862,35 +895,86 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     } else {
         book_large(a, s, m);
     }
+    const bool large = !given && m > kBookLdsSyms;
 
     // ---- 7. container layout ----
     if (tid == 0) {
         a.ctl->n_active = m;
-        a.ctl->max_len = s.word[2];
         a.ctl->enc_in_window = (outside & 1) ? 0u : 1u;
         a.ctl->len_in_window = (outside & 2) ? 0u : 1u;
-        if (a.hdr) {
-            Header h = a.proto;
-            h.n_active = m;
-            h.max_len = s.word[2];
-            h.n_rec = (uint32_t)n_rec;
-            h.n_vrec = (uint32_t)n_vrec;
-            h.nnz = nnz;
-            h.off_payload = align16(h.off_outlier + 8ull * n_rec);
-            h.payload_words = 0;
-            h.total_bytes = 0;
-            h.status = 1;                      // overwritten by the encode kernel's last workgroup
-            a.ctl->off_payload = h.off_payload;
-            if (h.off_payload > a.capacity) atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
-            *a.hdr = h;
-            // zero the padding between sections
-            uint8_t *base = reinterpret_cast<uint8_t *>(a.hdr);
-            for (uint64_t o = h.off_len + nbins; o < h.off_chunk; ++o) base[o] = 0;
-            for (uint64_t o = h.off_chunk + 4ull * h.n_chunks; o < h.off_outlier; ++o) base[o] = 0;
-            if (h.off_payload <= a.capacity)
-                for (uint64_t o = h.off_outlier + 8ull * n_rec; o < h.off_payload; ++o) base[o] = 0;
+        if (!large || !a.presorted) book_finish(a, m, s.word[2], n_rec, n_vrec, nnz);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The rest of a large alphabet's code book (more than kBookLdsSyms symbols occur, presorted), by whole grids instead of the
+// one workgroup that built the tree: a walk to the root is a chain of some twenty dependent loads, and the canonical
+// codes visit every symbol of the alphabet.  64 x 256 x 56 x 56 at a bound of 1e-4, 65536
+// bins: k_codebook 406 us, now 272 and 28 behind it.
+// k_book_depths: one leaf per thread; it also counts the lengths per tile of kBookBlock symbols.
+// k_book_codes: a tile per workgroup; the code of a symbol is the first code of its length plus the number of smaller
+// symbols of that length: those of the tiles in front, of the wavefronts in front and of the lanes in front.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBookDepthBlock) void k_book_depths(BookArgs a) {
+    const uint32_t m = a.ctl->n_active;
+    const uint32_t i = blockIdx.x * (uint32_t)kBookDepthBlock + threadIdx.x;
+    if (m <= kBookLdsSyms || i >= m) return;
+    const uint32_t root = m - 2u;
+    uint32_t depth = 1;
+    for (uint32_t p = a.scratch.leaf_parent[i]; p != root && depth < 64u; p = a.scratch.int_parent[p]) ++depth;
+    const uint32_t sym = (uint32_t)(a.scratch.keys[i] & 0xffffu);
+    a.len_out[sym] = (uint8_t)depth;
+    atomicAdd(&a.scratch.tile_cnt[sym / (uint32_t)kBookBlock * kBookLens + depth], 1u);
+}
+
+__global__ __launch_bounds__(kBookBlock) void k_book_codes(BookArgs a) {
+    constexpr uint32_t kWaves = kBookBlock / kWave;
+    __shared__ uint32_t s_cnt[kBookLens], s_before[kBookLens], s_findex[kBookLens], s_wc[kWaves][kBookLens], s_max;
+    __shared__ uint64_t s_first[kBookLens];
+    const uint32_t m = a.ctl->n_active;
+    if (m <= kBookLdsSyms) return;
+    const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), wave = tid / (uint32_t)kWave;
+    const uint32_t sym = blockIdx.x * (uint32_t)kBookBlock + tid;
+    const uint32_t L = sym < a.nbins ? (uint32_t)a.len_out[sym] : 0u;
+    for (uint32_t i = tid; i < kWaves * kBookLens; i += kBookBlock) s_wc[i / kBookLens][i % kBookLens] = 0;
+    if (tid < kBookLens) {
+        uint32_t all = 0, before = 0;
+#pragma unroll 8
+        for (uint32_t t = 0; t < gridDim.x; ++t) {
+            const uint32_t c = a.scratch.tile_cnt[t * kBookLens + tid];
+            all += c;
+            before += t < blockIdx.x ? c : 0u;
+        }
+        s_cnt[tid] = all;
+        s_before[tid] = before;
+    }
+    __syncthreads();
+    if (tid < (uint32_t)kWave) {
+        uint32_t mx, mn;
+        const bool ok = canonical_first_codes_wave(s_cnt, m, s_first, s_findex, &mx, &mn);
+        if (tid == 0) {
+            s_max = mx;
+            if (!ok && blockIdx.x == 0) atomicOr(&a.ctl->status, (uint32_t)ST_INTERNAL);
         }
     }
+    uint32_t in_wave = 0;
+    uint64_t todo = wave_ballot(L != 0u);
+    while (todo) {                                       // one step per length that occurs in the wavefront
+        const uint32_t Lc = (uint32_t)__builtin_amdgcn_readlane((int)L, __builtin_ctzll(todo));
+        const uint64_t same = wave_ballot(L == Lc);
+        if (L == Lc) in_wave = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        if (lane == 0) s_wc[wave][Lc] = (uint32_t)__popcll(same);
+        todo &= ~same;
+    }
+    __syncthreads();
+    if (L) {
+        uint32_t before = s_before[L];
+        for (uint32_t w = 0; w < wave; ++w) before += s_wc[w][L];
+        const uint64_t code = s_first[L] + before + in_wave;
+        a.enc[sym] = (code << 6) | (uint64_t)(L & 63u);
+        if (a.code_out) a.code_out[sym] = code;
+    }
+    if (blockIdx.x == 0 && tid == 0) book_finish(a, m, s_max, a.ctl->n_rec, a.ctl->n_vrec, a.ctl->nnz);
 }
 
 // ---------------------------------------------------------------------------

@@ -45,3 +45,25 @@ def test_edges(oracle, m, nbins):
             assert np.array_equal(lens.cpu().numpy(), want), (kind, total)
             assert np.array_equal(codes.cpu().numpy().view(np.uint64), oracle.canonical_codes(want)), (kind, total)
     ctx.close()
+
+
+@pytest.mark.parametrize("nbins,m", [(4096, 2049), (8192, 8192), (8194, 2048), (8194, 2049), (8194, 8194), (9001, 2500), (16384, 16383),
+                                     (32768, 5000), (65535, 65535), (65536, 2049), (65536, 4097), (65536, 30000), (65536, 65536)])
+def test_more_symbols_than_lds(oracle, nbins, m):
+    """Trees in global memory: finished by one workgroup (up to 8192 bins) or by whole grids (more)."""
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(m * 7 + nbins)
+    ctx = comet.Context(max_elems=4096, max_nbins=65536)
+    lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+    codes = torch.empty(nbins, dtype=torch.int64, device="cuda")
+    for kind in ("flat", "doubling", "steps", "geometric", "random"):
+        h = np.zeros(nbins, np.uint32)
+        h[np.sort(rng.choice(nbins, m, replace=False))] = _hist(kind, m, rng)
+        want = oracle.code_lengths(h)
+        lens.fill_(77)
+        codes.fill_(77)
+        ctx.comet_stage_codebook(torch.from_numpy(h.view(np.int32)).cuda(), nbins, lens, codes)
+        ctx.comet_sync()
+        assert np.array_equal(lens.cpu().numpy(), want), kind
+        assert np.array_equal(codes.cpu().numpy().view(np.uint64), oracle.canonical_codes(want)), kind
+    ctx.close()
