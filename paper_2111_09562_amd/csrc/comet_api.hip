@@ -383,7 +383,7 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     encode_geometry(ctx, a.n_chunks, &seg, &grid);
     a.seg_chunks = seg;
     // table and a zero entry (or, for a large alphabet, the lengths of enc_len_window() symbols: whichever is larger), word counts
-    const size_t lenw = enc_len_window(nbins) + 8u;
+    const size_t lenw = a.len8 ? enc_len_window(nbins) + 8u : 0u;
     const size_t tbl_bytes = ((size_t)a.tbl_n + 1u) * 8u;
     a.tbl_room = (uint32_t)((a.tbl_n < nbins && lenw > tbl_bytes ? lenw : tbl_bytes) + 7u) & ~7u;
     const size_t lds_count = (size_t)a.tbl_room + (size_t)seg * 4u;
@@ -393,12 +393,14 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     a.desc = desc; a.ctl = &ctx->state->ctl;
     a.latched = container ? &ctx->state->latched : nullptr;
     const bool full = (a.tbl_n == nbins);
+    const bool wide = a.len8 && enc_wide(nbins);             // (a stage call brings no lengths)
 #define COMET_LAUNCH_ENC(S)                                                                                            \
     do {                                                                                                               \
         {                                                                                                              \
             TimedScope ts(ctx, st, COMET_KERNEL_ENCODE_COUNT);                                                         \
-            if (full) hipLaunchKernelGGL((k_encode_count<S, true>), dim3(grid), dim3(kEncBlock), lds_count, st, a);    \
-            else hipLaunchKernelGGL((k_encode_count<S, false>), dim3(grid), dim3(kEncBlock), lds_count, st, a);        \
+            if (full) hipLaunchKernelGGL((k_encode_count<S, true, kEncBlock>), dim3(grid), dim3(kEncBlock), lds_count, st, a);    \
+            else if (wide) hipLaunchKernelGGL((k_encode_count<S, false, kEncBlockWide>), dim3(grid), dim3(kEncBlockWide), lds_count, st, a); \
+            else hipLaunchKernelGGL((k_encode_count<S, false, kEncBlock>), dim3(grid), dim3(kEncBlock), lds_count, st, a);        \
         }                                                                                                              \
         TimedScope ts(ctx, st, COMET_KERNEL_ENCODE);                                                                   \
         if (full) hipLaunchKernelGGL((k_encode_pack<S, true>), dim3(grid), dim3(kEncBlock), lds_pack, st, a);          \
@@ -550,6 +552,10 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     if ((e = hipFuncSetAttribute((const void *)k_reconstruct<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
         return fail(hip_fail(e, "hipFuncSetAttribute(k_reconstruct<1>)"));
     if (fused_opt_in() != COMET_OK) return fail(COMET_ERR_HIP);
+    for (const void *fn : {(const void *)k_encode_count<64, false, kEncBlockWide>, (const void *)k_encode_count<128, false, kEncBlockWide>,
+                           (const void *)k_encode_count<256, false, kEncBlockWide>})
+        if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
+            return fail(hip_fail(e, "hipFuncSetAttribute(k_encode_count)"));
     if ((e = hipFuncSetAttribute((const void *)k_code_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
         return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));

@@ -129,9 +129,13 @@ __global__ void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, c
 constexpr int kEncBlock = 256;             // four wavefronts, each encodes 256 symbols per step cooperatively
 constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
 // Code lengths (one byte each) the count kernel caches in LDS instead of part of the encode table, if every symbol that
-// occurs lies among them: 16384 around the centre (the room of the table's cached part), 32768 for the largest alphabets
-// (whose symbols spread wider; twice the LDS, which costs the smaller ones more than it gains them).
-__host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u ? nbins : (nbins <= 32768u ? 16384u : 32768u); }
+// occurs lies among them: 16384 around the centre (the room of the table's cached part).  Above 32768 bins: all of
+// them (64 KB), with twice the wavefronts per workgroup, so that a compute unit holds as many as with a window of
+// 32768; a field whose codes reached beyond such a window was looked up in global memory instead, 98 us for
+// 64 x 256 x 56 x 56 at a bound of 1e-4, now 38.
+constexpr int kEncBlockWide = 512;
+__host__ __device__ inline bool enc_wide(uint32_t nbins) { return nbins > 32768u; }
+__host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u || enc_wide(nbins) ? nbins : 16384u; }
 constexpr uint32_t kEncSegChunksMax = 4096;   // chunks per workgroup segment (their word counts live in LDS)
 
 struct EncodeArgs {
@@ -175,7 +179,7 @@ constexpr uint32_t kEncUnroll = 4;         // steps of 256 symbols a wavefront h
 constexpr uint32_t kEncStepWordsMax = 468; // 256 code words of up to 58 bits, in 32-bit words, plus slack
 constexpr uint32_t kEncBufWords = 640;     // assembly buffer of a wavefront (ordinary code books fill a fraction of it)
 // S: symbols per chunk (64, 128, 256); FULLTBL: the whole encode table is in LDS
-template <int S, bool FULLTBL> __global__ void k_encode_count(EncodeArgs a);
+template <int S, bool FULLTBL, int NT> __global__ void k_encode_count(EncodeArgs a);   // NT threads (kEncBlock, or kEncBlockWide)
 template <int S, bool FULLTBL> __global__ void k_encode_pack(EncodeArgs a);
 
 // ---- decode tables ------------------------------------------------------------

@@ -60,14 +60,14 @@ __device__ inline void fetch_steps(const uint16_t *codes, uint64_t n, uint32_t c
 }  // namespace
 
 // ---------------------------------------------------------------------------
-template <int S, bool FULLTBL>
-__global__ __launch_bounds__(kEncBlock) void k_encode_count(EncodeArgs a) {
+template <int S, bool FULLTBL, int NT>
+__global__ __launch_bounds__(NT) void k_encode_count(EncodeArgs a) {
     constexpr int LPC = S / 4;                       // lanes per chunk
     constexpr int CPS = 256 / S;                     // chunks per wavefront step
     extern __shared__ uint64_t s_dyn_enc[];
     uint64_t *s_tbl = s_dyn_enc;                                                // a.tbl_n entries and a zero entry
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(s_dyn_enc) + a.tbl_room);   // a.seg_chunks word counts
-    __shared__ uint32_t s_part32[kEncBlock / kWave];
+    __shared__ uint32_t s_part32[NT / kWave];
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = (uint32_t)lane_id();
@@ -79,9 +79,14 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_count(EncodeArgs a) {
     const uint32_t lenw_n = enc_len_window(a.nbins), lenw_lo = (a.nbins - lenw_n) / 2u;
     if (lengths_only) {
         uint8_t *s_len8 = reinterpret_cast<uint8_t *>(s_tbl);
-        for (uint32_t i = tid; i <= lenw_n; i += kEncBlock) s_len8[i] = (i < lenw_n) ? a.len8[lenw_lo + i] : a.len8[0];
+        uint32_t done = 0;
+        if (lenw_lo == 0u) {                         // (the length section starts at a multiple of 16 bytes)
+            done = lenw_n & ~7u;
+            for (uint32_t i = tid; i < done / 8u; i += NT) reinterpret_cast<uint2 *>(s_len8)[i] = reinterpret_cast<const uint2 *>(a.len8)[i];
+        }
+        for (uint32_t i = done + tid; i <= lenw_n; i += NT) s_len8[i] = (i < lenw_n) ? a.len8[lenw_lo + i] : a.len8[0];
     } else {
-        for (uint32_t i = tid; i <= a.tbl_n; i += kEncBlock) s_tbl[i] = (i < a.tbl_n) ? a.enc[a.tbl_lo + i] : (FULLTBL ? 0ull : a.enc[0]);
+        for (uint32_t i = tid; i <= a.tbl_n; i += NT) s_tbl[i] = (i < a.tbl_n) ? a.enc[a.tbl_lo + i] : (FULLTBL ? 0ull : a.enc[0]);
     }
     __syncthreads();
 
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_count(EncodeArgs a) {
     // The loop over the steps, once per way of looking a code up (the choice is the same for every thread).
     auto sweep = [&](auto tbl) {
     // kEncUnroll steps per iteration, their loads issued together
-    for (uint32_t st0 = wave * kEncUnroll; st0 < steps; st0 += (kEncBlock / kWave) * kEncUnroll) {
+    for (uint32_t st0 = wave * kEncUnroll; st0 < steps; st0 += (NT / kWave) * kEncUnroll) {
         uint2 v[kEncUnroll];
         fetch_steps<S>(a.codes, a.n, c_lo, st0, steps, lane, v);
 #pragma unroll
@@ -127,13 +132,13 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_count(EncodeArgs a) {
     else sweep(TableView<0>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
     __syncthreads();
 
-    // counts -> segment-relative exclusive offsets, kEncBlock consecutive chunks at a time
+    // counts -> segment-relative exclusive offsets, NT consecutive chunks at a time
     uint32_t running = 0;
-    for (uint32_t base = 0; base < nc; base += kEncBlock) {
+    for (uint32_t base = 0; base < nc; base += NT) {
         const uint32_t idx = base + tid;
         const uint32_t cnt = (idx < nc) ? s_cnt[idx] : 0u;
         uint32_t tot;
-        const uint32_t ex = block_excl_scan<uint32_t, kEncBlock / kWave>(cnt, s_part32, tot);
+        const uint32_t ex = block_excl_scan<uint32_t, NT / kWave>(cnt, s_part32, tot);
         if (idx < nc) a.chunk_off[c_lo + idx] = running + ex;
         running += tot;
     }
@@ -410,8 +415,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
 }
 
 #define COMET_INST_ENC(S)                                                  \
-    template __global__ void k_encode_count<S, true>(EncodeArgs);          \
-    template __global__ void k_encode_count<S, false>(EncodeArgs);         \
+    template __global__ void k_encode_count<S, true, kEncBlock>(EncodeArgs);    \
+    template __global__ void k_encode_count<S, false, kEncBlock>(EncodeArgs);   \
+    template __global__ void k_encode_count<S, false, kEncBlockWide>(EncodeArgs); \
     template __global__ void k_encode_pack<S, true>(EncodeArgs);           \
     template __global__ void k_encode_pack<S, false>(EncodeArgs);
 COMET_INST_ENC(64)
