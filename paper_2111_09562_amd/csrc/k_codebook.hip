@@ -609,6 +609,82 @@ __device__ inline void book_tree(BookLds &s, uint32_t m, const uint64_t (&key)[2
     __syncthreads();
 }
 
+// The rounds of a tree in global memory while more than `stop` items wait, by the whole workgroup, with the round's items in
+// LDS: the next kBookWin leaves and nodes come in with one memory round trip, the threads count those of weight <= t in
+// registers, ranks are searched in LDS, and the new nodes' weights are sums of neighbours in merged order, stored in a
+// row.  32-bit weights: all of them together stay below 2^31.  A round that takes a whole window (thousands of leaves of one
+// weight) goes through the general routines.  About 4.5 us a round instead of 8 (searches for the counts and the
+// ranks in global memory, atomic additions).
+constexpr uint32_t kBookWin = 2u * (uint32_t)kBookBlock;
+__device__ inline void huffman_rounds_window(const uint64_t *keys, uint64_t *iw, uint32_t *leaf_parent, uint32_t *int_parent,
+                                             uint32_t m, uint32_t *s_x, uint32_t *s_part, uint32_t stop,
+                                             uint32_t &li, uint32_t &ii, uint32_t &ni) {
+    const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1), wave = tid / (uint32_t)kWave;
+    uint32_t *leaf = s_x, *node = s_x + kBookWin, *merged = s_x + 2u * kBookWin;
+    auto below = [](const uint32_t *arr, uint32_t n, uint32_t w, uint32_t or_equal) -> uint32_t {     // entries < w + or_equal
+        uint32_t lo = 0, hi = n;
+        const uint32_t lim = w + or_equal;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (arr[mid] < lim) lo = mid + 1u; else hi = mid;
+        }
+        return lo;
+    };
+    li = 0; ii = 0; ni = 0;
+    while ((m - li) + (ni - ii) > stop) {
+        uint32_t a[2], b[2];
+#pragma unroll
+        for (uint32_t v = 0; v < 2; ++v) {
+            const uint32_t i = tid + v * (uint32_t)kBookBlock;
+            a[v] = li + i < m ? (uint32_t)(keys[li + i] >> 16) : ~0u;
+            b[v] = ii + i < ni ? (uint32_t)iw[ii + i] : ~0u;
+        }
+#pragma unroll
+        for (uint32_t v = 0; v < 2; ++v) {
+            leaf[tid + v * (uint32_t)kBookBlock] = a[v];
+            node[tid + v * (uint32_t)kBookBlock] = b[v];
+        }
+        __syncthreads();
+        const uint32_t a0 = leaf[0], a1 = leaf[1], b0 = node[0], b1 = node[1];
+        const uint32_t t = a0 <= b0 ? a0 + (a1 <= b0 ? a1 : b0) : b0 + (a0 <= b1 ? a0 : b1);      // the two lightest (they exist)
+        const uint32_t ca = (uint32_t)__popcll(wave_ballot(a[0] <= t)) + (uint32_t)__popcll(wave_ballot(a[1] <= t));
+        const uint32_t cb = (uint32_t)__popcll(wave_ballot(b[0] <= t)) + (uint32_t)__popcll(wave_ballot(b[1] <= t));
+        if (lane == 0) s_part[wave] = ca | (cb << 16);
+        __syncthreads();
+        uint32_t both = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < (uint32_t)(kBookBlock / kWave); ++w) both += s_part[w];
+        uint32_t nl = both & 0xffffu, nn = both >> 16;
+        if (nl == kBookWin || nn == kBookWin) {              // (uniform) perhaps more than the window shows
+            round_control<false, true>(keys, iw, m, li, ii, ni, &nl, &nn);
+            round_items<4u>(keys, iw, leaf_parent, int_parent, li, ii, ni, nl, nn, tid, (uint32_t)kBookBlock);
+        } else {
+            if ((nl + nn) & 1u) {
+                const uint32_t la = nl ? leaf[nl - 1u] : 0u, lb = nn ? node[nn - 1u] : 0u;
+                if (nn && (!nl || la <= lb)) --nn; else --nl;
+            }
+#pragma unroll
+            for (uint32_t v = 0; v < 2; ++v) {
+                const uint32_t i = tid + v * (uint32_t)kBookBlock;
+                if (i < nl) {
+                    const uint32_t rank = i + below(node, nn, a[v], 0u);
+                    merged[rank] = a[v];
+                    leaf_parent[li + i] = ni + (rank >> 1);
+                }
+                if (i < nn) {
+                    const uint32_t rank = i + below(leaf, nl, b[v], 1u);
+                    merged[rank] = b[v];
+                    int_parent[ii + i] = ni + (rank >> 1);
+                }
+            }
+            __syncthreads();
+            for (uint32_t k = tid; k < (nl + nn) >> 1; k += (uint32_t)kBookBlock) iw[ni + k] = (uint64_t)merged[2u * k] + merged[2u * k + 1u];
+        }
+        __syncthreads();
+        li += nl; ii += nn; ni += (nl + nn) >> 1;
+    }
+}
+
 // More symbols than fit LDS, built from the histogram in global memory; keys[0, m): the leaves in order if presorted.
 __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     const uint32_t tid = threadIdx.x;
@@ -640,13 +716,30 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     if (!a.presorted) bitonic_sort(keys, m2);
     // ---- 3. two-queue merge in rounds ----
     {
-        // The first rounds merge thousands of light leaves each: in global memory, by everybody.  Most
+        // The first rounds merge hundreds and thousands of light leaves each: in global memory, by everybody.  Most
         // rounds come later, with few items each: once the L leaves and N nodes that wait make at most
         // kBookLdsSyms / 2 items, they move to LDS (L + 2N - 1 nodes at the end, which fit), the rounds
         // are finished there, and the parents go back with the offset of the first node moved.
         uint32_t li, ii, ni;
-        huffman_rounds<false>(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, [] { __syncthreads(); },
-                              kBookLdsSyms / 2u, li, ii, ni);
+        bool narrow = a.narrow != 0u;
+        if (!a.hdr) {                                        // (a stage call: any frequencies)
+            uint64_t total = 0, sum = 0;
+            for (uint32_t i = tid; i < m; i += kBookBlock) sum += keys[i] >> 16;
+            sum = wave_sum<uint64_t>(sum);
+            uint64_t *part64 = reinterpret_cast<uint64_t *>(s.u.exchange);
+            __syncthreads();
+            if ((tid & (uint32_t)(kWave - 1)) == 0u) part64[tid / (uint32_t)kWave] = sum;
+            __syncthreads();
+            for (uint32_t w = 0; w < kBookBlock / kWave; ++w) total += part64[w];
+            narrow = total < 0x7fffffffull;
+            __syncthreads();
+        }
+        static_assert(sizeof(s.u.exchange) >= 16u * kBookWin, "window of both queues and the merged order");
+        if (narrow)
+            huffman_rounds_window(keys, iw, leaf_parent, int_parent, m, reinterpret_cast<uint32_t *>(s.u.exchange), s.part, kBookLdsSyms / 2u, li, ii, ni);
+        else
+            huffman_rounds<false>(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, [] { __syncthreads(); },
+                                  kBookLdsSyms / 2u, li, ii, ni);
         const uint32_t L = m - li, N = ni - ii;
         if (L + N > 1u) {
             uint64_t *l_keys = s.u.large.keys, *l_iw = s.u.large.iw;

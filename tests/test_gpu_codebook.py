@@ -56,9 +56,12 @@ def test_more_symbols_than_lds(oracle, nbins, m):
     ctx = comet.Context(max_elems=4096, max_nbins=65536)
     lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
     codes = torch.empty(nbins, dtype=torch.int64, device="cuda")
-    for kind in ("flat", "doubling", "steps", "geometric", "random"):
+    for kind in ("flat", "doubling", "steps", "geometric", "random", "largest 32-bit total", "64-bit total"):
+        f = _hist("random" if "total" in kind else kind, m, rng)
+        if "total" in kind:                               # (the limit of 32-bit weights)
+            f[int(np.argmax(f))] += 2 ** 31 - (2 if "largest" in kind else 1) - int(f.sum())
         h = np.zeros(nbins, np.uint32)
-        h[np.sort(rng.choice(nbins, m, replace=False))] = _hist(kind, m, rng)
+        h[np.sort(rng.choice(nbins, m, replace=False))] = f
         want = oracle.code_lengths(h)
         lens.fill_(77)
         codes.fill_(77)
