@@ -222,8 +222,7 @@ struct TablesArgs {
     const uint8_t *len;        // u8[nbins]
     uint32_t nbins;
     DecodeTables t;
-    uint32_t compact_only;     // 1: the caller decodes with kernels that use the compact table whenever it
-                               //    exists, so the general table need not be filled in that case
+    uint32_t compact_only;     // 1: the caller decodes with the chunk decoders, which never read the general table
     uint32_t general_unless_chunk64;   // 1: ... except for a container whose chunks are not 64 symbols (its kernel reads the general table)
     Control *ctl;
     uint32_t reset_ctl;        // 1: this kernel is the first of its call and clears *ctl itself (no separate fill before it)
