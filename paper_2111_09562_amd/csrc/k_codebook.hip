@@ -1090,7 +1090,7 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     __shared__ uint32_t s_findex[65];
     __shared__ uint32_t s_lim18[20];                                // limits of the lengths up to 18, of codes left-aligned in 18 bits
     __shared__ uint32_t s_off[20];                                  // place in canonical order minus first code, of those lengths
-    __shared__ uint32_t s_ok, s_maxlen, s_m;
+    __shared__ uint32_t s_ok, s_code_ok, s_maxlen, s_m;             // header accepted; lengths are a complete code (a word each: a wavefront may still read the first when another stores the second)
     __shared__ uint16_t s_sorted[kLut16MaxBins];                    // symbols in canonical order (the first ones, of a larger alphabet)
     __shared__ uint32_t s_wc[kWaves][64];                           // symbols per (wavefront, length), then those of the wavefronts in front
 
@@ -1194,7 +1194,7 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
         wave_lds_fence();
         uint32_t mx, mn;
         const bool ok = m != 0u && canonical_first_codes_wave(s_cnt, m, s_first, s_findex, &mx, &mn);
-        if (tid == 0) { s_maxlen = mx; s_m = m; s_ok = ok ? 1u : 0u; }
+        if (tid == 0) { s_maxlen = mx; s_m = m; s_code_ok = ok ? 1u : 0u; }
         if (ok) {
             wave_lds_fence();                                // the first codes of the other lengths
             const uint32_t L = tid ? tid : 64u;              // one length per lane
@@ -1217,7 +1217,7 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
         }
     }
     __syncthreads();
-    if (!s_ok) {
+    if (!s_code_ok) {
         if (tid == 0) raise_format();
         return;
     }
