@@ -130,13 +130,17 @@ constexpr int kEncBlock = 256;             // four wavefronts, each encodes 256 
 constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
 // Code lengths (one byte each) the count kernel caches in LDS instead of part of the encode table, if every symbol that
 // occurs lies among them: 16384 around the centre (the room of the table's cached part).  Above 32768 bins: all of
-// them (64 KB), with twice the wavefronts per workgroup, so that a compute unit holds as many as with a window of
-// 32768; a field whose codes reached beyond such a window was looked up in global memory instead, 98 us for
-// 64 x 256 x 56 x 56 at a bound of 1e-4, now 38.
+// them (64 KB), with twice the wavefronts per workgroup, so that a compute unit holds sixteen of them (two workgroups; a
+// window of 32768 lengths, three workgroups of half the size: twelve); a field whose codes reached beyond such a window
+// was looked up in global memory instead, 98 us for 64 x 256 x 56 x 56 at a bound of 1e-4, now 38.
 constexpr int kEncBlockWide = 512;
 __host__ __device__ inline bool enc_wide(uint32_t nbins) { return nbins > 32768u; }
 __host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u || enc_wide(nbins) ? nbins : 16384u; }
-constexpr uint32_t kEncSegChunksMax = 4096;   // chunks per workgroup segment (their word counts live in LDS)
+// Chunks per workgroup segment (their word counts live in LDS).  The largest alphabet's lengths, the counts of the largest
+// segment and the scan's words have to fit LDS twice: with 4096 chunks they were 80 bytes too many, and one workgroup per
+// compute unit took 362 us for 128 x 64 x 224 x 224; two take 240.
+constexpr uint32_t kEncSegChunksMax = 4064;
+static_assert(2u * (65536u + 8u + 4u * kEncSegChunksMax + 4u * (kEncBlockWide / kWave)) <= kLdsPerCu, "two workgroups of the wide count kernel per compute unit");
 
 struct EncodeArgs {
     const uint16_t *codes;
