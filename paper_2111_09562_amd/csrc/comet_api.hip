@@ -99,6 +99,9 @@ struct ZeroLayout {          // sub-allocation of the zero region for one call
     uint64_t off_hist, off_parts, off_desc_q, off_desc_e, bytes;
 };
 
+// Does the row-walking quantise kernel count its codes (what it can of them, for an alphabet larger than its window)?
+bool quantize_counts(uint64_t n, uint32_t nbins) { return nbins <= kHistWindowMax || n >= kQuantCountMin; }
+
 // partial histograms of the row-walking quantise kernel for an alphabet of nbins
 uint32_t hist_copies(uint32_t nbins) {
     const uint32_t c = kQuantHistPartsWords / (nbins ? nbins : 1u);
@@ -259,27 +262,35 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         a.hist_copies = hist_copies(nbins);
         a.hist_shift = a.win_n <= 2048u ? 2u : 0u;            // four copies while they fit 32 KB
         const bool full = a.win_n == nbins;
-        const size_t lds = full ? (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u : 0u;
-        // (an alphabet larger than the window: the codes are counted from memory, behind the sweep)
+        const bool counts = quantize_counts(n, nbins);
+        const size_t lds = counts ? (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u + (full ? 0u : (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u) : 0u;
+        a.run_from = ctx->run_count + 3u * ctx->max_runs;
+        // (an alphabet larger than the window: what the sweep does not count is counted from memory, behind it)
         auto count_codes = [&]() {
             if (full || reuse_len) return;
             CodeHistArgs h{};
             h.codes = codes; h.n = n; h.nbins = nbins; h.radius = nbins / 2u;
             h.win_n = nbins < kCodeHistWindow ? nbins : kCodeHistWindow;
             h.win_lo = (nbins - h.win_n) / 2u;
+            h.run_from = a.run_from;
+            h.divRun = make_fastdiv(g.rows_per_wave * s.w);
             h.parts = hist_parts; h.copies = a.hist_copies;
-            // one workgroup per compute unit, with at least 8192 codes (clearing and adding up its bins costs as much as those)
+            // one workgroup per compute unit, with at least 8192 codes (clearing and adding up its bins costs as much as those);
+            // runs have 2048 codes or more and are at most 4 * kQuantRunsPerSimd per compute unit, so a slice sees fewer than kCodeHistRuns
+            static_assert(8192u / 2048u + 3u <= kCodeHistRuns && 4u * kQuantRunsPerSimd + 3u <= kCodeHistRuns, "runs of a slice");
             uint64_t wg = (n + 8191u) / 8192u;
             if (wg > (uint64_t)ctx->num_cu) wg = (uint64_t)ctx->num_cu;
             const size_t lds_h = ((size_t)h.win_n + 4u * kCodeHistHot + kCodeHistBlock) * 4u;
-            hipLaunchKernelGGL(k_code_hist, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
+            if (counts) hipLaunchKernelGGL(k_code_hist<true>, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
+            else hipLaunchKernelGGL(k_code_hist<false>, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
         };
 #define COMET_LAUNCH_QR_IN(VEC, NSEG, MULTI, IN)                                                                       \
         do {                                                                                                           \
             {                                                                                                          \
                 TimedScope ts(ctx, st, COMET_KERNEL_QUANTIZE);                                                         \
-                if (full) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, true, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);   \
-                else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, false, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);       \
+                if (full) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistFull, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);        \
+                else if (counts) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistPart, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a); \
+                else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistNone, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);             \
             }                                                                                                          \
             count_codes();                                                                                             \
             TimedScope ts(ctx, st, COMET_KERNEL_GATHER);                                                               \
@@ -292,8 +303,8 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
             if (!reuse_len) { COMET_LAUNCH_QR_IN(VEC, NSEG, MULTI, 0); break; }                                        \
             {                                                                                                          \
                 TimedScope ts(ctx, st, COMET_KERNEL_QUANTIZE);                                                         \
-                if (a.enc_n == nbins) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, true, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a); \
-                else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, false, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a);                 \
+                if (a.enc_n == nbins) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistFull, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a); \
+                else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistNone, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a);                 \
             }                                                                                                          \
             TimedScope ts(ctx, st, COMET_KERNEL_GATHER);                                                               \
             hipLaunchKernelGGL((k_gather_records<VEC, NSEG, MULTI, true>), dim3(grid), dim3(kQuantBlock), lds_reuse, st, a); \
@@ -445,13 +456,15 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
         }
         // a few wavefronts per SIMD, but runs of at least 2048 elements (every run re-reads one row)
         // All runs should be resident at once: a run that has to wait for a place makes the launch take two rounds.
-        // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (a
-        // histogram window of 8192 bins leaves room for three; the encoder's ring and tables of the single-pass
+        // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (the
+        // histogram window of a large alphabet leaves room for three; the encoder's ring and tables of the single-pass
         // compression for four).
         uint32_t runs_per_simd = chunk_align ? kQuantRunsPerSimdSingle : kQuantRunsPerSimd;
         if (!chunk_align) {
-            const size_t window = nbins <= kHistWindowMax ? (((size_t)nbins << (nbins <= 2048u ? 2u : 0u)) + kQuantBlock) * 4u : 0u;
-            const size_t lds = window + kQuantStaticLds;
+            const uint32_t win_n = nbins < kHistWindowMax ? nbins : kHistWindowMax;
+            const size_t window = (((size_t)win_n << (win_n <= 2048u ? 2u : 0u)) + kQuantBlock) * 4u +
+                                  (win_n < nbins ? (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u : 0u);
+            const size_t lds = (quantize_counts(n, nbins) ? window : 0u) + kQuantStaticLds;
             const uint32_t fit = (uint32_t)(kLdsPerCu / lds);
             if (fit < runs_per_simd) runs_per_simd = fit ? fit : 1u;
         }
@@ -556,9 +569,9 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
                            (const void *)k_encode_count<256, false, kEncBlockWide>})
         if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
             return fail(hip_fail(e, "hipFuncSetAttribute(k_encode_count)"));
-    if ((e = hipFuncSetAttribute((const void *)k_code_hist, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
-        return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));
+    for (const void *fn : {(const void *)k_code_hist<true>, (const void *)k_code_hist<false>})
+        if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
+            return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->occ_quant, k_quantize<true>, kQuantBlock, 4096 + kQuantRecLds * 8) != hipSuccess || c->occ_quant < 1) c->occ_quant = 4;
     (void)rc;
     *out = c;

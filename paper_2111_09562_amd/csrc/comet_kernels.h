@@ -8,7 +8,7 @@ namespace comet {
 // ---- quantise (prequantise + Lorenzo + codes + histogram + records) ----------
 constexpr int kQuantBlock = 256;
 constexpr int kQuantTile = 4096;           // elements per tile: 256 lanes x 4 iterations x float4
-constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup (row-walking kernel: larger alphabets are counted by k_code_hist)
+constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup
 
 struct QuantArgs {
     const void *x;             // fp32; the row-walking kernels also take IEEE half or bfloat16 (template parameter IN)
@@ -37,6 +37,7 @@ struct QuantArgs {
     uint32_t zero_pair;        //   container version 2: (centre << 16) | centre, else 0
     uint32_t *chunk_off;       //   chunk table of the container: offsets relative to the run (k_place_payload makes them absolute)
     uint32_t *run_words;       //   words of every run
+    uint32_t *run_from;        // kHistPart: element of every run from which on k_code_hist counts its codes
     uint32_t *work_words;      //   work area: the words of the run that starts at element e at word e / 2
     uint16_t *codes;
     uint32_t *hist;            // u32[nbins], zeroed
@@ -53,17 +54,28 @@ constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane of the row-walking ker
 constexpr uint32_t kQuantRecRun = 768;    // outlier records staged per run (one run of rows per wavefront)
 constexpr uint32_t kQuantRecLds2 = 256;   // records a wavefront buffers in LDS before it writes them to the staging area in bulk
 constexpr uint32_t kQuantRunsPerSimd = 5; // runs the launch aims at, per SIMD
+// Alphabets larger than the histogram window: a wavefront counts its run's codes while those outside the window, which it
+// lists in LDS (kQuantOowList of them) and adds to a partial histogram in bulk, are at most kQuantOowFree plus one in
+// kQuantOowShare; beyond, k_code_hist counts them from memory (why the line lies there: see that kernel) ...
+constexpr uint32_t kQuantOowList = 512, kQuantOowFree = 32, kQuantOowShare = 32;
+// ... and only for tensors of at least so many elements.  Smaller ones leave all codes to k_code_hist: beginning to count costs
+// 10 to 30 us where a run then stops (LDS for three workgroups per compute unit instead of five, bins to add up), which
+// fine bounds do.  Measured, all codes in k_code_hist / counted here, us: 12.8 M elements at 1e-4, 65536 bins 349 / 377, at 1e-2, 16384 bins
+// 114 / 109; 51.4 M 507 / 521, 222 / 201; 67.4 M 552 / 557, 266 / 228; 205 M 1237 / 1231, 684 / 569.
+constexpr uint64_t kQuantCountMin = 1ull << 26;
 constexpr uint32_t kQuantStaticLds = 8448; // static LDS of k_quantize_rows (the record buffers of its four wavefronts and a few words), rounded up
 constexpr uint32_t kLdsPerCu = 160u * 1024u;
 constexpr uint32_t kQuantRunsPerSimdSingle = 4;   //   ... of the single-pass compression (all of them resident at once)
 constexpr uint32_t kQuantHistCopiesMax = 32;        // partial histograms the workgroups spread their flushes over
 constexpr uint32_t kQuantHistPartsWords = 8u * 65536u;    // all copies together have at most this many entries (2 MB: eight copies of the largest alphabet)
 // VEC adjacent columns per lane (2 needs an even W and 8-byte aligned input), NSEG segments of 64 lanes per row,
-// MULTI: several rows per step; FULLWIN: the histogram is made here (every bin is in the LDS window), else by k_code_hist from the codes
-// REUSE: code book reuse: escapes follow the given length table, no histogram (FULLWIN is then true and unused)
+// MULTI: several rows per step; HIST: which codes are counted here: all (every bin is in the LDS window), those of a run as
+// long as few of them lie outside the window, or none (k_code_hist counts the others)
+// REUSE: code book reuse: escapes follow the given length table, no histogram (kHistFull then says that the whole encode table is in LDS, kHistNone that part of it is)
 // IN: element type of x (0 fp32, 1 IEEE half, 2 bfloat16; 16-bit inputs are widened exactly as they are loaded;
 // VEC = 2 then needs 4-byte aligned input)
-template <int VEC, int NSEG, bool MULTI, bool FULLWIN, bool REUSE = false, int IN = 0> __global__ void k_quantize_rows(QuantArgs a);
+constexpr int kHistNone = 0, kHistFull = 1, kHistPart = 2;
+template <int VEC, int NSEG, bool MULTI, int HIST, bool REUSE = false, int IN = 0> __global__ void k_quantize_rows(QuantArgs a);
 template <int VEC, int NSEG, bool MULTI, bool REUSE = false, int IN = 0> __global__ void k_gather_records(QuantArgs a);
 constexpr uint32_t kQuantReuseMaxBins = 8192;   // largest alphabet whose length table the REUSE kernels keep in LDS
 
@@ -71,15 +83,18 @@ constexpr uint32_t kQuantReuseMaxBins = 8192;   // largest alphabet whose length
 constexpr int kCodeHistBlock = 1024;
 constexpr uint32_t kCodeHistWindow = 32768;   // bins counted in LDS at most (128 KB: one workgroup per compute unit)
 constexpr uint32_t kCodeHistHot = 1024;       // innermost bins with four counters each
+constexpr uint32_t kCodeHistRuns = 64;        // runs of the quantise kernel that reach into a workgroup's slice, at most
 struct CodeHistArgs {
     const uint16_t *codes;     // 8-byte aligned (its 16-byte loads need four)
     uint64_t n;
     uint32_t nbins, radius;
     uint32_t win_lo, win_n;    // bins counted in LDS
+    const uint32_t *run_from;  // SHARED: per run, element of the run from which on its codes are counted here
+    FastDiv divRun;            // SHARED: elements per run
     uint32_t *parts;           // `copies` partial histograms of nbins entries
     uint32_t copies;
 };
-__global__ void k_code_hist(CodeHistArgs a);
+template <bool SHARED> __global__ void k_code_hist(CodeHistArgs a);   // SHARED: the quantise kernel has counted part of them (kHistPart); else all codes
 
 // ---- statistics ---------------------------------------------------------------
 constexpr int kStatsBlock = 256;

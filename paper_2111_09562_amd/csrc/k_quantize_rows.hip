@@ -81,6 +81,12 @@ template <int IN> __device__ inline float load_elem(const void *x, size_t i) {
 struct SweepCounts {
     uint32_t nnz_lane = 0;      // per lane: non-zero inputs
     uint32_t vrec = 0;          // wavefront-uniform: verbatim records
+    // kHistPart (all wavefront-uniform):
+    bool counting = true;       //   the codes are (still) counted here
+    uint32_t from = 0;          //   if not: first element of the run that is not
+    uint32_t oow = 0;           //   codes outside the histogram window among those counted
+    uint16_t *oow_list = nullptr;   //   LDS, kQuantOowList entries of this wavefront: such codes on their way to a partial histogram
+    uint32_t oow_held = 0;      //   entries of the list in use (what the caller finds there it counts)
 };
 
 // One sweep of a wavefront over rows [row_lo, row_hi).  PASS 0: everything (codes, histogram,
@@ -88,17 +94,18 @@ struct SweepCounts {
 // and a record that does not fit raises ST_CAPACITY.  Returns the number of records of the run.
 // VEC: adjacent columns per lane (1, or 2 for even W: one 8-byte load, one packed code store and
 // one cross-lane shift per pair); NSEG: segments of 64 lanes per row (1, 2, 4, 8); MULTI: a row
-// takes at most 32 lanes, K rows per step (NSEG == 1); FULLWIN: every histogram bin is in the LDS
-// window, and the codes are counted here (else k_code_hist does that).
+// takes at most 32 lanes, K rows per step (NSEG == 1); HIST: the codes are counted here (kHistFull: every bin is in the LDS
+// window), as long as few of them lie outside the window (kHistPart), or not (kHistNone).
 // REUSE: code book reuse.  s_len (LDS, u8[nbins]) holds the code lengths the caller brought; a code
 // whose length is 0 becomes an escape, there is no histogram, and an escape that the table has no
 // code word for raises ST_CODEBOOK.  In PASS 0 the codes go to the ring of `enc` in LDS and are encoded
-// from there (tbl: the encode table; FULLWIN then says that all of it is in LDS).
-template <int VEC, int NSEG, bool MULTI, bool FULLWIN, int PASS, bool REUSE = false, int IN = 0>
+// from there (tbl: the encode table; kHistFull then says that all of it is in LDS).
+template <int VEC, int NSEG, bool MULTI, int HIST, int PASS, bool REUSE = false, int IN = 0>
 __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint32_t row_hi, uint32_t lane, uint32_t *s_hist,
                                       uint32_t hist_dummy, uint2 *s_buf, uint2 *rec_dst, uint64_t rec_cap, SweepCounts &cnt,
                                       const uint8_t *s_len = nullptr, RunEncoder *enc = nullptr,
-                                      const TableView<FULLWIN> *tbl = nullptr) {
+                                      const TableView<HIST == kHistFull> *tbl = nullptr) {
+    constexpr bool FULLWIN = HIST == kHistFull;
     const uint32_t W = a.divW.d, H = a.divH.d;
     const uint32_t LPR = W / (uint32_t)VEC;         // lanes per row
     const int32_t radius = a.radius;
@@ -212,6 +219,15 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
         cur += buffered;
         buffered = 0;
     };
+    auto flush_oow = [&]() {                                     // the listed codes -> partial histogram
+        wave_lds_fence();
+        // (the workgroup's partial histogram: the codes just outside the window are few and frequent, and all
+        // workgroups adding to one copy of them queue up on a handful of cache lines)
+        uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
+        for (uint32_t i = lane; i < cnt.oow_held; i += kWave) atomicAdd(&part[cnt.oow_list[i]], 1u);
+        wave_lds_fence();
+        cnt.oow_held = 0;
+    };
     uint16_t *ring_w = (PASS == 0 && REUSE) ? const_cast<uint16_t *>(enc->ring) : nullptr;
     // REUSE: does the given table have a code word for this code?  From the length table; the single-pass sweep with
     // the whole encode table in LDS reads that instead (an entry is 0 for a symbol without a code word), which saves
@@ -237,6 +253,10 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
             const uint32_t soff = (t0 + u) * stride;
             int32_t carry_q = 0;                                // last column of the previous segment (uniform)
             const uint32_t hmask = h_row ? ~0u : 0u;            // !MULTI: "has a row above"
+            if (PASS == 0 && !REUSE && HIST == kHistPart && cnt.counting && cnt.oow > kQuantOowFree + soff / kQuantOowShare) {   // (uniform)
+                cnt.counting = false;
+                cnt.from = soff;
+            }
 #pragma unroll
             for (int s = 0; s < NSEG; ++s) {
                 const bool valid = FULL ? col_ok[s] : (col[s] + soff < n_el);
@@ -295,13 +315,31 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                     sm[v] = wave_ballot(susp[v]) & vmask;
                     any_rec |= em[v] | sm[v];
                     if (PASS == 0) cnt.nnz_lane += (x[v] != 0.0f) ? 1u : 0u;   // lanes without an element hold 0
-                    if (PASS == 0 && !REUSE && FULLWIN) {
+                    if (PASS == 0 && !REUSE && HIST != kHistNone) {
                         // Histogram: no divergent branch (switching the execution mask costs more than the
                         // atomic).  Lanes that count nothing add to a word of their own; the centre bin is
                         // not counted here, it is what is left of the workgroup's elements.  The window is
                         // replicated: lanes that meet in one bin mostly use different copies.
                         const bool count = valid && code[v] != (uint32_t)radius;
-                        atomicAdd(&s_hist[count ? (code[v] << a.hist_shift) + hist_sub : hist_dummy], 1u);
+                        if (FULLWIN) {
+                            atomicAdd(&s_hist[count ? (code[v] << a.hist_shift) + hist_sub : hist_dummy], 1u);
+                        } else if (cnt.counting) {               // uniform
+                            const uint32_t bin = code[v] - a.win_lo;
+                            const bool inwin = bin < a.win_n;
+                            atomicAdd(&s_hist[(count && inwin) ? (bin << a.hist_shift) + hist_sub : hist_dummy], 1u);
+                            // A code outside the window goes to a list in LDS and from there, in bulk, to a partial
+                            // histogram: an atomic on global memory in this loop would make every step wait for all
+                            // loads in flight.
+                            const uint64_t om = wave_ballot(count && !inwin);
+                            if (om != 0ull) {
+                                const uint32_t n_new = (uint32_t)__popcll(om);
+                                if (cnt.oow_held + n_new > kQuantOowList) flush_oow();
+                                if (count && !inwin)
+                                    cnt.oow_list[cnt.oow_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u))] = (uint16_t)code[v];
+                                cnt.oow_held += n_new;
+                                cnt.oow += n_new;
+                            }
+                        }
                     }
                 }
                 if (PASS == 0 && REUSE) {
@@ -387,6 +425,7 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
     }
     drain(n_el, true);
     flush_records();
+    if (PASS == 0 && !REUSE && HIST == kHistPart) cnt.from = cnt.counting || cnt.from > n_el ? n_el : cnt.from;
     return cur;
 }
 
@@ -401,15 +440,16 @@ __device__ inline void run_rows(const QuantArgs &a, uint32_t run, uint32_t *lo, 
 }  // namespace
 
 // One run per wavefront, kQuantBlock / 64 runs per workgroup.
-template <int VEC, int NSEG, bool MULTI, bool FULLWIN, bool REUSE, int IN>
+template <int VEC, int NSEG, bool MULTI, int HIST, bool REUSE, int IN>
 __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
+    constexpr bool FULLWIN = HIST == kHistFull;
     extern __shared__ uint32_t s_dyn_qr[];          // histogram window: a.win_n bins, 1 << a.hist_shift copies of each;
                                                     // then one word per thread for the lanes that count nothing
                                                     // (REUSE: the given length table instead, u8[nbins])
     constexpr int kWaves = kQuantBlock / kWave;
     uint32_t *s_hist = s_dyn_qr;
     __shared__ uint64_t s_part64[kWaves];
-    __shared__ uint32_t s_tot[kWaves][3];
+    __shared__ uint32_t s_tot[kWaves][HIST == kHistPart ? 5 : 3];
     __shared__ uint2 s_recbuf[kWaves][kQuantRecLds2];   // outlier records of a wavefront on their way to the staging area
 
     const uint32_t tid = threadIdx.x;
@@ -425,7 +465,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     }
     // REUSE: behind the length table the cached part of the encode table (and a zero entry), then per
     // wavefront the ring of codes (and the word lanes without an element write to) and the assembly buffer
-    // (no length table if the whole encode table is there: FULLWIN)
+    // (no length table if the whole encode table is there: kHistFull)
     uint64_t *s_tbl = reinterpret_cast<uint64_t *>(s_len + (FULLWIN ? 0u : ((a.nbins + 7u) & ~7u)));
     uint16_t *s_ring = reinterpret_cast<uint16_t *>(s_tbl + a.enc_n + 1u) + wave * (kEncRingSyms + 4u);
     uint32_t *s_asm = reinterpret_cast<uint32_t *>(reinterpret_cast<uint16_t *>(s_tbl + a.enc_n + 1u) + kWaves * (kEncRingSyms + 4u)) + wave * kEncRunBufWords;
@@ -434,7 +474,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
             for (uint32_t i = tid; i < a.nbins; i += kQuantBlock) s_len[i] = a.reuse_len[i];
         for (uint32_t i = tid; i <= a.enc_n; i += kQuantBlock) s_tbl[i] = (i < a.enc_n) ? a.enc[a.enc_lo + i] : 0ull;
         for (uint32_t i = lane; i < kEncRunBufWords; i += kWave) s_asm[i] = 0;
-    } else if (FULLWIN) {
+    } else if (HIST != kHistNone) {
         for (uint32_t i = tid; i < (a.win_n << a.hist_shift); i += kQuantBlock) s_hist[i] = 0;
     }
     __syncthreads();
@@ -443,6 +483,8 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     uint32_t row_lo, row_hi;
     run_rows(a, run, &row_lo, &row_hi);
     SweepCounts cnt;
+    // (a window that does not hold every bin: behind it and the threads' dummy words, a list per wavefront)
+    if (!REUSE && HIST == kHistPart) cnt.oow_list = reinterpret_cast<uint16_t *>(s_hist + (a.win_n << a.hist_shift) + kQuantBlock) + wave * kQuantOowList;
     uint32_t my_records = 0;
     RunEncoder enc;
     TableView<FULLWIN> tbl{s_tbl, a.enc, a.enc_lo, a.enc_n, a.nbins};
@@ -455,7 +497,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         enc.zero_pair = a.zero_pair;
     }
     if (row_hi > row_lo)
-        my_records = sweep_rows<VEC, NSEG, MULTI, FULLWIN, 0, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, (a.win_n << a.hist_shift) + tid, s_recbuf[wave],
+        my_records = sweep_rows<VEC, NSEG, MULTI, HIST, 0, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, (a.win_n << a.hist_shift) + tid, s_recbuf[wave],
                                                                  reinterpret_cast<uint2 *>(a.stage) + (size_t)run * kQuantRecRun, kQuantRecRun, cnt, s_len,
                                                                  REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
     if (REUSE) {
@@ -469,6 +511,10 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     if (lane == 0) {
         a.run_count[run] = my_records;
         s_tot[wave][0] = my_records; s_tot[wave][1] = nnz_wave; s_tot[wave][2] = cnt.vrec;
+        if (HIST == kHistPart) {
+            s_tot[wave][3] = cnt.from;                       // elements whose codes are counted here
+            s_tot[wave][4] = cnt.oow != cnt.oow_held;        // part of them is in a partial histogram already
+        }
     }
 
     // ---- flush the private histogram ----
@@ -483,24 +529,35 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         for (int w = 0; w < kWaves; ++w) t += s_tot[w][tid];
         a.run_count[gridDim.x * kWaves + tid * gridDim.x + blockIdx.x] = t;   // three arrays of one entry per workgroup
     }
-    if (REUSE || !FULLWIN) return;                  // no histogram (uniform: every thread has passed the barrier above)
+    if (REUSE || HIST == kHistNone) return;         // no histogram (uniform: every thread has passed the barrier above)
+    const uint64_t r0 = (uint64_t)blockIdx.x * kWaves * a.rows_per_wave;
+    uint64_t r1 = r0 + (uint64_t)kWaves * a.rows_per_wave;
+    if (r1 > a.rows_total) r1 = a.rows_total;
+    uint64_t elems = (r1 > r0) ? (r1 - r0) * a.divW.d : 0ull;
     uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
     uint64_t counted = 0;
+    if (HIST == kHistPart) {
+        uint32_t here = 0, begun = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) { here += s_tot[w][3]; begun |= s_tot[w][4]; }
+        // runs that stopped counting soon after they began: adding up their few hundred bins would cost more (25 us of
+        // a sweep of 58) than counting those codes once more with the others
+        const bool drop = !begun && here < elems / 16u;     // (uniform)
+        if (lane == 0) a.run_from[run] = drop ? 0u : cnt.from;
+        if (drop) return;
+        for (uint32_t i = lane; i < cnt.oow_held; i += kWave) atomicAdd(&part[cnt.oow_list[i]], 1u);
+        elems = here;
+        counted = lane ? 0ull : (uint64_t)cnt.oow;
+    }
     for (uint32_t i = tid; i < a.win_n; i += kQuantBlock) {
         uint32_t v = 0;
         for (uint32_t k = 0; k < (1u << a.hist_shift); ++k) v += s_hist[(i << a.hist_shift) + k];
         counted += v;
-        if (v) atomicAdd(&part[i], v);
+        if (v) atomicAdd(&part[a.win_lo + i], v);
     }
     uint64_t total;
     (void)block_excl_scan<uint64_t, kWaves>(counted, s_part64, total);
-    if (tid == 0) {
-        const uint64_t r0 = (uint64_t)blockIdx.x * kWaves * a.rows_per_wave;
-        uint64_t r1 = r0 + (uint64_t)kWaves * a.rows_per_wave;
-        if (r1 > a.rows_total) r1 = a.rows_total;
-        const uint64_t elems = (r1 > r0) ? (r1 - r0) * a.divW.d : 0ull;
-        if (elems > total) atomicAdd(&part[a.radius], (uint32_t)(elems - total));
-    }
+    if (tid == 0 && elems > total) atomicAdd(&part[a.radius], (uint32_t)(elems - total));
 }
 
 // Moves the staged records of every run to their final, ordered place; same grid as k_quantize_rows.
@@ -584,22 +641,21 @@ __global__ __launch_bounds__(kQuantBlock) void k_gather_records(QuantArgs a) {
         uint32_t row_lo, row_hi;
         run_rows(a, run, &row_lo, &row_hi);
         SweepCounts unused;
-        (void)sweep_rows<VEC, NSEG, MULTI, true, 1, REUSE, IN>(a, row_lo, row_hi, lane, nullptr, 0, s_recbuf[wave], dst, room, unused, s_len);
+        (void)sweep_rows<VEC, NSEG, MULTI, kHistFull, 1, REUSE, IN>(a, row_lo, row_hi, lane, nullptr, 0, s_recbuf[wave], dst, room, unused, s_len);
     }
 }
 
 #define COMET_INST_QR(VEC, NSEG, MULTI)                                                          \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, true, false, 0>(QuantArgs);       \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, false, false, 0>(QuantArgs);      \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, true, true, 0>(QuantArgs);        \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, false, true, 0>(QuantArgs);       \
-    template __global__ void k_gather_records<VEC, NSEG, MULTI, false, 0>(QuantArgs);            \
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistFull, true, 0>(QuantArgs);   \
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistNone, true, 0>(QuantArgs);   \
     template __global__ void k_gather_records<VEC, NSEG, MULTI, true, 0>(QuantArgs);             \
-    COMET_INST_QR16(VEC, NSEG, MULTI, 1)                                                         \
-    COMET_INST_QR16(VEC, NSEG, MULTI, 2)
-#define COMET_INST_QR16(VEC, NSEG, MULTI, IN)                                                    \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, true, false, IN>(QuantArgs);      \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, false, false, IN>(QuantArgs);     \
+    COMET_INST_QR_IN(VEC, NSEG, MULTI, 0)                                                        \
+    COMET_INST_QR_IN(VEC, NSEG, MULTI, 1)                                                        \
+    COMET_INST_QR_IN(VEC, NSEG, MULTI, 2)
+#define COMET_INST_QR_IN(VEC, NSEG, MULTI, IN)                                                   \
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistFull, false, IN>(QuantArgs); \
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistPart, false, IN>(QuantArgs); \
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistNone, false, IN>(QuantArgs); \
     template __global__ void k_gather_records<VEC, NSEG, MULTI, false, IN>(QuantArgs);
 COMET_INST_QR(1, 1, true)
 COMET_INST_QR(1, 1, false)
@@ -610,7 +666,7 @@ COMET_INST_QR(2, 1, true)
 COMET_INST_QR(2, 1, false)
 COMET_INST_QR(2, 2, false)
 COMET_INST_QR(2, 4, false)
-#undef COMET_INST_QR16
+#undef COMET_INST_QR_IN
 #undef COMET_INST_QR
 
 }  // namespace comet

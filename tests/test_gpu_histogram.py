@@ -30,3 +30,44 @@ def test_counts(oracle, nbins, shape):
         used = ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, out)
         assert np.array_equal(out[:used].cpu().numpy(), oracle.compress(x, eb, nbins, 64)), spread
     ctx.close()
+
+
+@pytest.mark.parametrize("nbins", [8194, 40000, 65536])
+@pytest.mark.parametrize("shape", [(64, 64, 128, 129), (2, 69400, 22, 22), (1, 8200, 91, 91), (17, 16, 512, 511), (21, 64, 224, 224), (1, 1, 131080, 512), (9, 4100, 43, 43)])
+def test_counts_shared_by_two_kernels(nbins, shape):
+    """From 2^26 elements on the quantise kernel counts a run's codes as long as few of them lie outside its window, and the
+    second kernel counts the rest: fields that change from row to row, from plane to plane and once, between no code
+    outside, a few, about one in 32 (where the line lies) and most of them, so that runs of both kinds and points inside
+    a run meet in one slice of the second kernel, and widths that put both off the groups of eight codes it loads."""
+    from paper_2111_09562_amd import comet
+    n = int(np.prod(shape))
+    assert n >= 1 << 26
+    g = torch.Generator(device="cuda").manual_seed(nbins + n)
+    ctx = comet.Context(max_elems=n, max_nbins=65536)
+    codes = torch.empty(n, dtype=torch.int16, device="cuda")
+    hist = torch.empty(nbins, dtype=torch.int32, device="cuda")
+    rec = torch.empty(4 * n, dtype=torch.int32, device="cuda")
+    counts = torch.empty(3, dtype=torch.int64, device="cuda")
+    eb = 1e-3
+    noise = torch.randn(shape, device="cuda", generator=g)
+
+    def pick(values, where):
+        return torch.tensor(values, device="cuda")[torch.randint(len(values), where, device="cuda", generator=g)]
+    rows = shape[:3] + (1,)
+    n_rows = shape[0] * shape[1] * shape[2]
+    once = (torch.arange(n_rows, device="cuda") > 0.4 * n_rows).reshape(rows)
+    spread = {"none": torch.full(rows, 5.0, device="cuda"),
+              "rows": pick([1.0, 900.0, 1000.0, 2500.0, 9000.0], rows),
+              "planes": pick([1.0, 900.0, 1000.0, 2500.0], shape[:2] + (1, 1)),
+              "near the line": torch.full(rows, 950.0, device="cuda"),
+              "once": torch.where(once, 9000.0, 5.0),
+              "few": torch.where(torch.rand(rows, device="cuda", generator=g) < 0.02, 5000.0, 40.0),
+              "escapes": torch.where(torch.rand(rows, device="cuda", generator=g) < 0.5, 2.0 * nbins, 40.0)}
+    for kind, s in spread.items():
+        ctx.comet_stage_quantize((noise * s * (2 * eb)).contiguous(), eb, nbins, codes, hist, rec, counts)
+        ctx.comet_sync()
+        want = torch.zeros(nbins, dtype=torch.int64, device="cuda")
+        for part in codes.split(1 << 25):
+            want += torch.bincount(part.to(torch.int64) & 0xffff, minlength=nbins)
+        assert bool((hist.to(torch.int64) == want).all()), kind
+    ctx.close()
