@@ -214,7 +214,7 @@ constexpr uint64_t band_bytes_max(uint64_t n) {
 
 int fused_opt_in();          // k_decode_scan: opt in to its dynamic LDS size (defined with the decompression)
 // segments of the encode kernel: (chunks per segment, number of segments)
-void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t *seg_chunks, uint32_t *n_seg);
+void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t nbins, uint32_t *seg_chunks, uint32_t *n_seg);
 // Work split of the quantise kernel.  rows: the row-walking kernel (planes up to kQuantRowsMaxW
 // columns) with `grid` workgroups of four wavefronts, each wavefront on rows_per_wave consecutive
 // rows; otherwise the flat-tile kernel with `grid` segments of tiles.
@@ -391,7 +391,7 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     a.tbl_n = nbins < kEncTableMax ? nbins : kEncTableMax;
     a.tbl_lo = (nbins - a.tbl_n) / 2u;
     uint32_t seg, grid;
-    encode_geometry(ctx, a.n_chunks, &seg, &grid);
+    encode_geometry(ctx, a.n_chunks, nbins, &seg, &grid);
     a.seg_chunks = seg;
     // table and a zero entry (or, for a large alphabet, the lengths of enc_len_window() symbols: whichever is larger), word counts
     const size_t lenw = a.len8 ? enc_len_window(nbins) + 8u : 0u;
@@ -425,13 +425,14 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     return COMET_OK;
 }
 
-void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t *seg_chunks, uint32_t *n_seg) {
+void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t nbins, uint32_t *seg_chunks, uint32_t *n_seg) {
     // one segment of consecutive chunks per workgroup: about as many segments as workgroups fit the chip
     const uint64_t want = (uint64_t)ctx->num_cu * 6u;
     uint64_t seg = (n_chunks + want - 1) / want;
     seg = (seg + 3u) & ~(uint64_t)3u;
     if (seg < 4u) seg = 4u;
-    if (seg > kEncSegChunksMax) seg = kEncSegChunksMax;
+    const uint64_t most = enc_wide(nbins) ? kEncSegChunksWide : kEncSegChunksMax;
+    if (seg > most) seg = most;
     *seg_chunks = (uint32_t)seg;
     *n_seg = (uint32_t)((n_chunks + seg - 1) / seg);
 }
@@ -509,7 +510,7 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
 
     // scan descriptors: one per segment of the quantise / encode kernels (worst case over chunk sizes)
     const uint64_t tiles_q = (uint64_t)c->num_cu * 16u + 16u;
-    const uint64_t tiles_e = (uint64_t)c->num_cu * 8u + max_elems / 64u / kEncSegChunksMax + 16u;
+    const uint64_t tiles_e = (uint64_t)c->num_cu * 8u + max_elems / 64u / kEncSegChunksWide + 16u;
     const ZeroLayout z = zero_layout(kMaxBins, kMaxBins, tiles_q, tiles_e);   // the partial histograms take up to 2 MB
     c->zero_cap = z.bytes;
     const uint64_t state_bytes = offsetof(DevState, ctl) + z.bytes;
@@ -650,7 +651,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     const uint32_t S = ctx->chunk_syms;
     const uint64_t n_chunks = (n + S - 1) / S;
     uint32_t e_seg, e_grid;
-    encode_geometry(ctx, n_chunks, &e_seg, &e_grid);
+    encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
     const uint64_t tiles_q = quantize_geometry(ctx, s, n, dev_in, nbins, in_type ? 2u : 4u, dev_len ? S : 0u).grid;
     const uint64_t tiles_e = e_grid;
 
@@ -1277,7 +1278,7 @@ int comet_stage_encode(comet_ctx *ctx, const uint16_t *dev_codes, uint64_t n, ui
     hipStream_t st = (hipStream_t)stream;
     const uint64_t n_chunks = (n + chunk_syms - 1) / chunk_syms;
     uint32_t e_seg, e_grid;
-    encode_geometry(ctx, n_chunks, &e_seg, &e_grid);
+    encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
     const uint64_t tiles_e = e_grid;
     const ZeroLayout z = zero_layout(0, 0, 1, tiles_e);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;

@@ -151,11 +151,12 @@ constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
 constexpr int kEncBlockWide = 512;
 __host__ __device__ inline bool enc_wide(uint32_t nbins) { return nbins > 32768u; }
 __host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u || enc_wide(nbins) ? nbins : 16384u; }
-// Chunks per workgroup segment (their word counts live in LDS).  The largest alphabet's lengths, the counts of the largest
-// segment and the scan's words have to fit LDS twice: with 4096 chunks they were 80 bytes too many, and one workgroup per
-// compute unit took 362 us for 128 x 64 x 224 x 224; two take 240.
-constexpr uint32_t kEncSegChunksMax = 4064;
-static_assert(2u * (65536u + 8u + 4u * kEncSegChunksMax + 4u * (kEncBlockWide / kWave)) <= kLdsPerCu, "two workgroups of the wide count kernel per compute unit");
+constexpr uint32_t kEncSegChunksMax = 4096;   // chunks per workgroup segment (their word counts live in LDS)
+// ... for enc_wide() alphabets: the lengths, the counts of the largest segment and the scan's words have to fit LDS twice.  With
+// 4096 chunks they were 80 bytes too many, and one workgroup per compute unit took 362 us for 128 x 64 x 224 x 224; two
+// take 240.  (Other alphabets keep the larger segments: 16384 bins 1152 us at that size instead of 1216.)
+constexpr uint32_t kEncSegChunksWide = 4064;
+static_assert(2u * (65536u + 8u + 4u * kEncSegChunksWide + 4u * (kEncBlockWide / kWave)) <= kLdsPerCu, "two workgroups of the wide count kernel per compute unit");
 
 struct EncodeArgs {
     const uint16_t *codes;
