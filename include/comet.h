@@ -239,15 +239,19 @@ int comet_stage_reconstruct(comet_ctx *ctx, const uint16_t *dev_codes, const uin
                             comet_shape shape, uint32_t nbins, float eb, void *stream, float *dev_out);
 
 /* ---- per-kernel timing, for benchmarks ---------------------------------------
- * When enabled, every kernel the context launches is bracketed by two HIP events
+ * When enabled, every step below of a call on the context is bracketed by two HIP events
  * recorded on the call's stream.  comet_profile_read waits for those events and
- * returns, for kernel `kernel_id`, the number of launches since the last
- * comet_profile_reset and their summed duration in milliseconds.  Kernel ids:
- * 0 quantize (sweep), 1 codebook, 2 encode (pack pass), 3 decode tables,
- * 4 reconstruct (scans + store; for planes wider than 512 columns the fused
- * decode + reconstruct kernel), 5 Huffman decode, 6 gather of the outlier
+ * returns, for `kernel_id`, the number of brackets since the last
+ * comet_profile_reset ("launches") and their summed duration in milliseconds.  Kernel ids:
+ * 0 quantize (sweep; alphabets beyond 8192 bins and planes of at most 512 columns: a second
+ * one for the histogram of the codes the sweep does not count), 1 codebook (a large alphabet's
+ * sort, merge and code kernels included), 2 encode (pack pass), 3 decode tables,
+ * 4 reconstruct (scans + store; planes cut into bands, as all wider than 512 columns are: the kernels
+ * of the bands together), 5 Huffman decode, 6 gather of the outlier
  * records, 7 encode (count pass), 8 decompression in one kernel (Huffman decode, reconstruction and
- * store; containers with chunks of 64 symbols and planes of at most 512 columns).
+ * store; containers with chunks of 64 symbols and planes of at most 512 columns, unless they are cut into bands).
+ * What clears a call's control block, and the general kernel that stands behind 8 for other chunk
+ * sizes, are not timed.
  * At most 16384 launches are kept between resets; further ones are not timed. */
 #define COMET_KERNEL_QUANTIZE 0
 #define COMET_KERNEL_CODEBOOK 1

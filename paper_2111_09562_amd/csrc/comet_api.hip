@@ -281,6 +281,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
             uint64_t wg = (n + 8191u) / 8192u;
             if (wg > (uint64_t)ctx->num_cu) wg = (uint64_t)ctx->num_cu;
             const size_t lds_h = ((size_t)h.win_n + 4u * kCodeHistHot + kCodeHistBlock) * 4u;
+            TimedScope ts(ctx, st, COMET_KERNEL_QUANTIZE);
             if (counts) hipLaunchKernelGGL(k_code_hist<true>, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
             else hipLaunchKernelGGL(k_code_hist<false>, dim3((uint32_t)wg), dim3(kCodeHistBlock), lds_h, st, h);
         };

@@ -71,3 +71,19 @@ def test_counts_shared_by_two_kernels(nbins, shape):
             want += torch.bincount(part.to(torch.int64) & 0xffff, minlength=nbins)
         assert bool((hist.to(torch.int64) == want).all()), kind
     ctx.close()
+
+
+@pytest.mark.parametrize("nbins,shape,want", [(1024, (2, 8, 56, 56), 1), (8192, (2, 8, 56, 56), 1), (8194, (2, 8, 56, 56), 2), (65536, (2, 8, 56, 56), 2), (65536, (1, 1, 8, 600), 1)])
+def test_the_histogram_is_timed_with_the_quantiser(nbins, shape, want):
+    """The per-kernel timers: an alphabet beyond the sweep's window has its histogram in a kernel of its own, which the
+    quantiser's figure includes (planes of more than 512 columns have another sweep, which counts everything)."""
+    from paper_2111_09562_amd import comet
+    x = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(nbins)).clamp_min_(0.0)
+    ctx = comet.Context(x.numel(), nbins)
+    ctx.comet_profile_enable(True)
+    ctx.comet_profile_reset()
+    box = torch.empty(comet.comet_compress_bound(shape, nbins, 64), dtype=torch.uint8, device="cuda")
+    ctx.comet_compress(x, 1e-3, nbins, box)
+    assert ctx.comet_profile_read(0)[0] == want
+    assert ctx.comet_profile_read(0)[1] > 0.0
+    ctx.close()
