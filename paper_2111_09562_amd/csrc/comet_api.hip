@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/comet.h"
+#include "comet_bands.h"
 #include "comet_kernels.h"
 
 using namespace comet;
@@ -177,39 +178,6 @@ bool recon_geometry(comet_shape s, ReconGeometry *g) {
     }
     g->lds = (size_t)g->tile_rows * g->pitch * 4u + (g->use_carry ? (size_t)s.w * 4u : 0u);
     return g->lds <= 96u * 1024u;
-}
-
-// Reconstruction in bands (k_band_*): columns per lane, rows per band, segments per row, bands per plane, units, and
-// the offsets of the three arrays of sums inside their workspace of `bytes` bytes.
-struct BandGeom { uint32_t vec, R, segs, bands; uint64_t n_units, off_row, off_unit, bytes; };
-// About 2^19 * 64 elements or more: bands of 64 rows; smaller tensors: fewer rows, so that there are enough units to
-// fill the chip (a unit has 128 columns at most; 2^19 / 128 = 4096 units, four per SIMD).
-BandGeom band_geometry(comet_shape s, uint64_t n, uint32_t vec) {
-    BandGeom g{};
-    g.vec = vec;
-    const uint32_t seg_w = (uint32_t)kWave * vec;
-    g.segs = (s.w + seg_w - 1u) / seg_w;
-    uint64_t R = n >> 19;
-    if (R < kBandRowsMin) R = kBandRowsMin;
-    if (R > kBandRowsMax) R = kBandRowsMax;
-    g.bands = (uint32_t)((s.h + R - 1u) / R);
-    g.R = (s.h + g.bands - 1u) / g.bands;
-    g.bands = (s.h + g.R - 1u) / g.R;
-    const uint64_t pb = (uint64_t)s.n * s.c * g.bands;
-    g.n_units = pb * g.segs;
-    g.off_row = g.bands > 1u ? align_up(4ull * pb * s.w, 256) : 0u;           // (one band per plane: no column sums)
-    g.off_unit = g.off_row + (g.segs > 1u ? align_up(4ull * g.n_units * g.R, 256) : 0u);
-    g.bytes = g.off_unit + align_up(4ull * g.n_units, 256);
-    return g;
-}
-constexpr uint32_t kBandMinW = 128;     // narrower planes leave lanes of a unit idle (and a workgroup of k_decode_scan shares a plane)
-// What the sums of any tensor of up to n elements take, planes of at least kBandMinW columns: a column sum per
-// R / 2 or more elements (R: rows per band as above; 8n / R is below 4.7 MB until R reaches its limit of 64), a row sum
-// per 43 (129 columns, one per lane, three segments) times three halves (the rows of a plane's bands are at most half
-// as many again as its own), a unit sum per row sum at the most.
-constexpr uint64_t band_bytes_max(uint64_t n) {
-    const uint64_t col = n < (8ull << 20) ? n : (n / 8u > (8ull << 20) ? n / 8u : (8ull << 20));
-    return col + 4u * (n / 32u + n / 128u) + 4u * (n / 40u) + 8192u;
 }
 
 int fused_opt_in();          // k_decode_scan: opt in to its dynamic LDS size (defined with the decompression)
@@ -841,37 +809,6 @@ void launch_decode_chunks(const DecompWs &ws, const DsArgs &d, hipStream_t st) {
     hipLaunchKernelGGL(k_decode_chunks, dim3(grid), dim3(kDsBlock), (size_t)kDsWaves * kDsStageWords * 4u, st, d);
 }
 
-// Planes of at most 512 columns: is the reconstruction in bands quicker than the kernels with a plane per wavefront or
-// workgroup?  Those take as long as their longest serial chain (or as the elements take, for many planes); the bands
-// have no chain, and move more bytes.  Estimates in us from measurements (old kernel / bands):
-//   k_decode_scan, a plane per wavefront (10 us a strip of 4032 elements, 20 with one column per lane):
-//     4 planes of 512 x 512 672 / 48, 64 721 / 91, 1024 848 / 991; 256 planes of 257 x 257 361 / 99, 1024 452 / 340, 4096 757 / 1260
-//   k_decode_scan, a plane's strips dealt to the sixteen wavefronts of a workgroup (20 us a round):
-//     8 planes of 3000 x 256 265 / 84, 32 of 256 x 256 45 / 51, 512 of them 75 / 127
-//   k_scan_store (a plane per wavefront, 0.25 us a row and 0.06 more per 64 lanes of it; 1.3 us per million elements,
-//   2 if a row takes more than 128 lanes), chunks of 128 symbols:
-//     16 planes of 224 x 224 107 / 52, 4096 of them 664 / 767, 1024 of 512 x 512 1086 / 955, 4096 of 257 x 257 973 / 1227
-bool band_pays(int num_cu, comet_shape s, uint64_t n, bool chunk64, uint32_t vec) {
-    const uint64_t planes = (uint64_t)s.n * s.c, P = (uint64_t)s.h * s.w;
-    const uint32_t lpr = s.w / vec;
-    const double mega = (double)n * 1e-6;
-    if (!chunk64) {                                          // (the decoding itself is the same kernel on both sides)
-        const double row = 0.25 + 0.06 * (double)((lpr + 63u) / 64u);
-        const uint64_t waves = (uint64_t)num_cu * 32u;
-        const double chain = row * (double)s.h * (double)((planes + waves - 1u) / waves);
-        const double flow = (lpr <= 128u ? 1.3 : 2.0) * mega;
-        return 30.0 + (vec == 2u ? 1.7 : 2.6) * mega < (chain > flow ? chain : flow);
-    }
-    const double bands = 45.0 + (vec == 2u ? 3.6 : 4.5) * mega;
-    const uint64_t strip = 4032u / s.w * s.w, strips = (P + strip - 1u) / strip;
-    if (lpr <= 128u) {
-        const uint64_t seg_planes = (planes + (uint64_t)num_cu - 1u) / (uint64_t)num_cu;
-        return bands < 20.0 * (double)((seg_planes * strips + (uint64_t)kFuWaves - 1u) / (uint64_t)kFuWaves);
-    }
-    const uint64_t waves = (uint64_t)num_cu * kFuWaves;
-    return bands < (vec == 2u ? 10.0 : 20.0) * (double)(strips * ((planes + waves - 1u) / waves));
-}
-
 int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, comet_shape s, void *stream, void *dev_out, int out_type) {
     uint64_t n;
     if (!dev_in || !dev_out || !shape_elems(s, &n) || s.w > kMaxW || ((uintptr_t)dev_in & 15u)) return COMET_ERR_INVALID;
@@ -889,9 +826,10 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
     const uint32_t ppi = lpr <= 16u ? 4u * (16u / lpr) : (lpr <= 32u ? 2u : 1u);
     // (buffer offsets: a strip of whole rows, or the planes side by side in a wavefront, stays below 2^28 elements)
     const bool fast_path = s.w <= kDsMaxW && (uint64_t)ppi * s.h * s.w < (1ull << 28);
-    const BandGeom bg = band_geometry(s, n, vec);
+    const uint64_t planes = (uint64_t)s.n * s.c;
+    const BandGeom bg = band_geometry(planes, s.h, s.w, vec);
     const bool bands = s.w >= kBandMinW && bg.bytes <= ws.band_bytes && bg.n_units < (1ull << 31) &&
-                       (!fast_path || band_pays(ws.num_cu, s, n, ws.chunk_syms == 64u, vec));
+                       (!fast_path || band_pays(ws.num_cu, planes, s.h, s.w, bg, ws.chunk_syms == 64u));
     if (out_type != 0 && !fast_path) return COMET_ERR_INVALID;       // 16-bit outputs: planes of at most kDsMaxW columns
     // Chunks of 64 symbols (what the caller's context compresses with tells what to expect) go through the
     // single fused kernel; it leaves a container with another chunk size alone, and the kernels launched
@@ -927,7 +865,6 @@ int decompress_impl(const DecompWs &ws, const void *dev_in, uint64_t bytes, come
         const bool coop = nseg <= 2;
         FusedGeom fg = fused_geometry(ws.num_cu, s);
         if (coop) {
-            const uint64_t planes = (uint64_t)s.n * s.c;
             fg.grid = (uint32_t)(planes < (uint64_t)ws.num_cu ? planes : (uint64_t)ws.num_cu);
         }
         f.G = fg.G; f.n_units = fg.n_units;

@@ -1,6 +1,7 @@
 // Kernel argument blocks and launch constants shared by the host API and the
 // kernel translation units.
 #pragma once
+#include "comet_bands.h"
 #include "comet_dev.h"
 
 namespace comet {
@@ -322,7 +323,7 @@ template <int NSEG, int MODE, int OUT = 0, int VEC = 1> __global__ void k_scan_s
 
 // ---- reconstruct from the residuals of k_decode_chunks, planes cut into bands of rows and segments of columns -------
 constexpr int kBandBlock = 256;                       // four wavefronts, each on a unit of its own
-constexpr uint32_t kBandRowsMin = 8u, kBandRowsMax = 64u;   // rows of a unit (the upper limit: one lane per row)
+static_assert(kBandLanes == (uint32_t)kWave && kBandRowsMax <= kBandLanes, "lanes of a unit");
 
 struct BandArgs {
     const uint8_t *container;
@@ -345,6 +346,7 @@ template <int OUT> __global__ void k_band_verbatim(BandArgs a);
 
 // ---- decode + reconstruct in one kernel (planes up to 512 columns, chunks of 64 symbols) ----------
 constexpr int kFuWaves = 16;                          // wavefronts per workgroup, each working on its own; one workgroup per CU
+static_assert((uint32_t)kFuWaves == kBandFuWaves, "the rule for bands counts with them");
 constexpr int kFuBlock = kFuWaves * kWave;
 constexpr uint32_t kFuStripWords = 64u * 32u;         // a strip's residuals, element after element (64 chunks of 64 int16); before that, the words of its chunks
 constexpr uint32_t kFuEscEntries = 32u;               // values of a strip's escaped residuals kept in LDS

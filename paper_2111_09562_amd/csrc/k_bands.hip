@@ -15,7 +15,9 @@
 // twice), but a plane is no longer a serial chain.  Bound by the memory behind the residual stores for large tensors,
 // by the five launches for small ones.  32 planes of 480 x 854 (13.1 M elements), the whole decompression: 5210 us with
 // a plane per wavefront (k_reconstruct, strips of 8192 elements one after the other), 85 us in these; 3.6 us per
-// further million elements.
+// further million elements.  The sums above a unit are added up by the unit, so what is read of them grows with the square
+// of the bands per plane: nothing to speak of for images, but a plane of 2097151 x 128 takes 19 ms, 18 of them for that (see
+// band_pays).
 #include "comet_kernels.h"
 #include "comet_scan.h"
 
