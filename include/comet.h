@@ -62,7 +62,7 @@ typedef struct {
 
 /* Create a context able to handle tensors of up to max_elems elements and
  * max_nbins quantisation bins.  Allocates 2 bytes per element plus about 40 MB
- * (2.4 bytes per element from about 80 million elements on) of device workspace
+ * (2.14 bytes per element from about 230 million elements on) of device workspace
  * on the current device.  *ctx is set on success. */
 int comet_create(comet_ctx **ctx, uint64_t max_elems, uint32_t max_nbins);
 void comet_destroy(comet_ctx *ctx);
@@ -153,7 +153,7 @@ int comet_decompress_16(comet_ctx *ctx, const void *dev_in, uint64_t bytes, come
 /* comet_decompress for callers that cannot allocate device memory or hold a context: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  No comet_create is needed and
  * the call allocates nothing: its control block, decode tables and work buffer live in a static device
- * array inside the library (about 13 MiB, held by every GPU the library runs on until the process
+ * array inside the library (about 11 MiB, held by every GPU the library runs on until the process
  * ends), which limits the tensor to COMET_STATIC_MAX_ELEMS elements (COMET_ERR_NOMEM beyond).
  * dev_in, bytes, shape, stream, dev_out: as for comet_decompress.  dev_status: device memory, one
  * int32 owned by the caller, or NULL; when the call's kernels have run it holds COMET_OK, or

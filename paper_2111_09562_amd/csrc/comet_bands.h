@@ -28,21 +28,23 @@ inline BandGeom band_geometry(uint64_t planes, uint32_t H, uint32_t W, uint32_t 
     g.bands = (uint32_t)((H + R - 1u) / R);
     g.R = (H + g.bands - 1u) / g.bands;
     g.bands = (H + g.R - 1u) / g.R;
-    const uint64_t pb = planes * g.bands;
-    g.n_units = pb * g.segs;
-    g.off_row = g.bands > 1u ? band_align(4ull * pb * W, 256) : 0u;           // (one band per plane: no column sums)
-    g.off_unit = g.off_row + (g.segs > 1u ? band_align(4ull * g.n_units * g.R, 256) : 0u);
-    g.bytes = g.off_unit + band_align(4ull * g.n_units, 256);
+    // sums that some unit reads: of columns for every band of a plane but its last, of rows for every segment but the
+    // last, of whole units if there are both
+    g.n_units = planes * g.bands * g.segs;
+    g.off_row = band_align(4ull * planes * (g.bands - 1u) * W, 256);
+    g.off_unit = g.off_row + band_align(4ull * planes * g.bands * (g.segs - 1u) * g.R, 256);
+    g.bytes = g.off_unit + (g.bands > 1u && g.segs > 1u ? band_align(4ull * g.n_units, 256) : 0u);
     return g;
 }
 constexpr uint32_t kBandMinW = 128;     // narrower planes leave lanes of a unit idle (and a workgroup of k_decode_scan shares a plane)
-// What the sums of any tensor of up to n elements take, planes of at least kBandMinW columns: a column sum per
-// R / 2 or more elements (R: rows per band as above; 8n / R is below 4.7 MB until R reaches its limit of 64), a row sum
-// per 43 (129 columns, one per lane, three segments) times three halves (the rows of a plane's bands are at most half
-// as many again as its own), a unit sum per row sum at the most.
+// What the sums of any tensor of up to n elements take, planes of at least kBandMinW columns.  With R0 the rows per band that
+// band_geometry starts from (8 below 4.7 million elements, about n / 2^19 up to 2^25, then 64): less than a column sum per R0
+// elements (2^21 of them at most below 2^25 elements); less than a row sum per 64, times ten ninths (a plane of nine rows has
+// bands of five); a unit sum per 43 (129 columns in three segments) times (R0 + 1) / 2.
 constexpr uint64_t band_bytes_max(uint64_t n) {
-    const uint64_t col = n < (8ull << 20) ? n : (n / 8u > (8ull << 20) ? n / 8u : (8ull << 20));
-    return col + 4u * (n / 32u + n / 128u) + 4u * (n / 40u) + 8192u;
+    const uint64_t col = n / 2u < (5ull << 19) ? n / 2u : (n / 16u > (5ull << 19) ? n / 16u : (5ull << 19));
+    const uint64_t unit = n / 48u < (1ull << 17) ? n / 48u : (n / 348u > (1ull << 17) ? n / 348u : (1ull << 17));
+    return col + n / 14u + unit + 1024u;
 }
 
 // Planes of at most 512 columns: is the reconstruction in bands quicker than the kernels with a plane per wavefront or

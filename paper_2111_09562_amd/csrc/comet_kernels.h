@@ -333,9 +333,9 @@ struct BandArgs {
     FastDiv divBands;          // bands per plane
     uint32_t n_units;          // planes * bands * segments; segments of a band are neighbours, bands of a plane as well
     int16_t *resid;            // work buffer: one int16 residual per element
-    int32_t *col_sums;         // [planes * bands][W]
-    int32_t *row_sums;         // [n_units][R]
-    int32_t *unit_sums;        // [n_units]
+    int32_t *col_sums;         // [plane][band, but the last][W]
+    int32_t *row_sums;         // [plane, band][segment, but the last][R]
+    int32_t *unit_sums;        // [n_units]: of those that are neither in the last band nor in the last segment
     void *out;
     Control *ctl;
 };

@@ -138,14 +138,14 @@ __global__ __launch_bounds__(kBandBlock) void k_band_sums(BandArgs a) {
         row = lane == r ? total : row;
         unit = (int32_t)((uint32_t)unit + (uint32_t)total);
     });
-    if (b.s + 1u < a.divSegs.d && lane < b.rows) a.row_sums[(size_t)u * a.R + lane] = row;
+    if (b.s + 1u < a.divSegs.d && lane < b.rows) a.row_sums[((size_t)b.pb * (a.divSegs.d - 1u) + b.s) * a.R + lane] = row;
     if (b.band + 1u < a.divBands.d) {
-        int32_t *dst = a.col_sums + (size_t)b.pb * a.W + b.s * (uint32_t)kWave * VEC + lane * VEC;
+        int32_t *dst = a.col_sums + (size_t)(b.pb - b.plane) * a.W + b.s * (uint32_t)kWave * VEC + lane * VEC;
         if (lane < b.lanes) {
             if (VEC == 2) *reinterpret_cast<int2 *>(dst) = make_int2(col[0], col[VEC - 1]);
             else *dst = col[0];
         }
-        if (lane == 0) a.unit_sums[u] = unit;
+        if (b.s + 1u < a.divSegs.d && lane == 0) a.unit_sums[u] = unit;
     }
 }
 
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBandBlock) void k_band_store(BandArgs a) {
 #pragma unroll
     for (int v = 0; v < VEC; ++v) q[v] = 0;
     if (lane < b.lanes) {
-        const int32_t *src = a.col_sums + (size_t)(b.pb - b.band) * a.W + b.s * (uint32_t)kWave * VEC + lane * VEC;
+        const int32_t *src = a.col_sums + (size_t)b.plane * (a.divBands.d - 1u) * a.W + b.s * (uint32_t)kWave * VEC + lane * VEC;
 #pragma unroll 8
         for (uint32_t k = 0; k < b.band; ++k, src += a.W) {
             if (VEC == 2) { const int2 t = *reinterpret_cast<const int2 *>(src); q[0] += (uint32_t)t.x; q[VEC - 1] += (uint32_t)t.y; }
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kBandBlock) void k_band_store(BandArgs a) {
     // left of my rows (lane r: row r), and above and left of me
     uint32_t left = 0, corner = 0;
     if (lane < b.rows) {
-        const int32_t *src = a.row_sums + (size_t)(u - b.s) * a.R + lane;
+        const int32_t *src = a.row_sums + (size_t)b.pb * (segs - 1u) * a.R + lane;
 #pragma unroll 8
         for (uint32_t k = 0; k < b.s; ++k, src += a.R) left += (uint32_t)*src;
     }

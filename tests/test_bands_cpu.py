@@ -66,9 +66,18 @@ def test_bands_cover_the_plane_and_fit_the_workspace(bands):
             what = (planes, h, w, vec)
             assert 1 <= R <= 64 and (nb - 1) * R < h <= nb * R, what
             assert (segs - 1) * 64 * vec < w <= segs * 64 * vec and units == planes * nb * segs, what
-            assert nb == 1 or off_row >= 4 * planes * nb * w, what
-            assert segs == 1 or off_unit - off_row >= 4 * units * R, what
+            assert off_row >= 4 * planes * (nb - 1) * w and off_unit - off_row >= 4 * planes * nb * (segs - 1) * R, what
+            assert total - off_unit >= (4 * units if nb > 1 and segs > 1 else 0), what
             assert total <= bands.bytes_max(n), what
+
+
+def test_the_workspace_is_a_small_part_of_a_context(bands):
+    """Every context holds it, also where no plane is wide: within a fourteenth of the two bytes per element that the
+    codes take for large tensors, and a few megabytes for small ones."""
+    for n in (1, 1000, 1 << 20, 1 << 22, 1 << 25):
+        assert bands.bytes_max(n) <= min(n, 6 << 20) + 1024
+    for n in (1 << 26, 411041792, 2 ** 31 - 1):
+        assert bands.bytes_max(n) <= 2 * n / 14
 
 
 # us with a plane per wavefront or workgroup / in bands, chunks of 64 symbols, two columns per lane where the width is even
