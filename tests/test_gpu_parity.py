@@ -408,12 +408,14 @@ def test_which_kernels_decompress(comet, oracle):
     (8, 4000, 7, 7),       # ... strips whose rows do not divide evenly among the eight runs (a shorter last run), two strips per segment
     (3, 500, 14, 14),      # ... the same with two columns per lane
     (5, 700, 7, 7),        # ... and with a single short strip
-    (1, 3, 1500, 128),     # the widest plane that goes this way
+    (1, 3, 1500, 126),     # 47 and more strips per segment: the hand-over goes round the sixteen wavefronts three times
+    (1, 3, 1500, 127),     # ... with one column per lane
+    (1, 56, 1500, 128),    # ... the widest plane that goes this way with one segment of 64 lanes (fewer planes are cut into bands)
     (2, 3, 300, 130),      # just beyond it with two columns per lane: two segments of 64 lanes, still dealt to all wavefronts
     (3, 5, 60, 256),       # the widest plane that goes this way with two columns per lane
-    (2, 3, 150, 129),      # one column per lane beyond 128 columns: a segment per wavefront, sums stay in registers
-    (1, 2, 200, 258),      # the same with two columns per lane
-    (1, 2, 700, 224),      # four segments of 64 lanes... two columns per lane, planes much larger than a strip
+    (1, 700, 150, 129),    # one column per lane beyond 128 columns: a segment per wavefront, sums stay in registers, five strips per plane
+    (3, 100, 100, 258),    # the same with two columns per lane, seven strips per plane
+    (1, 32, 700, 224),     # two segments of 64 lanes, planes of 39 strips
 ])
 def test_fused_decompression_strips(comet, oracle, shape):
     """Decompression in one kernel on shapes whose planes, strips and segments do not line up: planes larger and
@@ -427,13 +429,16 @@ def test_fused_decompression_strips(comet, oracle, shape):
         flat[i] = [np.inf, -np.inf, 3.0e9, -0.0, np.nan][i % 5]
     ctx = comet.Context(max_elems=x.size, max_nbins=1024)
     ctx.comet_set_chunk_syms(64)
+    ctx.comet_profile_enable(True)
     for eb, nbins in [(1e-2, 1024), (2e-3, 16), (1e-3, 64)]:
         buf = oracle.compress(x, eb, nbins, 64)
         want = oracle.decompress(buf).ravel()
         cont = dev(np.concatenate([buf, np.zeros((-buf.size) % 16, np.uint8)]))
         y = torch.empty(x.size, dtype=torch.float32, device="cuda")
+        ctx.comet_profile_reset()
         ctx.comet_decompress(cont, buf.size, shape, y)
         ctx.comet_sync()
+        assert (ctx.comet_profile_read(8)[0], ctx.comet_profile_read(5)[0]) == (1, 0), "not decompressed in one kernel"
         got = y.cpu().numpy()
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (shape, eb, nbins, int(np.flatnonzero(got.view(np.uint32) != want.view(np.uint32))[0]))
         if shape[3] <= 512:
