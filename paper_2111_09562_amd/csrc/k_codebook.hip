@@ -165,9 +165,10 @@ __device__ inline uint32_t next_pow2(uint32_t v) {
     return p;
 }
 
-__device__ inline uint64_t lane_value64_any(uint64_t v, uint32_t src) {      // src: wavefront-uniform
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)src);
+// Value of lane `src` (wavefront-uniform).
+__device__ inline uint32_t lane_value(uint32_t v, uint32_t src) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)src); }
+__device__ inline uint64_t lane_value(uint64_t v, uint32_t src) {
+    const uint32_t lo = lane_value((uint32_t)v, src), hi = lane_value((uint32_t)(v >> 32), src);
     return ((uint64_t)hi << 32) | lo;
 }
 
@@ -197,9 +198,9 @@ __device__ inline bool canonical_first_codes_wave(const uint32_t *cnt, uint32_t 
         first_code[L] = (L <= 57u) ? excl >> (57u - L) : excl << (L - 57u);
         first_index[L] = idx_incl - c;
     }
-    const uint64_t kraft = lane_value64_any(incl, 63);       // in units of 2^-57
+    const uint64_t kraft = lane_value(incl, 63);       // in units of 2^-57
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)idx_incl, 63);
-    if (L == 0u) { first_code[64] = lane_value64_any(excl, 63) << 7; first_index[64] = total; }   // (length 64 is never valid)
+    if (L == 0u) { first_code[64] = lane_value(excl, 63) << 7; first_index[64] = total; }   // (length 64 is never valid)
     const uint32_t max_len = c64 ? 64u : (used ? 63u - (uint32_t)__builtin_clzll(used) : 0u);
     const uint32_t min_len = used ? (uint32_t)__builtin_ctzll(used) : (c64 ? 64u : 0u);
     bool ok = !broken && total + c64 == n_active && max_len != 0u && max_len <= 57u && kraft <= (1ull << 57);
@@ -213,9 +214,7 @@ __device__ inline bool canonical_first_codes_wave(const uint32_t *cnt, uint32_t 
 }  // namespace
 
 
-// The merge rounds.  NT lanes take part (a whole workgroup, or one wavefront when
-// the arrays are in LDS and the rounds are short); `sync` is the barrier that
-// matches NT.
+// The merge rounds.
 //
 // State: leaves [li, m) and internal nodes [ii, ni) not yet merged.  With t the sum
 // of the two smallest heads, every new node weighs at least t, so every waiting item
@@ -223,7 +222,8 @@ __device__ inline bool canonical_first_codes_wave(const uint32_t *cnt, uint32_t 
 // order (leaf before node on equal weight) and paired consecutively, are exactly the
 // next steps of the sequential two-queue construction.  An odd item out waits for the
 // next round.  iw[0, m) must be zero on entry.
-// Same count, by one whole wavefront probing 64 consecutive entries per step
+//
+// Entries of arr[begin, end) with (arr[i] >> shift) <= t, by one whole wavefront probing 64 consecutive ones per step
 // (the entries are sorted, so the lanes that pass form a prefix).
 __device__ inline uint32_t count_below_wave(const uint64_t *arr, uint32_t begin, uint32_t end, uint64_t t, int shift) {
     uint32_t cnt = 0;
@@ -261,9 +261,9 @@ __device__ inline uint32_t count_below_block(const uint64_t *arr, uint32_t begin
 }
 
 // One round, control part: how many leaves (nl) and internal nodes (nn) are merged now.  Uniform
-// over the callers; WAVE: the counts are taken by a whole wavefront probing 64 entries per step;
-// BLOCK: by the whole workgroup (every thread of it calls).
-template <bool WAVE, bool BLOCK = false>
+// over the callers.  BLOCK: the counts are taken by the whole workgroup (every thread of it calls), else
+// by a whole wavefront probing 64 entries per step.
+template <bool BLOCK>
 __device__ inline void round_control(const uint64_t *keys, const uint64_t *iw, uint32_t m, uint32_t li, uint32_t ii, uint32_t ni,
                                      uint32_t *nl_out, uint32_t *nn_out) {
     const uint64_t inf = ~0ull;
@@ -273,8 +273,8 @@ __device__ inline void round_control(const uint64_t *keys, const uint64_t *iw, u
     if (a0 <= b0) { s0 = a0; s1 = (a1 <= b0) ? a1 : b0; }
     else { s0 = b0; s1 = (a0 <= b1) ? a0 : b1; }
     const uint64_t t = s0 + s1;
-    uint32_t nl = BLOCK ? count_below_block(keys, li, m, t, 16) : (WAVE ? count_below_wave(keys, li, m, t, 16) : count_below(keys, li, m, t, 16, false));
-    uint32_t nn = BLOCK ? count_below_block(iw, ii, ni, t, 0) : (WAVE ? count_below_wave(iw, ii, ni, t, 0) : count_below(iw, ii, ni, t, 0, false));
+    uint32_t nl = BLOCK ? count_below_block(keys, li, m, t, 16) : count_below_wave(keys, li, m, t, 16);
+    uint32_t nn = BLOCK ? count_below_block(iw, ii, ni, t, 0) : count_below_wave(iw, ii, ni, t, 0);
     if ((nl + nn) & 1u) {
         const uint64_t la = nl ? keys[li + nl - 1] >> 16 : 0, lb = nn ? iw[ii + nn - 1] : 0;
         if (nn && (!nl || la <= lb)) --nn; else --nl;
@@ -336,24 +336,18 @@ __device__ inline void round_items(const uint64_t *keys, uint64_t *iw, uint32_t 
     }
 }
 
-// Rounds while more than `stop` items wait; the state is handed back.
-template <bool WAVE, typename Sync>
+// Rounds by the whole workgroup while more than `stop` items wait; the state is handed back.
 __device__ inline void huffman_rounds(const uint64_t *keys, uint64_t *iw, uint32_t *leaf_parent, uint32_t *int_parent,
-                                      uint32_t m, uint32_t lane, uint32_t nlanes, Sync sync, uint32_t stop,
-                                      uint32_t &li, uint32_t &ii, uint32_t &ni) {
+                                      uint32_t m, uint32_t stop, uint32_t &li, uint32_t &ii, uint32_t &ni) {
     li = 0; ii = 0; ni = 0;
     while ((m - li) + (ni - ii) > stop) {
         uint32_t nl, nn;
-        round_control<WAVE, !WAVE>(keys, iw, m, li, ii, ni, &nl, &nn);     // (not WAVE: the whole workgroup is here)
-        round_items<WAVE ? 1u : 4u>(keys, iw, leaf_parent, int_parent, li, ii, ni, nl, nn, lane, nlanes);
-        sync();
+        round_control<true>(keys, iw, m, li, ii, ni, &nl, &nn);
+        round_items<4u>(keys, iw, leaf_parent, int_parent, li, ii, ni, nl, nn, threadIdx.x, (uint32_t)kBookBlock);
+        __syncthreads();
         li += nl; ii += nn; ni += (nl + nn) >> 1;
     }
 }
-
-__device__ inline uint64_t lane_value64(uint64_t v, uint32_t src) { return lane_value64_any(v, src); }
-__device__ inline uint64_t lane_value(uint64_t v, uint32_t src) { return lane_value64_any(v, src); }
-__device__ inline uint32_t lane_value(uint32_t v, uint32_t src) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)src); }
 
 // The same rounds for arrays in LDS, by the whole workgroup.  The first wavefront runs the rounds of
 // at most 64 items alone and in registers: lane l holds the l-th waiting leaf and the l-th waiting
@@ -373,7 +367,7 @@ __device__ inline void huffman_rounds_lds(const uint64_t *keys, uint64_t *iw, ui
             while ((m - li) + (ni - ii) > 1u) {
                 const uint64_t A = li + lane < m ? keys[li + lane] >> 16 : inf;      // waiting leaves
                 const uint64_t B = ii + lane < ni ? iw[ii + lane] : inf;             // waiting nodes
-                const uint64_t a0 = lane_value64(A, 0), a1 = lane_value64(A, 1), b0 = lane_value64(B, 0), b1 = lane_value64(B, 1);
+                const uint64_t a0 = lane_value(A, 0), a1 = lane_value(A, 1), b0 = lane_value(B, 0), b1 = lane_value(B, 1);
                 uint64_t s0, s1;
                 if (a0 <= b0) { s0 = a0; s1 = (a1 <= b0) ? a1 : b0; }
                 else { s0 = b0; s1 = (a0 <= b1) ? a0 : b1; }
@@ -382,7 +376,7 @@ __device__ inline void huffman_rounds_lds(const uint64_t *keys, uint64_t *iw, ui
                 uint32_t nn = (uint32_t)__popcll(wave_ballot(B != inf && B <= t));
                 if (nl == (uint32_t)kWave || nn == (uint32_t)kWave) break;   // there may be more beyond the window: everybody's round
                 if ((nl + nn) & 1u) {
-                    const uint64_t la = nl ? lane_value64(A, nl - 1u) : 0, lb = nn ? lane_value64(B, nn - 1u) : 0;
+                    const uint64_t la = nl ? lane_value(A, nl - 1u) : 0, lb = nn ? lane_value(B, nn - 1u) : 0;
                     if (nn && (!nl || la <= lb)) --nn; else --nl;
                 }
                 if (nl + nn > (uint32_t)kWave) break;        // more items than lanes: everybody's round
@@ -393,14 +387,14 @@ __device__ inline void huffman_rounds_lds(const uint64_t *keys, uint64_t *iw, ui
                     uint32_t before_leaf = 0, before_node = 0;
                     if (nn <= nl) {
                         for (uint32_t k = 0; k < nn; ++k) {
-                            const uint64_t bk = lane_value64(B, k);
+                            const uint64_t bk = lane_value(B, k);
                             before_leaf += (bk < A) ? 1u : 0u;
                             const uint32_t c = (uint32_t)__popcll(wave_ballot(lane < nl && A <= bk));
                             before_node = (lane == k) ? c : before_node;
                         }
                     } else {
                         for (uint32_t k = 0; k < nl; ++k) {
-                            const uint64_t ak = lane_value64(A, k);
+                            const uint64_t ak = lane_value(A, k);
                             before_node += (ak <= B) ? 1u : 0u;
                             const uint32_t c = (uint32_t)__popcll(wave_ballot(lane < nn && B < ak));
                             before_leaf = (lane == k) ? c : before_leaf;
@@ -453,7 +447,7 @@ __device__ inline void huffman_rounds_lds(const uint64_t *keys, uint64_t *iw, ui
         li = state[0]; ii = state[1]; ni = state[2];
         if ((m - li) + (ni - ii) <= 1u) break;
         uint32_t nl, nn;
-        round_control<true>(keys, iw, m, li, ii, ni, &nl, &nn);
+        round_control<false>(keys, iw, m, li, ii, ni, &nl, &nn);
         round_items(keys, iw, leaf_parent, int_parent, li, ii, ni, nl, nn, tid, nthreads);
         __syncthreads();
         li += nl; ii += nn; ni += (nl + nn) >> 1;
@@ -656,7 +650,7 @@ __device__ inline void huffman_rounds_window(const uint64_t *keys, uint64_t *iw,
         for (uint32_t w = 0; w < (uint32_t)(kBookBlock / kWave); ++w) both += s_part[w];
         uint32_t nl = both & 0xffffu, nn = both >> 16;
         if (nl == kBookWin || nn == kBookWin) {              // (uniform) perhaps more than the window shows
-            round_control<false, true>(keys, iw, m, li, ii, ni, &nl, &nn);
+            round_control<true>(keys, iw, m, li, ii, ni, &nl, &nn);
             round_items<4u>(keys, iw, leaf_parent, int_parent, li, ii, ni, nl, nn, tid, (uint32_t)kBookBlock);
         } else {
             if ((nl + nn) & 1u) {
@@ -738,8 +732,7 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
         if (narrow)
             huffman_rounds_window(keys, iw, leaf_parent, int_parent, m, reinterpret_cast<uint32_t *>(s.u.exchange), s.part, kBookLdsSyms / 2u, li, ii, ni);
         else
-            huffman_rounds<false>(keys, iw, leaf_parent, int_parent, m, tid, (uint32_t)kBookBlock, [] { __syncthreads(); },
-                                  kBookLdsSyms / 2u, li, ii, ni);
+            huffman_rounds(keys, iw, leaf_parent, int_parent, m, kBookLdsSyms / 2u, li, ii, ni);
         const uint32_t L = m - li, N = ni - ii;
         if (L + N > 1u) {
             uint64_t *l_keys = s.u.large.keys, *l_iw = s.u.large.iw;

@@ -65,10 +65,9 @@ struct DsTables {
     int32_t escape;             // residual value that stands for the escape symbol in the work buffer
 };
 
-// Codes longer than the look-up table: canonical search by length, from the shortest length the
-// table entry says this prefix can have.
-__device__ inline int32_t decode_long(uint64_t win, uint32_t start, uint32_t lut_bits, const DsTables &t, uint32_t *len_out) {
-    uint32_t L = start > lut_bits ? start : lut_bits + 1u;
+// Codes longer than both levels of the compact table, or without a second level: canonical search by length.
+__device__ inline int32_t decode_long(uint64_t win, const DsTables &t, uint32_t *len_out) {
+    uint32_t L = (uint32_t)kLut16Bits + 1u;
     while (L < t.max_len && win >= t.limit[L]) ++L;
     if (L > 57u) L = 57u;
     uint64_t idx = t.findex[L] + ((win >> (64u - L)) - t.first[L]);
@@ -80,7 +79,7 @@ __device__ inline int32_t decode_long(uint64_t win, uint32_t start, uint32_t lut
     return sym ? (int32_t)sym - t.radius : t.escape;
 }
 
-// The same for the table of lengths: place in canonical order of the code that starts win.
+// The same for the table of lengths, from the shortest length its entry gives: place in canonical order of the code that starts win.
 __device__ inline uint32_t place_long(uint64_t win, uint32_t start, const DsTables &t, uint32_t *len_out) {
     uint32_t L = start;
     while (L < t.max_len && win >= t.limit[L]) ++L;
@@ -150,7 +149,7 @@ struct BitBuf {
                 // second level: the prefix's sub-table on the next 1, 2, 4 or 6 bits; what is longer still
                 // (or has no sub-table) is searched by length
                 const bool found = second_level(t, e, win, L, d);
-                if (!found) d = decode_long(win, 0u, (uint32_t)kBits, t, &L);
+                if (!found) d = decode_long(win, t, &L);
                 if (pos + L >= 64u) {            // the code runs into the look-ahead word: move one word on here
                     advance();
                     pos -= 32u;                  // (modulo 2^32; the sum below is in range again)
