@@ -87,3 +87,21 @@ def test_the_histogram_is_timed_with_the_quantiser(nbins, shape, want):
     assert ctx.comet_profile_read(0)[0] == want
     assert ctx.comet_profile_read(0)[1] > 0.0
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", [1, 2])
+@pytest.mark.parametrize("shape", [(21, 64, 224, 224), (64, 64, 128, 129), (17, 4100, 31, 32)])
+def test_16_bit_tensors_shared_by_two_kernels(kind, shape):
+    """The same division for 16-bit inputs: the container is the one of the widened tensor, byte for byte."""
+    from paper_2111_09562_amd import comet
+    nbins, eb = 65536, 1e-3
+    n = int(np.prod(shape))
+    assert n >= 1 << 26
+    g = torch.Generator(device="cuda").manual_seed(n + kind)
+    spread = torch.tensor([1.0, 900.0, 1000.0, 9000.0], device="cuda")[torch.randint(4, shape[:3] + (1,), device="cuda", generator=g)]
+    x = (torch.randn(shape, device="cuda", generator=g) * spread * (2 * eb)).to([torch.float16, torch.bfloat16][kind - 1])
+    ctx = comet.Context(n, nbins)
+    boxes = [torch.zeros(4 * n + (1 << 20), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    used = [ctx.comet_compress_16(x, eb, nbins, boxes[0]), ctx.comet_compress(x.float(), eb, nbins, boxes[1])]
+    assert used[0] == used[1] and torch.equal(boxes[0], boxes[1])
+    ctx.close()
