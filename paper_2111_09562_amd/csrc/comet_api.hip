@@ -1023,7 +1023,7 @@ int static_scratch(StaticDev *out) {
         if (!ptr) return COMET_ERR_HIP;
         int cus = 0;
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        // the kernel for planes wider than 512 columns needs more than 64 KB of dynamic LDS
+        // the general kernel (other chunk sizes behind k_decode_scan) may need more than 64 KB of dynamic LDS
         HIP_TRY(hipFuncSetAttribute((const void *)k_reconstruct<0>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
         {
             const int rc = fused_opt_in();

@@ -148,7 +148,10 @@ constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
 // occurs lies among them: 16384 around the centre (the room of the table's cached part).  Above 32768 bins: all of
 // them (64 KB), with twice the wavefronts per workgroup, so that a compute unit holds sixteen of them (two workgroups; a
 // window of 32768 lengths, three workgroups of half the size: twelve); a field whose codes reached beyond such a window
-// was looked up in global memory instead, 98 us for 64 x 256 x 56 x 56 at a bound of 1e-4, now 38.
+// was looked up in global memory instead, 98 us for 64 x 256 x 56 x 56 at a bound of 1e-4, now 38.  Between 16384 and 32768
+// bins it is still 16384 of them: all would cost a field whose symbols lie among those 2 % (32768 bins, 128 x 64 x 224 x 224
+// smoothed at 3.2e-4 the whole compression 1561 -> 1595 us: fewer workgroups per compute unit) and spare one that
+// reaches beyond them the look-ups in global memory (Laplace at 1e-3 2076 -> 1683).
 constexpr int kEncBlockWide = 512;
 __host__ __device__ inline bool enc_wide(uint32_t nbins) { return nbins > 32768u; }
 __host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u || enc_wide(nbins) ? nbins : 16384u; }

@@ -607,8 +607,8 @@ __device__ inline void book_tree(BookLds &s, uint32_t m, const uint64_t (&key)[2
 // LDS: the next kBookWin leaves and nodes come in with one memory round trip, the threads count those of weight <= t in
 // registers, ranks are searched in LDS, and the new nodes' weights are sums of neighbours in merged order, stored in a
 // row.  32-bit weights: all of them together stay below 2^31.  A round that takes a whole window (thousands of leaves of one
-// weight) goes through the general routines.  About 4.5 us a round instead of 8 (searches for the counts and the
-// ranks in global memory, atomic additions).
+// weight, as the first rounds of a heavy-tailed alphabet have) goes through the general routines.  About 4.5 us a round
+// instead of 8 (searches for the counts and the ranks in global memory, atomic additions).
 constexpr uint32_t kBookWin = 2u * (uint32_t)kBookBlock;
 __device__ inline void huffman_rounds_window(const uint64_t *keys, uint64_t *iw, uint32_t *leaf_parent, uint32_t *int_parent,
                                              uint32_t m, uint32_t *s_x, uint32_t *s_part, uint32_t stop,
@@ -996,7 +996,8 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
 // The rest of a large alphabet's code book (more than kBookLdsSyms symbols occur, presorted), by whole grids instead of the
 // one workgroup that built the tree: a walk to the root is a chain of some twenty dependent loads, and the canonical
 // codes visit every symbol of the alphabet.  64 x 256 x 56 x 56 at a bound of 1e-4, 65536
-// bins: k_codebook 406 us, now 272 and 28 behind it.
+// bins: k_codebook 406 us with them, 272 without (190 since huffman_rounds_window), and 28 behind it.  Where at most
+// kBookLdsSyms symbols of such an alphabet occur they return at once and cost 9 us.
 // k_book_depths: one leaf per thread; it also counts the lengths per tile of kBookBlock symbols.
 // k_book_codes: a tile per workgroup; the code of a symbol is the first code of its length plus the number of smaller
 // symbols of that length: those of the tiles in front, of the wavefronts in front and of the lanes in front.
@@ -1072,7 +1073,8 @@ __global__ __launch_bounds__(kBookBlock) void k_book_codes(BookArgs a) {
 // ordering need three barriers whatever the alphabet; a table entry finds its length by comparison with the first
 // twelve limits and its symbol by arithmetic, and the second level, whose prefixes are the end of the first one with
 // sizes that never decrease, is laid out in closed form.  1024 bins: 6.1 us instead of 12.7 (binary searches over
-// the limits, a scan over the prefixes), 4096 bins: 8 instead of 18, 65536 bins: 45 instead of 111.
+// the limits, a scan over the prefixes), 4096 bins: 8 instead of 18, 65536 bins: 45 instead of 111 (53 since it
+// builds the table of lengths and the residuals in canonical order for those).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     __builtin_amdgcn_s_setprio(3);                  // as k_codebook: a single workgroup others wait for
