@@ -687,6 +687,7 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     uint32_t *leaf_parent = a.scratch.leaf_parent, *int_parent = a.scratch.int_parent;
     // ---- 1. the symbols that occur as sort keys (frequency << 16 | symbol), unless the sort kernels have done that ----
     if (!a.presorted) {
+        __syncthreads();                                     // (everybody has read the counts per wavefront in s.part, which the scans below overwrite)
         uint32_t done = 0;
         for (uint32_t base = 0; base < nbins; base += kBookBlock) {
             const uint32_t sy = base + tid;

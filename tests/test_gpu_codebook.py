@@ -70,3 +70,30 @@ def test_more_symbols_than_lds(oracle, nbins, m):
         assert np.array_equal(lens.cpu().numpy(), want), kind
         assert np.array_equal(codes.cpu().numpy().view(np.uint64), oracle.canonical_codes(want)), kind
     ctx.close()
+
+
+@pytest.mark.parametrize("nbins", [4096, 8192])
+def test_more_symbols_than_lds_beside_other_work(oracle, nbins):
+    """The same by one workgroup, over and over, with its wavefronts slowed down unevenly by kernels on another stream: the
+    number of symbols is taken from words of LDS that the construction uses again."""
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(nbins)
+    ctx = comet.Context(max_elems=4096, max_nbins=65536)
+    side = torch.cuda.Stream()
+    busy = torch.randn(1 << 24, device="cuda")
+    cases = []
+    for m in (2048, 2049, 3000, nbins):
+        h = np.zeros(nbins, np.uint32)
+        h[np.sort(rng.choice(nbins, m, replace=False))] = rng.integers(1, 1 << 14, m)
+        cases.append((torch.from_numpy(h.view(np.int32)).cuda(), torch.from_numpy(oracle.code_lengths(h)).cuda()))
+    torch.cuda.synchronize()
+    outs = []
+    for i in range(40):
+        with torch.cuda.stream(side):
+            busy.mul_(1.0)
+        lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+        ctx.comet_stage_codebook(cases[i % 4][0], nbins, lens)
+        outs.append(lens)
+    ctx.comet_sync()
+    assert all(torch.equal(lens, cases[i % 4][1]) for i, lens in enumerate(outs))
+    ctx.close()
