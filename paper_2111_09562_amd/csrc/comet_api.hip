@@ -84,6 +84,7 @@ struct comet_ctx {
     // pinned host
     DevState *host_state = nullptr;
     Header *host_hdr = nullptr;
+    CallResult *host_result = nullptr;              // written by the kernel that seals a container's header
     // occupancy (workgroups per CU) measured once
     double *stats = nullptr;      // kStatsPartialMax partial sums and, behind them, the mean
     int occ_quant = 1;
@@ -350,7 +351,7 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
 
 int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nbins, uint32_t chunk_syms,
                   hipStream_t st, uint32_t *chunk_off, uint8_t *container, uint64_t capacity,
-                  uint32_t *payload, uint64_t payload_cap, uint64_t *payload_words_out, uint64_t *desc) {
+                  uint32_t *payload, uint64_t payload_cap, uint64_t *payload_words_out, uint64_t *desc, CallResult *host = nullptr) {
     EncodeArgs a{};
     a.len8 = container ? container + kHeaderBytes : nullptr;      // the length section k_codebook has written
     a.codes = codes; a.n = n; a.chunk_syms = chunk_syms;
@@ -372,6 +373,7 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     a.payload = payload; a.payload_cap_words = payload_cap; a.payload_words_out = payload_words_out;
     a.desc = desc; a.ctl = &ctx->state->ctl;
     a.latched = container ? &ctx->state->latched : nullptr;
+    a.host = host;
     const bool full = (a.tbl_n == nbins);
     const bool wide = a.len8 && enc_wide(nbins);             // (a stage call brings no lengths)
 #define COMET_LAUNCH_ENC(S)                                                                                            \
@@ -525,9 +527,10 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
         c->tables.lut16 = (uint16_t *)(blob + o_lut16);
         c->tables.sub16 = (uint16_t *)(blob + o_sub16);
     }
-    if ((e = hipHostMalloc((void **)&c->host_state, sizeof(DevState) + sizeof(Header), hipHostMallocDefault)) != hipSuccess)
+    if ((e = hipHostMalloc((void **)&c->host_state, sizeof(DevState) + sizeof(Header) + sizeof(CallResult), hipHostMallocDefault)) != hipSuccess)
         return fail(COMET_ERR_NOMEM);
     c->host_hdr = reinterpret_cast<Header *>(reinterpret_cast<uint8_t *>(c->host_state) + sizeof(DevState));
+    c->host_result = reinterpret_cast<CallResult *>(c->host_hdr + 1);
 
     // kernels that need more than 64 KB of dynamic LDS must opt in
     if ((e = hipFuncSetAttribute((const void *)k_reconstruct<0>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
@@ -673,7 +676,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         p.rows_per_wave = g.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
         p.n_runs = (p.rows_total + g.rows_per_wave - 1u) / g.rows_per_wave;
         p.chunk_syms = S; p.work_words = sp.work_words; p.container = out; p.capacity = capacity;
-        p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched;
+        p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched; p.host = bytes_out ? ctx->host_result : nullptr;
         constexpr uint32_t per_wg = (uint32_t)(kPlaceBlock / kWave);
         TimedScope ts(ctx, st, COMET_KERNEL_ENCODE);
         hipLaunchKernelGGL(k_place_payload, dim3((p.n_runs + per_wg - 1u) / per_wg), dim3(kPlaceBlock), 0, st, p);
@@ -681,15 +684,14 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     } else {
         if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, ctx->codes, hist, hist_parts, rec, rec_cap, desc_q, nullptr, in_type))) return rc;
         if ((rc = launch_codebook(ctx, b, st))) return rc;
-        if ((rc = launch_encode(ctx, ctx->codes, n, nbins, S, st, chunk_off, out, capacity, nullptr, 0, nullptr, desc_e))) return rc;
+        if ((rc = launch_encode(ctx, ctx->codes, n, nbins, S, st, chunk_off, out, capacity, nullptr, 0, nullptr, desc_e,
+                                bytes_out ? ctx->host_result : nullptr))) return rc;
     }
     if (bytes_out) {
-        HIP_TRY(hipMemcpyAsync(ctx->host_state, ctx->state, sizeof(DevState), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         // this call's own bits, and whatever earlier asynchronous calls on this context have latched
-        const uint32_t own = ctx->host_state->ctl.status;
-        const uint32_t stt = own | ctx->host_state->latched;
-        if (!own) *bytes_out = ctx->host_state->ctl.total_bytes;
+        const uint32_t own = ctx->host_result->own, stt = ctx->host_result->latched;
+        if (!own) *bytes_out = ctx->host_result->total_bytes;
         if (stt) {
             HIP_TRY(hipMemsetAsync(&ctx->state->latched, 0, 4, st));
             HIP_TRY(hipStreamSynchronize(st));

@@ -162,6 +162,19 @@ constexpr uint32_t kEncSegChunksMax = 4096;   // chunks per workgroup segment (t
 constexpr uint32_t kEncSegChunksWide = 4064;
 static_assert(2u * (65536u + 8u + 4u * kEncSegChunksWide + 4u * (kEncBlockWide / kWave)) <= kLdsPerCu, "two workgroups of the wide count kernel per compute unit");
 
+// What a call that waits for its container's size is told.  The kernel that seals the header stores it straight into
+// the context's pinned host memory, and the end of the stream's work makes it visible: a copy of the control block behind
+// that kernel cost 1.8 us of a call (one image, 64 x 28 x 28: 62.0 -> 60.2).
+struct CallResult {
+    uint64_t total_bytes;
+    uint32_t own;              // ST_* bits of this call
+    uint32_t latched;          // those and what earlier asynchronous calls on the context have latched
+};
+__device__ inline void tell_host(CallResult *host, uint64_t total, uint32_t own, uint32_t *latched) {
+    const uint32_t before = own || host ? atomicOr(latched, own) : 0u;
+    if (host) { host->total_bytes = total; host->own = own; host->latched = before | own; }
+}
+
 struct EncodeArgs {
     const uint16_t *codes;
     uint64_t n;
@@ -182,6 +195,7 @@ struct EncodeArgs {
     uint64_t *desc;            // words of every segment (written by the count kernel, read by the pack kernel)
     Control *ctl;
     uint32_t *latched;         // product path: the context's persistent status word (the pack kernel seals the header); else null
+    CallResult *host;          // product path: pinned host memory for a caller that waits, or null
     uint32_t zero_pair;        // container version 2: (centre << 16) | centre, a chunk of nothing but centre codes takes no words; else 0
 };
 // single-pass compression: the words of every run from the work area to the payload
@@ -195,6 +209,7 @@ struct PlaceArgs {
     uint64_t capacity;
     Control *ctl;
     uint32_t *latched;             // the context's persistent status word
+    CallResult *host;              // pinned host memory for a caller that waits, or null
 };
 constexpr int kPlaceBlock = 256;
 __global__ void k_place_payload(PlaceArgs a);

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
             h->total_bytes = total;
             h->status = stt ? 1u : 0u;
             a.ctl->total_bytes = total;
-            if (stt) atomicOr(a.latched, stt);        // folded into the context's persistent word
+            tell_host(a.host, total, stt, a.latched);  // (the bits are folded into the context's persistent word)
         }
     }
     __syncthreads();                                  // table and buffers ready
@@ -394,10 +394,8 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
         a.ctl->total_bytes = total;
         if (off_payload <= a.capacity)
             for (uint64_t o = rec_end; o < off_payload; ++o) a.container[o] = 0;     // padding behind the records
-        if (stt) {
-            atomicOr(&a.ctl->status, stt);
-            atomicOr(a.latched, stt);
-        }
+        if (stt) atomicOr(&a.ctl->status, stt);
+        tell_host(a.host, total, stt, a.latched);
     }
     if (earlier) return;
     const uint64_t cap_words = (a.capacity >= off_payload) ? (a.capacity - off_payload) / 4u : 0u;
