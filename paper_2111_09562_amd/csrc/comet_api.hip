@@ -77,6 +77,8 @@ struct comet_ctx {
     uint32_t *run_count = nullptr;   //   and per run: record count, non-zero inputs, verbatim records
     uint64_t max_runs = 0;
     uint64_t stage_bytes = 0;        // size of rec_stage, which also holds the band sums of a decompression
+    uint32_t *hist_parts = nullptr;  // partial histograms of the row-walking quantise kernel, kPartsBytes
+    bool parts_clean = false;        //   they are zero: the last call that used them has launched all of its kernels
     uint64_t *enc = nullptr;
     BookScratch book{};
     DecodeTables tables{};
@@ -97,8 +99,10 @@ struct comet_ctx {
 
 namespace {
 
+constexpr uint64_t kPartsBytes = 4ull * kQuantHistPartsWords + 256u;
+
 struct ZeroLayout {          // sub-allocation of the zero region for one call
-    uint64_t off_hist, off_parts, off_desc_q, off_desc_e, bytes;
+    uint64_t off_hist, off_desc_q, off_desc_e, bytes;
 };
 
 // Does the row-walking quantise kernel count its codes (what it can of them, for an alphabet larger than its window)?
@@ -106,19 +110,18 @@ bool quantize_counts(uint64_t n, uint32_t nbins) { return nbins <= kHistWindowMa
 
 // partial histograms of the row-walking quantise kernel for an alphabet of nbins
 uint32_t hist_copies(uint32_t nbins) {
-    const uint32_t c = kQuantHistPartsWords / (nbins ? nbins : 1u);
+    if (nbins <= kBookPartsMax) return kQuantHistCopiesBook;
+    const uint32_t c = kQuantHistPartsWords / nbins;
     return c < 1u ? 1u : (c > kQuantHistCopiesMax ? kQuantHistCopiesMax : c);
 }
 
-// nbins_hist: entries of the histogram itself (0 if the caller brings its own), nbins_parts: alphabet
-// the partial histograms are for (0: none)
-ZeroLayout zero_layout(uint32_t nbins_hist, uint32_t nbins_parts, uint64_t tiles_q, uint64_t tiles_e) {
+// nbins_hist: entries of the histogram itself (0 if the caller brings its own)
+ZeroLayout zero_layout(uint32_t nbins_hist, uint64_t tiles_q, uint64_t tiles_e) {
     ZeroLayout z;
     uint64_t o = align_up(sizeof(Control), 256);
     z.off_desc_q = o; o += align_up(8 * tiles_q, 256);
     z.off_desc_e = o; o += align_up(8 * tiles_e, 256);
     z.off_hist = o; o += align_up(4ull * nbins_hist, 256);
-    z.off_parts = o; o += align_up(4ull * nbins_parts * hist_copies(nbins_parts), 256);
     z.bytes = o;
     return z;
 }
@@ -131,8 +134,10 @@ int status_to_error(uint32_t st) {
     return COMET_OK;
 }
 
-// Clears the zero region of a call (control block, descriptors, histograms): one launch, and a plain
-// kernel rather than a memset node for callers that capture the call in a graph.  n16: 16-byte words.
+// Clears the zero region of a call (control block, descriptors, histograms): a plain kernel rather than a memset
+// node for callers that capture the call in a graph.  n16: 16-byte words.  The row-walking path does without: its first kernel
+// clears the control block, and its last one leaves the partial histograms zero for the next call (a launch of its
+// own in front of the first one cost every compression 3 us).
 __global__ __launch_bounds__(256) void k_clear(uint4 *p, uint32_t n16) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i < n16) p[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -202,11 +207,13 @@ struct SinglePass {
     uint32_t *work_words;      // n / 2 words
 };
 
+// recs: receives what the kernels behind this one need to place the outlier records (n_wg == 0: they are in place already)
+// reset_ctl: the kernel clears the call's control block (row-walking kernel, no reuse)
 // reuse_len: code book reuse (device u8[nbins], row-walking kernel only, with sp); else null
 // in_type: element type of x (0 fp32, COMET_F16, COMET_BF16; the 16-bit types: row-walking kernel only, no reuse)
 int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, float eb, uint32_t nbins,
                     hipStream_t st, uint16_t *codes, uint32_t *hist, uint32_t *hist_parts, uint32_t *rec, uint64_t rec_cap,
-                    uint64_t *desc, const uint8_t *reuse_len = nullptr, int in_type = 0, const SinglePass *sp = nullptr) {
+                    uint64_t *desc, RecordArgs *recs, bool reset_ctl, const uint8_t *reuse_len = nullptr, int in_type = 0, const SinglePass *sp = nullptr) {
     if (in_type != 0 && (reuse_len || s.w > kQuantRowsMaxW)) return COMET_ERR_INVALID;
     if ((reuse_len != nullptr) != (sp != nullptr)) return COMET_ERR_INVALID;
     QuantArgs a{};
@@ -226,6 +233,10 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         a.rows_per_step = g.rows_per_step;
         if ((uint64_t)grid * (kQuantBlock / kWave) > ctx->max_runs) return COMET_ERR_INTERNAL;
         a.stage = ctx->rec_stage;
+        {
+            const uint64_t room = ctx->stage_bytes / 8u / ((uint64_t)grid * kQuantWaves), most = 2ull * g.rows_per_wave * s.w;    // (two records per element at most)
+            a.rec_run = (uint32_t)(room < most ? room : most);
+        }
         a.run_count = ctx->run_count;
         a.hist_parts = hist_parts;
         a.hist_copies = hist_copies(nbins);
@@ -234,6 +245,11 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         const bool counts = quantize_counts(n, nbins);
         const size_t lds = counts ? (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u + (full ? 0u : (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u) : 0u;
         a.run_from = ctx->run_count + 3u * ctx->max_runs;
+        a.reset_ctl = reset_ctl ? 1u : 0u;
+        RecordArgs &ra = *recs;
+        ra.x = x; ra.in_type = (uint32_t)in_type; ra.divW = a.divW; ra.divH = a.divH; ra.r = a.r; ra.ebx2 = a.ebx2; ra.eb = eb;
+        ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.rows_total = a.rows_total; ra.rows_per_wave = a.rows_per_wave;
+        ra.n_wg = grid; ra.stage = ctx->rec_stage; ra.rec_run = a.rec_run; ra.run_count = ctx->run_count; ra.rec = rec; ra.rec_cap = rec_cap; ra.ctl = a.ctl;
         // (an alphabet larger than the window: what the sweep does not count is counted from memory, behind it)
         auto count_codes = [&]() {
             if (full || reuse_len) return;
@@ -263,8 +279,6 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
                 else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistNone, false, IN>), dim3(grid), dim3(kQuantBlock), lds, st, a);             \
             }                                                                                                          \
             count_codes();                                                                                             \
-            TimedScope ts(ctx, st, COMET_KERNEL_GATHER);                                                               \
-            hipLaunchKernelGGL((k_gather_records<VEC, NSEG, MULTI, false, IN>), dim3(grid), dim3(kQuantBlock), 0, st, a); \
         } while (0)
 #define COMET_LAUNCH_QR(VEC, NSEG, MULTI)                                                                              \
         do {                                                                                                           \
@@ -276,8 +290,6 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
                 if (a.enc_n == nbins) hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistFull, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a); \
                 else hipLaunchKernelGGL((k_quantize_rows<VEC, NSEG, MULTI, kHistNone, true>), dim3(grid), dim3(kQuantBlock), lds_single, st, a);                 \
             }                                                                                                          \
-            TimedScope ts(ctx, st, COMET_KERNEL_GATHER);                                                               \
-            hipLaunchKernelGGL((k_gather_records<VEC, NSEG, MULTI, true>), dim3(grid), dim3(kQuantBlock), lds_reuse, st, a); \
         } while (0)
         a.reuse_len = reuse_len;
         const size_t lds_reuse = ((size_t)nbins + 7u) & ~(size_t)7u;    // the given length table, one byte per bin
@@ -308,7 +320,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
 #undef COMET_LAUNCH_QR
 #undef COMET_LAUNCH_QR_IN
     } else {
-        if (reuse_len) return COMET_ERR_INVALID;          // the flat-tile kernel has no code book reuse
+        if (reuse_len || reset_ctl) return COMET_ERR_INVALID;          // the flat-tile kernel has no code book reuse
         // one segment of consecutive tiles per workgroup, about as many workgroups as fit the chip at once
         a.tiles_per_seg = (a.n_tiles + grid - 1) / grid;
         a.rec_lds = kQuantRecLds;
@@ -317,6 +329,26 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         if (a.win_n == nbins) hipLaunchKernelGGL(k_quantize<true>, dim3(grid), dim3(kQuantBlock), lds, st, a);
         else hipLaunchKernelGGL(k_quantize<false>, dim3(grid), dim3(kQuantBlock), lds, st, a);
     }
+    HIP_TRY(hipGetLastError());
+    return COMET_OK;
+}
+
+// Partial histograms that are zero, whatever the last call has left there, for a call that adds to them: dirty from here until all of
+// its kernels have been launched.
+int clean_parts(comet_ctx *ctx, hipStream_t st) {
+    if (!ctx->parts_clean) {
+        hipLaunchKernelGGL(k_clear, dim3((uint32_t)(kPartsBytes / 16u + 255u) / 256u), dim3(256), 0, st, reinterpret_cast<uint4 *>(ctx->hist_parts), (uint32_t)(kPartsBytes / 16u));
+        HIP_TRY(hipGetLastError());
+    }
+    ctx->parts_clean = false;
+    return COMET_OK;
+}
+
+// The outlier records of a quantisation that no code book follows; hist: receives the sum of the partial histograms, or null.
+int launch_gather(comet_ctx *ctx, const RecordArgs &recs, hipStream_t st, uint32_t *hist, const uint32_t *parts) {
+    TimedScope ts(ctx, st, COMET_KERNEL_GATHER);
+    const uint32_t runs = recs.n_wg * kQuantWaves;
+    hipLaunchKernelGGL(k_gather_records, dim3((runs + kRecordRuns - 1u) / kRecordRuns), dim3(kRecordBlock), 0, st, recs, hist, parts, hist_copies(recs.nbins));
     HIP_TRY(hipGetLastError());
     return COMET_OK;
 }
@@ -340,7 +372,8 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
         b.scratch.keys = src; b.scratch.iw = dst;
         b.presorted = 1u;
     }
-    hipLaunchKernelGGL(k_codebook, dim3(1), dim3(kBookBlock), 0, st, b);
+    const uint32_t runs = b.recs.n_wg * kQuantWaves;
+    hipLaunchKernelGGL(k_codebook, dim3(1u + (runs + kRecordRuns - 1u) / kRecordRuns), dim3(kBookBlock), 0, st, b);
     if (b.presorted) {                                       // (they leave an alphabet whose occurring symbols fit LDS alone)
         hipLaunchKernelGGL(k_book_depths, dim3((b.nbins + kBookDepthBlock - 1u) / kBookDepthBlock), dim3(kBookDepthBlock), 0, st, b);
         hipLaunchKernelGGL(k_book_codes, dim3((b.nbins + kBookBlock - 1u) / kBookBlock), dim3(kBookBlock), 0, st, b);
@@ -351,7 +384,8 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
 
 int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nbins, uint32_t chunk_syms,
                   hipStream_t st, uint32_t *chunk_off, uint8_t *container, uint64_t capacity,
-                  uint32_t *payload, uint64_t payload_cap, uint64_t *payload_words_out, uint64_t *desc, CallResult *host = nullptr) {
+                  uint32_t *payload, uint64_t payload_cap, uint64_t *payload_words_out, uint64_t *desc,
+                  CallResult *host = nullptr, uint32_t *clear = nullptr, uint64_t clear_bytes = 0) {
     EncodeArgs a{};
     a.len8 = container ? container + kHeaderBytes : nullptr;      // the length section k_codebook has written
     a.codes = codes; a.n = n; a.chunk_syms = chunk_syms;
@@ -374,6 +408,7 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     a.desc = desc; a.ctl = &ctx->state->ctl;
     a.latched = container ? &ctx->state->latched : nullptr;
     a.host = host;
+    a.clear = reinterpret_cast<uint4 *>(clear); a.clear_n16 = (uint32_t)((clear_bytes + 15u) / 16u);
     const bool full = (a.tbl_n == nbins);
     const bool wide = a.len8 && enc_wide(nbins);             // (a stage call brings no lengths)
 #define COMET_LAUNCH_ENC(S)                                                                                            \
@@ -482,17 +517,21 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     // scan descriptors: one per segment of the quantise / encode kernels (worst case over chunk sizes)
     const uint64_t tiles_q = (uint64_t)c->num_cu * 16u + 16u;
     const uint64_t tiles_e = (uint64_t)c->num_cu * 8u + max_elems / 64u / kEncSegChunksWide + 16u;
-    const ZeroLayout z = zero_layout(kMaxBins, kMaxBins, tiles_q, tiles_e);   // the partial histograms take up to 2 MB
+    const ZeroLayout z = zero_layout(kMaxBins, tiles_q, tiles_e);
     c->zero_cap = z.bytes;
-    const uint64_t state_bytes = offsetof(DevState, ctl) + z.bytes;
+    const uint64_t parts_at = align_up(offsetof(DevState, ctl) + z.bytes, 256);
+    const uint64_t state_bytes = parts_at + kPartsBytes;     // the partial histograms behind it: 2 MB
     if ((e = hipMalloc((void **)&c->state, state_bytes)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     if ((e = hipMemset(c->state, 0, state_bytes)) != hipSuccess) return fail(hip_fail(e, "hipMemset"));
     c->zero_region = reinterpret_cast<uint8_t *>(&c->state->ctl);
+    c->hist_parts = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(c->state) + parts_at);
+    c->parts_clean = true;                                   // (just cleared)
     if ((e = hipMalloc((void **)&c->codes, align_up(2 * max_elems + 64, 256))) != hipSuccess) return fail(COMET_ERR_NOMEM);
     if ((e = hipMalloc((void **)&c->enc, 8ull * kMaxBins)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     if ((e = hipMalloc((void **)&c->stats, 8ull * (kStatsPartialMax + 1u))) != hipSuccess) return fail(COMET_ERR_NOMEM);
     c->max_runs = (uint64_t)c->num_cu * 4u * kQuantRunsPerSimd + 8u;
     c->stage_bytes = c->max_runs * kQuantRecRun * 8ull;
+    if (c->stage_bytes < align_up(2 * max_elems, 256)) c->stage_bytes = align_up(2 * max_elems, 256);      // a record for every fourth element
     if (c->stage_bytes < band_bytes_max(max_elems)) c->stage_bytes = band_bytes_max(max_elems);
     if ((e = hipMalloc((void **)&c->rec_stage, c->stage_bytes)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     // (a fourth array of one entry per run: the words of every run of the single-pass compression)
@@ -624,8 +663,8 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     const uint64_t n_chunks = (n + S - 1) / S;
     uint32_t e_seg, e_grid;
     encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
-    const uint64_t tiles_q = quantize_geometry(ctx, s, n, dev_in, nbins, in_type ? 2u : 4u, dev_len ? S : 0u).grid;
-    const uint64_t tiles_e = e_grid;
+    const QuantGeom qg = quantize_geometry(ctx, s, n, dev_in, nbins, in_type ? 2u : 4u, dev_len ? S : 0u);
+    const uint64_t tiles_q = qg.grid, tiles_e = e_grid;
 
     Header proto{};
     proto.magic = kMagic; proto.version = ctx->zero_chunks ? 2u : 1u; proto.N = s.n; proto.C = s.c; proto.H = s.h; proto.W = s.w;
@@ -638,15 +677,15 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     proto.off_outlier = align16(proto.off_chunk + 4 * n_chunks);
     if (proto.off_outlier > capacity) return COMET_ERR_CAPACITY;
 
-    const ZeroLayout z = zero_layout(nbins, nbins, tiles_q, tiles_e);
+    const ZeroLayout z = zero_layout(nbins, tiles_q, tiles_e);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
-    {
+    if (!qg.rows) {                                          // (flat tiles count in places that start at zero)
         const uint32_t n16 = (uint32_t)(z.bytes / 16u);      // the layout is made of 256-byte pieces
         hipLaunchKernelGGL(k_clear, dim3((n16 + 255u) / 256u), dim3(256), 0, st, reinterpret_cast<uint4 *>(ctx->zero_region), n16);
         HIP_TRY(hipGetLastError());
     }
+    const bool parts = qg.rows && !dev_len;                  // this call adds to the partial histograms
     uint32_t *hist = reinterpret_cast<uint32_t *>(ctx->zero_region + z.off_hist);
-    uint32_t *hist_parts = reinterpret_cast<uint32_t *>(ctx->zero_region + z.off_parts);
     uint64_t *desc_q = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_q);
     uint64_t *desc_e = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_e);
     uint8_t *out = static_cast<uint8_t *>(dev_out);
@@ -659,22 +698,24 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     const uint64_t rec_cap = (capacity - proto.off_outlier) / 8u;
     uint32_t *chunk_off = reinterpret_cast<uint32_t *>(out + proto.off_chunk);
     int rc;
+    RecordArgs recs{};
     if (dev_len) {
         // Single pass over the input: the code book first (header, length section, encode table), then the quantise
         // kernel encodes its own codes into the work area, then the words of every run move to their place.
+        b.reset_ctl = 1u;
         if ((rc = launch_codebook(ctx, b, st))) return rc;
-        const QuantGeom g = quantize_geometry(ctx, s, n, dev_in, nbins, 4u, S);
         SinglePass sp{};
         sp.enc = ctx->enc; sp.chunk_syms = S;
         sp.zero_pair = ctx->zero_chunks ? ((nbins / 2u) << 16) | (nbins / 2u) : 0u;
         sp.chunk_off = chunk_off;
         sp.run_words = ctx->run_count + 3u * ctx->max_runs;
         sp.work_words = reinterpret_cast<uint32_t *>(ctx->codes);
-        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, hist, hist_parts, rec, rec_cap, desc_q, dev_len, 0, &sp))) return rc;
+        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, hist, nullptr, rec, rec_cap, desc_q, &recs, false, dev_len, 0, &sp))) return rc;
+        if ((rc = launch_gather(ctx, recs, st, nullptr, nullptr))) return rc;
         PlaceArgs p{};
         p.run_words = sp.run_words;
-        p.rows_per_wave = g.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
-        p.n_runs = (p.rows_total + g.rows_per_wave - 1u) / g.rows_per_wave;
+        p.rows_per_wave = qg.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
+        p.n_runs = (p.rows_total + qg.rows_per_wave - 1u) / qg.rows_per_wave;
         p.chunk_syms = S; p.work_words = sp.work_words; p.container = out; p.capacity = capacity;
         p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched; p.host = bytes_out ? ctx->host_result : nullptr;
         constexpr uint32_t per_wg = (uint32_t)(kPlaceBlock / kWave);
@@ -682,10 +723,19 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         hipLaunchKernelGGL(k_place_payload, dim3((p.n_runs + per_wg - 1u) / per_wg), dim3(kPlaceBlock), 0, st, p);
         HIP_TRY(hipGetLastError());
     } else {
-        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, ctx->codes, hist, hist_parts, rec, rec_cap, desc_q, nullptr, in_type))) return rc;
+        if (parts && (rc = clean_parts(ctx, st))) return rc;
+        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, ctx->codes, hist, ctx->hist_parts, rec, rec_cap, desc_q, &recs, qg.rows, nullptr, in_type))) return rc;
+        if (parts && nbins > kBookPartsMax && nbins <= kBookBySymbolMax) {
+            if ((rc = launch_gather(ctx, recs, st, hist, ctx->hist_parts))) return rc;
+        } else {
+            b.recs = recs;
+            if (parts) { b.hist_parts = ctx->hist_parts; b.hist_copies = hist_copies(nbins); b.hist_sum = hist; }
+        }
         if ((rc = launch_codebook(ctx, b, st))) return rc;
         if ((rc = launch_encode(ctx, ctx->codes, n, nbins, S, st, chunk_off, out, capacity, nullptr, 0, nullptr, desc_e,
-                                bytes_out ? ctx->host_result : nullptr))) return rc;
+                                bytes_out ? ctx->host_result : nullptr, parts ? ctx->hist_parts : nullptr,
+                                parts ? 4ull * nbins * hist_copies(nbins) : 0ull))) return rc;
+        if (parts) ctx->parts_clean = true;
     }
     if (bytes_out) {
         HIP_TRY(hipStreamSynchronize(st));
@@ -1183,14 +1233,19 @@ int comet_stage_quantize(comet_ctx *ctx, const float *dev_in, comet_shape s, flo
     if (n > ctx->max_elems) return COMET_ERR_NOMEM;
     hipStream_t st = (hipStream_t)stream;
     const uint64_t tiles_q = quantize_geometry(ctx, s, n, dev_in, nbins).grid;
-    const ZeroLayout z = zero_layout(0, nbins, tiles_q, 1);
+    const ZeroLayout z = zero_layout(0, tiles_q, 1);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
     HIP_TRY(hipMemsetAsync(ctx->zero_region, 0, z.bytes, st));
     HIP_TRY(hipMemsetAsync(dev_hist, 0, 4ull * nbins, st));
     uint64_t *desc_q = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_q);
-    uint32_t *hist_parts = reinterpret_cast<uint32_t *>(ctx->zero_region + z.off_parts);
-    int rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, dev_codes, dev_hist, hist_parts, dev_records, rec_capacity, desc_q);
+    RecordArgs recs{};
+    int rc;
+    if ((rc = clean_parts(ctx, st))) return rc;
+    rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, dev_codes, dev_hist, ctx->hist_parts, dev_records, rec_capacity, desc_q, &recs, false);
     if (rc) return rc;
+    if (recs.n_wg && (rc = launch_gather(ctx, recs, st, dev_hist, ctx->hist_parts))) return rc;
+    if ((rc = clean_parts(ctx, st))) return rc;              // (at once, not in the next call: that one may have been captured in a graph already)
+    ctx->parts_clean = true;
     HIP_TRY(hipMemcpyAsync(dev_counts, &ctx->state->ctl.n_rec, 24, hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_latch, dim3(1), dim3(1), 0, st, ctx->state);
     HIP_TRY(hipGetLastError());
@@ -1220,7 +1275,7 @@ int comet_stage_encode(comet_ctx *ctx, const uint16_t *dev_codes, uint64_t n, ui
     uint32_t e_seg, e_grid;
     encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
     const uint64_t tiles_e = e_grid;
-    const ZeroLayout z = zero_layout(0, 0, 1, tiles_e);
+    const ZeroLayout z = zero_layout(0, 1, tiles_e);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
     HIP_TRY(hipMemsetAsync(ctx->zero_region, 0, z.bytes, st));
     uint64_t *desc_e = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_e);

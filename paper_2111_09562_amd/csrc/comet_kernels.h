@@ -8,6 +8,7 @@ namespace comet {
 
 // ---- quantise (prequantise + Lorenzo + codes + histogram + records) ----------
 constexpr int kQuantBlock = 256;
+constexpr uint32_t kQuantWaves = (uint32_t)(kQuantBlock / kWave);   // runs per workgroup of the row-walking kernel
 constexpr int kQuantTile = 4096;           // elements per tile: 256 lanes x 4 iterations x float4
 constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup
 
@@ -26,11 +27,13 @@ struct QuantArgs {
     uint32_t rows_per_wave;    //   consecutive rows per wavefront (a multiple of rows_per_step)
     uint32_t rows_per_step;    //   rows a wavefront covers per step (64 / lanes per row if a row takes at most 32 lanes, else 1)
     uint32_t hist_shift;       //   log2 of the copies of the LDS histogram window (lane & (copies - 1) picks one)
-    uint32_t *stage;           //   staging area: kQuantRecRun (key, payload) pairs per run
-    uint32_t *run_count;       //   three arrays of one entry per run: records, non-zero inputs, verbatim records
+    uint32_t *stage;           //   staging area: rec_run (key, payload) pairs per run
+    uint32_t rec_run;
+    uint32_t *run_count;       //   records per run; then per workgroup: records, non-zero inputs, verbatim records
     const uint8_t *reuse_len;  //   code book reuse (REUSE kernels): u8[nbins] code lengths; a code of length 0 becomes an escape; no histogram
-    uint32_t *hist_parts;      //   hist_copies partial histograms of nbins entries, zeroed: workgroup b adds to copy b % hist_copies
-    uint32_t hist_copies;      //   (k_gather_records adds them up into hist)
+    uint32_t *hist_parts;      //   hist_copies partial histograms of nbins entries, zero: workgroup b adds to copy b % hist_copies
+    uint32_t hist_copies;      //   (the code book kernels add them up)
+    uint32_t reset_ctl;        //   1: this kernel is the first of its call and clears *ctl itself
     // single-pass compression (REUSE kernels): the codes are encoded by the wavefront that makes them
     const uint64_t *enc;       //   encode table of the given lengths: (code << 6) | length per symbol
     uint32_t enc_lo, enc_n;    //   table entries [enc_lo, enc_lo + enc_n) are cached in LDS
@@ -41,18 +44,44 @@ struct QuantArgs {
     uint32_t *run_from;        // kHistPart: element of every run from which on k_code_hist counts its codes
     uint32_t *work_words;      //   work area: the words of the run that starts at element e at word e / 2
     uint16_t *codes;
-    uint32_t *hist;            // u32[nbins], zeroed
-    uint32_t *rec;             // (key, payload) pairs
+    uint32_t *hist;            // flat tiles: u32[nbins], zeroed
+    uint32_t *rec;             // flat tiles: (key, payload) pairs
     uint64_t rec_cap;          // capacity in records
     uint64_t *desc;            // chained-scan descriptors, one per segment, zeroed
     Control *ctl;
 };
+
+// What the kernels behind the row-walking quantise kernel need to bring its outlier records into element order.
+struct RecordArgs {
+    const void *x;             // the input (for runs with more records than their staging area holds)
+    uint32_t in_type;          // 0 fp32, 1 IEEE half, 2 bfloat16
+    FastDiv divW, divH;
+    float r, ebx2, eb;
+    int32_t radius;
+    uint32_t nbins;
+    const uint8_t *reuse_len;  // code book reuse: the given lengths, or null
+    uint32_t rows_total, rows_per_wave;
+    uint32_t n_wg;             // workgroups of the quantise kernel (kQuantWaves runs each); 0: there are no records to place
+    const uint32_t *stage;     // rec_run (key, payload) pairs per run
+    uint32_t rec_run;
+    const uint32_t *run_count; // as in QuantArgs
+    uint32_t *rec;             // (key, payload) pairs of the container, in element order
+    uint64_t rec_cap;          // room for so many
+    Control *ctl;
+};
+constexpr int kRecordBlock = 1024;
+constexpr uint32_t kRecordRuns = (uint32_t)(kRecordBlock / kWave);   // runs per workgroup
+// hist: if not null, the sum of the `copies` partial histograms of nbins entries in `parts` goes there
+__global__ void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies);
 constexpr uint32_t kEncRingSyms = 1024;    // single-pass compression: codes a wavefront keeps in LDS between quantisation and encoding (a batch of at most 512, and less than 256 not yet encoded)
 constexpr uint32_t kEncRunBufWords = 476;  //   its assembly buffer: the words of one step of 256 symbols (at most 456 of code words of 57 bits, two more touched) and slack
 constexpr uint32_t kQuantRecLds = 3072;   // outlier records buffered in LDS per workgroup (24 KB)
 template <bool FULLWIN> __global__ void k_quantize(QuantArgs a);   // flat tiles, any plane width; FULLWIN: every bin is in the LDS window
 constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane of the row-walking kernel
-constexpr uint32_t kQuantRecRun = 768;    // outlier records staged per run (one run of rows per wavefront)
+// Outlier records staged per run (one run of rows per wavefront): the staging area of a context holds one for every fourth element,
+// and at least kQuantRecRun per run.  A run with more has its records derived from the input once more, which takes twice the time of the
+// quantise kernel itself; a container of such a tensor is hardly smaller than the tensor (8 bytes per record alone).
+constexpr uint32_t kQuantRecRun = 768;
 constexpr uint32_t kQuantRecLds2 = 256;   // records a wavefront buffers in LDS before it writes them to the staging area in bulk
 constexpr uint32_t kQuantRunsPerSimd = 5; // runs the launch aims at, per SIMD
 // Alphabets larger than the histogram window: a wavefront counts its run's codes while those outside the window, which it
@@ -67,8 +96,14 @@ constexpr uint64_t kQuantCountMin = 1ull << 26;
 constexpr uint32_t kQuantStaticLds = 8448; // static LDS of k_quantize_rows (the record buffers of its four wavefronts and a few words), rounded up
 constexpr uint32_t kLdsPerCu = 160u * 1024u;
 constexpr uint32_t kQuantRunsPerSimdSingle = 4;   //   ... of the single-pass compression (all of them resident at once)
-constexpr uint32_t kQuantHistCopiesMax = 32;        // partial histograms the workgroups spread their flushes over
-constexpr uint32_t kQuantHistPartsWords = 8u * 65536u;    // all copies together have at most this many entries (2 MB: eight copies of the largest alphabet)
+// Partial histograms the workgroups spread their flushes over: the occupied bins are a few cache lines, and a thousand
+// workgroups adding to one copy of them queue up for 10 to 20 us.  Up to kBookPartsMax bins the one workgroup of the code book
+// kernel adds them up itself: 8 copies (32 of them: 64 x 64 x 112 x 112, 1024 bins 153.0 us instead of 151.5).  Above, many
+// workgroups do, of k_gather_records or k_book_sort_tiles (the code book kernel's one: 64 x 256 x 56 x 56, 8192 bins 161.3 us -> 164.7):
+// up to 32 copies and 2 MB (eight of the largest alphabet).
+constexpr uint32_t kQuantHistCopiesMax = 32, kQuantHistCopiesBook = 8;
+constexpr uint32_t kBookPartsMax = 2048;   // (no alphabet of the code book kernel's that has more symbols than fit its LDS)
+constexpr uint32_t kQuantHistPartsWords = 8u * 65536u;
 // VEC adjacent columns per lane (2 needs an even W and 8-byte aligned input), NSEG segments of 64 lanes per row,
 // MULTI: several rows per step; HIST: which codes are counted here: all (every bin is in the LDS window), those of a run as
 // long as few of them lie outside the window, or none (k_code_hist counts the others)
@@ -77,7 +112,6 @@ constexpr uint32_t kQuantHistPartsWords = 8u * 65536u;    // all copies together
 // VEC = 2 then needs 4-byte aligned input)
 constexpr int kHistNone = 0, kHistFull = 1, kHistPart = 2;
 template <int VEC, int NSEG, bool MULTI, int HIST, bool REUSE = false, int IN = 0> __global__ void k_quantize_rows(QuantArgs a);
-template <int VEC, int NSEG, bool MULTI, bool REUSE = false, int IN = 0> __global__ void k_gather_records(QuantArgs a);
 constexpr uint32_t kQuantReuseMaxBins = 8192;   // largest alphabet whose length table the REUSE kernels keep in LDS
 
 // ---- histogram of the codes of a large alphabet ----------------------------------
@@ -119,6 +153,11 @@ constexpr uint32_t kBookLens = 65u;        // lengths 0 .. 64 (64 stands for eve
 
 struct BookArgs {
     const uint32_t *hist;
+    const uint32_t *hist_parts;  // up to kBookPartsMax bins: kQuantHistCopiesBook partial histograms instead of hist; above kBookBySymbolMax,
+    uint32_t hist_copies;        // k_book_sort_tiles adds hist_copies of them up into hist_sum (which hist then points to)
+    uint32_t *hist_sum;
+    RecordArgs recs;           // outlier records to place beside the code book, by the workgroups behind the first one (n_wg == 0: none)
+    uint32_t reset_ctl;        // 1: this kernel is the first of its call and clears *ctl itself
     const uint8_t *given_len;  // code book reuse: take these lengths instead of building them from hist (which is then unused)
     uint32_t nbins;
     uint8_t *len_out;          // u8[nbins]
@@ -197,6 +236,8 @@ struct EncodeArgs {
     uint32_t *latched;         // product path: the context's persistent status word (the pack kernel seals the header); else null
     CallResult *host;          // product path: pinned host memory for a caller that waits, or null
     uint32_t zero_pair;        // container version 2: (centre << 16) | centre, a chunk of nothing but centre codes takes no words; else 0
+    uint4 *clear;              // pack kernel: clear_n16 16-byte words that the next call on the context finds zero (the partial histograms,
+    uint32_t clear_n16;        // which have been read by now)
 };
 // single-pass compression: the words of every run from the work area to the payload
 struct PlaceArgs {

@@ -15,7 +15,10 @@
 // symbol); two queues; at every step the two smallest heads are merged, the leaf
 // first when a leaf and an internal node weigh the same; internal nodes are
 // consumed in creation order.
+#include <type_traits>
+
 #include "comet_kernels.h"
+#include "comet_records.h"
 
 namespace comet {
 
@@ -510,6 +513,7 @@ struct BookLds {
     uint32_t findex[65];
     uint32_t part[kBookBlock / kWave];
     uint32_t word[4];
+    uint64_t total[3];                // records, non-zero inputs, verbatim records of the tensor
 };
 static_assert(sizeof(BookLds) <= 64u * 1024u, "static LDS");
 
@@ -570,10 +574,19 @@ __device__ inline void book_first_codes(const BookArgs &a, BookLds &s, uint32_t 
     __syncthreads();
 }
 
+// The tensor's record counts, a wavefront each (the second to the fourth, while the first one builds the tree).
+__device__ inline void book_totals(const RecordArgs &recs, BookLds &s) {
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / (uint32_t)kWave)), lane = (uint32_t)lane_id();
+    if (recs.n_wg && wave >= 1u && wave <= 3u) {
+        const uint64_t total = record_total(recs, wave - 1u, lane);
+        if (lane == 0) s.total[wave - 1u] = total;
+    }
+}
+
 // The code lengths (s.depth, s.cnt) of m <= kBookLdsSyms symbols: thread i holds the i-th and, n_keys == 2, the
 // (i + kBookBlock)-th (frequency, place in s.sym) key in order; all ones behind the last.
 template <typename W>
-__device__ inline void book_tree(BookLds &s, uint32_t m, const uint64_t (&key)[2], uint32_t n_keys) {
+__device__ inline void book_tree(BookLds &s, const RecordArgs &recs, uint32_t m, const uint64_t (&key)[2], uint32_t n_keys) {
     const uint32_t tid = threadIdx.x;
     // ---- leaves in order, waiting; no nodes yet ----
     W *leafw = reinterpret_cast<W *>(s.u.q.leafw), *nodew = reinterpret_cast<W *>(s.u.q.nodew);
@@ -589,6 +602,7 @@ __device__ inline void book_tree(BookLds &s, uint32_t m, const uint64_t (&key)[2
     for (uint32_t i = tid; i < m + (uint32_t)kWave; i += kBookBlock) nodew[i] = ~(W)0;
     __syncthreads();
     if (tid < (uint32_t)kWave) huffman_rounds_wave<W>(leafw, nodew, s.v.t.parent, m, tid);
+    else book_totals(recs, s);
     __syncthreads();
     // ---- depth of every leaf: walk to the root (node m - 2) ----
     for (uint32_t i = tid; i < m; i += kBookBlock) {
@@ -685,6 +699,7 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     const uint32_t nbins = a.nbins;
     uint64_t *keys = a.scratch.keys, *iw = a.scratch.iw;
     uint32_t *leaf_parent = a.scratch.leaf_parent, *int_parent = a.scratch.int_parent;
+    book_totals(a.recs, s);
     // ---- 1. the symbols that occur as sort keys (frequency << 16 | symbol), unless the sort kernels have done that ----
     if (!a.presorted) {
         __syncthreads();                                     // (everybody has read the counts per wavefront in s.part, which the scans below overwrite)
@@ -827,7 +842,14 @@ __device__ inline void book_finish(const BookArgs &a, uint32_t m, uint32_t max_l
 __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
     __shared__ uint64_t s_x[2 * kBookBlock];
     const uint32_t s = blockIdx.x * (uint32_t)kBookBlock + threadIdx.x;
-    const uint32_t f = s < a.nbins ? a.hist[s] : 0u;
+    uint32_t f = 0;
+    if (a.hist_copies) {                            // the partial histograms of the quantise kernel
+#pragma unroll
+        for (uint32_t k = 0; k < kQuantHistCopiesMax; ++k) f += (k < a.hist_copies && s < a.nbins) ? a.hist_parts[(size_t)k * a.nbins + s] : 0u;
+        if (s < a.nbins) a.hist_sum[s] = f;
+    } else {
+        f = s < a.nbins ? a.hist[s] : 0u;
+    }
     if (!f && s < a.nbins) {                        // unused symbol: length 0 everywhere
         a.len_out[s] = 0;
         a.enc[s] = 0;
@@ -856,16 +878,24 @@ __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *
 }
 
 __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
+    static_assert(kBookBlock == kRecordBlock, "workgroups of both kinds in one launch");
+    __shared__ BookLds s;
+    if (blockIdx.x != 0u) {                                  // the workgroups behind the first one bring the outlier records into order
+        static_assert(sizeof(s.u) >= kRecordRuns * kDeriveBuf * sizeof(uint2), "a buffer per wavefront");
+        const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+        place_records(a.recs, (blockIdx.x - 1u) * kRecordRuns + w, (uint32_t)lane_id(), reinterpret_cast<uint2 *>(&s.u) + w * kDeriveBuf);
+        return;
+    }
     // One workgroup on the critical path of its stream, often next to the streaming kernels of
     // other streams: its wavefronts go first whenever they are ready to issue.
     __builtin_amdgcn_s_setprio(3);
-    __shared__ BookLds s;
     const uint32_t tid = threadIdx.x, lane = tid & (uint32_t)(kWave - 1);
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     const uint32_t nbins = a.nbins;
     const bool given = a.given_len != nullptr;
-    // (what the header takes from the control block: asked for now, needed last)
-    const uint64_t n_rec = a.ctl->n_rec, n_vrec = a.ctl->n_vrec, nnz = a.ctl->nnz;
+    // (what the header takes from the control block, unless the counts are added up here: asked for now, needed last)
+    const uint64_t ctl_rec = a.ctl->n_rec, ctl_vrec = a.ctl->n_vrec, ctl_nnz = a.ctl->nnz;
+    if (a.reset_ctl && tid < sizeof(Control) / 4u) reinterpret_cast<uint32_t *>(a.ctl)[tid] = 0u;   // (before the first barrier: nothing has raised a bit yet)
     if (tid < 65) s.cnt[tid] = 0;
     if (tid < 4) s.word[tid] = 0;
     __syncthreads();
@@ -881,12 +911,34 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     const uint32_t s0 = wave * iters * (uint32_t)kWave;
     uint32_t f[kGroup];
     auto fetch = [&](uint32_t g) {
+        if (a.hist_parts && nbins <= kBookPartsMax) {        // partial histograms, all loads in flight together (g == 0)
+            constexpr uint32_t kJ = kBookPartsMax / (uint32_t)kBookBlock, kC = kQuantHistCopiesBook;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.hist_parts), 0, (int)(kC * nbins * 4u), 0x00020000);
+            uint32_t v[kJ][kC];
+#pragma unroll
+            for (uint32_t j = 0; j < kJ; ++j) {
+                const uint32_t sy = s0 + j * (uint32_t)kWave + lane;
+                const int at = j < iters && sy < nbins ? (int)(sy * 4u) : (int)0x80000000;
+#pragma unroll
+                for (uint32_t k = 0; k < kC; ++k) v[j][k] = __builtin_amdgcn_raw_buffer_load_b32(r, at, (int)(k * nbins * 4u), 0);
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < kGroup; ++j) {
+                f[j] = 0;
+                if (j < kJ) {
+#pragma unroll
+                    for (uint32_t k = 0; k < kC; ++k) f[j] += v[j < kJ ? j : 0][k];
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (uint32_t j = 0; j < kGroup; ++j) {
             const uint32_t sy = s0 + (g + j) * (uint32_t)kWave + lane;
             f[j] = (g + j < iters && sy < nbins) ? (given ? (uint32_t)a.given_len[sy] : a.hist[sy]) : 0u;
         }
     };
+    static_assert(kBookPartsMax <= kGroup * (uint32_t)kBookBlock, "one group");
     uint32_t mine = 0;
     {
         bool out1 = false, out2 = false;
@@ -973,8 +1025,8 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
                 block_sort<2>(key, s.u.exchange, n2);
             }
             const uint32_t n_keys = n2 <= (uint32_t)kBookBlock ? 1u : 2u;
-            if (narrow) book_tree<uint32_t>(s, m, key, n_keys);
-            else book_tree<uint64_t>(s, m, key, n_keys);
+            if (narrow) book_tree<uint32_t>(s, a.recs, m, key, n_keys);
+            else book_tree<uint64_t>(s, a.recs, m, key, n_keys);
         }
         // ---- 5. canonical codes ----
         book_first_codes(a, s, m, given);
@@ -986,6 +1038,9 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
 
     // ---- 7. container layout ----
     if (tid == 0) {
+        const bool counted = a.recs.n_wg != 0u;
+        const uint64_t n_rec = counted ? s.total[0] : ctl_rec, n_vrec = counted ? s.total[2] : ctl_vrec, nnz = counted ? s.total[1] : ctl_nnz;
+        if (counted) { a.ctl->n_rec = n_rec; a.ctl->n_vrec = n_vrec; a.ctl->nnz = nnz; }
         a.ctl->n_active = m;
         a.ctl->enc_in_window = (outside & 1) ? 0u : 1u;
         a.ctl->len_in_window = (outside & 2) ? 0u : 1u;
@@ -1368,6 +1423,26 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
         }
     }
     if (tid == 0) { a.t.meta[3] = (uint32_t)radius; a.t.meta[4] = compact ? 1u : 0u; }
+}
+
+// The outlier records by a kernel of its own: where no code book is built behind the quantise kernel (a stage call) or it was
+// built in front of it (compression with a given one).  The first workgroup adds up the counts as well.
+__global__ __launch_bounds__(kRecordBlock) void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies) {
+    __shared__ uint2 s_buf[kRecordRuns][kDeriveBuf];
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = (uint32_t)lane_id();
+    for (uint32_t b = blockIdx.x * (uint32_t)kRecordBlock + threadIdx.x; hist && b < a.nbins; b += gridDim.x * (uint32_t)kRecordBlock) {
+        uint32_t v = 0, p[kQuantHistCopiesMax];              // (every copy in flight at once)
+#pragma unroll
+        for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) p[j] = (j < copies) ? parts[(size_t)j * a.nbins + b] : 0u;
+#pragma unroll
+        for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) v += p[j];
+        hist[b] = v;
+    }
+    if (blockIdx.x == 0u && wave < 3u) {
+        const uint64_t total = record_total(a, wave, lane);
+        if (lane == 0) *(wave == 0u ? &a.ctl->n_rec : (wave == 1u ? &a.ctl->nnz : &a.ctl->n_vrec)) = total;
+    }
+    place_records(a, blockIdx.x * kRecordRuns + wave, lane, s_buf[wave]);
 }
 
 }  // namespace comet

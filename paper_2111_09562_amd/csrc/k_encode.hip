@@ -162,6 +162,8 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
     uint32_t *buf = s_buf + wave * kEncBufWords;
     for (uint32_t i = lane; i < kEncBufWords; i += kWave) buf[i] = 0;
 
+    for (uint32_t i = blockIdx.x * kEncBlock + tid; i < a.clear_n16; i += gridDim.x * kEncBlock) a.clear[i] = make_uint4(0u, 0u, 0u, 0u);
+
     uint32_t *payload;
     uint64_t cap_words;
     if (a.container) {

@@ -24,11 +24,11 @@
 // Outlier records (escapes and verbatim values) must end up in the container in
 // element order.  k_quantize_rows appends them, in order, to a staging area of
 // its run (through a small LDS buffer, so that the main loop holds no global store
-// the compiler cannot count) and leaves the count; k_gather_records, a second small
-// kernel, adds up the counts in front of a run and moves its records to their final
-// place (a run with more records than its staging area holds is swept again, this
-// time writing in place).  The histogram goes the same way: LDS windows are added
-// to one of several partial histograms, which k_gather_records adds up.  Nothing
+// the compiler cannot count) and leaves the count; further workgroups of the code book
+// kernel add up the counts in front of a run and move its records to their final
+// place (comet_records.h; a run with more records than its staging area holds is gone
+// through again there).  The histogram goes the same way: LDS windows are added
+// to one of several partial histograms, which the code book kernel adds up.  Nothing
 // waits for anything inside a kernel.
 //
 // Compression with a given code book (the REUSE kernels) is a single pass over the input: the
@@ -89,18 +89,17 @@ struct SweepCounts {
     uint32_t oow_held = 0;      //   entries of the list in use (what the caller finds there it counts)
 };
 
-// One sweep of a wavefront over rows [row_lo, row_hi).  PASS 0: everything (codes, histogram,
-// counters), records into rec_dst[0 .. rec_cap) (the rest is only counted); PASS 1: records only,
-// and a record that does not fit raises ST_CAPACITY.  Returns the number of records of the run.
+// One sweep of a wavefront over rows [row_lo, row_hi): codes, histogram, counters, records into rec_dst[0 .. rec_cap)
+// (the rest is only counted).  Returns the number of records of the run.
 // VEC: adjacent columns per lane (1, or 2 for even W: one 8-byte load, one packed code store and
 // one cross-lane shift per pair); NSEG: segments of 64 lanes per row (1, 2, 4, 8); MULTI: a row
 // takes at most 32 lanes, K rows per step (NSEG == 1); HIST: the codes are counted here (kHistFull: every bin is in the LDS
 // window), as long as few of them lie outside the window (kHistPart), or not (kHistNone).
 // REUSE: code book reuse.  s_len (LDS, u8[nbins]) holds the code lengths the caller brought; a code
 // whose length is 0 becomes an escape, there is no histogram, and an escape that the table has no
-// code word for raises ST_CODEBOOK.  In PASS 0 the codes go to the ring of `enc` in LDS and are encoded
+// code word for raises ST_CODEBOOK.  The codes go to the ring of `enc` in LDS and are encoded
 // from there (tbl: the encode table; kHistFull then says that all of it is in LDS).
-template <int VEC, int NSEG, bool MULTI, int HIST, int PASS, bool REUSE = false, int IN = 0>
+template <int VEC, int NSEG, bool MULTI, int HIST, bool REUSE = false, int IN = 0>
 __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint32_t row_hi, uint32_t lane, uint32_t *s_hist,
                                       uint32_t hist_dummy, uint2 *s_buf, uint2 *rec_dst, uint64_t rec_cap, SweepCounts &cnt,
                                       const uint8_t *s_len = nullptr, RunEncoder *enc = nullptr,
@@ -213,7 +212,6 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
         wave_lds_fence();
         for (uint32_t i = lane; i < buffered; i += kWave) {
             if (cur + i < rec_cap) rec_dst[cur + i] = s_buf[i];
-            else if (PASS == 1) atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
         }
         wave_lds_fence();
         cur += buffered;
@@ -228,17 +226,17 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
         wave_lds_fence();
         cnt.oow_held = 0;
     };
-    uint16_t *ring_w = (PASS == 0 && REUSE) ? const_cast<uint16_t *>(enc->ring) : nullptr;
+    uint16_t *ring_w = REUSE ? const_cast<uint16_t *>(enc->ring) : nullptr;
     // REUSE: does the given table have a code word for this code?  From the length table; the single-pass sweep with
     // the whole encode table in LDS reads that instead (an entry is 0 for a symbol without a code word), which saves
     // the length table's LDS.
     auto has_code = [&](uint32_t c) -> bool {
-        if (PASS == 0 && REUSE && FULLWIN) return reinterpret_cast<const uint32_t *>(tbl->lds)[2u * c] != 0u;
+        if (REUSE && FULLWIN) return reinterpret_cast<const uint32_t *>(tbl->lds)[2u * c] != 0u;
         return s_len[c] != 0;
     };
     // single-pass compression: encode what the ring holds of the run's first `produced` symbols
     auto drain = [&](uint32_t produced, bool final) {
-        if (PASS == 0 && REUSE) {
+        if (REUSE) {
             if (!final && produced - enc->consumed < 256u) return;
             wave_lds_fence();
             if (a.chunk_syms == 64u) enc->template drain<64, FULLWIN>(*tbl, lane, produced, final);
@@ -253,7 +251,7 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
             const uint32_t soff = (t0 + u) * stride;
             int32_t carry_q = 0;                                // last column of the previous segment (uniform)
             const uint32_t hmask = h_row ? ~0u : 0u;            // !MULTI: "has a row above"
-            if (PASS == 0 && !REUSE && HIST == kHistPart && cnt.counting && cnt.oow > kQuantOowFree + soff / kQuantOowShare) {   // (uniform)
+            if (!REUSE && HIST == kHistPart && cnt.counting && cnt.oow > kQuantOowFree + soff / kQuantOowShare) {   // (uniform)
                 cnt.counting = false;
                 cnt.from = soff;
             }
@@ -314,8 +312,8 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                     em[v] = wave_ballot(!inr[v]) & vmask;
                     sm[v] = wave_ballot(susp[v]) & vmask;
                     any_rec |= em[v] | sm[v];
-                    if (PASS == 0) cnt.nnz_lane += (x[v] != 0.0f) ? 1u : 0u;   // lanes without an element hold 0
-                    if (PASS == 0 && !REUSE && HIST != kHistNone) {
+                    cnt.nnz_lane += (x[v] != 0.0f) ? 1u : 0u;   // lanes without an element hold 0
+                    if (!REUSE && HIST != kHistNone) {
                         // Histogram: no divergent branch (switching the execution mask costs more than the
                         // atomic).  Lanes that count nothing add to a word of their own; the centre bin is
                         // not counted here, it is what is left of the workgroup's elements.  The window is
@@ -342,12 +340,12 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                         }
                     }
                 }
-                if (PASS == 0 && REUSE) {
+                if (REUSE) {
                     // into the ring (lanes without an element write behind it)
                     const uint32_t at = valid ? ((col[s] + soff) & (kEncRingSyms - 1u)) : kEncRingSyms;
                     if (VEC == 2) *reinterpret_cast<uint32_t *>(ring_w + at) = code[0] | (code[VEC - 1] << 16);
                     else ring_w[at] = (uint16_t)code[0];
-                } else if (PASS == 0) {
+                } else {
                     const int voff = FULL ? (int)(col[s] * 2u) : (int)((col[s] + soff) * 2u);
                     const int sof = FULL ? (int)(soff * 2u) : 0;
                     if (VEC == 2) __builtin_amdgcn_raw_buffer_store_b32(code[0] | (code[VEC - 1] << 16), r_c, voff, sof, 0);
@@ -357,7 +355,7 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                 // columns, escape before verbatim).  One wavefront-uniform test per slot.  They go to a small LDS
                 // buffer and leave in bulk, so that the loop holds no global store outside this branch. ----
                 if (any_rec != 0ull) {
-                    if (REUSE && PASS == 0) {                    // an escape, and the table has no code word for it
+                    if (REUSE) {                    // an escape, and the table has no code word for it
                         uint64_t any_e = 0ull;
 #pragma unroll
                         for (int v = 0; v < VEC; ++v) any_e |= em[v];
@@ -381,7 +379,7 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
                         add += (uint32_t)__popcll(em[v]) + (uint32_t)__popcll(vm[v]);
                         before += __builtin_amdgcn_mbcnt_hi((uint32_t)(em[v] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)em[v], 0u));
                         if (vm[v]) before += __builtin_amdgcn_mbcnt_hi((uint32_t)(vm[v] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vm[v], 0u));
-                        if (PASS == 0) cnt.vrec += (uint32_t)__popcll(vm[v]);
+                        cnt.vrec += (uint32_t)__popcll(vm[v]);
                     }
                     if (add) {
                         if (buffered + add > kQuantRecLds2) flush_records();
@@ -425,7 +423,7 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
     }
     drain(n_el, true);
     flush_records();
-    if (PASS == 0 && !REUSE && HIST == kHistPart) cnt.from = cnt.counting || cnt.from > n_el ? n_el : cnt.from;
+    if (!REUSE && HIST == kHistPart) cnt.from = cnt.counting || cnt.from > n_el ? n_el : cnt.from;
     return cur;
 }
 
@@ -455,6 +453,8 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
+    // (nothing in this kernel reads the control block or raises a bit in it, but in the REUSE kernels, which are not the first)
+    if (!REUSE && a.reset_ctl && blockIdx.x == 0u && tid < sizeof(Control) / 4u) reinterpret_cast<uint32_t *>(a.ctl)[tid] = 0u;
     uint8_t *s_len = reinterpret_cast<uint8_t *>(s_dyn_qr);
     if (REUSE && (a.ctl->status & (uint32_t)ST_CODEBOOK)) {
         // k_codebook has refused the given table (the same for every thread): nothing is encoded with it, and the
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         enc.zero_pair = a.zero_pair;
     }
     if (row_hi > row_lo)
-        my_records = sweep_rows<VEC, NSEG, MULTI, HIST, 0, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, (a.win_n << a.hist_shift) + tid, s_recbuf[wave],
-                                                                 reinterpret_cast<uint2 *>(a.stage) + (size_t)run * kQuantRecRun, kQuantRecRun, cnt, s_len,
+        my_records = sweep_rows<VEC, NSEG, MULTI, HIST, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, (a.win_n << a.hist_shift) + tid, s_recbuf[wave],
+                                                                 reinterpret_cast<uint2 *>(a.stage) + (size_t)run * a.rec_run, a.rec_run, cnt, s_len,
                                                                  REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
     if (REUSE) {
         if (lane == 0) a.run_words[run] = enc.wrun;
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     // ---- flush the private histogram ----
     // Into one of several partial histograms: the occupied bins are a few cache lines, and thousands
     // of workgroups adding to the same lines would queue up behind each other for longer than the
-    // sweep takes.  k_gather_records adds the copies up.
+    // sweep takes.  The code book kernel adds the copies up.
     // centre bin = elements of the workgroup - everything counted elsewhere
     __syncthreads();
     if (tid < 3u) {
@@ -560,103 +560,16 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     if (tid == 0 && elems > total) atomicAdd(&part[a.radius], (uint32_t)(elems - total));
 }
 
-// Moves the staged records of every run to their final, ordered place; same grid as k_quantize_rows.
-template <int VEC, int NSEG, bool MULTI, bool REUSE, int IN>
-__global__ __launch_bounds__(kQuantBlock) void k_gather_records(QuantArgs a) {
-    constexpr int kWaves = kQuantBlock / kWave;
-    extern __shared__ uint32_t s_dyn_gr[];          // REUSE: the given length table, u8[nbins] (for runs that are swept again)
-    __shared__ uint64_t s_part64[kWaves];
-    __shared__ uint2 s_recbuf[kWaves][kQuantRecLds2];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
-    const uint32_t n_runs = gridDim.x * kWaves;
-    const uint32_t run0 = blockIdx.x * kWaves;
-
-    uint8_t *s_len = reinterpret_cast<uint8_t *>(s_dyn_gr);
-    if (REUSE) {
-        for (uint32_t i = tid; i < a.nbins; i += kQuantBlock) s_len[i] = a.reuse_len[i];
-        __syncthreads();
-    }
-    // histogram: one thread per bin adds up the partial histograms
-    for (uint32_t b = blockIdx.x * kQuantBlock + tid; !REUSE && b < a.nbins; b += gridDim.x * kQuantBlock) {
-        uint32_t v = 0;
-        uint32_t p[kQuantHistCopiesMax];                                    // every copy in flight at once: one round trip
-#pragma unroll
-        for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) p[j] = (j < a.hist_copies) ? a.hist_parts[(size_t)j * a.nbins + b] : 0u;
-#pragma unroll
-        for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) v += p[j];
-        a.hist[b] = v;
-    }
-
-    // sum of the per-workgroup counters wg[0 .. count) over the workgroup, eight loads in flight per thread
-    auto total_of = [&](const uint32_t *wg, uint32_t count) {
-        uint64_t sum = 0;
-        for (uint32_t i0 = 0; i0 < count; i0 += 8u * kQuantBlock) {
-            uint32_t v[8];
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) {
-                const uint32_t i = i0 + j * kQuantBlock + tid;
-                v[j] = (i < count) ? wg[i] : 0u;
-            }
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) sum += v[j];
-        }
-        uint64_t total;
-        (void)block_excl_scan<uint64_t, kWaves>(sum, s_part64, total);
-        return total;
-    };
-    const uint32_t *wg_rec = a.run_count + n_runs, *wg_nnz = wg_rec + gridDim.x, *wg_vrec = wg_nnz + gridDim.x;
-    // records of all workgroups in front of mine
-    uint64_t base = total_of(wg_rec, blockIdx.x);
-    uint32_t mine = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t c = a.run_count[run0 + w];
-        if ((uint32_t)w < wave) base += c;
-        if ((uint32_t)w == wave) mine = c;
-    }
-    if (blockIdx.x + 1u == gridDim.x && tid == kQuantBlock - 1) a.ctl->n_rec = base + mine;   // last run: base covers all runs before it
-    // two of the first workgroups (little in front of them) total the other counters, one each
-    if (blockIdx.x == 0) {
-        const uint64_t nnz_total = total_of(wg_nnz, gridDim.x);
-        if (tid == 0) a.ctl->nnz = nnz_total;
-    }
-    if (blockIdx.x == (gridDim.x > 1u ? 1u : 0u)) {
-        const uint64_t vrec_total = total_of(wg_vrec, gridDim.x);
-        if (tid == 0) a.ctl->n_vrec = vrec_total;
-    }
-    if (!mine) return;
-    const uint32_t run = run0 + wave;
-    uint2 *dst = reinterpret_cast<uint2 *>(a.rec) + base;
-    const uint64_t room = (base < a.rec_cap) ? a.rec_cap - base : 0ull;
-    if (mine <= kQuantRecRun) {
-        const uint2 *src = reinterpret_cast<const uint2 *>(a.stage) + (size_t)run * kQuantRecRun;
-        for (uint32_t i = lane; i < mine; i += kWave) {
-            if (i < room) dst[i] = src[i];
-            else atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
-        }
-    } else {
-        // more outliers than the staging area of a run holds: derive them again, in place
-        uint32_t row_lo, row_hi;
-        run_rows(a, run, &row_lo, &row_hi);
-        SweepCounts unused;
-        (void)sweep_rows<VEC, NSEG, MULTI, kHistFull, 1, REUSE, IN>(a, row_lo, row_hi, lane, nullptr, 0, s_recbuf[wave], dst, room, unused, s_len);
-    }
-}
-
 #define COMET_INST_QR(VEC, NSEG, MULTI)                                                          \
     template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistFull, true, 0>(QuantArgs);   \
     template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistNone, true, 0>(QuantArgs);   \
-    template __global__ void k_gather_records<VEC, NSEG, MULTI, true, 0>(QuantArgs);             \
     COMET_INST_QR_IN(VEC, NSEG, MULTI, 0)                                                        \
     COMET_INST_QR_IN(VEC, NSEG, MULTI, 1)                                                        \
     COMET_INST_QR_IN(VEC, NSEG, MULTI, 2)
 #define COMET_INST_QR_IN(VEC, NSEG, MULTI, IN)                                                   \
     template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistFull, false, IN>(QuantArgs); \
     template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistPart, false, IN>(QuantArgs); \
-    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistNone, false, IN>(QuantArgs); \
-    template __global__ void k_gather_records<VEC, NSEG, MULTI, false, IN>(QuantArgs);
+    template __global__ void k_quantize_rows<VEC, NSEG, MULTI, kHistNone, false, IN>(QuantArgs);
 COMET_INST_QR(1, 1, true)
 COMET_INST_QR(1, 1, false)
 COMET_INST_QR(1, 2, false)

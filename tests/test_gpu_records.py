@@ -1,0 +1,98 @@
+"""Outlier records that the code book kernel's further workgroups bring into order, and the partial histograms that a
+call leaves zero for the next one.  Containers against the CPU oracle's, byte for byte."""
+import numpy as np
+import pytest
+
+from paper_2111_09562_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# 10.5 million elements are the fewest whose runs take every place of the staging area, so that a run's share of it (768
+# records of 2048 elements) can overflow; widths around the 256 elements a wavefront takes per step and the four of a lane.
+OVERFLOW = [(1, 1200, 2953, 3), (40, 1000, 266, 1), (5, 64, 181, 182), (2, 173, 60, 511), (1, 33, 624, 512), (7, 331, 18, 255)]
+
+
+@pytest.mark.parametrize("shape", OVERFLOW)
+@pytest.mark.parametrize("kind", ["float32", "float16", "bfloat16", "codebook"])
+def test_more_records_than_the_staging_area_holds(oracle, shape, kind):
+    from paper_2111_09562_amd import comet
+    n = int(np.prod(shape))
+    assert n >= 2048 * 5120
+    eb, nbins = 1e-2, 16
+    rng = np.random.default_rng(n)
+    x = np.zeros(shape, np.float32).reshape(-1)
+    few = rng.random(n) < 0.004                               # quiet stretches, stretches where every element escapes, and in between
+    x[:] = rng.standard_normal(n).astype(np.float32)
+    x[n // 5:n // 3] *= few[n // 5:n // 3]
+    at = rng.choice(n, 4000, replace=False)
+    x[at] = rng.choice(np.array([np.inf, -np.inf, np.nan, 3e7, -0.0], np.float32), at.size)
+    x[n // 2:n // 2 + 3000] = np.inf                          # two records per element: escaped and verbatim
+    x[n // 2 + 3000:n // 2 + 6000] = np.where(np.arange(3000) % 2, np.float32(np.inf), np.float32(1000.0))
+    x = x.reshape(shape)
+    ctx = comet.Context(n, nbins)
+    ctx.comet_set_chunk_syms(64)
+    box = torch.zeros(comet.comet_compress_bound(shape, nbins, 64), dtype=torch.uint8, device="cuda")
+    if kind == "codebook":
+        book = np.zeros(nbins, np.uint8)
+        book[[0, 6, 7, 8, 9]] = [1, 3, 3, 3, 3]               # most of the alphabet has no code word
+        want = oracle.compress_with_lengths(x, eb, nbins, 64, book)
+        used = ctx.comet_compress_with_codebook(torch.from_numpy(x).cuda(), eb, nbins, torch.from_numpy(book).cuda(), box)
+    elif kind == "float32":
+        want = oracle.compress(x, eb, nbins, 64)
+        used = ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, box)
+    else:
+        xt = torch.from_numpy(x).to(getattr(torch, kind))
+        want = oracle.compress(xt.float().numpy(), eb, nbins, 64)
+        used = ctx.comet_compress_16(xt.cuda(), eb, nbins, box)
+    assert used == want.size
+    assert np.array_equal(box[:used].cpu().numpy(), want)
+    small = torch.zeros(used // 3 // 16 * 16, dtype=torch.uint8, device="cuda")      # no room for all records: refused, and nothing behind the buffer is touched
+    if kind == "float32":
+        room = torch.full((small.numel() + 4096,), 77, dtype=torch.uint8, device="cuda")
+        with pytest.raises(comet.CometError) as ei:
+            ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, room[:small.numel()])
+        assert ei.value.code == comet.ERR_CAPACITY
+        assert bool((room[small.numel():] == 77).all())
+        assert ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, box) == used
+        assert np.array_equal(box[:used].cpu().numpy(), want)
+    ctx.close()
+
+
+def test_alphabets_in_turn_on_one_context(oracle):
+    """Every path leaves the partial histograms zero: alphabets on both sides of every rule that adds them up, stage
+    calls, given code books, wide planes and refused containers between them, each with the oracle's container."""
+    from paper_2111_09562_amd import comet
+    shape, wide = (3, 8, 41, 58), (1, 2, 37, 700)
+    x, y = synth.relu_blur(shape, 5, blur=3, shift=-0.2), synth.relu_blur(wide, 6, blur=3, shift=-0.2)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    n = x.size
+    ctx = comet.Context(max(n, y.size), 65536)
+    ctx.comet_set_chunk_syms(64)
+    box = torch.zeros(comet.comet_compress_bound(shape, 65536, 64), dtype=torch.uint8, device="cuda")
+    codes = torch.empty(n, dtype=torch.int16, device="cuda")
+    rec, counts = torch.empty(4 * n, dtype=torch.int32, device="cuda"), torch.empty(3, dtype=torch.int64, device="cuda")
+
+    def full(nbins, eb=1e-3):
+        want = oracle.compress(x, eb, nbins, 64)
+        assert ctx.comet_compress(xd, eb, nbins, box) == want.size, nbins
+        assert np.array_equal(box[:want.size].cpu().numpy(), want), nbins
+
+    for nbins in (65536, 64, 1024, 2048, 2050, 4096, 8192, 8194, 40002, 1022, 6, 16384, 1024):
+        full(nbins)
+        hist = torch.empty(nbins, dtype=torch.int32, device="cuda")
+        ctx.comet_stage_quantize(xd, 1e-2, nbins, codes, hist, rec, counts)
+        got = codes.cpu().numpy().view(np.uint16)
+        assert np.array_equal(hist.cpu().numpy().view(np.uint32), np.bincount(got, minlength=nbins)), nbins
+        full(nbins)
+        want = oracle.compress(y, 1e-3, nbins, 64)
+        assert ctx.comet_compress(yd, 1e-3, nbins, box) == want.size
+        assert np.array_equal(box[:want.size].cpu().numpy(), want), nbins
+        full(1024)
+        if nbins <= 8192:
+            book = box[comet.HEADER_BYTES:comet.HEADER_BYTES + 1024].clone()
+            ctx.comet_compress_with_codebook(xd, 1e-3, 1024, book, box)
+        with pytest.raises(comet.CometError):
+            ctx.comet_compress(xd, 1e-3, 1024, box[:16384])
+        full(1024)
+    ctx.close()
