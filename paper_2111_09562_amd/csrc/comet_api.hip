@@ -461,7 +461,8 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
             for (uint32_t w = s.w; (w & 1u) == 0u && rows_per_chunk > 1u; w >>= 1) rows_per_chunk >>= 1;
             unit = K / std::gcd(K, rows_per_chunk) * rows_per_chunk;
         }
-        // a few wavefronts per SIMD, but runs of at least 2048 elements (every run re-reads one row)
+        // a few wavefronts per SIMD, but runs of at least 2048 elements (every run re-reads one row), or fewer, down to 512, while
+        // that leaves SIMDs without a run (one image, 64 x 28 x 28: 26 wavefronts -> 102, the call 36.5 us -> 33.2)
         // All runs should be resident at once: a run that has to wait for a place makes the launch take two rounds.
         // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (the
         // histogram window of a large alphabet leaves room for three; the encoder's ring and tables of the single-pass
@@ -477,7 +478,8 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
         }
         const uint64_t want = (uint64_t)ctx->num_cu * 4u * runs_per_simd;
         uint64_t per = (rows_total + want - 1) / want;
-        const uint64_t min_rows = (2048u + s.w - 1u) / s.w;
+        const uint64_t share = n / ((uint64_t)ctx->num_cu * 4u), least = share < 512u ? 512u : (share < 2048u ? share : 2048u);
+        const uint64_t min_rows = (least + s.w - 1u) / s.w;
         if (per < min_rows) per = min_rows;
         per = (per + unit - 1) / unit * unit;
         if (per > rows_total) per = (rows_total + unit - 1) / unit * unit;
