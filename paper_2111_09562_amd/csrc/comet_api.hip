@@ -713,10 +713,10 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         sp.run_words = ctx->run_count + 3u * ctx->max_runs;
         sp.work_words = reinterpret_cast<uint32_t *>(ctx->codes);
         if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, hist, nullptr, rec, rec_cap, desc_q, &recs, false, dev_len, 0, &sp))) return rc;
-        if ((rc = launch_gather(ctx, recs, st, nullptr, nullptr))) return rc;
         PlaceArgs p{};
         p.run_words = sp.run_words;
         p.rows_per_wave = qg.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
+        p.recs = recs;
         p.n_runs = (p.rows_total + qg.rows_per_wave - 1u) / qg.rows_per_wave;
         p.chunk_syms = S; p.work_words = sp.work_words; p.container = out; p.capacity = capacity;
         p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched; p.host = bytes_out ? ctx->host_result : nullptr;

@@ -248,6 +248,7 @@ struct PlaceArgs {
     const uint32_t *work_words;    // the run that starts at element e has its words from word e / 2 on
     uint8_t *container;
     uint64_t capacity;
+    RecordArgs recs;               // the outlier records, which each wavefront places for its own run as well
     Control *ctl;
     uint32_t *latched;             // the context's persistent status word
     CallResult *host;              // pinned host memory for a caller that waits, or null

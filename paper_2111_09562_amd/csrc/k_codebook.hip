@@ -1425,8 +1425,8 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     if (tid == 0) { a.t.meta[3] = (uint32_t)radius; a.t.meta[4] = compact ? 1u : 0u; }
 }
 
-// The outlier records by a kernel of its own: where no code book is built behind the quantise kernel (a stage call) or it was
-// built in front of it (compression with a given one).  The first workgroup adds up the counts as well.
+// The outlier records by a kernel of its own, with the sum of the partial histograms: where no code book is built behind the quantise
+// kernel (a stage call) or the partial histograms are more than its one workgroup should add up.  The first workgroup adds up the counts as well.
 __global__ __launch_bounds__(kRecordBlock) void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies) {
     __shared__ uint2 s_buf[kRecordRuns][kDeriveBuf];
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = (uint32_t)lane_id();

@@ -26,6 +26,7 @@
 
 #include "comet_kernels.h"
 #include "comet_encode.h"
+#include "comet_records.h"
 
 namespace comet {
 
@@ -337,19 +338,22 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
 
 // ---------------------------------------------------------------------------
 // Single-pass compression, last step.  The quantise kernel has left the words of every run of
-// rows in a work area, with chunk offsets relative to the run, and k_gather_records the number
-// of outlier records, which decides where the payload starts.  One wavefront per run: the words
+// rows in a work area, with chunk offsets relative to the run, and its outlier records in a staging area; the number of
+// all records decides where the payload starts.  One wavefront per run: the words
 // in front of the run are added up (the counts of all runs in front of the workgroup, by the
-// whole workgroup), the run's words are copied to their place and its chunk offsets made
-// absolute.  The wavefront of the last run seals the header.  Nothing is copied if an earlier
-// kernel of the call has raised an error.
+// whole workgroup), and so are all records; the run's words are copied to their place and its chunk offsets made
+// absolute, and its records go to theirs (a kernel of its own for them cost 4.7 us).  The wavefront of the last run seals the
+// header.  Nothing is copied if an earlier kernel of the call has raised an error.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     constexpr int kWaves = kPlaceBlock / kWave;
-    __shared__ uint64_t s_part64[kWaves];
+    static_assert((uint32_t)kWaves == kQuantWaves, "a workgroup's runs are those of a workgroup of the quantise kernel");
+    __shared__ uint64_t s_part64[kWaves], s_all64[kWaves];
+    __shared__ uint2 s_buf[kWaves][kDeriveBuf];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
+    const uint32_t earlier = a.ctl->status;                  // what the kernels before this one raised
     const uint32_t run0 = blockIdx.x * kWaves, run = run0 + wave;
 
     uint64_t sum = 0;
@@ -363,8 +367,22 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
 #pragma unroll
         for (uint32_t j = 0; j < 8; ++j) sum += v[j];
     }
-    uint64_t base;
+    // all records: of the workgroups in front, of mine and behind
+    uint64_t sum_rec = 0;
+    const uint32_t *wg_rec = a.recs.run_count + a.recs.n_wg * kQuantWaves;
+    for (uint32_t i0 = 0; i0 < a.recs.n_wg; i0 += 8u * kPlaceBlock) {
+        uint32_t v[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t i = i0 + j * kPlaceBlock + tid;
+            v[j] = (i < a.recs.n_wg) ? wg_rec[i] : 0u;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) sum_rec += v[j];
+    }
+    uint64_t base, n_rec;
     (void)block_excl_scan<uint64_t, kWaves>(sum, s_part64, base);
+    (void)block_excl_scan<uint64_t, kWaves>(sum_rec, s_all64, n_rec);
     uint32_t mine = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
@@ -375,22 +393,24 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     if (run >= a.n_runs) return;
 
     Header *h = reinterpret_cast<Header *>(a.container);
-    const uint64_t n_rec = a.ctl->n_rec;
     const uint64_t rec_end = h->off_outlier + 8ull * n_rec;
     const uint64_t off_payload = align16(rec_end);
-    const uint32_t earlier = a.ctl->status;                  // what the kernels before this one raised
     const uint64_t pw_mine = base + mine;
-    if (run + 1u == a.n_runs && lane == 0) {
+    const bool last = run + 1u == a.n_runs;                  // (uniform)
+    uint64_t nnz = 0, n_vrec = 0;
+    if (last) { nnz = record_total(a.recs, 1u, lane); n_vrec = record_total(a.recs, 2u, lane); }
+    if (last && lane == 0) {
         uint32_t stt = earlier;
         const uint64_t total = off_payload + 4ull * pw_mine;
         if (pw_mine > 0xffffffffull || total > a.capacity) stt |= (uint32_t)ST_CAPACITY;   // (chunk offsets are 32-bit word indices)
         h->n_rec = (uint32_t)n_rec;
-        h->n_vrec = (uint32_t)a.ctl->n_vrec;
-        h->nnz = a.ctl->nnz;
+        h->n_vrec = (uint32_t)n_vrec;
+        h->nnz = nnz;
         h->off_payload = off_payload;
         h->payload_words = pw_mine;
         h->total_bytes = total;
         h->status = stt ? 1u : 0u;
+        a.ctl->n_rec = n_rec; a.ctl->n_vrec = n_vrec; a.ctl->nnz = nnz;
         a.ctl->off_payload = off_payload;
         a.ctl->payload_words = pw_mine;
         a.ctl->total_bytes = total;
@@ -412,6 +432,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     uint32_t *chunk_off = reinterpret_cast<uint32_t *>(a.container + h->off_chunk);
     const uint32_t c_lo = (uint32_t)(e_lo / a.chunk_syms), c_hi = (uint32_t)((e_hi + a.chunk_syms - 1u) / a.chunk_syms);
     for (uint32_t c = c_lo + lane; c < c_hi; c += kWave) chunk_off[c] = (uint32_t)(base + chunk_off[c]);
+    place_records(a.recs, run, lane, s_buf[wave]);
 }
 
 #define COMET_INST_ENC(S)                                                  \
