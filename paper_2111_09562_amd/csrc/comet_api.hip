@@ -373,7 +373,8 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
         b.presorted = 1u;
     }
     const uint32_t runs = b.recs.n_wg * kQuantWaves;
-    hipLaunchKernelGGL(k_codebook, dim3(1u + (runs + kRecordRuns - 1u) / kRecordRuns), dim3(kBookBlock), 0, st, b);
+    b.lds_leaves = b.presorted ? kBookLdsLeaves : 0u;
+    hipLaunchKernelGGL(k_codebook, dim3(1u + (runs + kRecordRuns - 1u) / kRecordRuns), dim3(kBookBlock), b.presorted ? kBookLdsBytesLarge : kBookLdsBytes, st, b);
     if (b.presorted) {                                       // (they leave an alphabet whose occurring symbols fit LDS alone)
         hipLaunchKernelGGL(k_book_depths, dim3((b.nbins + kBookDepthBlock - 1u) / kBookDepthBlock), dim3(kBookDepthBlock), 0, st, b);
         hipLaunchKernelGGL(k_book_codes, dim3((b.nbins + kBookBlock - 1u) / kBookBlock), dim3(kBookBlock), 0, st, b);
@@ -583,6 +584,8 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
                            (const void *)k_encode_count<256, false, kEncBlockWide>})
         if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024)) != hipSuccess)
             return fail(hip_fail(e, "hipFuncSetAttribute(k_encode_count)"));
+    if ((e = hipFuncSetAttribute((const void *)k_codebook, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBookLdsBytesLarge)) != hipSuccess)
+        return fail(hip_fail(e, "hipFuncSetAttribute(k_codebook)"));
     for (const void *fn : {(const void *)k_code_hist<true>, (const void *)k_code_hist<false>})
         if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
             return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));

@@ -40,6 +40,8 @@ struct Control {
     uint32_t max_len;
     uint32_t enc_in_window;  // k_codebook: every symbol with a code word, but for the escape symbol, lies in the part of the encode table the encoders cache in LDS
     uint32_t len_in_window;  // k_codebook: ... in the (wider) part whose lengths the count kernel caches
+    uint32_t outside;        // k_book_sort_tiles: bit 0: a symbol outside the first part occurs, bit 1: outside the second
+    uint32_t pad;
 };
 
 // Orders the LDS accesses of the lanes of one wavefront (writes before, reads after).  Only the
@@ -48,6 +50,14 @@ struct Control {
 __device__ inline void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup", "local");
     __builtin_amdgcn_wave_barrier();
+}
+
+// A barrier of the workgroup that orders accesses to LDS only: __syncthreads also waits until every global store in flight has
+// arrived, which costs a loop that stores results it never reads a round trip per turn.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Lanes of the wavefront for which `p` holds.  (The HIP __ballot takes an int: its bool -> int -> compare

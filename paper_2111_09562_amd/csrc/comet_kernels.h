@@ -165,6 +165,7 @@ struct BookArgs {
     uint64_t *enc;             // u64[nbins]: (code << 6) | len, 0 for unused symbols
     BookScratch scratch;
     uint32_t presorted;        // scratch.keys holds the leaves in (frequency, symbol) order (k_book_sort_tiles, k_book_merge) if more than kBookLdsSyms symbols occur
+    uint32_t lds_leaves;       // leaves whose weights fit the LDS of the launch (presorted)
     uint32_t narrow;           // all frequencies together are below 2^31 - 1 (a container's header only; a stage call looks for itself)
     Control *ctl;
     // container finalisation (null header = stage call)
@@ -172,6 +173,9 @@ struct BookArgs {
     Header proto;              // host-filled fields
     uint64_t capacity;
 };
+// Dynamic LDS of k_codebook: BookLds; alphabets of more than kBookBySymbolMax bins: what a compute unit has but for a kilobyte, for the weights
+// of up to kBookLdsLeaves leaves and one word.
+constexpr uint32_t kBookLdsBytes = 70016u, kBookLdsBytesLarge = kLdsPerCu - 1024u, kBookLdsLeaves = kBookLdsBytesLarge / 4u - 4u;
 __global__ void k_codebook(BookArgs a);
 constexpr int kBookMergeBlock = 256;
 constexpr int kBookDepthBlock = 256;

@@ -515,7 +515,7 @@ struct BookLds {
     uint32_t word[4];
     uint64_t total[3];                // records, non-zero inputs, verbatim records of the tensor
 };
-static_assert(sizeof(BookLds) <= 64u * 1024u, "static LDS");
+static_assert(sizeof(BookLds) <= kBookLdsBytes, "dynamic LDS");
 
 // Canonical codes of the symbols sym[0, m) (ascending) from their lengths: the code of a symbol is the first code of its
 // length plus the number of smaller symbols of the same length (per wavefront the lanes of one length are found with a
@@ -693,6 +693,103 @@ __device__ inline void huffman_rounds_window(const uint64_t *keys, uint64_t *iw,
     }
 }
 
+// Entries of w[lo, hi), sorted ascending, that are <= t; by every wavefront for itself, 64 probes at a time.
+__device__ inline uint32_t count_le_wave(const uint32_t *w, uint32_t lo, uint32_t hi, uint32_t t, uint32_t lane) {
+    const uint32_t begin = lo;
+    while (lo < hi) {
+        const uint32_t stride = (hi - lo + (uint32_t)kWave - 1u) / (uint32_t)kWave;
+        const uint32_t p = lo + (lane + 1u) * stride - 1u;                // (the probes that pass are the first ones)
+        const uint32_t c = (uint32_t)__popcll(wave_ballot(p < hi && w[p] <= t));
+        lo += c * stride;
+        if (stride == 1u) break;
+        hi = lo + stride - 1u < hi ? lo + stride - 1u : hi;
+    }
+    return lo - begin;
+}
+
+// All rounds of a tree with the weights of m <= kBookLdsLeaves presorted leaves in LDS, by the whole workgroup: w[i] is the weight of
+// leaf i until it is merged, and w[k] that of node k from then on.  (Two items make a node, so node k is made after leaf k has been
+// merged: the nodes never need a place that a waiting leaf has.)  A round takes the items of weight <= t, or the first kRoundItems of
+// them in merged order: thread by thread the new nodes find their two items by a search along the diagonal of both queues, and
+// their weights are stored once everybody has read.  Weights of all leaves together: below 2^31.
+// Bound by the latency of the searches in LDS; 26 000 symbols take 26 rounds, most of a few thousand items.  With the queues in global
+// memory (huffman_rounds_window) the queues' next items and the new nodes went through L2 in every round: 64 x 256 x 56 x 56 at 1e-4, 65536
+// bins 515 us -> 406, 64 x 28 x 28 (Laplace) 278 -> 151.
+constexpr uint32_t kRoundNodes = 4;                          // new nodes per thread and round
+constexpr uint32_t kRoundItems = 2u * kRoundNodes * (uint32_t)kBookBlock;
+__device__ inline void huffman_rounds_weights(const uint64_t *keys, uint32_t *w, uint32_t *leaf_parent, uint32_t *int_parent, uint32_t m) {
+    const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id();
+    for (uint32_t i0 = tid; i0 < m; i0 += 8u * (uint32_t)kBookBlock) {
+        uint64_t k[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8u; ++j) k[j] = i0 + j * (uint32_t)kBookBlock < m ? keys[i0 + j * (uint32_t)kBookBlock] : 0ull;
+#pragma unroll
+        for (uint32_t j = 0; j < 8u; ++j)
+            if (i0 + j * (uint32_t)kBookBlock < m) w[i0 + j * (uint32_t)kBookBlock] = (uint32_t)(k[j] >> 16);
+    }
+    lds_barrier();
+    uint32_t li = 0, ii = 0, ni = 0;                         // leaves and nodes merged so far, nodes made so far
+    while ((m - li) + (ni - ii) > 1u) {
+        const uint32_t a0 = li < m ? w[li] : ~0u, a1 = li + 1u < m ? w[li + 1u] : ~0u;
+        const uint32_t b0 = ii < ni ? w[ii] : ~0u, b1 = ii + 1u < ni ? w[ii + 1u] : ~0u;
+        const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a0 <= b0 ? a0 + (a1 <= b0 ? a1 : b0) : b0 + (a0 <= b1 ? a0 : b1)));      // the two lightest (they exist)
+        uint32_t nl = count_le_wave(w, li, m - li < kRoundItems ? m : li + kRoundItems, t, lane);
+        uint32_t nn = count_le_wave(w, ii, ni - ii < kRoundItems ? ni : ii + kRoundItems, t, lane);
+        uint32_t items = nl + nn;
+        items = items < kRoundItems ? items & ~1u : kRoundItems;          // (an odd one out waits)
+        const uint32_t nodes = items / 2u;
+        // leaves among the first `diag` items in merged order (a leaf before a node of the same weight)
+        uint32_t lo[kRoundNodes], hi[kRoundNodes], sum[kRoundNodes], longest = nl < nn ? nl : nn;
+#pragma unroll
+        for (uint32_t v = 0; v < kRoundNodes; ++v) {
+            const uint32_t diag = 2u * (v * (uint32_t)kBookBlock + tid);
+            lo[v] = diag > nn ? diag - nn : 0u;
+            hi[v] = diag < nl ? diag : nl;
+            if (diag >= items) hi[v] = lo[v];
+        }
+        for (; longest; longest >>= 1) {
+#pragma unroll
+            for (uint32_t v = 0; v < kRoundNodes; ++v) {
+                if (v * (uint32_t)kBookBlock >= nodes) break;             // (uniform)
+                const uint32_t diag = 2u * (v * (uint32_t)kBookBlock + tid);
+                const uint32_t mid = (lo[v] + hi[v]) >> 1;
+                const bool on = lo[v] < hi[v];
+                const bool leaf = on && w[li + mid] <= w[ii + diag - 1u - mid];
+                lo[v] = leaf ? mid + 1u : lo[v];
+                hi[v] = on && !leaf ? mid : hi[v];
+            }
+        }
+#pragma unroll
+        for (uint32_t v = 0; v < kRoundNodes; ++v) {
+            sum[v] = 0;
+            const uint32_t k = v * (uint32_t)kBookBlock + tid;
+            if (k < nodes) {
+                uint32_t i = lo[v], j = 2u * k - lo[v];
+#pragma unroll
+                for (uint32_t two = 0; two < 2u; ++two) {
+                    const uint32_t x = i < nl ? w[li + i] : ~0u, y = j < nn ? w[ii + j] : ~0u;
+                    const bool leaf = i < nl && (j >= nn || x <= y);
+                    if (leaf) leaf_parent[li + i] = ni + k; else int_parent[ii + j] = ni + k;
+                    sum[v] += leaf ? x : y;
+                    i += leaf ? 1u : 0u;
+                    j += leaf ? 0u : 1u;
+                }
+                if (k + 1u == nodes) { w[m] = i; }           // (leaves merged in this round, for everybody)
+            }
+        }
+        lds_barrier();
+        const uint32_t took = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[m]);
+#pragma unroll
+        for (uint32_t v = 0; v < kRoundNodes; ++v) {
+            const uint32_t k = v * (uint32_t)kBookBlock + tid;
+            if (k < nodes) w[ni + k] = sum[v];
+        }
+        lds_barrier();
+        li += took; ii += items - took; ni += nodes;
+    }
+    __syncthreads();
+}
+
 // More symbols than fit LDS, built from the histogram in global memory; keys[0, m): the leaves in order if presorted.
 __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     const uint32_t tid = threadIdx.x;
@@ -720,7 +817,6 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
     }
     const uint32_t m2 = next_pow2(m);
     if (!a.presorted) for (uint32_t i = m + tid; i < m2; i += kBookBlock) keys[i] = ~0ull;
-    for (uint32_t i = tid; i < m; i += kBookBlock) iw[i] = 0;
     __syncthreads();
     // ---- 2. leaves in (frequency, symbol) order ----
     if (!a.presorted) bitonic_sort(keys, m2);
@@ -745,6 +841,18 @@ __device__ inline void book_large(const BookArgs &a, BookLds &s, uint32_t m) {
             __syncthreads();
         }
         static_assert(sizeof(s.u.exchange) >= 16u * kBookWin, "window of both queues and the merged order");
+        if (a.presorted && narrow && m <= a.lds_leaves) {
+            // (the weights take the room of everything else in LDS; what is still needed of it waits in registers)
+            __syncthreads();
+            const uint64_t t0 = s.total[0], t1 = s.total[1], t2 = s.total[2];
+            __syncthreads();
+            huffman_rounds_weights(keys, reinterpret_cast<uint32_t *>(&s), leaf_parent, int_parent, m);
+            if (tid == 0) { s.total[0] = t0; s.total[1] = t1; s.total[2] = t2; }
+            __syncthreads();
+            return;                                          // the rest by whole grids: k_book_depths, k_book_codes
+        }
+        for (uint32_t i = tid; i < m; i += kBookBlock) iw[i] = 0;
+        __syncthreads();
         if (narrow)
             huffman_rounds_window(keys, iw, leaf_parent, int_parent, m, reinterpret_cast<uint32_t *>(s.u.exchange), s.part, kBookLdsSyms / 2u, li, ii, ni);
         else
@@ -856,8 +964,14 @@ __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
         if (a.code_out) a.code_out[s] = 0;
     }
     if (threadIdx.x < kBookLens) a.scratch.tile_cnt[blockIdx.x * kBookLens + threadIdx.x] = 0;
+    const uint32_t win_n = a.nbins < kEncTableMax ? a.nbins : kEncTableMax, win_lo = (a.nbins - win_n) / 2u;
+    const uint32_t lenw_n = enc_len_window(a.nbins), lenw_lo = (a.nbins - lenw_n) / 2u;
     const uint32_t cnt = (uint32_t)__syncthreads_count(f != 0u);
-    if (threadIdx.x == 0 && cnt) atomicAdd(&a.ctl->n_active, cnt);
+    const bool out1 = __syncthreads_or(f != 0u && s != 0u && s - win_lo >= win_n) != 0, out2 = __syncthreads_or(f != 0u && s != 0u && s - lenw_lo >= lenw_n) != 0;
+    if (threadIdx.x == 0 && cnt) {
+        atomicAdd(&a.ctl->n_active, cnt);
+        if (out1 || out2) atomicOr(&a.ctl->outside, (out1 ? 1u : 0u) | (out2 ? 2u : 0u));
+    }
     uint64_t key[1] = {f ? (((uint64_t)f << 16) | s) : ((1ull << 63) | s)};
     block_sort<1>(key, s_x, (uint32_t)kBookBlock);
     a.scratch.keys[s] = key[0];
@@ -879,7 +993,8 @@ __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *
 
 __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     static_assert(kBookBlock == kRecordBlock, "workgroups of both kinds in one launch");
-    __shared__ BookLds s;
+    extern __shared__ __align__(16) uint8_t s_book[];        // BookLds, or the weights of a large alphabet's leaves
+    BookLds &s = *reinterpret_cast<BookLds *>(s_book);
     if (blockIdx.x != 0u) {                                  // the workgroups behind the first one bring the outlier records into order
         static_assert(sizeof(s.u) >= kRecordRuns * kDeriveBuf * sizeof(uint2), "a buffer per wavefront");
         const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -899,7 +1014,13 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     if (tid < 65) s.cnt[tid] = 0;
     if (tid < 4) s.word[tid] = 0;
     __syncthreads();
-
+    uint32_t m = 0, outside = 0;
+    bool large = false;
+    if (a.presorted && (m = a.ctl->n_active) > kBookLdsSyms) {       // (the sort kernels have counted and looked already)
+        large = true;
+        outside = a.ctl->outside;
+        book_large(a, s, m);
+    } else {
     // ---- 1. the symbols that occur.  A wavefront looks at consecutive symbols, kGroup x 64 at a time (their loads in
     // flight together); counted first, then listed, so that the list is in order of the symbols.  (And: does every
     // symbol that occurs, but for the escape symbol, lie in the part of the encode table that the encoders keep in
@@ -959,14 +1080,15 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
         }
     }
     __syncthreads();
-    uint32_t m = 0, at = 0;
+    uint32_t at = 0;
+    m = 0;
 #pragma unroll
     for (uint32_t w = 0; w < kBookBlock / kWave; ++w) {
         const uint32_t c = s.part[w];
         at += w < wave ? c : 0u;
         m += c;
     }
-    const uint32_t outside = s.word[0];
+    outside = s.word[0];
 
     if (given || m <= kBookLdsSyms) {
         uint16_t *syms = given ? s.u.given.sym : s.sym;
@@ -1032,9 +1154,10 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
         book_first_codes(a, s, m, given);
         book_codes(a, syms, depths, m, s.first, s.v.wc);
     } else {
+        large = true;
         book_large(a, s, m);
     }
-    const bool large = !given && m > kBookLdsSyms;
+    }
 
     // ---- 7. container layout ----
     if (tid == 0) {
