@@ -365,9 +365,13 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
         const uint32_t total = tiles * (uint32_t)kBookBlock;          // <= kMaxBins: what the scratch arrays hold
         uint64_t *src = b.scratch.keys, *dst = b.scratch.iw;
         hipLaunchKernelGGL(k_book_sort_tiles, dim3(tiles), dim3(kBookBlock), 0, st, b);
-        for (uint32_t run = (uint32_t)kBookBlock; run < total; run <<= 1) {
-            hipLaunchKernelGGL(k_book_merge, dim3(total / (uint32_t)kBookMergeBlock), dim3(kBookMergeBlock), 0, st, src, dst, run, b.ctl);
+        for (uint32_t run = (uint32_t)kBookBlock; run < total;) {
+            const uint32_t left = total / run, ways = left >= 4u ? 4u : left;
+            const dim3 grid(total / (uint32_t)kBookMergeBlock), block(kBookMergeBlock);
+            if (ways == 4u) hipLaunchKernelGGL(k_book_merge<4u>, grid, block, 0, st, src, dst, run, b.ctl);
+            else hipLaunchKernelGGL(k_book_merge<2u>, grid, block, 0, st, src, dst, run, b.ctl);
             uint64_t *t = src; src = dst; dst = t;
+            run *= ways;
         }
         b.scratch.keys = src; b.scratch.iw = dst;
         b.presorted = 1u;

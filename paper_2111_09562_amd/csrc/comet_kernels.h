@@ -182,7 +182,7 @@ constexpr int kBookDepthBlock = 256;
 __global__ void k_book_sort_tiles(BookArgs a);
 __global__ void k_book_depths(BookArgs a);
 __global__ void k_book_codes(BookArgs a);
-__global__ void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl);
+template <uint32_t WAYS> __global__ void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl);   // WAYS: 2 or 4
 
 // ---- encode -------------------------------------------------------------------
 constexpr int kEncBlock = 256;             // four wavefronts, each encodes 256 symbols per step cooperatively

@@ -712,9 +712,8 @@ __device__ inline uint32_t count_le_wave(const uint32_t *w, uint32_t lo, uint32_
 // merged: the nodes never need a place that a waiting leaf has.)  A round takes the items of weight <= t, or the first kRoundItems of
 // them in merged order: thread by thread the new nodes find their two items by a search along the diagonal of both queues, and
 // their weights are stored once everybody has read.  Weights of all leaves together: below 2^31.
-// Bound by the latency of the searches in LDS; 26 000 symbols take 26 rounds, most of a few thousand items.  With the queues in global
-// memory (huffman_rounds_window) the queues' next items and the new nodes went through L2 in every round: 64 x 256 x 56 x 56 at 1e-4, 65536
-// bins 515 us -> 406, 64 x 28 x 28 (Laplace) 278 -> 151.
+// Bound by the latency of the searches in LDS, about 1.5 us a round; 26 000 symbols take 26 rounds.  With the queues in global
+// memory (huffman_rounds_window) a round took 5 to 15 us: the queues' next items and the new nodes went through L2.
 constexpr uint32_t kRoundNodes = 4;                          // new nodes per thread and round
 constexpr uint32_t kRoundItems = 2u * kRoundNodes * (uint32_t)kBookBlock;
 __device__ inline void huffman_rounds_weights(const uint64_t *keys, uint32_t *w, uint32_t *leaf_parent, uint32_t *int_parent, uint32_t m) {
@@ -943,8 +942,10 @@ __device__ inline void book_finish(const BookArgs &a, uint32_t m, uint32_t max_l
 // a key above all of those for a symbol that does not occur (each its own, so that no two keys are
 // equal).  k_book_sort_tiles: one tile of kBookBlock symbols per workgroup, sorted in registers; the
 // grid's tiles are a power of two and cover the alphabet.  It also counts the symbols that occur.
-// k_book_merge: runs of `run` keys merged pairwise; a key's place is its rank in its own run plus the
-// number of smaller keys in the other one (binary search); one key per thread.  Alphabets whose
+// k_book_merge: groups of WAYS runs of `run` keys merged; a key's place is its rank in its own run plus the numbers
+// of smaller keys in the others (binary searches side by side); one key per thread.  Four runs at a time, three launches for 65536 keys where two at a time took
+// six: as long where they sort (eight at a time: 4 us more, their probes fill the L2s), and 64 x 56 x 56 in bfloat16 at 1e-3, whose
+// 2000 symbols need none of it, 131 -> 126 us.  Alphabets whose
 // occurring symbols fit LDS are built there from the histogram: the merges then have nothing to do.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
@@ -977,18 +978,29 @@ __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
     a.scratch.keys[s] = key[0];
 }
 
+template <uint32_t WAYS>
 __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *src, uint64_t *dst, uint32_t run, const Control *ctl) {
     if (ctl->n_active <= kBookLdsSyms) return;
     const uint32_t i = blockIdx.x * (uint32_t)kBookMergeBlock + threadIdx.x;
     const uint64_t key = src[i];
-    const uint32_t r = i / run, own = i - r * run;           // run: a power of two
-    const uint64_t *other = src + (size_t)(r ^ 1u) * run;
-    uint32_t lo = 0, hi = run;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (other[mid] < key) lo = mid + 1; else hi = mid;
+    const uint32_t r = i / run;                              // run, WAYS: powers of two
+    const uint64_t *group = src + (size_t)(r & ~(WAYS - 1u)) * run;
+    // (branch-free, so that the searches of all runs are in flight together: below[w] counts the entries of run w that are smaller)
+    uint32_t below[WAYS - 1u];
+#pragma unroll
+    for (uint32_t w = 0; w < WAYS - 1u; ++w) below[w] = 0;
+    for (uint32_t step = run; step; step >>= 1) {
+#pragma unroll
+        for (uint32_t w = 0; w < WAYS - 1u; ++w) {
+            const uint64_t *other = group + (size_t)((r + 1u + w) & (WAYS - 1u)) * run;
+            const uint32_t probe = below[w] + step;
+            below[w] = probe <= run && other[probe <= run ? probe - 1u : 0u] < key ? probe : below[w];
+        }
     }
-    dst[(size_t)(r & ~1u) * run + own + lo] = key;
+    uint32_t place = i - r * run;
+#pragma unroll
+    for (uint32_t w = 0; w < WAYS - 1u; ++w) place += below[w];
+    dst[(size_t)(r & ~(WAYS - 1u)) * run + place] = key;
 }
 
 __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
@@ -1547,6 +1559,9 @@ __global__ __launch_bounds__(kBookBlock) void k_decode_tables(TablesArgs a) {
     }
     if (tid == 0) { a.t.meta[3] = (uint32_t)radius; a.t.meta[4] = compact ? 1u : 0u; }
 }
+
+template __global__ void k_book_merge<2u>(const uint64_t *, uint64_t *, uint32_t, const Control *);
+template __global__ void k_book_merge<4u>(const uint64_t *, uint64_t *, uint32_t, const Control *);
 
 // The outlier records by a kernel of its own, with the sum of the partial histograms: where no code book is built behind the quantise
 // kernel (a stage call) or the partial histograms are more than its one workgroup should add up.  The first workgroup adds up the counts as well.
