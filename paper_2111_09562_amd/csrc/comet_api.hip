@@ -407,7 +407,9 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
     const size_t tbl_bytes = ((size_t)a.tbl_n + 1u) * 8u;
     a.tbl_room = (uint32_t)((a.tbl_n < nbins && lenw > tbl_bytes ? lenw : tbl_bytes) + 7u) & ~7u;
     const size_t lds_count = (size_t)a.tbl_room + (size_t)seg * 4u;
-    const size_t lds_pack = ((size_t)a.tbl_n + 1u) * 8u + (size_t)(kEncBlock / kWave) * kEncBufWords * 4u;
+    static_assert(kBookBySymbolMax >= kEncPackWindow, "the window lies inside the alphabet");
+    const bool pack_wide = nbins > kBookBySymbolMax && seg >= kEncPackMinChunks;
+    const size_t lds_pack = (pack_wide ? (size_t)kEncPackWindow * 4u : ((size_t)a.tbl_n + 1u) * 8u) + (size_t)((pack_wide ? kEncBlockWide : kEncBlock) / kWave) * kEncBufWords * 4u;
     a.chunk_off = chunk_off; a.container = container; a.capacity = capacity;
     a.payload = payload; a.payload_cap_words = payload_cap; a.payload_words_out = payload_words_out;
     a.desc = desc; a.ctl = &ctx->state->ctl;
@@ -425,8 +427,9 @@ int launch_encode(comet_ctx *ctx, const uint16_t *codes, uint64_t n, uint32_t nb
             else hipLaunchKernelGGL((k_encode_count<S, false, kEncBlock>), dim3(grid), dim3(kEncBlock), lds_count, st, a);        \
         }                                                                                                              \
         TimedScope ts(ctx, st, COMET_KERNEL_ENCODE);                                                                   \
-        if (full) hipLaunchKernelGGL((k_encode_pack<S, true>), dim3(grid), dim3(kEncBlock), lds_pack, st, a);          \
-        else hipLaunchKernelGGL((k_encode_pack<S, false>), dim3(grid), dim3(kEncBlock), lds_pack, st, a);              \
+        if (full) hipLaunchKernelGGL((k_encode_pack<S, true, kEncBlock>), dim3(grid), dim3(kEncBlock), lds_pack, st, a); \
+        else if (pack_wide) hipLaunchKernelGGL((k_encode_pack<S, false, kEncBlockWide>), dim3(grid), dim3(kEncBlockWide), lds_pack, st, a); \
+        else hipLaunchKernelGGL((k_encode_pack<S, false, kEncBlock>), dim3(grid), dim3(kEncBlock), lds_pack, st, a);   \
     } while (0)
     if (chunk_syms == 64u) COMET_LAUNCH_ENC(64);
     else if (chunk_syms == 128u) COMET_LAUNCH_ENC(128);

@@ -40,8 +40,8 @@ struct Control {
     uint32_t max_len;
     uint32_t enc_in_window;  // k_codebook: every symbol with a code word, but for the escape symbol, lies in the part of the encode table the encoders cache in LDS
     uint32_t len_in_window;  // k_codebook: ... in the (wider) part whose lengths the count kernel caches
-    uint32_t outside;        // k_book_sort_tiles: bit 0: a symbol outside the first part occurs, bit 1: outside the second
-    uint32_t pad;
+    uint32_t outside;        // k_book_sort_tiles: bit 0: a symbol outside the first part occurs, bit 1: outside the second, bit 2: outside the third
+    uint32_t pack_in_window; // ... in the part whose entries the pack kernel caches, and no code word is too long for those
 };
 
 // Orders the LDS accesses of the lanes of one wavefront (writes before, reads after).  Only the

@@ -38,6 +38,31 @@ struct TableView {
     }
 };
 
+// The pack kernel's view of a large alphabet: entries of 32 bits, (code << 5) | length, of the symbols [lo, lo + n) in LDS, twice the
+// symbols of the entries above in the same room; a code word of more than 27 bits has kPackLong in the place of its length and
+// is looked up in global memory, as a symbol outside the range is.  ALL: no symbol that occurs needs that, but for the escape
+// symbol 0, whose (64-bit) entry is `escape`.
+constexpr uint32_t kPackLong = 31u;
+__device__ inline uint32_t pack_entry(uint64_t e) {
+    const uint32_t len = (uint32_t)e & 63u;
+    return len <= kPackBits ? (uint32_t)(e >> 6 << 5) | len : kPackLong;
+}
+template <bool ALL>
+struct PackView {
+    const uint32_t *lds;
+    const uint64_t *glob;
+    uint64_t escape;
+    uint32_t lo, n, nbins;
+    __device__ inline uint64_t full(uint32_t code) const {
+        const uint32_t i = code - lo;                 // (a code below lo wraps to a large number)
+        const uint32_t e = i < n ? lds[i] : kPackLong;
+        const uint64_t wide = ((uint64_t)(e >> 5) << 6) | (e & 31u);
+        if (ALL) return i < n ? wide : escape;
+        if ((e & 31u) != kPackLong) return wide;
+        return code < nbins ? glob[code] : 0ull;      // (a code outside the alphabet cannot come from the quantise kernel: no bits)
+    }
+};
+
 // The code lengths alone, one byte each, of the symbols [lo, lo + n) in LDS; behind them the escape symbol's.  For the
 // count kernel when every symbol that occurs lies in that range (Control::len_in_window): eight times the symbols of the
 // encode table's cached part in the same LDS, and no look-up in global memory.

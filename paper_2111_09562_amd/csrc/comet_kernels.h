@@ -187,6 +187,7 @@ template <uint32_t WAYS> __global__ void k_book_merge(const uint64_t *src, uint6
 // ---- encode -------------------------------------------------------------------
 constexpr int kEncBlock = 256;             // four wavefronts, each encodes 256 symbols per step cooperatively
 constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
+constexpr uint32_t kPackBits = 27u;        // longest code word of an entry of 32 bits
 // Code lengths (one byte each) the count kernel caches in LDS instead of part of the encode table, if every symbol that
 // occurs lies among them: 16384 around the centre (the room of the table's cached part).  Above 32768 bins: all of
 // them (64 KB), with twice the wavefronts per workgroup, so that a compute unit holds sixteen of them (two workgroups; a
@@ -196,6 +197,13 @@ constexpr uint32_t kEncTableMax = 2048;    // table entries cached in LDS
 // smoothed at 3.2e-4 the whole compression 1561 -> 1595 us: fewer workgroups per compute unit) and spare one that
 // reaches beyond them the look-ups in global memory (Laplace at 1e-3 2076 -> 1683).
 constexpr int kEncBlockWide = 512;
+// Entries of 32 bits the pack kernel caches in LDS for alphabets beyond kBookBySymbolMax bins, with eight wavefronts per workgroup (the
+// room per wavefront of four wavefronts' 2048 entries of 64 bits): a look-up in global memory costs a cycle per lane.  128 x 64 x 224 x 224
+// Laplace at 1e-3, 65536 bins the whole compression 1660 us -> 1431, 64 x 256 x 56 x 56 at 1e-4 406 -> 391; for segments of fewer than
+// kEncPackMinChunks chunks filling the table costs more than it saves (1 x 64 x 56 x 56 126 -> 136), and where nearly all symbols lie among 2048 entries it
+// is only longer (64 x 256 x 56 x 56, 4096 bins with 4096 such entries 154 -> 164).
+constexpr uint32_t kEncPackWindow = 8192, kEncPackMinChunks = 512;
+static_assert((kEncTableMax + 1u) * 8u <= kEncPackWindow * 4u, "either kind of entries");
 __host__ __device__ inline bool enc_wide(uint32_t nbins) { return nbins > 32768u; }
 __host__ __device__ inline uint32_t enc_len_window(uint32_t nbins) { return nbins <= 16384u || enc_wide(nbins) ? nbins : 16384u; }
 constexpr uint32_t kEncSegChunksMax = 4096;   // chunks per workgroup segment (their word counts live in LDS)
@@ -265,7 +273,7 @@ constexpr uint32_t kEncStepWordsMax = 468; // 256 code words of up to 58 bits, i
 constexpr uint32_t kEncBufWords = 640;     // assembly buffer of a wavefront (ordinary code books fill a fraction of it)
 // S: symbols per chunk (64, 128, 256); FULLTBL: the whole encode table is in LDS
 template <int S, bool FULLTBL, int NT> __global__ void k_encode_count(EncodeArgs a);   // NT threads (kEncBlock, or kEncBlockWide)
-template <int S, bool FULLTBL> __global__ void k_encode_pack(EncodeArgs a);
+template <int S, bool FULLTBL, int NT> __global__ void k_encode_pack(EncodeArgs a);
 
 // ---- decode tables ------------------------------------------------------------
 constexpr int kLutBits = 11;

@@ -968,11 +968,11 @@ __global__ __launch_bounds__(kBookBlock) void k_book_sort_tiles(BookArgs a) {
     const uint32_t win_n = a.nbins < kEncTableMax ? a.nbins : kEncTableMax, win_lo = (a.nbins - win_n) / 2u;
     const uint32_t lenw_n = enc_len_window(a.nbins), lenw_lo = (a.nbins - lenw_n) / 2u;
     const uint32_t cnt = (uint32_t)__syncthreads_count(f != 0u);
-    const bool out1 = __syncthreads_or(f != 0u && s != 0u && s - win_lo >= win_n) != 0, out2 = __syncthreads_or(f != 0u && s != 0u && s - lenw_lo >= lenw_n) != 0;
-    if (threadIdx.x == 0 && cnt) {
-        atomicAdd(&a.ctl->n_active, cnt);
-        if (out1 || out2) atomicOr(&a.ctl->outside, (out1 ? 1u : 0u) | (out2 ? 2u : 0u));
-    }
+    const uint32_t packw_n = kEncPackWindow, packw_lo = (a.nbins - packw_n) / 2u;       // (more bins than that)
+    const uint32_t out = f != 0u && s != 0u ? (s - win_lo >= win_n ? 1u : 0u) | (s - lenw_lo >= lenw_n ? 2u : 0u) | (s - packw_lo >= packw_n ? 4u : 0u) : 0u;
+    const uint64_t out0 = wave_ballot((out & 1u) != 0u), out1 = wave_ballot((out & 2u) != 0u), out2 = wave_ballot((out & 4u) != 0u);
+    if (threadIdx.x == 0 && cnt) atomicAdd(&a.ctl->n_active, cnt);
+    if ((out0 | out1 | out2) != 0ull && lane_id() == 0) atomicOr(&a.ctl->outside, (out0 ? 1u : 0u) | (out1 ? 2u : 0u) | (out2 ? 4u : 0u));
     uint64_t key[1] = {f ? (((uint64_t)f << 16) | s) : ((1ull << 63) | s)};
     block_sort<1>(key, s_x, (uint32_t)kBookBlock);
     a.scratch.keys[s] = key[0];
@@ -1039,6 +1039,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     // LDS?)  Code book reuse: the given length takes the place of the frequency. ----
     const uint32_t win_n = nbins < kEncTableMax ? nbins : kEncTableMax, win_lo = (nbins - win_n) / 2u;
     const uint32_t lenw_n = enc_len_window(nbins), lenw_lo = (nbins - lenw_n) / 2u;
+    const uint32_t packw_n = nbins < kEncPackWindow ? nbins : kEncPackWindow, packw_lo = (nbins - packw_n) / 2u;
     constexpr uint32_t kGroup = 8;
     const uint32_t iters = (nbins + (uint32_t)kBookBlock - 1u) / (uint32_t)kBookBlock;      // steps of 64 symbols per wavefront
     const uint32_t s0 = wave * iters * (uint32_t)kWave;
@@ -1074,7 +1075,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     static_assert(kBookPartsMax <= kGroup * (uint32_t)kBookBlock, "one group");
     uint32_t mine = 0;
     {
-        bool out1 = false, out2 = false;
+        bool out1 = false, out2 = false, out3 = false;
         for (uint32_t g = 0; g < iters; g += kGroup) {
             fetch(g);
 #pragma unroll
@@ -1083,9 +1084,10 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
                 mine += (uint32_t)__popcll(wave_ballot(f[j] != 0u));
                 out1 = out1 || (f[j] != 0u && sy != 0u && sy - win_lo >= win_n);
                 out2 = out2 || (f[j] != 0u && sy != 0u && sy - lenw_lo >= lenw_n);
+                out3 = out3 || (f[j] != 0u && sy != 0u && sy - packw_lo >= packw_n);
             }
         }
-        const uint32_t outside = (wave_ballot(out1) ? 1u : 0u) | (wave_ballot(out2) ? 2u : 0u);
+        const uint32_t outside = (wave_ballot(out1) ? 1u : 0u) | (wave_ballot(out2) ? 2u : 0u) | (wave_ballot(out3) ? 4u : 0u);
         if (lane == 0) {
             s.part[wave] = mine;
             if (outside) atomicOr(&s.word[0], outside);
@@ -1179,6 +1181,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
         a.ctl->n_active = m;
         a.ctl->enc_in_window = (outside & 1) ? 0u : 1u;
         a.ctl->len_in_window = (outside & 2) ? 0u : 1u;
+        a.ctl->pack_in_window = (outside & 4) || large || s.word[2] > kPackBits ? 0u : 1u;
         if (!large || !a.presorted) book_finish(a, m, s.word[2], n_rec, n_vrec, nnz);
     }
 }
@@ -1252,6 +1255,7 @@ __global__ __launch_bounds__(kBookBlock) void k_book_codes(BookArgs a) {
         a.enc[sym] = (code << 6) | (uint64_t)(L & 63u);
         if (a.code_out) a.code_out[sym] = code;
     }
+    if (blockIdx.x == 0 && tid == 0) a.ctl->pack_in_window = (a.ctl->outside & 4u) || s_max > kPackBits ? 0u : 1u;
     if (blockIdx.x == 0 && tid == 0) book_finish(a, m, s_max, a.ctl->n_rec, a.ctl->n_vrec, a.ctl->nnz);
 }
 

@@ -147,23 +147,31 @@ __global__ __launch_bounds__(NT) void k_encode_count(EncodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-template <int S, bool FULLTBL>
-__global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
+template <int S, bool FULLTBL, int NT>
+__global__ __launch_bounds__(NT) void k_encode_pack(EncodeArgs a) {
     constexpr int LPC = S / 4;
     constexpr int CPS = 256 / S;
     extern __shared__ uint64_t s_dyn_enc[];
-    uint64_t *s_tbl = s_dyn_enc;                                                // a.tbl_n entries and a zero entry
-    uint32_t *s_buf = reinterpret_cast<uint32_t *>(s_dyn_enc + a.tbl_n + 1u);   // one assembly buffer per wavefront
-    __shared__ uint64_t s_part64[kEncBlock / kWave];
+    constexpr bool NARROW = NT == kEncBlockWide;                                // a large alphabet: entries of 32 bits
+    uint64_t *s_tbl = s_dyn_enc;                                                // a.tbl_n entries and a zero entry, or kEncPackWindow of 32 bits
+    uint32_t *s_tbl32 = reinterpret_cast<uint32_t *>(s_dyn_enc);
+    uint32_t *s_buf = NARROW ? s_tbl32 + kEncPackWindow : reinterpret_cast<uint32_t *>(s_dyn_enc + a.tbl_n + 1u);   // one assembly buffer per wavefront
+    const uint32_t pack_lo = (a.nbins - kEncPackWindow) / 2u;
+    __shared__ uint64_t s_part64[NT / kWave];
 
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));   // a scalar: what derives from it stays scalar
-    for (uint32_t i = tid; i <= a.tbl_n; i += kEncBlock) s_tbl[i] = (i < a.tbl_n) ? a.enc[a.tbl_lo + i] : (FULLTBL ? 0ull : a.enc[0]);
+    const bool few = !FULLTBL && a.ctl->enc_in_window;       // every symbol that occurs lies among the middle 2048 (the escape symbol apart)
+    if (NARROW && !few) {
+        for (uint32_t i = tid; i < kEncPackWindow; i += NT) s_tbl32[i] = pack_entry(a.enc[pack_lo + i]);
+    } else {
+        for (uint32_t i = tid; i <= a.tbl_n; i += NT) s_tbl[i] = (i < a.tbl_n) ? a.enc[a.tbl_lo + i] : (FULLTBL ? 0ull : a.enc[0]);
+    }
     uint32_t *buf = s_buf + wave * kEncBufWords;
     for (uint32_t i = lane; i < kEncBufWords; i += kWave) buf[i] = 0;
 
-    for (uint32_t i = blockIdx.x * kEncBlock + tid; i < a.clear_n16; i += gridDim.x * kEncBlock) a.clear[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (uint32_t i = blockIdx.x * NT + tid; i < a.clear_n16; i += gridDim.x * NT) a.clear[i] = make_uint4(0u, 0u, 0u, 0u);
 
     uint32_t *payload;
     uint64_t cap_words;
@@ -185,18 +193,18 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
 
     // words of all segments in front of mine
     uint64_t sum = 0;
-    for (uint32_t i0 = 0; i0 < seg; i0 += 8u * kEncBlock) {              // eight loads in flight per thread
+    for (uint32_t i0 = 0; i0 < seg; i0 += 8u * NT) {              // eight loads in flight per thread
         uint64_t v[8];
 #pragma unroll
         for (uint32_t j = 0; j < 8; ++j) {
-            const uint32_t idx = i0 + j * kEncBlock + tid;
+            const uint32_t idx = i0 + j * NT + tid;
             v[j] = (idx < seg) ? a.desc[idx] : 0ull;
         }
 #pragma unroll
         for (uint32_t j = 0; j < 8; ++j) sum += v[j];
     }
     uint64_t base;
-    (void)block_excl_scan<uint64_t, kEncBlock / kWave>(sum, s_part64, base);
+    (void)block_excl_scan<uint64_t, NT / kWave>(sum, s_part64, base);
     bool overflow = false;
     if (seg + 1u == gridDim.x && tid == 0) {
         const uint64_t pw = base + a.desc[seg];
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
         }
         wave_lds_fence();
     };
-    constexpr uint32_t kStride = (kEncBlock / kWave) * kEncUnroll;
+    constexpr uint32_t kStride = (NT / kWave) * kEncUnroll;
     // The loop over the steps, once per way of looking a code up (the choice is the same for every thread), and once
     // more for the tensor's last segment: everywhere else every step has its 256 symbols, and the loop tests nothing.
     auto sweep = [&](auto tbl, auto tail_tag) {
@@ -325,13 +333,16 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_pack(EncodeArgs a) {
     auto sweep_with = [&](auto tbl) {
         if (whole) sweep(tbl, std::false_type{}); else sweep(tbl, std::true_type{});
     };
-    if (FULLTBL) sweep_with(TableView<1>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
-    else if (a.ctl->enc_in_window) sweep_with(TableView<2>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
-    else sweep_with(TableView<0>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
+    if constexpr (FULLTBL) sweep_with(TableView<1>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
+    else if (few) sweep_with(TableView<2>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
+    else if constexpr (NARROW) {
+        if (a.ctl->pack_in_window) sweep_with(PackView<true>{s_tbl32, a.enc, a.enc[0], pack_lo, kEncPackWindow, a.nbins});
+        else sweep_with(PackView<false>{s_tbl32, a.enc, 0ull, pack_lo, kEncPackWindow, a.nbins});
+    } else sweep_with(TableView<0>{s_tbl, a.enc, a.tbl_lo, a.tbl_n, a.nbins});
     // chunk offsets become absolute (every wavefront has consumed the relative ones of its steps
     // only after this barrier)
     __syncthreads();
-    for (uint32_t idx = tid; idx < nc; idx += kEncBlock) a.chunk_off[c_lo + idx] = (uint32_t)(base + a.chunk_off[c_lo + idx]);
+    for (uint32_t idx = tid; idx < nc; idx += NT) a.chunk_off[c_lo + idx] = (uint32_t)(base + a.chunk_off[c_lo + idx]);
     if (overflow) atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
 
 }
@@ -439,8 +450,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     template __global__ void k_encode_count<S, true, kEncBlock>(EncodeArgs);    \
     template __global__ void k_encode_count<S, false, kEncBlock>(EncodeArgs);   \
     template __global__ void k_encode_count<S, false, kEncBlockWide>(EncodeArgs); \
-    template __global__ void k_encode_pack<S, true>(EncodeArgs);           \
-    template __global__ void k_encode_pack<S, false>(EncodeArgs);
+    template __global__ void k_encode_pack<S, true, kEncBlock>(EncodeArgs);     \
+    template __global__ void k_encode_pack<S, false, kEncBlock>(EncodeArgs);    \
+    template __global__ void k_encode_pack<S, false, kEncBlockWide>(EncodeArgs);
 COMET_INST_ENC(64)
 COMET_INST_ENC(128)
 COMET_INST_ENC(256)

@@ -1,0 +1,64 @@
+"""The pack kernel of large alphabets on large tensors (entries of 32 bits in LDS): code words too long for those, symbols at the edges
+of the cached range and outside it, the escape symbol, every symbol inside.  Bit-exact against the CPU oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+N = 64 * 512 * 1536 + 64 * 4 + 37                         # segments of just over 512 chunks on 256 compute units, the last chunk short
+
+
+@pytest.mark.parametrize("nbins", [8194, 65536])
+def test_codes_of_every_length(oracle, nbins):
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(nbins)
+    lo = (nbins - 8192) // 2
+    edge = np.array([0, 1, lo - 1, lo, lo + 8191, lo + 8192, nbins - 1]) % nbins
+    syms = np.unique(np.concatenate([edge, rng.choice(nbins, 60, replace=False)]))
+    rng.shuffle(syms)
+    w = 0.6 ** np.arange(syms.size)                       # lengths 1, 2, 3, ... for as long as the counts last
+    codes = syms[np.searchsorted(np.cumsum(w / w.sum()), rng.random(N), side="right").clip(0, syms.size - 1)].astype(np.uint16)
+    at = rng.choice(N, 40 * syms.size, replace=False)     # every symbol occurs
+    codes[at] = np.tile(syms, 40).astype(np.uint16)
+    hist = oracle.histogram(codes, nbins).astype(np.uint64)
+    fib = [1, 1]
+    while len(fib) < 44:
+        fib.append(fib[-1] + fib[-2])
+    deep = np.zeros(nbins, np.uint32)                     # a code book of its own: a chain of lengths up to 43
+    deep[syms[:44]] = np.array(fib, np.uint32)[::-1]
+    deep[syms[44:]] = 1 << 20
+    for h in (hist.astype(np.uint32), deep):
+        ln = oracle.code_lengths(h)
+        assert h is not deep or ln.max() > 31
+        want_off, want_payload = oracle.encode(codes, nbins, 64, ln, oracle.canonical_codes(ln))
+        lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+        off = torch.empty((N + 63) // 64, dtype=torch.int32, device="cuda")
+        payload = torch.zeros(want_payload.size + 16, dtype=torch.int32, device="cuda")
+        pw = torch.zeros(1, dtype=torch.int64, device="cuda")
+        big = comet.Context(N, 65536)
+        big.comet_stage_codebook(torch.from_numpy(h.view(np.int32)).cuda(), nbins, lens)
+        big.comet_stage_encode(torch.from_numpy(codes.view(np.int16)).cuda(), N, nbins, 64, off, payload, pw)
+        big.comet_sync()
+        assert int(pw.item()) == want_payload.size
+        assert np.array_equal(off.cpu().numpy().view(np.uint32), want_off)
+        assert np.array_equal(payload.cpu().numpy().view(np.uint32)[:want_payload.size], want_payload)
+        big.close()
+
+
+@pytest.mark.parametrize("scale", [0.2, 1.9, 2.4])
+def test_symbols_inside_and_outside_the_range(oracle, scale):
+    """Residuals within 1000 (the middle 2048 entries), within 4000 (the 8192 of the pack kernel) and beyond, with a few escapes."""
+    from paper_2111_09562_amd import comet
+    shape, eb, nbins = (3, 256, 257, 256), 1e-3, 65536
+    rng = np.random.default_rng(1)
+    x = (rng.random(shape, dtype=np.float32) * np.float32(scale))
+    x[:, 1::2, :, :] *= np.float32(0.3)
+    x.reshape(-1)[rng.choice(x.size, 500, replace=False)] = 1000.0
+    want = oracle.compress(x, eb, nbins, 64)
+    ctx = comet.Context(x.size, nbins)
+    ctx.comet_set_chunk_syms(64)
+    box = torch.zeros(want.size + (-want.size) % 16 + 4096, dtype=torch.uint8, device="cuda")
+    assert ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, box) == want.size
+    assert np.array_equal(box[:want.size].cpu().numpy(), want)
+    ctx.close()
