@@ -87,9 +87,7 @@ struct comet_ctx {
     DevState *host_state = nullptr;
     Header *host_hdr = nullptr;
     CallResult *host_result = nullptr;              // written by the kernel that seals a container's header
-    // occupancy (workgroups per CU) measured once
     double *stats = nullptr;      // kStatsPartialMax partial sums and, behind them, the mean
-    int occ_quant = 1;
     // optional per-kernel timing
     struct Timed { uint32_t id; hipEvent_t a, b; };
     bool profiling = false;
@@ -102,11 +100,12 @@ namespace {
 constexpr uint64_t kPartsBytes = 4ull * kQuantHistPartsWords + 256u;
 
 struct ZeroLayout {          // sub-allocation of the zero region for one call
-    uint64_t off_hist, off_desc_q, off_desc_e, bytes;
+    uint64_t off_hist, off_desc_e, bytes;
 };
 
 // Does the row-walking quantise kernel count its codes (what it can of them, for an alphabet larger than its window)?
-bool quantize_counts(uint64_t n, uint32_t nbins) { return nbins <= kHistWindowMax || n >= kQuantCountMin; }
+// (Planes wider than kQuantRowsMaxW: all of them.)
+bool quantize_counts(uint64_t n, uint32_t w, uint32_t nbins) { return nbins <= kHistWindowMax || n >= kQuantCountMin || w > kQuantRowsMaxW; }
 
 // partial histograms of the row-walking quantise kernel for an alphabet of nbins
 uint32_t hist_copies(uint32_t nbins) {
@@ -116,10 +115,9 @@ uint32_t hist_copies(uint32_t nbins) {
 }
 
 // nbins_hist: entries of the histogram itself (0 if the caller brings its own)
-ZeroLayout zero_layout(uint32_t nbins_hist, uint64_t tiles_q, uint64_t tiles_e) {
+ZeroLayout zero_layout(uint32_t nbins_hist, uint64_t tiles_e) {
     ZeroLayout z;
     uint64_t o = align_up(sizeof(Control), 256);
-    z.off_desc_q = o; o += align_up(8 * tiles_q, 256);
     z.off_desc_e = o; o += align_up(8 * tiles_e, 256);
     z.off_hist = o; o += align_up(4ull * nbins_hist, 256);
     z.bytes = o;
@@ -135,9 +133,9 @@ int status_to_error(uint32_t st) {
 }
 
 // Clears the zero region of a call (control block, descriptors, histograms): a plain kernel rather than a memset
-// node for callers that capture the call in a graph.  n16: 16-byte words.  The row-walking path does without: its first kernel
+// node for callers that capture the call in a graph.  n16: 16-byte words.  A compression does without: its first kernel
 // clears the control block, and its last one leaves the partial histograms zero for the next call (a launch of its
-// own in front of the first one cost every compression 3 us).
+// own in front of the first one cost every call 3 us).
 __global__ __launch_bounds__(256) void k_clear(uint4 *p, uint32_t n16) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i < n16) p[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -189,12 +187,10 @@ bool recon_geometry(comet_shape s, ReconGeometry *g) {
 int fused_opt_in();          // k_decode_scan: opt in to its dynamic LDS size (defined with the decompression)
 // segments of the encode kernel: (chunks per segment, number of segments)
 void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t nbins, uint32_t *seg_chunks, uint32_t *n_seg);
-// Work split of the quantise kernel.  rows: the row-walking kernel (planes up to kQuantRowsMaxW
-// columns) with `grid` workgroups of four wavefronts, each wavefront on rows_per_wave consecutive
-// rows; otherwise the flat-tile kernel with `grid` segments of tiles.
+// Work split of the quantise kernel: `grid` workgroups of four wavefronts, each wavefront on rows_per_wave consecutive rows.
 // vec: columns per lane of the row-walking kernel (2 if W is even and the input is 8-byte aligned).
 // chunk_align: if not 0, every run is a whole number of chunks of that many symbols (single-pass compression).
-struct QuantGeom { bool rows; uint32_t grid, rows_per_wave, rows_per_step, vec; };
+struct QuantGeom { uint32_t grid, run_elems, rows_per_wave, rows_per_step, vec; };
 // nbins: the alphabet (its histogram window decides how many workgroups a compute unit holds at once).
 QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, const void *x, uint32_t nbins, uint32_t elem_bytes = 4, uint32_t chunk_align = 0);
 
@@ -207,15 +203,15 @@ struct SinglePass {
     uint32_t *work_words;      // n / 2 words
 };
 
-// recs: receives what the kernels behind this one need to place the outlier records (n_wg == 0: they are in place already)
-// reset_ctl: the kernel clears the call's control block (row-walking kernel, no reuse)
+// recs: receives what the kernels behind this one need to place the outlier records
+// reset_ctl: the kernel clears the call's control block (no reuse)
 // reuse_len: code book reuse (device u8[nbins], row-walking kernel only, with sp); else null
 // in_type: element type of x (0 fp32, COMET_F16, COMET_BF16; the 16-bit types: row-walking kernel only, no reuse)
 int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, float eb, uint32_t nbins,
-                    hipStream_t st, uint16_t *codes, uint32_t *hist, uint32_t *hist_parts, uint32_t *rec, uint64_t rec_cap,
-                    uint64_t *desc, RecordArgs *recs, bool reset_ctl, const uint8_t *reuse_len = nullptr, int in_type = 0, const SinglePass *sp = nullptr) {
+                    hipStream_t st, uint16_t *codes, uint32_t *hist_parts, uint32_t *rec, uint64_t rec_cap,
+                    RecordArgs *recs, bool reset_ctl, const uint8_t *reuse_len = nullptr, int in_type = 0, const SinglePass *sp = nullptr) {
     if (in_type != 0 && (reuse_len || s.w > kQuantRowsMaxW)) return COMET_ERR_INVALID;
-    if ((reuse_len != nullptr) != (sp != nullptr)) return COMET_ERR_INVALID;
+    if ((reuse_len != nullptr) != (sp != nullptr) || (reuse_len && s.w > kQuantRowsMaxW)) return COMET_ERR_INVALID;
     QuantArgs a{};
     a.x = x; a.n = n;
     a.divW = make_fastdiv(s.w); a.divH = make_fastdiv(s.h);
@@ -223,18 +219,17 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
     a.radius = (int32_t)(nbins / 2u); a.nbins = nbins;
     a.win_n = nbins < kHistWindowMax ? nbins : kHistWindowMax;
     a.win_lo = (nbins - a.win_n) / 2u;
-    a.n_tiles = (uint32_t)((n + kQuantTile - 1) / kQuantTile);
-    a.codes = codes; a.hist = hist; a.rec = rec; a.rec_cap = rec_cap; a.desc = desc; a.ctl = &ctx->state->ctl;
+    a.codes = codes; a.ctl = &ctx->state->ctl;
     const QuantGeom g = quantize_geometry(ctx, s, n, x, nbins, in_type ? 2u : 4u, sp ? sp->chunk_syms : 0u);
     const uint32_t grid = g.grid;
-    if (g.rows) {
+    {
         a.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h);
         a.rows_per_wave = g.rows_per_wave;
         a.rows_per_step = g.rows_per_step;
         if ((uint64_t)grid * (kQuantBlock / kWave) > ctx->max_runs) return COMET_ERR_INTERNAL;
         a.stage = ctx->rec_stage;
         {
-            const uint64_t room = ctx->stage_bytes / 8u / ((uint64_t)grid * kQuantWaves), most = 2ull * g.rows_per_wave * s.w;    // (two records per element at most)
+            const uint64_t room = ctx->stage_bytes / 8u / ((uint64_t)grid * kQuantWaves), most = 2ull * g.run_elems;    // (two records per element at most)
             a.rec_run = (uint32_t)(room < most ? room : most);
         }
         a.run_count = ctx->run_count;
@@ -242,23 +237,23 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         a.hist_copies = hist_copies(nbins);
         a.hist_shift = a.win_n <= 2048u ? 2u : 0u;            // four copies while they fit 32 KB
         const bool full = a.win_n == nbins;
-        const bool counts = quantize_counts(n, nbins);
+        const bool counts = quantize_counts(n, s.w, nbins);
         const size_t lds = counts ? (((size_t)a.win_n << a.hist_shift) + kQuantBlock) * 4u + (full ? 0u : (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u) : 0u;
         a.run_from = ctx->run_count + 3u * ctx->max_runs;
         a.reset_ctl = reset_ctl ? 1u : 0u;
         RecordArgs &ra = *recs;
         ra.x = x; ra.in_type = (uint32_t)in_type; ra.divW = a.divW; ra.divH = a.divH; ra.r = a.r; ra.ebx2 = a.ebx2; ra.eb = eb;
-        ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.rows_total = a.rows_total; ra.rows_per_wave = a.rows_per_wave;
+        ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.n = n; ra.run_elems = a.run_elems = g.run_elems;
         ra.n_wg = grid; ra.stage = ctx->rec_stage; ra.rec_run = a.rec_run; ra.run_count = ctx->run_count; ra.rec = rec; ra.rec_cap = rec_cap; ra.ctl = a.ctl;
         // (an alphabet larger than the window: what the sweep does not count is counted from memory, behind it)
         auto count_codes = [&]() {
-            if (full || reuse_len) return;
+            if (full || reuse_len || s.w > kQuantRowsMaxW) return;
             CodeHistArgs h{};
             h.codes = codes; h.n = n; h.nbins = nbins; h.radius = nbins / 2u;
             h.win_n = nbins < kCodeHistWindow ? nbins : kCodeHistWindow;
             h.win_lo = (nbins - h.win_n) / 2u;
             h.run_from = a.run_from;
-            h.divRun = make_fastdiv(g.rows_per_wave * s.w);
+            h.divRun = make_fastdiv(g.run_elems);
             h.parts = hist_parts; h.copies = a.hist_copies;
             // one workgroup per compute unit, with at least 8192 codes (clearing and adding up its bins costs as much as those);
             // runs have 2048 codes or more and are at most 4 * kQuantRunsPerSimd per compute unit, so a slice sees fewer than kCodeHistRuns
@@ -305,7 +300,14 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
                          (size_t)(kQuantBlock / kWave) * ((kEncRingSyms + 4u) * 2u + kEncRunBufWords * 4u);
         }
         const uint32_t lanes_per_row = s.w / g.vec;
-        if (g.vec == 2u) {
+        if (s.w > kQuantRowsMaxW) {
+            TimedScope ts(ctx, st, COMET_KERNEL_QUANTIZE);
+            const dim3 gr(grid), bl(kQuantBlock);
+            if (g.vec == 2u && full) hipLaunchKernelGGL((k_quantize_rows<2, 0, false, kHistFull, false, 0>), gr, bl, lds, st, a);
+            else if (g.vec == 2u) hipLaunchKernelGGL((k_quantize_rows<2, 0, false, kHistPart, false, 0>), gr, bl, lds, st, a);
+            else if (full) hipLaunchKernelGGL((k_quantize_rows<1, 0, false, kHistFull, false, 0>), gr, bl, lds, st, a);
+            else hipLaunchKernelGGL((k_quantize_rows<1, 0, false, kHistPart, false, 0>), gr, bl, lds, st, a);
+        } else if (g.vec == 2u) {
             if (lanes_per_row <= 32u) COMET_LAUNCH_QR(2, 1, true);
             else if (lanes_per_row <= 64u) COMET_LAUNCH_QR(2, 1, false);
             else if (lanes_per_row <= 128u) COMET_LAUNCH_QR(2, 2, false);
@@ -319,15 +321,6 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         }
 #undef COMET_LAUNCH_QR
 #undef COMET_LAUNCH_QR_IN
-    } else {
-        if (reuse_len || reset_ctl) return COMET_ERR_INVALID;          // the flat-tile kernel has no code book reuse
-        // one segment of consecutive tiles per workgroup, about as many workgroups as fit the chip at once
-        a.tiles_per_seg = (a.n_tiles + grid - 1) / grid;
-        a.rec_lds = kQuantRecLds;
-        const size_t lds = (size_t)a.win_n * 4u + (size_t)kQuantRecLds * 8u;
-        TimedScope ts(ctx, st, COMET_KERNEL_QUANTIZE);
-        if (a.win_n == nbins) hipLaunchKernelGGL(k_quantize<true>, dim3(grid), dim3(kQuantBlock), lds, st, a);
-        else hipLaunchKernelGGL(k_quantize<false>, dim3(grid), dim3(kQuantBlock), lds, st, a);
     }
     HIP_TRY(hipGetLastError());
     return COMET_OK;
@@ -454,8 +447,7 @@ void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t nbins, ui
 QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, const void *x, uint32_t nbins, uint32_t elem_bytes, uint32_t chunk_align) {
     QuantGeom g{};
     g.vec = 1;
-    if (s.w <= kQuantRowsMaxW) {
-        g.rows = true;
+    {
         const uint64_t rows_total = (uint64_t)s.n * s.c * s.h;
         // two columns per lane: every row then starts at an even element, so pairs are aligned to their size
         if ((s.w & 1u) == 0u && ((uintptr_t)x & (2u * elem_bytes - 1u)) == 0u) g.vec = 2;
@@ -480,13 +472,23 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
             const uint32_t win_n = nbins < kHistWindowMax ? nbins : kHistWindowMax;
             const size_t window = (((size_t)win_n << (win_n <= 2048u ? 2u : 0u)) + kQuantBlock) * 4u +
                                   (win_n < nbins ? (size_t)(kQuantBlock / kWave) * kQuantOowList * 2u : 0u);
-            const size_t lds = (quantize_counts(n, nbins) ? window : 0u) + kQuantStaticLds;
+            const size_t lds = (quantize_counts(n, s.w, nbins) ? window : 0u) + kQuantStaticLds;
             const uint32_t fit = (uint32_t)(kLdsPerCu / lds);
             if (fit < runs_per_simd) runs_per_simd = fit ? fit : 1u;
         }
         const uint64_t want = (uint64_t)ctx->num_cu * 4u * runs_per_simd;
-        uint64_t per = (rows_total + want - 1) / want;
         const uint64_t share = n / ((uint64_t)ctx->num_cu * 4u), least = share < 512u ? 512u : (share < 2048u ? share : 2048u);
+        if (s.w > kQuantRowsMaxW) {
+            // wide planes: whole rows, or less than half a row, in multiples of a batch of steps
+            uint64_t per = (n + want - 1) / want;
+            if (per < least) per = least;
+            per = 2u * per < s.w ? (per + 255u) / 256u * 256u : (per + s.w - 1u) / s.w * s.w;
+            const uint64_t waves = (n + per - 1) / per;
+            g.run_elems = (uint32_t)per;
+            g.grid = (uint32_t)((waves + kQuantWaves - 1u) / kQuantWaves);
+            return g;
+        }
+        uint64_t per = (rows_total + want - 1) / want;
         const uint64_t min_rows = (least + s.w - 1u) / s.w;
         if (per < min_rows) per = min_rows;
         per = (per + unit - 1) / unit * unit;
@@ -495,15 +497,10 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
         // the run count is in the thousands unless the tensor itself is small
         const uint64_t waves = (rows_total + per - 1) / per;
         g.rows_per_wave = (uint32_t)per;
+        g.run_elems = (uint32_t)(per * s.w);
         g.grid = (uint32_t)((waves + (kQuantBlock / kWave) - 1) / (kQuantBlock / kWave));
         return g;
     }
-    const uint64_t n_tiles = (n + kQuantTile - 1) / kQuantTile;
-    uint64_t grid = (uint64_t)ctx->num_cu * (uint64_t)ctx->occ_quant;
-    if (grid > n_tiles) grid = n_tiles;
-    const uint64_t per = (n_tiles + grid - 1) / grid;
-    g.grid = (uint32_t)((n_tiles + per - 1) / per);
-    return g;
 }
 
 }  // namespace
@@ -525,9 +522,8 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
 
     // scan descriptors: one per segment of the quantise / encode kernels (worst case over chunk sizes)
-    const uint64_t tiles_q = (uint64_t)c->num_cu * 16u + 16u;
     const uint64_t tiles_e = (uint64_t)c->num_cu * 8u + max_elems / 64u / kEncSegChunksWide + 16u;
-    const ZeroLayout z = zero_layout(kMaxBins, tiles_q, tiles_e);
+    const ZeroLayout z = zero_layout(kMaxBins, tiles_e);
     c->zero_cap = z.bytes;
     const uint64_t parts_at = align_up(offsetof(DevState, ctl) + z.bytes, 256);
     const uint64_t state_bytes = parts_at + kPartsBytes;     // the partial histograms behind it: 2 MB
@@ -596,7 +592,6 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     for (const void *fn : {(const void *)k_code_hist<true>, (const void *)k_code_hist<false>})
         if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)((kCodeHistWindow + 4u * kCodeHistHot + kCodeHistBlock) * 4u))) != hipSuccess)
             return fail(hip_fail(e, "hipFuncSetAttribute(k_code_hist)"));
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->occ_quant, k_quantize<true>, kQuantBlock, 4096 + kQuantRecLds * 8) != hipSuccess || c->occ_quant < 1) c->occ_quant = 4;
     (void)rc;
     *out = c;
     return COMET_OK;
@@ -676,7 +671,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     uint32_t e_seg, e_grid;
     encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
     const QuantGeom qg = quantize_geometry(ctx, s, n, dev_in, nbins, in_type ? 2u : 4u, dev_len ? S : 0u);
-    const uint64_t tiles_q = qg.grid, tiles_e = e_grid;
+    const uint64_t tiles_e = e_grid;
 
     Header proto{};
     proto.magic = kMagic; proto.version = ctx->zero_chunks ? 2u : 1u; proto.N = s.n; proto.C = s.c; proto.H = s.h; proto.W = s.w;
@@ -689,16 +684,10 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
     proto.off_outlier = align16(proto.off_chunk + 4 * n_chunks);
     if (proto.off_outlier > capacity) return COMET_ERR_CAPACITY;
 
-    const ZeroLayout z = zero_layout(nbins, tiles_q, tiles_e);
+    const ZeroLayout z = zero_layout(nbins, tiles_e);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
-    if (!qg.rows) {                                          // (flat tiles count in places that start at zero)
-        const uint32_t n16 = (uint32_t)(z.bytes / 16u);      // the layout is made of 256-byte pieces
-        hipLaunchKernelGGL(k_clear, dim3((n16 + 255u) / 256u), dim3(256), 0, st, reinterpret_cast<uint4 *>(ctx->zero_region), n16);
-        HIP_TRY(hipGetLastError());
-    }
-    const bool parts = qg.rows && !dev_len;                  // this call adds to the partial histograms
+    const bool parts = !dev_len;                             // this call adds to the partial histograms
     uint32_t *hist = reinterpret_cast<uint32_t *>(ctx->zero_region + z.off_hist);
-    uint64_t *desc_q = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_q);
     uint64_t *desc_e = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_e);
     uint8_t *out = static_cast<uint8_t *>(dev_out);
 
@@ -722,7 +711,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         sp.chunk_off = chunk_off;
         sp.run_words = ctx->run_count + 3u * ctx->max_runs;
         sp.work_words = reinterpret_cast<uint32_t *>(ctx->codes);
-        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, hist, nullptr, rec, rec_cap, desc_q, &recs, false, dev_len, 0, &sp))) return rc;
+        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, nullptr, rec, rec_cap, &recs, false, dev_len, 0, &sp))) return rc;
         PlaceArgs p{};
         p.run_words = sp.run_words;
         p.rows_per_wave = qg.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
@@ -736,7 +725,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         HIP_TRY(hipGetLastError());
     } else {
         if (parts && (rc = clean_parts(ctx, st))) return rc;
-        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, ctx->codes, hist, ctx->hist_parts, rec, rec_cap, desc_q, &recs, qg.rows, nullptr, in_type))) return rc;
+        if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, ctx->codes, ctx->hist_parts, rec, rec_cap, &recs, true, nullptr, in_type))) return rc;
         if (parts && nbins > kBookPartsMax && nbins <= kBookBySymbolMax) {
             if ((rc = launch_gather(ctx, recs, st, hist, ctx->hist_parts))) return rc;
         } else {
@@ -1244,18 +1233,16 @@ int comet_stage_quantize(comet_ctx *ctx, const float *dev_in, comet_shape s, flo
         ((uintptr_t)dev_codes & 7u) || ((uintptr_t)dev_records & 7u)) return COMET_ERR_INVALID;
     if (n > ctx->max_elems) return COMET_ERR_NOMEM;
     hipStream_t st = (hipStream_t)stream;
-    const uint64_t tiles_q = quantize_geometry(ctx, s, n, dev_in, nbins).grid;
-    const ZeroLayout z = zero_layout(0, tiles_q, 1);
+    const ZeroLayout z = zero_layout(0, 1);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
     HIP_TRY(hipMemsetAsync(ctx->zero_region, 0, z.bytes, st));
     HIP_TRY(hipMemsetAsync(dev_hist, 0, 4ull * nbins, st));
-    uint64_t *desc_q = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_q);
     RecordArgs recs{};
     int rc;
     if ((rc = clean_parts(ctx, st))) return rc;
-    rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, dev_codes, dev_hist, ctx->hist_parts, dev_records, rec_capacity, desc_q, &recs, false);
+    rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, dev_codes, ctx->hist_parts, dev_records, rec_capacity, &recs, false);
     if (rc) return rc;
-    if (recs.n_wg && (rc = launch_gather(ctx, recs, st, dev_hist, ctx->hist_parts))) return rc;
+    if ((rc = launch_gather(ctx, recs, st, dev_hist, ctx->hist_parts))) return rc;
     if ((rc = clean_parts(ctx, st))) return rc;              // (at once, not in the next call: that one may have been captured in a graph already)
     ctx->parts_clean = true;
     HIP_TRY(hipMemcpyAsync(dev_counts, &ctx->state->ctl.n_rec, 24, hipMemcpyDeviceToDevice, st));
@@ -1287,7 +1274,7 @@ int comet_stage_encode(comet_ctx *ctx, const uint16_t *dev_codes, uint64_t n, ui
     uint32_t e_seg, e_grid;
     encode_geometry(ctx, n_chunks, nbins, &e_seg, &e_grid);
     const uint64_t tiles_e = e_grid;
-    const ZeroLayout z = zero_layout(0, 1, tiles_e);
+    const ZeroLayout z = zero_layout(0, tiles_e);
     if (z.bytes > ctx->zero_cap) return COMET_ERR_NOMEM;
     HIP_TRY(hipMemsetAsync(ctx->zero_region, 0, z.bytes, st));
     uint64_t *desc_e = reinterpret_cast<uint64_t *>(ctx->zero_region + z.off_desc_e);

@@ -1,6 +1,5 @@
 // Shared device-side definitions of libcomet: container header, per-call control
-// block, wavefront/block scans and the single-pass chained scan used to place
-// variable-size output (outlier records, Huffman words) deterministically.
+// block, wavefront/block scans.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -23,13 +22,10 @@ struct Header {
 };
 static_assert(sizeof(Header) == kHeaderBytes, "header layout");
 
-// Per-call control block in the workspace; zeroed (with the histogram and the
-// scan descriptors that follow it) by one memset before every call.
+// Per-call control block in the workspace; zeroed by the first kernel of every call.
 struct Control {
-    uint32_t ticket_q;      // next tile of the quantise kernel
-    uint32_t ticket_e;      // next tile of the encode kernel
-    uint32_t done_e;        // encode workgroups that have finished
     uint32_t status;        // ST_* bits of this call
+    uint32_t pad;
     uint64_t n_rec;         // all outlier records
     uint64_t n_vrec;        // verbatim (type 1) records
     uint64_t nnz;           // non-zero inputs
@@ -127,65 +123,6 @@ __device__ inline T block_excl_scan(T v, T *s_part, T &total) {
     __syncthreads();
     total = tot;
     return off + incl - v;
-}
-
-// ---------------------------------------------------------------------------
-// Chained scan (single pass, decoupled look-back) over tiles taken in ticket
-// order.  One 64-bit descriptor per tile: the top two bits say whether the low
-// 62 bits hold nothing yet (0), the tile's own aggregate (1) or the inclusive
-// prefix up to and including the tile (2).  A tile only ever waits for tiles
-// with smaller tickets, and a ticket is taken before its tile is touched, so
-// the tile with the smallest unfinished ticket is always running: every wait
-// ends.  The whole state of a tile is one word, so relaxed agent-scope atomics
-// are enough.  Must be called by all 64 lanes of one wavefront; returns the
-// exclusive prefix of `tile`.  A bounded spin turns a broken invariant into an
-// error flag instead of a hang.
-// ---------------------------------------------------------------------------
-constexpr uint64_t kDescAgg = 1ull << 62;
-constexpr uint64_t kDescIncl = 2ull << 62;
-constexpr uint64_t kDescMask = (1ull << 62) - 1ull;
-
-__device__ inline uint64_t desc_load(const uint64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline void desc_store(uint64_t *p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ inline uint64_t chained_scan_wave(uint64_t *desc, uint32_t tile, uint64_t aggregate, uint32_t *status) {
-    const int lane = lane_id();
-    if (tile == 0) {
-        if (lane == 0) desc_store(&desc[0], kDescIncl | aggregate);
-        return 0;
-    }
-    if (lane == 0) desc_store(&desc[tile], kDescAgg | aggregate);
-    uint64_t excl = 0;
-    int64_t window_end = (int64_t)tile - 1;
-    bool failed = false;
-    while (true) {
-        const int64_t idx = window_end - lane;
-        uint64_t v = kDescIncl;            // virtual tiles before tile 0: inclusive prefix 0
-        if (idx >= 0) {
-            uint32_t spins = 0;
-            do {
-                v = desc_load(&desc[idx]);
-                if ((v >> 62) != 0) break;
-                __builtin_amdgcn_s_sleep(1);
-            } while (++spins < (1u << 22));
-            if ((v >> 62) == 0) { failed = true; v = kDescIncl; }
-        }
-        const uint64_t incl_mask = __ballot((v >> 62) == 2);
-        if (incl_mask) {
-            const int first = __ffsll((unsigned long long)incl_mask) - 1;
-            excl += wave_sum<uint64_t>(lane <= first ? (v & kDescMask) : 0ull);
-            break;
-        }
-        excl += wave_sum<uint64_t>(v & kDescMask);
-        window_end -= kWave;
-    }
-    if (__ballot(failed) && lane == 0) atomicOr(status, (uint32_t)ST_INTERNAL);
-    if (lane == 0) desc_store(&desc[tile], kDescIncl | ((excl + aggregate) & kDescMask));
-    return excl;
 }
 
 }  // namespace comet

@@ -9,7 +9,6 @@ namespace comet {
 // ---- quantise (prequantise + Lorenzo + codes + histogram + records) ----------
 constexpr int kQuantBlock = 256;
 constexpr uint32_t kQuantWaves = (uint32_t)(kQuantBlock / kWave);   // runs per workgroup of the row-walking kernel
-constexpr int kQuantTile = 4096;           // elements per tile: 256 lanes x 4 iterations x float4
 constexpr uint32_t kHistWindowMax = 8192;  // LDS-private histogram bins per workgroup
 
 struct QuantArgs {
@@ -20,11 +19,9 @@ struct QuantArgs {
     int32_t radius;
     uint32_t nbins;
     uint32_t win_lo, win_n;    // histogram bins [win_lo, win_lo + win_n) are counted in LDS
-    uint32_t n_tiles;
-    uint32_t tiles_per_seg;    // consecutive tiles per workgroup (one segment each)
-    uint32_t rec_lds;          // records the LDS buffer of a workgroup can hold
-    uint32_t rows_total;       // row-walking kernel: planes * H rows of W elements
+    uint32_t rows_total;       // planes * H rows of W elements
     uint32_t rows_per_wave;    //   consecutive rows per wavefront (a multiple of rows_per_step)
+    uint32_t run_elems;        //   elements per run: rows_per_wave * W, or, for planes wider than kQuantRowsMaxW, what their runs hold
     uint32_t rows_per_step;    //   rows a wavefront covers per step (64 / lanes per row if a row takes at most 32 lanes, else 1)
     uint32_t hist_shift;       //   log2 of the copies of the LDS histogram window (lane & (copies - 1) picks one)
     uint32_t *stage;           //   staging area: rec_run (key, payload) pairs per run
@@ -44,10 +41,6 @@ struct QuantArgs {
     uint32_t *run_from;        // kHistPart: element of every run from which on k_code_hist counts its codes
     uint32_t *work_words;      //   work area: the words of the run that starts at element e at word e / 2
     uint16_t *codes;
-    uint32_t *hist;            // flat tiles: u32[nbins], zeroed
-    uint32_t *rec;             // flat tiles: (key, payload) pairs
-    uint64_t rec_cap;          // capacity in records
-    uint64_t *desc;            // chained-scan descriptors, one per segment, zeroed
     Control *ctl;
 };
 
@@ -60,7 +53,8 @@ struct RecordArgs {
     int32_t radius;
     uint32_t nbins;
     const uint8_t *reuse_len;  // code book reuse: the given lengths, or null
-    uint32_t rows_total, rows_per_wave;
+    uint64_t n;
+    uint32_t run_elems;        // elements per run
     uint32_t n_wg;             // workgroups of the quantise kernel (kQuantWaves runs each); 0: there are no records to place
     const uint32_t *stage;     // rec_run (key, payload) pairs per run
     uint32_t rec_run;
@@ -75,9 +69,7 @@ constexpr uint32_t kRecordRuns = (uint32_t)(kRecordBlock / kWave);   // runs per
 __global__ void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies);
 constexpr uint32_t kEncRingSyms = 1024;    // single-pass compression: codes a wavefront keeps in LDS between quantisation and encoding (a batch of at most 512, and less than 256 not yet encoded)
 constexpr uint32_t kEncRunBufWords = 476;  //   its assembly buffer: the words of one step of 256 symbols (at most 456 of code words of 57 bits, two more touched) and slack
-constexpr uint32_t kQuantRecLds = 3072;   // outlier records buffered in LDS per workgroup (24 KB)
-template <bool FULLWIN> __global__ void k_quantize(QuantArgs a);   // flat tiles, any plane width; FULLWIN: every bin is in the LDS window
-constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane of the row-walking kernel
+constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane whose rows a wavefront holds in registers; wider ones are walked in segments (NSEG == 0)
 // Outlier records staged per run (one run of rows per wavefront): the staging area of a context holds one for every fourth element,
 // and at least kQuantRecRun per run.  A run with more has its records derived from the input once more, which takes twice the time of the
 // quantise kernel itself; a container of such a tensor is hardly smaller than the tensor (8 bytes per record alone).

@@ -44,10 +44,8 @@ __device__ inline void derive_records(const RecordArgs &a, uint32_t run, uint32_
     constexpr uint32_t V = 4, kStep = V * kWave;             // elements per lane and step
     typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
     const uint32_t W = a.divW.d, H = a.divH.d;
-    const uint64_t row_lo = (uint64_t)run * a.rows_per_wave;
-    uint64_t row_hi = row_lo + a.rows_per_wave;
-    if (row_hi > a.rows_total) row_hi = a.rows_total;
-    const uint32_t e_lo = (uint32_t)(row_lo * W), e_hi = (uint32_t)(row_hi * W);
+    const uint64_t e_end = (uint64_t)(run + 1u) * a.run_elems;
+    const uint32_t e_lo = run * a.run_elems, e_hi = (uint32_t)(e_end < a.n ? e_end : a.n);       // (a run with records begins inside the tensor)
     const float eb_lo = a.eb * (1.0f - 0x1p-20f);            // (an fp32 error above needs the exact comparison)
     const uint32_t fits = room < count ? (uint32_t)room : count;
     auto elem = [&](uint32_t i) -> float {
@@ -74,6 +72,11 @@ __device__ inline void derive_records(const RecordArgs &a, uint32_t run, uint32_
         buffered = 0;
     };
     int32_t carry = 0, carry_u = 0;                          // minus what lane 63 held last, one step back: the left neighbours of lane 0
+    if (e_lo - fdiv(e_lo, a.divW) * W != 0u) {               // (a run that begins inside a row; the lane's masks drop what is not there)
+        auto quant = [&](float v) -> int32_t { const float t = v * a.r; return (fabsf(t) < 16777216.0f) ? (int32_t)rintf(t) : 0; };
+        carry = -quant(elem(e_lo - 1u));
+        carry_u = e_lo > W ? -quant(elem(e_lo - 1u - W)) : 0;
+    }
     auto fetch = [&](uint32_t e0, float (&x)[V], float (&up)[V]) {
         const uint32_t e = e0 + lane * V;
         if (IN == 0 && e0 >= W && e0 + kStep <= e_hi) {      // (uniform; everything is inside the tensor)

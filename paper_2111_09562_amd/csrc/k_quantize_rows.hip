@@ -1,4 +1,4 @@
-// Quantise kernels for planes up to 512 columns wide: prequantisation, 2-D Lorenzo
+// Quantise kernels: prequantisation, 2-D Lorenzo
 // prediction, quantisation codes, histogram and outlier records in one sweep over
 // the input (COMET Sec. 4.1, first three steps of the modified cuSZ pipeline;
 // Sec. 2.2 for the bound).
@@ -427,6 +427,188 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
     return cur;
 }
 
+// The same for planes of more than kQuantRowsMaxW columns.  (Before, a kernel of its own took those, with four loads and prequantisations per
+// element, its segments dealt by ticket and one histogram for all: 2 x 16 x 480 x 854 59 us of the round trip's 213, now
+// 180 us in all; 4 x 64 x 333 x 777, 4096 bins the compression 310 -> 221; 8 x 3 x 2048 x 2048 at 1e-4, 65536 bins 2288 -> 978.)  A step is a segment of 64 * VEC columns of one row, the run (elements
+// [e_lo, e_lo + n_el), which may begin and end inside a row) is walked segment by segment, and the row above comes from memory once more (the row before, which is in the caches) instead of from registers,
+// which would have to hold all segments of a row.  HIST: kHistFull, or kHistPart, which here counts all codes, those outside the window by way of
+// the list.
+template <int VEC, int HIST>
+__device__ inline uint32_t sweep_wide(const QuantArgs &a, uint32_t e_lo, uint32_t n_el, uint32_t lane, uint32_t *s_hist,
+                                      uint32_t hist_dummy, uint2 *s_buf, uint2 *rec_dst, uint64_t rec_cap, SweepCounts &cnt) {
+    constexpr uint32_t kSeg = (uint32_t)(kWave * VEC), U = 4u / VEC;        // columns per step; steps per batch of loads
+    const uint32_t W = a.divW.d, H = a.divH.d;
+    const uint32_t code_span = a.nbins - 1u;
+    const float eb_lo = a.eb * (1.0f - 0x1p-20f);
+    const uint32_t hist_sub = lane & ((1u << a.hist_shift) - 1u);
+    const uint32_t row_0 = fdiv(e_lo, a.divW), col_0 = e_lo - row_0 * W;
+    const uint32_t back = e_lo < W ? e_lo : W;                   // the descriptor starts a row above the run
+    const __amdgpu_buffer_rsrc_t r_x = rows_rsrc(static_cast<const float *>(a.x) + ((size_t)e_lo - back), (n_el + back) * 4u);
+    const __amdgpu_buffer_rsrc_t r_c = rows_rsrc(a.codes + e_lo, n_el * 2u);
+    uint32_t cur = 0, buffered = 0;                              // records so far, waiting in s_buf (uniform)
+    auto flush_records = [&]() {
+        wave_lds_fence();
+        for (uint32_t i = lane; i < buffered; i += kWave)
+            if (cur + i < rec_cap) rec_dst[cur + i] = s_buf[i];
+        wave_lds_fence();
+        cur += buffered;
+        buffered = 0;
+    };
+    auto flush_oow = [&]() {
+        wave_lds_fence();
+        uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
+        for (uint32_t i = lane; i < cnt.oow_held; i += kWave) atomicAdd(&part[cnt.oow_list[i]], 1u);
+        wave_lds_fence();
+        cnt.oow_held = 0;
+    };
+    // a segment ends after kSeg columns, with its row or with the run
+    auto segment = [&](uint32_t off, uint32_t col) {
+        uint32_t len = W - col < kSeg ? W - col : kSeg;
+        return n_el - off < len ? n_el - off : len;
+    };
+    uint32_t f_off = 0, f_col = col_0;                           // the next segment to ask for: its first element of the run, its column (uniform)
+    auto fetch = [&](float (&x)[U][VEC], float (&up)[U][VEC]) {
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t len = segment(f_off, f_col), e = f_off + lane * VEC;
+            // (an offset out of range where there is no element; above the tensor's first row the difference wraps and is out of range too)
+            const bool on = lane * VEC < len;
+            const int at = on ? (int)((back + e) * 4u) : (int)kOob, above = on ? (int)((back + e - W) * 4u) : (int)kOob;
+            if (VEC == 2) {
+                const u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(r_x, at, 0, 0), s = __builtin_amdgcn_raw_buffer_load_b64(r_x, above, 0, 0);
+                x[u][0] = __uint_as_float(r.x); x[u][VEC - 1] = __uint_as_float(r.y);
+                up[u][0] = __uint_as_float(s.x); up[u][VEC - 1] = __uint_as_float(s.y);
+            } else {
+                x[u][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_x, at, 0, 0));
+                up[u][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r_x, above, 0, 0));
+            }
+            f_off += len;
+            f_col += len;
+            f_col = f_col == W ? 0u : f_col;
+        }
+    };
+    uint32_t off_0 = 0, col = col_0, h = row_0 - fdiv(row_0, a.divH) * H;   // of the segment that is worked on (uniform)
+    int32_t carry = 0, carry_u = 0;                              // minus the elements in front of the segment and of the one above (uniform)
+    if (col_0) {
+        auto quant = [&](float v) -> int32_t { const float t = v * a.r; return (fabsf(t) < 16777216.0f) ? (int32_t)rintf(t) : 0; };
+        const float *x = static_cast<const float *>(a.x);
+        carry = -quant(x[e_lo - 1u]);
+        if (h) carry_u = -quant(x[e_lo - 1u - W]);
+    }
+    auto steps_of = [&](const float (&xb)[U][VEC], const float (&ub)[U][VEC]) {
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (off_0 >= n_el) break;                            // (uniform)
+            const uint32_t len = segment(off_0, col), off = off_0 + lane * VEC;
+            const bool valid = lane * VEC < len;
+            const uint64_t vmask = wave_ballot(valid);
+            float x[VEC], qf[VEC];
+            int32_t q[VEC], qu[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                x[v] = xb[u][v];
+                const float t = x[v] * a.r, tu = ub[u][v] * a.r;
+                qf[v] = (fabsf(t) < 16777216.0f) ? rintf(t) : 0.0f;
+                q[v] = (int32_t)qf[v];
+                qu[v] = (fabsf(tu) < 16777216.0f) ? (int32_t)rintf(tu) : 0;
+            }
+            int32_t nql = lane_left(-q[VEC - 1]), nqul = lane_left(-qu[VEC - 1]);
+            nql = lane == 0u ? carry : nql;
+            nqul = lane == 0u ? carry_u : nqul;
+            const bool row_ends = col + len == W;                // (uniform)
+            carry = row_ends ? 0 : __builtin_amdgcn_readlane(-q[VEC - 1], 63);
+            carry_u = row_ends ? 0 : __builtin_amdgcn_readlane(-qu[VEC - 1], 63);
+            const uint32_t hmask = h ? ~0u : 0u;                 // "has a row above"
+            uint64_t em[VEC], sm[VEC], any_rec = 0ull;
+            bool inr[VEC], susp[VEC];
+            int32_t d[VEC];
+            uint32_t code[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const uint32_t rd = v ? (uint32_t)q[v] - (uint32_t)q[v ? v - 1 : 0] : (uint32_t)q[0] + (uint32_t)nql;
+                const uint32_t ru = v ? (uint32_t)qu[v] - (uint32_t)qu[v ? v - 1 : 0] : (uint32_t)qu[0] + (uint32_t)nqul;
+                d[v] = (int32_t)(rd - (ru & hmask));
+                const uint32_t c = (uint32_t)d[v] + (uint32_t)a.radius;
+                inr[v] = (c - 1u) < code_span;
+                code[v] = inr[v] ? c : 0u;
+                const float err = fabsf(x[v] - qf[v] * a.ebx2);
+                susp[v] = !(err <= eb_lo);                       // also true for NaN / Inf / huge inputs
+                em[v] = wave_ballot(!inr[v]) & vmask;
+                sm[v] = wave_ballot(susp[v]) & vmask;
+                any_rec |= em[v] | sm[v];
+                cnt.nnz_lane += (x[v] != 0.0f) ? 1u : 0u;        // lanes without an element hold 0
+                const bool count = valid && code[v] != (uint32_t)a.radius;
+                if (HIST == kHistFull) {
+                    atomicAdd(&s_hist[count ? (code[v] << a.hist_shift) + hist_sub : hist_dummy], 1u);
+                } else {
+                    const uint32_t bin = code[v] - a.win_lo;
+                    const bool inwin = bin < a.win_n;
+                    atomicAdd(&s_hist[(count && inwin) ? (bin << a.hist_shift) + hist_sub : hist_dummy], 1u);
+                    const uint64_t om = wave_ballot(count && !inwin);
+                    if (om != 0ull) {
+                        const uint32_t n_new = (uint32_t)__popcll(om);
+                        if (cnt.oow_held + n_new > kQuantOowList) flush_oow();
+                        if (count && !inwin)
+                            cnt.oow_list[cnt.oow_held + __builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u))] = (uint16_t)code[v];
+                        cnt.oow_held += n_new;
+                        cnt.oow += n_new;
+                    }
+                }
+            }
+            const int at = valid ? (int)(off * 2u) : (int)kOob;
+            if (VEC == 2) __builtin_amdgcn_raw_buffer_store_b32(code[0] | (code[VEC - 1] << 16), r_c, at, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)code[0], r_c, at, 0, 0);
+            if (any_rec != 0ull) {                               // (the lanes' records in element order, as in sweep_rows)
+                uint64_t vm[VEC], any_s = 0ull;
+                bool verb[VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) { vm[v] = 0ull; verb[v] = false; any_s |= sm[v]; }
+                if (any_s != 0ull) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        if (valid && susp[v]) verb[v] = needs_verbatim_rows(x[v], q[v], a.r, a.ebx2, a.eb);
+                        vm[v] = wave_ballot(verb[v]);
+                    }
+                }
+                uint32_t add = 0, before = 0;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    add += (uint32_t)__popcll(em[v]) + (uint32_t)__popcll(vm[v]);
+                    before += __builtin_amdgcn_mbcnt_hi((uint32_t)(em[v] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)em[v], 0u));
+                    if (vm[v]) before += __builtin_amdgcn_mbcnt_hi((uint32_t)(vm[v] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vm[v], 0u));
+                    cnt.vrec += (uint32_t)__popcll(vm[v]);
+                }
+                if (add) {
+                    if (buffered + add > kQuantRecLds2) flush_records();
+                    uint32_t pos = buffered + before;
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        const uint32_t key = 2u * (e_lo + off + (uint32_t)v);
+                        if (valid && !inr[v]) s_buf[pos++] = make_uint2(key, (uint32_t)d[v]);
+                        if (verb[v]) s_buf[pos++] = make_uint2(key + 1u, __float_as_uint(x[v]));
+                    }
+                    buffered += add;
+                }
+            }
+            off_0 += len;
+            col = row_ends ? 0u : col + len;
+            if (row_ends) { ++h; h = (h == H) ? 0u : h; }
+        }
+    };
+    // two batches of steps alternate: the loads of one are in flight while the other is worked on
+    float xa[U][VEC], ua[U][VEC], xb[U][VEC], ub[U][VEC];
+    fetch(xa, ua);
+    while (off_0 < n_el) {
+        fetch(xb, ub);
+        steps_of(xa, ua);
+        fetch(xa, ua);
+        steps_of(xb, ub);
+    }
+    flush_records();
+    cnt.from = n_el;
+    return cur;
+}
+
 // rows [lo, hi) of run `run`
 __device__ inline void run_rows(const QuantArgs &a, uint32_t run, uint32_t *lo, uint32_t *hi) {
     const uint64_t r0 = (uint64_t)run * a.rows_per_wave;
@@ -438,6 +620,7 @@ __device__ inline void run_rows(const QuantArgs &a, uint32_t run, uint32_t *lo, 
 }  // namespace
 
 // One run per wavefront, kQuantBlock / 64 runs per workgroup.
+// NSEG == 0: planes of more than kQuantRowsMaxW columns.
 template <int VEC, int NSEG, bool MULTI, int HIST, bool REUSE, int IN>
 __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     constexpr bool FULLWIN = HIST == kHistFull;
@@ -480,8 +663,8 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     __syncthreads();
 
     const uint32_t run = blockIdx.x * kWaves + wave;
-    uint32_t row_lo, row_hi;
-    run_rows(a, run, &row_lo, &row_hi);
+    uint32_t row_lo = 0, row_hi = 0;
+    if (NSEG != 0) run_rows(a, run, &row_lo, &row_hi);
     SweepCounts cnt;
     // (a window that does not hold every bin: behind it and the threads' dummy words, a list per wavefront)
     if (!REUSE && HIST == kHistPart) cnt.oow_list = reinterpret_cast<uint16_t *>(s_hist + (a.win_n << a.hist_shift) + kQuantBlock) + wave * kQuantOowList;
@@ -496,10 +679,15 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         enc.r_chunk = rows_rsrc(a.chunk_off + e_lo / a.chunk_syms, (n_el + a.chunk_syms - 1u) / a.chunk_syms * 4u);
         enc.zero_pair = a.zero_pair;
     }
-    if (row_hi > row_lo)
-        my_records = sweep_rows<VEC, NSEG, MULTI, HIST, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, (a.win_n << a.hist_shift) + tid, s_recbuf[wave],
-                                                                 reinterpret_cast<uint2 *>(a.stage) + (size_t)run * a.rec_run, a.rec_run, cnt, s_len,
-                                                                 REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
+    uint2 *stage = reinterpret_cast<uint2 *>(a.stage) + (size_t)run * a.rec_run;
+    const uint32_t dummy = (a.win_n << a.hist_shift) + tid;
+    const uint64_t run_lo = (uint64_t)run * a.run_elems;
+    const uint32_t run_n = run_lo < a.n ? (a.n - run_lo < a.run_elems ? (uint32_t)(a.n - run_lo) : a.run_elems) : 0u;
+    if (run_n) {
+        if constexpr (NSEG == 0) my_records = sweep_wide<VEC, HIST>(a, (uint32_t)run_lo, run_n, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt);
+        else my_records = sweep_rows<VEC, NSEG, MULTI, HIST, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt, s_len,
+                                                                        REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
+    }
     if (REUSE) {
         if (lane == 0) a.run_words[run] = enc.wrun;
         // a run that needs more than 16 bits per symbol does not fit its work area: the table does not suit this tensor
@@ -530,10 +718,8 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
         a.run_count[gridDim.x * kWaves + tid * gridDim.x + blockIdx.x] = t;   // three arrays of one entry per workgroup
     }
     if (REUSE || HIST == kHistNone) return;         // no histogram (uniform: every thread has passed the barrier above)
-    const uint64_t r0 = (uint64_t)blockIdx.x * kWaves * a.rows_per_wave;
-    uint64_t r1 = r0 + (uint64_t)kWaves * a.rows_per_wave;
-    if (r1 > a.rows_total) r1 = a.rows_total;
-    uint64_t elems = (r1 > r0) ? (r1 - r0) * a.divW.d : 0ull;
+    const uint64_t e0 = (uint64_t)blockIdx.x * kWaves * a.run_elems, e1 = e0 + (uint64_t)kWaves * a.run_elems;
+    uint64_t elems = e0 < a.n ? (e1 < a.n ? e1 : a.n) - e0 : 0ull;
     uint32_t *part = a.hist_parts + (size_t)(blockIdx.x % a.hist_copies) * a.nbins;
     uint64_t counted = 0;
     if (HIST == kHistPart) {
@@ -581,5 +767,9 @@ COMET_INST_QR(2, 2, false)
 COMET_INST_QR(2, 4, false)
 #undef COMET_INST_QR_IN
 #undef COMET_INST_QR
+template __global__ void k_quantize_rows<1, 0, false, kHistFull, false, 0>(QuantArgs);
+template __global__ void k_quantize_rows<1, 0, false, kHistPart, false, 0>(QuantArgs);
+template __global__ void k_quantize_rows<2, 0, false, kHistFull, false, 0>(QuantArgs);
+template __global__ void k_quantize_rows<2, 0, false, kHistPart, false, 0>(QuantArgs);
 
 }  // namespace comet
