@@ -1,15 +1,16 @@
 // Codebook kernels (COMET Sec. 4.1, "customized Huffman coding"):
 //   k_codebook       histogram -> Huffman code lengths -> canonical codes -> encode
-//                    table; also lays out the container (header, section offsets).
+//                    table; also lays out the container (header, section offsets).  Its
+//                    workgroups behind the first one place the outlier records meanwhile.
 //   k_decode_tables  length table -> canonical decode tables; validates a header.
-// One workgroup each: the work is a few thousand symbols at most and sits on the
-// critical path between the two streaming kernels, so it is latency- not
+// One workgroup each for the tables: the work is a few thousand symbols at most and sits on
+// the critical path between the two streaming kernels, so it is latency- not
 // bandwidth-bound.  Alphabets up to kBookLdsSyms live entirely in LDS.  Larger ones:
 //   k_book_sort_tiles, k_book_merge  the leaves in (frequency, symbol) order, by as many
 //                    workgroups as the alphabet has tiles of 1024 symbols (a merge sort:
-//                    tiles sorted in registers, then runs merged pairwise by ranking);
-//                    k_codebook then merges in global memory while many items wait and
-//                    finishes in LDS.
+//                    tiles sorted in registers, then runs merged by ranking, four per launch);
+//                    k_codebook then builds the tree on the leaves' weights in LDS, or, where
+//                    those do not fit, in global memory while many items wait and in LDS at the end.
 //
 // Length rule (must give exactly one answer): leaves ordered by (frequency,
 // symbol); two queues; at every step the two smallest heads are merged, the leaf
@@ -1190,7 +1191,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
 // The rest of a large alphabet's code book (more than kBookLdsSyms symbols occur, presorted), by whole grids instead of the
 // one workgroup that built the tree: a walk to the root is a chain of some twenty dependent loads, and the canonical
 // codes visit every symbol of the alphabet.  64 x 256 x 56 x 56 at a bound of 1e-4, 65536
-// bins: k_codebook 406 us with them, 272 without (190 since huffman_rounds_window), and 28 behind it.  Where at most
+// bins: k_codebook 406 us with them, 272 without (85 since huffman_rounds_weights), and 28 behind it.  Where at most
 // kBookLdsSyms symbols of such an alphabet occur they return at once and cost 9 us.
 // k_book_depths: one leaf per thread; it also counts the lengths per tile of kBookBlock symbols.
 // k_book_codes: a tile per workgroup; the code of a symbol is the first code of its length plus the number of smaller
