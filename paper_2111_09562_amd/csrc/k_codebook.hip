@@ -1028,8 +1028,11 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
     const uint32_t nbins = a.nbins;
     const bool given = a.given_len != nullptr;
-    // (what the header takes from the control block, unless the counts are added up here: asked for now, needed last)
-    const uint64_t ctl_rec = a.ctl->n_rec, ctl_vrec = a.ctl->n_vrec, ctl_nnz = a.ctl->nnz;
+    // What the header takes from the control block, unless the counts are added up here: asked for now, needed last.  The first
+    // kernel of a call (a given code book) finds the call before it there: nothing is counted yet, and k_place_payload, which
+    // adds the records up, checks the room for them and clears the padding behind them.
+    uint64_t ctl_rec = 0, ctl_vrec = 0, ctl_nnz = 0;
+    if (!a.reset_ctl) { ctl_rec = a.ctl->n_rec; ctl_vrec = a.ctl->n_vrec; ctl_nnz = a.ctl->nnz; }
     if (a.reset_ctl && tid < sizeof(Control) / 4u) reinterpret_cast<uint32_t *>(a.ctl)[tid] = 0u;   // (before the first barrier: nothing has raised a bit yet)
     if (tid < 65) s.cnt[tid] = 0;
     if (tid < 4) s.word[tid] = 0;

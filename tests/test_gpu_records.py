@@ -96,3 +96,32 @@ def test_alphabets_in_turn_on_one_context(oracle):
             ctx.comet_compress(xd, 1e-3, 1024, box[:16384])
         full(1024)
     ctx.close()
+
+
+@pytest.mark.parametrize("sync", [True, False])
+@pytest.mark.parametrize("spare", [0, 1 << 21])
+def test_given_codebook_after_many_records(oracle, sync, spare):
+    """A compression with a given code book knows nothing of the records of the call before it: a buffer of exactly the
+    container's size is enough, and in a larger one the bytes behind the container stay as they were."""
+    from paper_2111_09562_amd import comet
+    rough = np.random.default_rng(5).standard_normal((1, 8, 129, 127)).astype(np.float32)
+    eb = 1e-2
+    many = oracle.compress(rough, eb, 16, 64)
+    records = oracle.parse_container(many)["n_records"]
+    assert records > 100_000 and records % 2 == 1 and many.size < 1 << 21      # (odd: padding behind the records)
+    x, old = synth.relu_blur((2, 4, 41, 58), 8, blur=3, shift=-0.2), synth.relu_blur((2, 4, 41, 58), 9, blur=3, shift=-0.2)
+    old[0, 0, 0, 0] = 1000.0                                  # (a code word for the escape)
+    book = oracle.parse_container(oracle.compress(old, eb, 256, 64))["len"].copy()
+    want = oracle.compress_with_lengths(x, eb, 256, 64, book)
+    ctx = comet.Context(rough.size, 1024)
+    ctx.comet_set_chunk_syms(64)
+    big = torch.zeros(comet.comet_compress_bound(rough.shape, 16, 64), dtype=torch.uint8, device="cuda")
+    assert ctx.comet_compress(torch.from_numpy(rough).cuda(), eb, 16, big) == many.size
+    cap = want.size + spare
+    room = torch.full((cap + 4096,), 77, dtype=torch.uint8, device="cuda")
+    used = ctx.comet_compress_with_codebook(torch.from_numpy(x).cuda(), eb, 256, torch.from_numpy(book).cuda(), room[:cap], sync=sync)
+    ctx.comet_sync()
+    assert not sync or used == want.size
+    assert np.array_equal(room[:want.size].cpu().numpy(), want)
+    assert bool((room[want.size:] == 77).all())
+    ctx.close()
