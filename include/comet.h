@@ -115,9 +115,8 @@ int comet_compress(comet_ctx *ctx, const float *dev_in, comet_shape shape, float
  * with comet_decompress to exactly the values comet_compress would give.  Everything else as
  * comet_compress.  Limits: nbins <= 8192 and planes of at most 512 columns (COMET_ERR_INVALID
  * otherwise).  A table that is no such code, that lacks a code word for the escape symbol when
- * the tensor needs one, or that spends more than 16 bits per symbol on some run of rows (about
- * 2048 elements or more: the encoded run does not fit its share of the workspace; such a table
- * expands the data) raises COMET_ERR_CODEBOOK (device-side: returned here if bytes_out is given,
+ * the tensor needs one, or that spends more than 16 bits per symbol on some run of rows (a run has
+ * 2048 elements or more, unless the tensor has fewer; such a table expands the data) raises COMET_ERR_CODEBOOK (device-side: returned here if bytes_out is given,
  * else by comet_sync); the caller then compresses in full. */
 int comet_compress_with_codebook(comet_ctx *ctx, const float *dev_in, comet_shape shape, float eb, uint32_t nbins,
                                  const uint8_t *dev_len, void *stream, void *dev_out, uint64_t capacity,

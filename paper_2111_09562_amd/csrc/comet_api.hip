@@ -190,7 +190,7 @@ void encode_geometry(const comet_ctx *ctx, uint64_t n_chunks, uint32_t nbins, ui
 // Work split of the quantise kernel: `grid` workgroups of four wavefronts, each wavefront on rows_per_wave consecutive rows.
 // vec: columns per lane of the row-walking kernel (2 if W is even and the input is 8-byte aligned).
 // chunk_align: if not 0, every run is a whole number of chunks of that many symbols (single-pass compression).
-struct QuantGeom { uint32_t grid, run_elems, rows_per_wave, rows_per_step, vec; };
+struct QuantGeom { uint32_t grid, run_elems, wg_elems, rows_per_wave, rows_per_wg, rows_per_step, vec, words64; };
 // nbins: the alphabet (its histogram window decides how many workgroups a compute unit holds at once).
 QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, const void *x, uint32_t nbins, uint32_t elem_bytes = 4, uint32_t chunk_align = 0);
 
@@ -200,7 +200,8 @@ struct SinglePass {
     uint32_t chunk_syms, zero_pair;
     uint32_t *chunk_off;       // chunk table of the container
     uint32_t *run_words;       // one entry per run
-    uint32_t *work_words;      // n / 2 words
+    uint32_t *work_words;      // kWordsRun or kWordsWide for every 64 symbols
+    uint64_t stage_bytes;      // what is left of the staging area for records
 };
 
 // recs: receives what the kernels behind this one need to place the outlier records
@@ -224,12 +225,12 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
     const uint32_t grid = g.grid;
     {
         a.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h);
-        a.rows_per_wave = g.rows_per_wave;
+        a.rows_per_wave = g.rows_per_wave; a.rows_per_wg = g.rows_per_wg;
         a.rows_per_step = g.rows_per_step;
         if ((uint64_t)grid * (kQuantBlock / kWave) > ctx->max_runs) return COMET_ERR_INTERNAL;
         a.stage = ctx->rec_stage;
         {
-            const uint64_t room = ctx->stage_bytes / 8u / ((uint64_t)grid * kQuantWaves), most = 2ull * g.run_elems;    // (two records per element at most)
+            const uint64_t room = (sp ? sp->stage_bytes : ctx->stage_bytes) / 8u / ((uint64_t)grid * kQuantWaves), most = 2ull * g.run_elems;    // (two records per element at most)
             a.rec_run = (uint32_t)(room < most ? room : most);
         }
         a.run_count = ctx->run_count;
@@ -243,7 +244,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         a.reset_ctl = reset_ctl ? 1u : 0u;
         RecordArgs &ra = *recs;
         ra.x = x; ra.in_type = (uint32_t)in_type; ra.divW = a.divW; ra.divH = a.divH; ra.r = a.r; ra.ebx2 = a.ebx2; ra.eb = eb;
-        ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.n = n; ra.run_elems = a.run_elems = g.run_elems;
+        ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.n = n; ra.run_elems = a.run_elems = g.run_elems; ra.wg_elems = g.wg_elems;
         ra.n_wg = grid; ra.stage = ctx->rec_stage; ra.rec_run = a.rec_run; ra.run_count = ctx->run_count; ra.rec = rec; ra.rec_cap = rec_cap; ra.ctl = a.ctl;
         // (an alphabet larger than the window: what the sweep does not count is counted from memory, behind it)
         auto count_codes = [&]() {
@@ -295,7 +296,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
             a.enc_n = nbins < kEncTableMax ? nbins : kEncTableMax;
             a.enc_lo = (nbins - a.enc_n) / 2u;
             a.chunk_syms = sp->chunk_syms; a.zero_pair = sp->zero_pair;
-            a.chunk_off = sp->chunk_off; a.run_words = sp->run_words; a.work_words = sp->work_words;
+            a.chunk_off = sp->chunk_off; a.run_words = sp->run_words; a.work_words = sp->work_words; a.words64 = g.words64;
             lds_single = (a.enc_n == nbins ? 0u : lds_reuse) + ((size_t)a.enc_n + 1u) * 8u +
                          (size_t)(kQuantBlock / kWave) * ((kEncRingSyms + 4u) * 2u + kEncRunBufWords * 4u);
         }
@@ -461,8 +462,8 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
             for (uint32_t w = s.w; (w & 1u) == 0u && rows_per_chunk > 1u; w >>= 1) rows_per_chunk >>= 1;
             unit = K / std::gcd(K, rows_per_chunk) * rows_per_chunk;
         }
-        // a few wavefronts per SIMD, but runs of at least 2048 elements (every run re-reads one row), or fewer, down to 512, while
-        // that leaves SIMDs without a run (one image, 64 x 28 x 28: 26 wavefronts -> 102, the call 36.5 us -> 33.2)
+        // a few wavefronts per SIMD, but runs of at least kReuseRunElems elements (every run re-reads one row), or fewer, down to
+        // kQuantRunMin, while that leaves SIMDs without a run (one image, 64 x 28 x 28: 26 wavefronts -> 102, the call 36.5 us -> 33.2)
         // All runs should be resident at once: a run that has to wait for a place makes the launch take two rounds.
         // A workgroup is one wavefront per SIMD; how many a compute unit holds follows from the LDS they need (the
         // histogram window of a large alphabet leaves room for three; the encoder's ring and tables of the single-pass
@@ -477,14 +478,15 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
             if (fit < runs_per_simd) runs_per_simd = fit ? fit : 1u;
         }
         const uint64_t want = (uint64_t)ctx->num_cu * 4u * runs_per_simd;
-        const uint64_t share = n / ((uint64_t)ctx->num_cu * 4u), least = share < 512u ? 512u : (share < 2048u ? share : 2048u);
+        const uint64_t share = n / ((uint64_t)ctx->num_cu * 4u);
+        const uint64_t least = chunk_align || share >= kReuseRunElems ? kReuseRunElems : (share < kQuantRunMin ? kQuantRunMin : share);
         if (s.w > kQuantRowsMaxW) {
             // wide planes: whole rows, or less than half a row, in multiples of a batch of steps
             uint64_t per = (n + want - 1) / want;
             if (per < least) per = least;
             per = 2u * per < s.w ? (per + 255u) / 256u * 256u : (per + s.w - 1u) / s.w * s.w;
             const uint64_t waves = (n + per - 1) / per;
-            g.run_elems = (uint32_t)per;
+            g.run_elems = (uint32_t)per; g.wg_elems = kQuantWaves * g.run_elems;
             g.grid = (uint32_t)((waves + kQuantWaves - 1u) / kQuantWaves);
             return g;
         }
@@ -496,9 +498,12 @@ QuantGeom quantize_geometry(const comet_ctx *ctx, comet_shape s, uint64_t n, con
         // a run must stay below 2^28 elements (buffer offsets): cannot be exceeded, rows_total * w < 2^31 and
         // the run count is in the thousands unless the tensor itself is small
         const uint64_t waves = (rows_total + per - 1) / per;
-        g.rows_per_wave = (uint32_t)per;
-        g.run_elems = (uint32_t)(per * s.w);
-        g.grid = (uint32_t)((waves + (kQuantBlock / kWave) - 1) / (kQuantBlock / kWave));
+        const bool quarters = chunk_align && share < kReuseRunElems && per >= 2u * unit;     // a workgroup takes one run (kReuseRunElems)
+        const uint64_t sub = quarters ? (per / unit + kQuantWaves - 1u) / kQuantWaves * unit : per, per_wg = quarters ? per : kQuantWaves * per;
+        g.words64 = quarters ? kWordsWide : kWordsRun;
+        g.rows_per_wave = (uint32_t)sub; g.rows_per_wg = (uint32_t)per_wg;
+        g.run_elems = (uint32_t)(sub * s.w); g.wg_elems = (uint32_t)(per_wg * s.w);
+        g.grid = (uint32_t)(quarters ? waves : (waves + kQuantWaves - 1u) / kQuantWaves);
         return g;
     }
 }
@@ -711,12 +716,18 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         sp.chunk_off = chunk_off;
         sp.run_words = ctx->run_count + 3u * ctx->max_runs;
         sp.work_words = reinterpret_cast<uint32_t *>(ctx->codes);
+        sp.stage_bytes = ctx->stage_bytes;
+        if (qg.words64 != kWordsRun) {                       // (tensors so small that the end of the staging area has room for any code words)
+            static_assert(4u * kQuantRunsPerSimd * kQuantRecRun * 8u >= 4u * kReuseRunElems * kWordsWide / 64u * 4u + 4u * 4u * 256u * 8u, "and for 256 records per run");
+            sp.stage_bytes = (sp.stage_bytes - (n + 63u) / 64u * kWordsWide * 4u) & ~255ull;
+            sp.work_words = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(ctx->rec_stage) + sp.stage_bytes);
+        }
         if ((rc = launch_quantize(ctx, dev_in, s, n, eb, nbins, st, nullptr, nullptr, rec, rec_cap, &recs, false, dev_len, 0, &sp))) return rc;
         PlaceArgs p{};
         p.run_words = sp.run_words;
-        p.rows_per_wave = qg.rows_per_wave; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
+        p.rows_per_wave = qg.rows_per_wave; p.rows_per_wg = qg.rows_per_wg; p.words64 = qg.words64; p.rows_total = (uint32_t)((uint64_t)s.n * s.c * s.h); p.W = s.w;
         p.recs = recs;
-        p.n_runs = (p.rows_total + qg.rows_per_wave - 1u) / qg.rows_per_wave;
+        p.n_runs = qg.words64 == kWordsRun ? (p.rows_total + qg.rows_per_wave - 1u) / qg.rows_per_wave : qg.grid * kQuantWaves;
         p.chunk_syms = S; p.work_words = sp.work_words; p.container = out; p.capacity = capacity;
         p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched; p.host = bytes_out ? ctx->host_result : nullptr;
         constexpr uint32_t per_wg = (uint32_t)(kPlaceBlock / kWave);

@@ -21,6 +21,7 @@ struct QuantArgs {
     uint32_t win_lo, win_n;    // histogram bins [win_lo, win_lo + win_n) are counted in LDS
     uint32_t rows_total;       // planes * H rows of W elements
     uint32_t rows_per_wave;    //   consecutive rows per wavefront (a multiple of rows_per_step)
+    uint32_t rows_per_wg;      //   rows per workgroup: kQuantWaves * rows_per_wave, or fewer (kReuseRunElems)
     uint32_t run_elems;        //   elements per run: rows_per_wave * W, or, for planes wider than kQuantRowsMaxW, what their runs hold
     uint32_t rows_per_step;    //   rows a wavefront covers per step (64 / lanes per row if a row takes at most 32 lanes, else 1)
     uint32_t hist_shift;       //   log2 of the copies of the LDS histogram window (lane & (copies - 1) picks one)
@@ -39,7 +40,8 @@ struct QuantArgs {
     uint32_t *chunk_off;       //   chunk table of the container: offsets relative to the run (k_place_payload makes them absolute)
     uint32_t *run_words;       //   words of every run
     uint32_t *run_from;        // kHistPart: element of every run from which on k_code_hist counts its codes
-    uint32_t *work_words;      //   work area: the words of the run that starts at element e at word e / 2
+    uint32_t *work_words;      //   work area: the words of the run that starts at element e at word e / 64 * words64
+    uint32_t words64;          //   kWordsRun or kWordsWide
     uint16_t *codes;
     Control *ctl;
 };
@@ -54,7 +56,7 @@ struct RecordArgs {
     uint32_t nbins;
     const uint8_t *reuse_len;  // code book reuse: the given lengths, or null
     uint64_t n;
-    uint32_t run_elems;        // elements per run
+    uint32_t run_elems, wg_elems;  // elements per run and per workgroup of the quantise kernel
     uint32_t n_wg;             // workgroups of the quantise kernel (kQuantWaves runs each); 0: there are no records to place
     const uint32_t *stage;     // rec_run (key, payload) pairs per run
     uint32_t rec_run;
@@ -69,6 +71,15 @@ constexpr uint32_t kRecordRuns = (uint32_t)(kRecordBlock / kWave);   // runs per
 __global__ void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies);
 constexpr uint32_t kEncRingSyms = 1024;    // single-pass compression: codes a wavefront keeps in LDS between quantisation and encoding (a batch of at most 512, and less than 256 not yet encoded)
 constexpr uint32_t kEncRunBufWords = 476;  //   its assembly buffer: the words of one step of 256 symbols (at most 456 of code words of 57 bits, two more touched) and slack
+// Compression with a given code book: what the words of a run of kReuseRunElems elements or more may take, 16 bits per symbol of
+// the whole run (more expands the data and is refused).  While such runs leave SIMDs without work (fewer elements than kReuseRunElems
+// per SIMD), a workgroup of four wavefronts takes one of them instead of four: its runs are a quarter as long, the words
+// of each may be of any length (kWordsWide), and the limit holds for the four of them together, so the length of a
+// run decides nothing about what is refused.
+// A call with a wavefront per run of 2048 elements / with four: 64 x 28 x 28 31.4 / 24.6 us, 4 x 64 x 56 x 56 32.2 / 27.1,
+// 10 x 64 x 56 x 56 (2.0 M elements) 34.0 / 31.8; beyond the line 12 x 64 x 56 x 56 34.6 / 38.6.
+constexpr uint32_t kReuseRunElems = 2048;
+constexpr uint32_t kWordsRun = 32, kWordsWide = 114;     // work words per 64 symbols: 16 bits per symbol, the longest code words (57 bits)
 constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane whose rows a wavefront holds in registers; wider ones are walked in segments (NSEG == 0)
 // Outlier records staged per run (one run of rows per wavefront): the staging area of a context holds one for every fourth element,
 // and at least kQuantRecRun per run.  A run with more has its records derived from the input once more, which takes twice the time of the
@@ -76,6 +87,7 @@ constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane whose rows a wavefront
 constexpr uint32_t kQuantRecRun = 768;
 constexpr uint32_t kQuantRecLds2 = 256;   // records a wavefront buffers in LDS before it writes them to the staging area in bulk
 constexpr uint32_t kQuantRunsPerSimd = 5; // runs the launch aims at, per SIMD
+constexpr uint32_t kQuantRunMin = 512;    // elements of the shortest run (whole rows, so a little more), while SIMDs have none
 // Alphabets larger than the histogram window: a wavefront counts its run's codes while those outside the window, which it
 // lists in LDS (kQuantOowList of them) and adds to a partial histogram in bulk, are at most kQuantOowFree plus one in
 // kQuantOowShare; beyond, k_code_hist counts them from memory (why the line lies there: see that kernel) ...
@@ -246,10 +258,11 @@ struct EncodeArgs {
 // single-pass compression: the words of every run from the work area to the payload
 struct PlaceArgs {
     const uint32_t *run_words;     // words of every run
-    uint32_t n_runs;               // runs that hold rows (the arrays have an entry for every wavefront of the grid)
-    uint32_t rows_per_wave, rows_total, W;
+    uint32_t n_runs;               // runs up to the last that holds rows, or a workgroup's more
+    uint32_t rows_per_wave, rows_per_wg, rows_total, W;
     uint32_t chunk_syms;
-    const uint32_t *work_words;    // the run that starts at element e has its words from word e / 2 on
+    const uint32_t *work_words;    // the run that starts at element e has its words from word e / 64 * words64 on
+    uint32_t words64;
     uint8_t *container;
     uint64_t capacity;
     RecordArgs recs;               // the outlier records, which each wavefront places for its own run as well

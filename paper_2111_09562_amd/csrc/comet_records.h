@@ -44,8 +44,9 @@ __device__ inline void derive_records(const RecordArgs &a, uint32_t run, uint32_
     constexpr uint32_t V = 4, kStep = V * kWave;             // elements per lane and step
     typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
     const uint32_t W = a.divW.d, H = a.divH.d;
-    const uint64_t e_end = (uint64_t)(run + 1u) * a.run_elems;
-    const uint32_t e_lo = run * a.run_elems, e_hi = (uint32_t)(e_end < a.n ? e_end : a.n);       // (a run with records begins inside the tensor)
+    const uint64_t wg_lo = (uint64_t)(run / kQuantWaves) * a.wg_elems, wg_hi = wg_lo + a.wg_elems < a.n ? wg_lo + a.wg_elems : a.n;
+    const uint64_t run_lo = wg_lo + run % kQuantWaves * a.run_elems;
+    const uint32_t e_lo = (uint32_t)run_lo, e_hi = (uint32_t)(run_lo + a.run_elems < wg_hi ? run_lo + a.run_elems : wg_hi);       // (a run with records begins inside the tensor)
     const float eb_lo = a.eb * (1.0f - 0x1p-20f);            // (an fp32 error above needs the exact comparison)
     const uint32_t fits = room < count ? (uint32_t)room : count;
     auto elem = [&](uint32_t i) -> float {

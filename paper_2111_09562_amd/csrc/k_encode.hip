@@ -430,14 +430,14 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
         if (stt) atomicOr(&a.ctl->status, stt);
         tell_host(a.host, total, stt, a.latched);
     }
-    if (earlier) return;
+    const uint64_t wg_lo = (uint64_t)blockIdx.x * a.rows_per_wg, row_lo = wg_lo + wave * a.rows_per_wave;
+    uint64_t row_hi = wg_lo + a.rows_per_wg < a.rows_total ? wg_lo + a.rows_per_wg : a.rows_total;
+    if (row_hi > row_lo + a.rows_per_wave) row_hi = row_lo + a.rows_per_wave;
+    if (earlier || row_hi <= row_lo) return;
     const uint64_t cap_words = (a.capacity >= off_payload) ? (a.capacity - off_payload) / 4u : 0u;
-    const uint64_t row_lo = (uint64_t)run * a.rows_per_wave;
-    uint64_t row_hi = row_lo + a.rows_per_wave;
-    if (row_hi > a.rows_total) row_hi = a.rows_total;
     const uint64_t e_lo = row_lo * a.W, e_hi = row_hi * a.W;
     uint32_t *payload = reinterpret_cast<uint32_t *>(a.container + off_payload);
-    const uint32_t *src = a.work_words + e_lo / 2u;
+    const uint32_t *src = a.work_words + e_lo / 64u * a.words64;
     for (uint32_t i = lane; i < mine; i += kWave)
         if (base + i < cap_words) payload[base + i] = src[i];
     uint32_t *chunk_off = reinterpret_cast<uint32_t *>(a.container + h->off_chunk);

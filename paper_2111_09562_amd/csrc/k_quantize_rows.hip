@@ -609,12 +609,13 @@ __device__ inline uint32_t sweep_wide(const QuantArgs &a, uint32_t e_lo, uint32_
     return cur;
 }
 
-// rows [lo, hi) of run `run`
-__device__ inline void run_rows(const QuantArgs &a, uint32_t run, uint32_t *lo, uint32_t *hi) {
-    const uint64_t r0 = (uint64_t)run * a.rows_per_wave;
-    if (r0 >= a.rows_total) { *lo = 0; *hi = 0; return; }
+// rows [lo, hi) of the workgroup's run `wave`
+__device__ inline void run_rows(const QuantArgs &a, uint32_t wave, uint32_t *lo, uint32_t *hi) {
+    const uint64_t w0 = (uint64_t)blockIdx.x * a.rows_per_wg, r0 = w0 + wave * a.rows_per_wave;
+    const uint64_t w1 = w0 + a.rows_per_wg < a.rows_total ? w0 + a.rows_per_wg : a.rows_total;
+    if (r0 >= w1) { *lo = 0; *hi = 0; return; }
     *lo = (uint32_t)r0;
-    *hi = (a.rows_total - *lo < a.rows_per_wave) ? a.rows_total : *lo + a.rows_per_wave;
+    *hi = (uint32_t)(w1 - r0 < a.rows_per_wave ? w1 : r0 + a.rows_per_wave);
 }
 
 }  // namespace
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     constexpr int kWaves = kQuantBlock / kWave;
     uint32_t *s_hist = s_dyn_qr;
     __shared__ uint64_t s_part64[kWaves];
-    __shared__ uint32_t s_tot[kWaves][HIST == kHistPart ? 5 : 3];
+    __shared__ uint32_t s_tot[kWaves][HIST == kHistPart ? 5 : (REUSE ? 4 : 3)];
     __shared__ uint2 s_recbuf[kWaves][kQuantRecLds2];   // outlier records of a wavefront on their way to the staging area
 
     const uint32_t tid = threadIdx.x;
@@ -664,7 +665,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
 
     const uint32_t run = blockIdx.x * kWaves + wave;
     uint32_t row_lo = 0, row_hi = 0;
-    if (NSEG != 0) run_rows(a, run, &row_lo, &row_hi);
+    if (NSEG != 0) run_rows(a, wave, &row_lo, &row_hi);
     SweepCounts cnt;
     // (a window that does not hold every bin: behind it and the threads' dummy words, a list per wavefront)
     if (!REUSE && HIST == kHistPart) cnt.oow_list = reinterpret_cast<uint16_t *>(s_hist + (a.win_n << a.hist_shift) + kQuantBlock) + wave * kQuantOowList;
@@ -674,19 +675,20 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     if (REUSE) {
         const uint32_t e_lo = row_lo * a.divW.d, n_el = (row_hi - row_lo) * a.divW.d;    // a whole number of chunks, but for the last run
         enc.ring = s_ring; enc.buf = s_asm;
-        enc.cap_words = n_el / 2u;
-        enc.r_words = rows_rsrc(a.work_words + e_lo / 2u, enc.cap_words * 4u);
+        enc.cap_words = a.words64 == kWordsRun ? n_el / 2u : (n_el + 63u) / 64u * a.words64;
+        enc.r_words = rows_rsrc(a.work_words + e_lo / 64u * a.words64, enc.cap_words * 4u);
         enc.r_chunk = rows_rsrc(a.chunk_off + e_lo / a.chunk_syms, (n_el + a.chunk_syms - 1u) / a.chunk_syms * 4u);
         enc.zero_pair = a.zero_pair;
     }
     uint2 *stage = reinterpret_cast<uint2 *>(a.stage) + (size_t)run * a.rec_run;
     const uint32_t dummy = (a.win_n << a.hist_shift) + tid;
-    const uint64_t run_lo = (uint64_t)run * a.run_elems;
-    const uint32_t run_n = run_lo < a.n ? (a.n - run_lo < a.run_elems ? (uint32_t)(a.n - run_lo) : a.run_elems) : 0u;
-    if (run_n) {
-        if constexpr (NSEG == 0) my_records = sweep_wide<VEC, HIST>(a, (uint32_t)run_lo, run_n, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt);
-        else my_records = sweep_rows<VEC, NSEG, MULTI, HIST, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt, s_len,
-                                                                        REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
+    if constexpr (NSEG == 0) {
+        const uint64_t run_lo = (uint64_t)run * a.run_elems;
+        const uint32_t run_n = run_lo < a.n ? (a.n - run_lo < a.run_elems ? (uint32_t)(a.n - run_lo) : a.run_elems) : 0u;
+        if (run_n) my_records = sweep_wide<VEC, HIST>(a, (uint32_t)run_lo, run_n, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt);
+    } else if (row_hi > row_lo) {
+        my_records = sweep_rows<VEC, NSEG, MULTI, HIST, REUSE, IN>(a, row_lo, row_hi, lane, s_hist, dummy, s_recbuf[wave], stage, a.rec_run, cnt, s_len,
+                                                                   REUSE ? &enc : nullptr, REUSE ? &tbl : nullptr);
     }
     if (REUSE) {
         if (lane == 0) a.run_words[run] = enc.wrun;
@@ -699,6 +701,7 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
     if (lane == 0) {
         a.run_count[run] = my_records;
         s_tot[wave][0] = my_records; s_tot[wave][1] = nnz_wave; s_tot[wave][2] = cnt.vrec;
+        if (REUSE) s_tot[wave][3] = enc.wrun;
         if (HIST == kHistPart) {
             s_tot[wave][3] = cnt.from;                       // elements whose codes are counted here
             s_tot[wave][4] = cnt.oow != cnt.oow_held;        // part of them is in a partial histogram already
@@ -716,6 +719,14 @@ __global__ __launch_bounds__(kQuantBlock) void k_quantize_rows(QuantArgs a) {
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) t += s_tot[w][tid];
         a.run_count[gridDim.x * kWaves + tid * gridDim.x + blockIdx.x] = t;   // three arrays of one entry per workgroup
+    }
+    if (REUSE && a.words64 != kWordsRun && tid == 0u) {      // the workgroup's runs together: 16 bits per symbol
+        uint32_t words = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) words += s_tot[w][REUSE ? 3 : 0];
+        const uint64_t w0 = (uint64_t)blockIdx.x * a.rows_per_wg;
+        const uint32_t rows = a.rows_total - w0 < a.rows_per_wg ? (uint32_t)(a.rows_total - w0) : a.rows_per_wg;
+        if (words > rows * a.divW.d / 2u) atomicOr(&a.ctl->status, (uint32_t)ST_CODEBOOK);
     }
     if (REUSE || HIST == kHistNone) return;         // no histogram (uniform: every thread has passed the barrier above)
     const uint64_t e0 = (uint64_t)blockIdx.x * kWaves * a.run_elems, e1 = e0 + (uint64_t)kWaves * a.run_elems;

@@ -1,0 +1,89 @@
+"""Room for the words of a compression with a given code book: 16 bits per symbol on a run of rows of 2048 elements or more, on
+average, wherever in the run they fall and however small the tensor is.  Containers against the CPU oracle's, byte for byte."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+EB, NBINS = 2.0 ** -7, 64
+CENTRE, RARE = NBINS // 2, 20                             # a code word of 1 bit, and one of the longest
+
+
+def _book(longest):
+    """Lengths 1, 2, ... and twice the longest: a complete code; the centre code has 1 bit, RARE and the escape have the longest."""
+    book = np.zeros(NBINS, np.uint8)
+    book[CENTRE], book[RARE], book[0] = 1, longest, longest
+    others = [c for c in range(1, NBINS) if c not in (CENTRE, RARE)]
+    book[others[:longest - 2]] = np.arange(2, longest, dtype=np.uint8)
+    assert sum(2.0 ** -int(v) for v in book if v) == 1.0
+    return book
+
+
+def _tensor(rare):
+    """The tensor whose codes are RARE where `rare` is set and the centre code elsewhere (multiples of 2 * EB, all exact)."""
+    q = np.cumsum(np.cumsum(np.where(rare, RARE - CENTRE, 0), axis=2), axis=3)
+    assert np.abs(q).max() < 1 << 23
+    return (q * (2.0 * EB)).astype(np.float32)
+
+
+def _run(oracle, rare, book, chunk, accepted=True):
+    from paper_2111_09562_amd import comet
+    x = _tensor(rare)
+    want = oracle.compress_with_lengths(x, EB, NBINS, chunk, book)
+    ctx = comet.Context(x.size, NBINS)
+    ctx.comet_set_chunk_syms(chunk)
+    box = torch.zeros(want.size, dtype=torch.uint8, device="cuda")
+    args = (torch.from_numpy(x).cuda(), EB, NBINS, torch.from_numpy(book).cuda(), box)
+    if accepted:
+        assert ctx.comet_compress_with_codebook(*args) == want.size
+        assert np.array_equal(box.cpu().numpy(), want)
+    else:
+        with pytest.raises(comet.CometError) as ei:
+            ctx.comet_compress_with_codebook(*args)
+        assert ei.value.code == comet.ERR_CODEBOOK
+    ctx.close()
+
+
+# widths whose runs are made of 2, 8, 64 and 2 rows at least (whole chunks of 64); one image and a few more
+@pytest.mark.parametrize("shape", [(1, 16, 64, 64), (2, 5, 56, 56), (3, 7, 32, 31), (1, 2, 224, 224), (9, 16, 60, 112), (40, 9, 60, 64)])
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+@pytest.mark.parametrize("longest", [20, 57])
+def test_a_burst_of_long_code_words(oracle, shape, chunk, longest):
+    """500 symbols in a row with the longest code words, every 6000 symbols: 20 or 57 bits there, 15 at most on 2048."""
+    e = np.arange(np.prod(shape)).reshape(shape)
+    _run(oracle, (e + 1234) % 6000 < 500, _book(longest), chunk)
+
+
+@pytest.mark.parametrize("planes", [2, 128, 500])
+@pytest.mark.parametrize("place", [0, 13, 31])
+def test_the_16th_bit(oracle, planes, place):
+    """Planes of 64 x 64, chunks of 64: a run is 32 rows.  50 symbols of 20 bits in every row take 32 words a row, 16 bits per
+    symbol on every run; one symbol more in one row, anywhere in a run, is too much for that run."""
+    shape = (1, planes, 64, 64)
+    rare = np.broadcast_to(np.arange(64) < 50, shape).copy()
+    _run(oracle, rare, _book(20), 64)
+    rare[0, planes // 2, 32 + place, 50] = True
+    _run(oracle, rare, _book(20), 64, accepted=False)
+    rare[0, planes // 2, 32 + (place + 5) % 32, :] = False   # ... unless another row of the run has room to spare
+    _run(oracle, rare, _book(20), 64)
+
+
+@pytest.mark.parametrize("shape", [(1, 660, 56, 56), (1, 2, 56, 56), (500, 4, 32, 31), (3, 100, 16, 224)])
+def test_records_of_short_runs(oracle, shape):
+    """Nearly every element an outlier and stored verbatim: more records than a short run's share of the staging area."""
+    from paper_2111_09562_amd import comet
+    n, eb, nbins = int(np.prod(shape)), 1e-2, 16
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal(n).astype(np.float32)
+    x[rng.choice(n, n // 3, replace=False)] = np.inf
+    x = x.reshape(shape)
+    book = np.zeros(nbins, np.uint8)
+    book[[0, 6, 7, 8, 9]] = [1, 3, 3, 3, 3]
+    want = oracle.compress_with_lengths(x, eb, nbins, 64, book)
+    ctx = comet.Context(n, nbins)
+    ctx.comet_set_chunk_syms(64)
+    box = torch.zeros(want.size, dtype=torch.uint8, device="cuda")
+    assert ctx.comet_compress_with_codebook(torch.from_numpy(x).cuda(), eb, nbins, torch.from_numpy(book).cuda(), box) == want.size
+    assert np.array_equal(box.cpu().numpy(), want)
+    ctx.close()
