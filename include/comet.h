@@ -61,8 +61,8 @@ typedef struct {
 } comet_info;
 
 /* Create a context able to handle tensors of up to max_elems elements and
- * max_nbins quantisation bins.  Allocates 2 bytes per element plus about 40 MB
- * (2.14 bytes per element from about 230 million elements on) of device workspace
+ * max_nbins quantisation bins.  Allocates 2 bytes per element plus about 42 MB
+ * (2.14 bytes per element plus about 8 MB from 240 million elements on) of device workspace
  * on the current device.  *ctx is set on success. */
 int comet_create(comet_ctx **ctx, uint64_t max_elems, uint32_t max_nbins);
 void comet_destroy(comet_ctx *ctx);

@@ -246,6 +246,7 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
         ra.x = x; ra.in_type = (uint32_t)in_type; ra.divW = a.divW; ra.divH = a.divH; ra.r = a.r; ra.ebx2 = a.ebx2; ra.eb = eb;
         ra.radius = a.radius; ra.nbins = nbins; ra.reuse_len = reuse_len; ra.n = n; ra.run_elems = a.run_elems = g.run_elems; ra.wg_elems = g.wg_elems;
         ra.n_wg = grid; ra.stage = ctx->rec_stage; ra.rec_run = a.rec_run; ra.run_count = ctx->run_count; ra.rec = rec; ra.rec_cap = rec_cap; ra.ctl = a.ctl;
+        ra.ring = record_ring(s.w);
         // (an alphabet larger than the window: what the sweep does not count is counted from memory, behind it)
         auto count_codes = [&]() {
             if (full || reuse_len || s.w > kQuantRowsMaxW) return;
@@ -341,8 +342,8 @@ int clean_parts(comet_ctx *ctx, hipStream_t st) {
 // The outlier records of a quantisation that no code book follows; hist: receives the sum of the partial histograms, or null.
 int launch_gather(comet_ctx *ctx, const RecordArgs &recs, hipStream_t st, uint32_t *hist, const uint32_t *parts) {
     TimedScope ts(ctx, st, COMET_KERNEL_GATHER);
-    const uint32_t runs = recs.n_wg * kQuantWaves;
-    hipLaunchKernelGGL(k_gather_records, dim3((runs + kRecordRuns - 1u) / kRecordRuns), dim3(kRecordBlock), 0, st, recs, hist, parts, hist_copies(recs.nbins));
+    static_assert((uint32_t)(kGatherBlock / kWave) == kQuantWaves, "its grid is the quantise kernel's");
+    hipLaunchKernelGGL(k_gather_records, dim3(recs.n_wg), dim3(kGatherBlock), kQuantWaves * record_lds(recs.ring), st, recs, hist, parts, hist_copies(recs.nbins));
     HIP_TRY(hipGetLastError());
     return COMET_OK;
 }
@@ -372,7 +373,18 @@ int launch_codebook(comet_ctx *ctx, BookArgs &b, hipStream_t st) {
     }
     const uint32_t runs = b.recs.n_wg * kQuantWaves;
     b.lds_leaves = b.presorted ? kBookLdsLeaves : 0u;
-    hipLaunchKernelGGL(k_codebook, dim3(1u + (runs + kRecordRuns - 1u) / kRecordRuns), dim3(kBookBlock), b.presorted ? kBookLdsBytesLarge : kBookLdsBytes, st, b);
+    constexpr uint32_t waves = (uint32_t)(kBookBlock / kWave);
+    static_assert(waves * (kDeriveBuf * 8u + 1024u * 4u) <= kBookLdsBytesLarge, "the widest ring");
+    uint32_t lds = b.presorted ? kBookLdsBytesLarge : kBookLdsBytes;
+    if (runs && lds < waves * record_lds(b.recs.ring)) lds = waves * record_lds(b.recs.ring);
+    // one workgroup with records per compute unit at most: a compute unit holds no second one, and the wavefronts that are left with a
+    // second run have their SIMD to themselves (a quarter of 411 M elements escaped: 1798 us with 320 workgroups, 1716 with 244)
+    const uint32_t cus = ctx->num_cu > 1 ? (uint32_t)ctx->num_cu - 1u : 1u;
+    uint32_t rec_wgs = (runs + waves - 1u) / waves;
+    if (rec_wgs > cus) rec_wgs = cus;
+    b.rec_wg_runs = rec_wgs ? (runs + rec_wgs - 1u) / rec_wgs : 0u;
+    if (rec_wgs) rec_wgs = (runs + b.rec_wg_runs - 1u) / b.rec_wg_runs;
+    hipLaunchKernelGGL(k_codebook, dim3(1u + rec_wgs), dim3(kBookBlock), lds, st, b);
     if (b.presorted) {                                       // (they leave an alphabet whose occurring symbols fit LDS alone)
         hipLaunchKernelGGL(k_book_depths, dim3((b.nbins + kBookDepthBlock - 1u) / kBookDepthBlock), dim3(kBookDepthBlock), 0, st, b);
         hipLaunchKernelGGL(k_book_codes, dim3((b.nbins + kBookBlock - 1u) / kBookBlock), dim3(kBookBlock), 0, st, b);
@@ -542,7 +554,6 @@ int comet_create(comet_ctx **out, uint64_t max_elems, uint32_t max_nbins) {
     if ((e = hipMalloc((void **)&c->stats, 8ull * (kStatsPartialMax + 1u))) != hipSuccess) return fail(COMET_ERR_NOMEM);
     c->max_runs = (uint64_t)c->num_cu * 4u * kQuantRunsPerSimd + 8u;
     c->stage_bytes = c->max_runs * kQuantRecRun * 8ull;
-    if (c->stage_bytes < align_up(2 * max_elems, 256)) c->stage_bytes = align_up(2 * max_elems, 256);      // a record for every fourth element
     if (c->stage_bytes < band_bytes_max(max_elems)) c->stage_bytes = band_bytes_max(max_elems);
     if ((e = hipMalloc((void **)&c->rec_stage, c->stage_bytes)) != hipSuccess) return fail(COMET_ERR_NOMEM);
     // (a fourth array of one entry per run: the words of every run of the single-pass compression)
@@ -732,7 +743,7 @@ int compress_impl(comet_ctx *ctx, const void *dev_in, int in_type, comet_shape s
         p.ctl = &ctx->state->ctl; p.latched = &ctx->state->latched; p.host = bytes_out ? ctx->host_result : nullptr;
         constexpr uint32_t per_wg = (uint32_t)(kPlaceBlock / kWave);
         TimedScope ts(ctx, st, COMET_KERNEL_ENCODE);
-        hipLaunchKernelGGL(k_place_payload, dim3((p.n_runs + per_wg - 1u) / per_wg), dim3(kPlaceBlock), 0, st, p);
+        hipLaunchKernelGGL(k_place_payload, dim3((p.n_runs + per_wg - 1u) / per_wg), dim3(kPlaceBlock), per_wg * record_lds(recs.ring), st, p);
         HIP_TRY(hipGetLastError());
     } else {
         if (parts && (rc = clean_parts(ctx, st))) return rc;

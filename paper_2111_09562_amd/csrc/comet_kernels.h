@@ -46,6 +46,8 @@ struct QuantArgs {
     Control *ctl;
 };
 
+constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane whose rows a wavefront holds in registers; wider ones are walked in segments (NSEG == 0)
+
 // What the kernels behind the row-walking quantise kernel need to bring its outlier records into element order.
 struct RecordArgs {
     const void *x;             // the input (for runs with more records than their staging area holds)
@@ -63,10 +65,15 @@ struct RecordArgs {
     const uint32_t *run_count; // as in QuantArgs
     uint32_t *rec;             // (key, payload) pairs of the container, in element order
     uint64_t rec_cap;          // room for so many
+    uint32_t ring;             // record_ring(W)
     Control *ctl;
 };
-constexpr int kRecordBlock = 1024;
-constexpr uint32_t kRecordRuns = (uint32_t)(kRecordBlock / kWave);   // runs per workgroup
+// Records that leave a run's staging area out are derived from the input once more (comet_records.h), with a buffer of kDeriveBuf records and
+// a ring of differences per wavefront: a power of two that holds a row and a step of 256 elements, or none.
+constexpr uint32_t kDeriveBuf = 256;
+inline uint32_t record_ring(uint32_t w) { return w < 4u || w > kQuantRowsMaxW ? 0u : (w <= 256u ? 512u : 1024u); }
+__host__ __device__ inline uint32_t record_lds(uint32_t ring) { return kDeriveBuf * 8u + ring * 4u; }    // bytes per wavefront
+constexpr int kGatherBlock = 256;
 // hist: if not null, the sum of the `copies` partial histograms of nbins entries in `parts` goes there
 __global__ void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies);
 constexpr uint32_t kEncRingSyms = 1024;    // single-pass compression: codes a wavefront keeps in LDS between quantisation and encoding (a batch of at most 512, and less than 256 not yet encoded)
@@ -80,10 +87,11 @@ constexpr uint32_t kEncRunBufWords = 476;  //   its assembly buffer: the words o
 // 10 x 64 x 56 x 56 (2.0 M elements) 34.0 / 31.8; beyond the line 12 x 64 x 56 x 56 34.6 / 38.6.
 constexpr uint32_t kReuseRunElems = 2048;
 constexpr uint32_t kWordsRun = 32, kWordsWide = 114;     // work words per 64 symbols: 16 bits per symbol, the longest code words (57 bits)
-constexpr uint32_t kQuantRowsMaxW = 512;  // widest plane whose rows a wavefront holds in registers; wider ones are walked in segments (NSEG == 0)
-// Outlier records staged per run (one run of rows per wavefront): the staging area of a context holds one for every fourth element,
-// and at least kQuantRecRun per run.  A run with more has its records derived from the input once more, which takes twice the time of the
-// quantise kernel itself; a container of such a tensor is hardly smaller than the tensor (8 bytes per record alone).
+// Outlier records staged per run (one run of rows per wavefront): kQuantRecRun of them while there are as many runs as there can
+// be, 31 MB of a context, more in fewer runs.  What a run has beyond that is derived from the input once more (comet_records.h).
+// 64 x 256 x 56 x 56, where a run's share is 7.6 % of its elements, 8 / 21 / 41 % records: 166 / 226 / 261 us; with room for 25 % of the elements
+// (103 MB) 162 / 205 / 326 (a slower derivation then).  411 M elements, a share of 1 %, 4 / 8 / 21 / 41 %: 1448 / 1566 / 1716 / 1866 us; with 822 MB
+// 1206 / 1310 / 1684 / 2516.  A container with 21 % records is hardly smaller than the tensor (8 bytes per record alone).
 constexpr uint32_t kQuantRecRun = 768;
 constexpr uint32_t kQuantRecLds2 = 256;   // records a wavefront buffers in LDS before it writes them to the staging area in bulk
 constexpr uint32_t kQuantRunsPerSimd = 5; // runs the launch aims at, per SIMD
@@ -161,6 +169,7 @@ struct BookArgs {
     uint32_t hist_copies;        // k_book_sort_tiles adds hist_copies of them up into hist_sum (which hist then points to)
     uint32_t *hist_sum;
     RecordArgs recs;           // outlier records to place beside the code book, by the workgroups behind the first one (n_wg == 0: none)
+    uint32_t rec_wg_runs;      // so many runs each (a wavefront per run, then the next)
     uint32_t reset_ctl;        // 1: this kernel is the first of its call and clears *ctl itself
     const uint8_t *given_len;  // code book reuse: take these lengths instead of building them from hist (which is then unused)
     uint32_t nbins;

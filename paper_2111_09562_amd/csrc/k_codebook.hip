@@ -1012,13 +1012,13 @@ __global__ __launch_bounds__(kBookMergeBlock) void k_book_merge(const uint64_t *
 }
 
 __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
-    static_assert(kBookBlock == kRecordBlock, "workgroups of both kinds in one launch");
     extern __shared__ __align__(16) uint8_t s_book[];        // BookLds, or the weights of a large alphabet's leaves
     BookLds &s = *reinterpret_cast<BookLds *>(s_book);
     if (blockIdx.x != 0u) {                                  // the workgroups behind the first one bring the outlier records into order
-        static_assert(sizeof(s.u) >= kRecordRuns * kDeriveBuf * sizeof(uint2), "a buffer per wavefront");
         const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-        place_records(a.recs, (blockIdx.x - 1u) * kRecordRuns + w, (uint32_t)lane_id(), reinterpret_cast<uint2 *>(&s.u) + w * kDeriveBuf);
+        const uint32_t run_0 = (blockIdx.x - 1u) * a.rec_wg_runs;
+        for (uint32_t r = w; r < a.rec_wg_runs; r += (uint32_t)(kBookBlock / kWave))
+            place_records(a.recs, run_0 + r, (uint32_t)lane_id(), reinterpret_cast<uint2 *>(s_book + w * record_lds(a.recs.ring)));
         return;
     }
     // One workgroup on the critical path of its stream, often next to the streaming kernels of
@@ -1580,10 +1580,10 @@ template __global__ void k_book_merge<4u>(const uint64_t *, uint64_t *, uint32_t
 
 // The outlier records by a kernel of its own, with the sum of the partial histograms: where no code book is built behind the quantise
 // kernel (a stage call) or the partial histograms are more than its one workgroup should add up.  The first workgroup adds up the counts as well.
-__global__ __launch_bounds__(kRecordBlock) void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies) {
-    __shared__ uint2 s_buf[kRecordRuns][kDeriveBuf];
+__global__ __launch_bounds__(kGatherBlock) void k_gather_records(RecordArgs a, uint32_t *hist, const uint32_t *parts, uint32_t copies) {
+    extern __shared__ __align__(16) uint8_t s_book[];        // record_lds(a.ring) bytes per wavefront
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = (uint32_t)lane_id();
-    for (uint32_t b = blockIdx.x * (uint32_t)kRecordBlock + threadIdx.x; hist && b < a.nbins; b += gridDim.x * (uint32_t)kRecordBlock) {
+    for (uint32_t b = blockIdx.x * (uint32_t)kGatherBlock + threadIdx.x; hist && b < a.nbins; b += gridDim.x * (uint32_t)kGatherBlock) {
         uint32_t v = 0, p[kQuantHistCopiesMax];              // (every copy in flight at once)
 #pragma unroll
         for (uint32_t j = 0; j < kQuantHistCopiesMax; ++j) p[j] = (j < copies) ? parts[(size_t)j * a.nbins + b] : 0u;
@@ -1595,7 +1595,7 @@ __global__ __launch_bounds__(kRecordBlock) void k_gather_records(RecordArgs a, u
         const uint64_t total = record_total(a, wave, lane);
         if (lane == 0) *(wave == 0u ? &a.ctl->n_rec : (wave == 1u ? &a.ctl->nnz : &a.ctl->n_vrec)) = total;
     }
-    place_records(a, blockIdx.x * kRecordRuns + wave, lane, s_buf[wave]);
+    place_records(a, blockIdx.x * (uint32_t)(kGatherBlock / kWave) + wave, lane, reinterpret_cast<uint2 *>(s_book + wave * record_lds(a.ring)));
 }
 
 }  // namespace comet

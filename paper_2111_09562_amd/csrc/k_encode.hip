@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     constexpr int kWaves = kPlaceBlock / kWave;
     static_assert((uint32_t)kWaves == kQuantWaves, "a workgroup's runs are those of a workgroup of the quantise kernel");
     __shared__ uint64_t s_part64[kWaves], s_all64[kWaves];
-    __shared__ uint2 s_buf[kWaves][kDeriveBuf];
+    extern __shared__ uint64_t s_dyn_enc[];                  // record_lds(a.recs.ring) bytes per wavefront
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / kWave));
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     uint32_t *chunk_off = reinterpret_cast<uint32_t *>(a.container + h->off_chunk);
     const uint32_t c_lo = (uint32_t)(e_lo / a.chunk_syms), c_hi = (uint32_t)((e_hi + a.chunk_syms - 1u) / a.chunk_syms);
     for (uint32_t c = c_lo + lane; c < c_hi; c += kWave) chunk_off[c] = (uint32_t)(base + chunk_off[c]);
-    place_records(a.recs, run, lane, s_buf[wave]);
+    place_records(a.recs, run, lane, reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(s_dyn_enc) + wave * record_lds(a.recs.ring)));
 }
 
 #define COMET_INST_ENC(S)                                                  \

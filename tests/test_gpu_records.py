@@ -125,3 +125,18 @@ def test_given_codebook_after_many_records(oracle, sync, spare):
     assert np.array_equal(room[:want.size].cpu().numpy(), want)
     assert bool((room[want.size:] == 77).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1000, 1 << 20, 64 * 256 * 56 * 56, 128 * 64 * 224 * 224])
+def test_workspace_of_a_context(n):
+    """What include/comet.h says a context allocates: 2 bytes per element and about 42 MB, or 2.14 bytes per element and 8 MB; each of its
+    allocations is rounded up to 2 MB."""
+    from paper_2111_09562_amd import comet
+    comet.lib()
+    torch.zeros(1, device="cuda")
+    comet.Context(1000, 65536).close()                       # (what the runtime allocates once)
+    free = torch.cuda.mem_get_info()[0]
+    ctx = comet.Context(n, 65536)
+    used = free - torch.cuda.mem_get_info()[0]
+    ctx.close()
+    assert 2 * n <= used <= max(2 * n + 44e6, 2.14 * n + 10e6)
