@@ -401,7 +401,10 @@ __device__ inline uint32_t sweep_rows(const QuantArgs &a, uint32_t row_lo, uint3
     float xa[U][NSEG][VEC], xb[U][NSEG][VEC];
     const std::true_type full{};
     const std::false_type general{};
-    const uint32_t n_full = n_steps / (2u * U) * (2u * U);      // steps covered by full double batches
+    // (a last step that has not all of its rows is none of them: its lanes are not all valid, and the encoder would be told of
+    // symbols that do not exist)
+    const uint32_t n_whole = n_steps * K == row_hi - row_lo ? n_steps : n_steps - 1u;
+    const uint32_t n_full = n_whole / (2u * U) * (2u * U);      // steps covered by full double batches
     uint32_t t0 = 0;
     if (n_full) {
         const uint32_t t_max = n_full - 1u;

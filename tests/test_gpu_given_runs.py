@@ -87,3 +87,28 @@ def test_records_of_short_runs(oracle, shape):
     assert ctx.comet_compress_with_codebook(torch.from_numpy(x).cuda(), eb, nbins, torch.from_numpy(book).cuda(), box) == want.size
     assert np.array_equal(box.cpu().numpy(), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("w", [1, 2, 3, 6, 10, 14, 20, 28, 30, 32, 56, 64])
+@pytest.mark.parametrize("chunk", [64, 256])
+def test_rows_that_do_not_fill_the_last_step(oracle, w, chunk):
+    """Narrow planes: a wavefront takes several rows a step, and the last step of a tensor has any number of them."""
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(w)
+    most = 128 * 21
+    ctx = comet.Context(2 * most * w, NBINS)
+    ctx.comet_set_chunk_syms(chunk)
+    full = torch.zeros(comet.comet_compress_bound((1, 1, 2 * most, w), NBINS, chunk), dtype=torch.uint8, device="cuda")
+    book = np.full(NBINS, 6, np.uint8)
+    heights = sorted({int(h) for h in np.concatenate([64 // w * np.arange(1, 21) - 1, 128 // w * np.arange(1, 21) - 1, rng.integers(1, most, 40)]) if h > 0})
+    for h in heights:
+        for planes in (1, 2):
+            x = (rng.integers(-3, 4, (planes, 1, h, w)) * (2.0 * EB)).astype(np.float32)
+            xd = torch.from_numpy(x).cuda()
+            want = oracle.compress_with_lengths(x, EB, NBINS, chunk, book)
+            assert ctx.comet_compress_with_codebook(xd, EB, NBINS, torch.from_numpy(book).cuda(), full) == want.size, (h, planes)
+            assert np.array_equal(full[:want.size].cpu().numpy(), want), (h, planes)
+            want = oracle.compress(x, EB, NBINS, chunk)
+            assert ctx.comet_compress(xd, EB, NBINS, full) == want.size, (h, planes)
+            assert np.array_equal(full[:want.size].cpu().numpy(), want), (h, planes)
+    ctx.close()
