@@ -46,9 +46,53 @@ def test_codes_of_every_length(oracle, nbins):
         big.close()
 
 
-@pytest.mark.parametrize("scale", [0.2, 1.9, 2.4])
-def test_symbols_inside_and_outside_the_range(oracle, scale):
-    """Residuals within 1000 (the middle 2048 entries), within 4000 (the 8192 of the pack kernel) and beyond, with a few escapes."""
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+@pytest.mark.parametrize("zero_chunks", [False, True])
+def test_chunk_sizes(oracle, chunk, zero_chunks):
+    """Just over 512 chunks of every size per segment, a short chunk at the end; stretches of nothing but the centre code, which
+    take no words in a container of version 2.  Code words start at a word, so a tensor that repeats a block of whole
+    chunks has the block's words again and again."""
+    from paper_2111_09562_amd import comet
+    nbins, n = 16384, chunk * 512 * 1536 + 4 * chunk + 37
+    rng = np.random.default_rng(chunk)
+    block = np.clip(nbins // 2 + np.rint(rng.standard_normal(chunk * 1357) * 2500), 1, nbins - 1).astype(np.uint16)
+    block[chunk * 100:chunk * 400] = nbins // 2
+    block[chunk * 500 - 3:chunk * 500 + chunk + 5] = nbins // 2
+    assert block.min() < (nbins - 8192) // 2                  # (symbols on both sides of the cached range, and in it)
+    times, rest = divmod(n, block.size)
+    tail = block[:rest]
+    hist = oracle.histogram(block, nbins) * np.uint32(times) + oracle.histogram(tail, nbins)
+    ln = oracle.code_lengths(hist)
+    words = oracle.canonical_codes(ln)
+    b_off, b_words = oracle.encode(block, nbins, chunk, ln, words, zero_chunks=zero_chunks)
+    t_off, t_words = oracle.encode(tail, nbins, chunk, ln, words, zero_chunks=zero_chunks)
+    ctx = comet.Context(n, nbins)
+    ctx.comet_set_zero_chunks(zero_chunks)
+    lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+    off = torch.empty((n + chunk - 1) // chunk, dtype=torch.int32, device="cuda")
+    total = times * b_words.size + t_words.size
+    payload = torch.zeros(total + 16, dtype=torch.int32, device="cuda")
+    pw = torch.zeros(1, dtype=torch.int64, device="cuda")
+    codes = torch.from_numpy(block.view(np.int16)).cuda().repeat(times + 1)[:n].contiguous()
+    ctx.comet_stage_codebook(torch.from_numpy(hist.astype(np.uint32).view(np.int32)).cuda(), nbins, lens)
+    ctx.comet_stage_encode(codes, n, nbins, chunk, off, payload, pw)
+    ctx.comet_sync()
+    assert np.array_equal(lens.cpu().numpy(), ln)
+    assert int(pw.item()) == total
+    got = payload.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:times * b_words.size].reshape(times, -1), np.broadcast_to(b_words, (times, b_words.size)))
+    assert np.array_equal(got[times * b_words.size:total], t_words)
+    assert not got[total:].any()
+    got = off.cpu().numpy().view(np.uint32)
+    steps = np.arange(times, dtype=np.uint64)[:, None] * b_words.size
+    assert np.array_equal(got[:times * 1357].reshape(times, -1), (steps + b_off).astype(np.uint32))
+    assert np.array_equal(got[times * 1357:], t_off + np.uint32(times * b_words.size))
+    ctx.close()
+
+
+@pytest.mark.parametrize("scale,lo,hi", [(0.2, 0, 1024), (1.9, 1024, 4096), (8.0, 4096, 32768)])
+def test_symbols_inside_and_outside_the_range(oracle, scale, lo, hi):
+    """Residuals within 1024 (the middle 2048 entries), within 4096 (the 8192 of the pack kernel) and beyond, with a few escapes."""
     from paper_2111_09562_amd import comet
     shape, eb, nbins = (3, 256, 257, 256), 1e-3, 65536
     rng = np.random.default_rng(1)
@@ -56,6 +100,8 @@ def test_symbols_inside_and_outside_the_range(oracle, scale):
     x[:, 1::2, :, :] *= np.float32(0.3)
     x.reshape(-1)[rng.choice(x.size, 500, replace=False)] = 1000.0
     want = oracle.compress(x, eb, nbins, 64)
+    used = np.flatnonzero(oracle.parse_container(want)["len"])
+    assert lo < np.abs(used[used > 0] - nbins // 2).max() < hi and used[0] == 0
     ctx = comet.Context(x.size, nbins)
     ctx.comet_set_chunk_syms(64)
     box = torch.zeros(want.size + (-want.size) % 16 + 4096, dtype=torch.uint8, device="cuda")

@@ -9,8 +9,10 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # 10.5 million elements are the fewest whose runs take every place of the staging area, so that a run's share of it (768
-# records of 2048 elements) can overflow; widths around the 256 elements a wavefront takes per step and the four of a lane.
-OVERFLOW = [(1, 1200, 2953, 3), (40, 1000, 266, 1), (5, 64, 181, 182), (2, 173, 60, 511), (1, 33, 624, 512), (7, 331, 18, 255)]
+# records of 2048 elements) can overflow; widths around the 256 elements a wavefront takes per step and the four of a lane, on both
+# sides of what the ring of differences takes (4 to 512 columns, 512 entries of it up to 256), whole fours and others, planes of one row.
+OVERFLOW = [(1, 1200, 2953, 3), (40, 1000, 266, 1), (5, 64, 181, 182), (2, 173, 60, 511), (1, 33, 624, 512), (7, 331, 18, 255),
+            (6, 421, 2083, 2), (11, 500, 477, 4), (3, 701, 1000, 5), (2, 129, 160, 256), (1, 80, 513, 257), (4, 1100, 43, 56), (1700, 110, 1, 57), (90, 230, 1, 508)]
 
 
 @pytest.mark.parametrize("shape", OVERFLOW)
@@ -65,7 +67,8 @@ def test_alphabets_in_turn_on_one_context(oracle):
     from paper_2111_09562_amd import comet
     shape, wide = (3, 8, 41, 58), (1, 2, 37, 700)
     x, y = synth.relu_blur(shape, 5, blur=3, shift=-0.2), synth.relu_blur(wide, 6, blur=3, shift=-0.2)
-    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    z = synth.relu_blur((1, 4, 41, 58), 7, blur=3, shift=-0.2)      # (compressed with the code book of x)
+    xd, yd, zd = (torch.from_numpy(t).cuda() for t in (x, y, z))
     n = x.size
     ctx = comet.Context(max(n, y.size), 65536)
     ctx.comet_set_chunk_syms(64)
@@ -91,7 +94,10 @@ def test_alphabets_in_turn_on_one_context(oracle):
         full(1024)
         if nbins <= 8192:
             book = box[comet.HEADER_BYTES:comet.HEADER_BYTES + 1024].clone()
-            ctx.comet_compress_with_codebook(xd, 1e-3, 1024, book, box)
+            want = oracle.compress_with_lengths(z, 1e-3, 1024, 64, book.cpu().numpy())
+            given = torch.zeros(want.size + (-want.size) % 16, dtype=torch.uint8, device="cuda")     # (no larger than the container)
+            assert ctx.comet_compress_with_codebook(zd, 1e-3, 1024, book, given) == want.size
+            assert np.array_equal(given[:want.size].cpu().numpy(), want), nbins
         with pytest.raises(comet.CometError):
             ctx.comet_compress(xd, 1e-3, 1024, box[:16384])
         full(1024)
@@ -129,8 +135,8 @@ def test_given_codebook_after_many_records(oracle, sync, spare):
 
 @pytest.mark.parametrize("n", [1000, 1 << 20, 64 * 256 * 56 * 56, 128 * 64 * 224 * 224])
 def test_workspace_of_a_context(n):
-    """What include/comet.h says a context allocates: 2 bytes per element and about 42 MB, or 2.14 bytes per element and 8 MB; each of its
-    allocations is rounded up to 2 MB."""
+    """What include/comet.h says a context allocates: 2 bytes per element and about 42 MB, or 2.14 bytes per element and 8 MB; what the
+    device reports goes in steps of 2 MB, a step or two more or less."""
     from paper_2111_09562_amd import comet
     comet.lib()
     torch.zeros(1, device="cuda")
@@ -139,4 +145,4 @@ def test_workspace_of_a_context(n):
     ctx = comet.Context(n, 65536)
     used = free - torch.cuda.mem_get_info()[0]
     ctx.close()
-    assert 2 * n <= used <= max(2 * n + 44e6, 2.14 * n + 10e6)
+    assert 2 * n <= used <= max(2 * n + 48e6, 2.14 * n + 14e6)
