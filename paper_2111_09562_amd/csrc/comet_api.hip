@@ -132,10 +132,10 @@ int status_to_error(uint32_t st) {
     return COMET_OK;
 }
 
-// Clears the zero region of a call (control block, descriptors, histograms): a plain kernel rather than a memset
-// node for callers that capture the call in a graph.  n16: 16-byte words.  A compression does without: its first kernel
-// clears the control block, and its last one leaves the partial histograms zero for the next call (a launch of its
-// own in front of the first one cost every call 3 us).
+// Clears memory: a plain kernel rather than a memset node for callers that capture the call in a graph.  n16: 16-byte words.
+// Only for partial histograms that a call may have left dirty: a compression's first kernel clears the control block, and its
+// last one leaves the partial histograms zero for the next call (a launch of its own in front of the first one cost
+// every call 3 us).
 __global__ __launch_bounds__(256) void k_clear(uint4 *p, uint32_t n16) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i < n16) p[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -258,8 +258,8 @@ int launch_quantize(comet_ctx *ctx, const void *x, comet_shape s, uint64_t n, fl
             h.divRun = make_fastdiv(g.run_elems);
             h.parts = hist_parts; h.copies = a.hist_copies;
             // one workgroup per compute unit, with at least 8192 codes (clearing and adding up its bins costs as much as those);
-            // runs have 2048 codes or more and are at most 4 * kQuantRunsPerSimd per compute unit, so a slice sees fewer than kCodeHistRuns
-            static_assert(8192u / 2048u + 3u <= kCodeHistRuns && 4u * kQuantRunsPerSimd + 3u <= kCodeHistRuns, "runs of a slice");
+            // runs have kQuantRunMin codes or more and are at most 4 * kQuantRunsPerSimd per compute unit, so a slice sees fewer than kCodeHistRuns
+            static_assert(8192u / kQuantRunMin + 3u <= kCodeHistRuns && 4u * kQuantRunsPerSimd + 3u <= kCodeHistRuns, "runs of a slice");
             uint64_t wg = (n + 8191u) / 8192u;
             if (wg > (uint64_t)ctx->num_cu) wg = (uint64_t)ctx->num_cu;
             const size_t lds_h = ((size_t)h.win_n + 4u * kCodeHistHot + kCodeHistBlock) * 4u;

@@ -187,7 +187,9 @@ struct BookArgs {
     uint64_t capacity;
 };
 // Dynamic LDS of k_codebook: BookLds; alphabets of more than kBookBySymbolMax bins: what a compute unit has but for a kilobyte, for the weights
-// of up to kBookLdsLeaves leaves and one word.
+// of up to kBookLdsLeaves leaves and one word.  The workgroups that place records ask for as much (one launch), so each waits for
+// a compute unit to itself; beside other streams that costs less than the tree in LDS saves: four layers at batch 16 on four
+// streams, 65536 bins, 1e-3 567 us -> 486, 1e-4 854 -> 600 (64 KB for all, tree in global memory, records in a kernel of their own).
 constexpr uint32_t kBookLdsBytes = 70016u, kBookLdsBytesLarge = kLdsPerCu - 1024u, kBookLdsLeaves = kBookLdsBytesLarge / 4u - 4u;
 __global__ void k_codebook(BookArgs a);
 constexpr int kBookMergeBlock = 256;
@@ -211,9 +213,17 @@ constexpr uint32_t kPackBits = 27u;        // longest code word of an entry of 3
 // reaches beyond them the look-ups in global memory (Laplace at 1e-3 2076 -> 1683).
 constexpr int kEncBlockWide = 512;
 // Entries of 32 bits the pack kernel caches in LDS for alphabets beyond kBookBySymbolMax bins, with eight wavefronts per workgroup (the
-// room per wavefront of four wavefronts' 2048 entries of 64 bits): a look-up in global memory costs a cycle per lane.  128 x 64 x 224 x 224
-// Laplace at 1e-3, 65536 bins the whole compression 1660 us -> 1431, 64 x 256 x 56 x 56 at 1e-4 406 -> 391; for segments of fewer than
-// kEncPackMinChunks chunks filling the table costs more than it saves (1 x 64 x 56 x 56 126 -> 136), and where nearly all symbols lie among 2048 entries it
+// room per wavefront of four wavefronts' 2048 entries of 64 bits): a look-up in global memory costs a cycle per lane.  Filling the
+// table costs a workgroup some 10 us, hence for segments of kEncPackMinChunks chunks and more only.  Whole compressions, us, without / with:
+//   elements        65536 bins, 1e-4   Laplace 1e-3   16384 bins, 3e-4   1e-3
+//     3 M                194 / 204       169 / 179        139 / 149      126 / 136
+//    13 M                240 / 243       206 / 215        173 / 180      159 / 165
+//    26 M                293 / 293       249 / 256        216 / 222      199 / 204
+//    51 M (the line)     400 / 387       342 / 344        303 / 304      282 / 285
+//   103 M                621 / 573       482 / 468        436 / 420      406 / 394
+//   206 M               1140 / 974       810 / 752        751 / 696      709 / 672
+// The cost is one of symbols, the rule counts chunks: with chunks of 128 or 256 symbols the figures are these within 1 % (256 symbols, 103 M
+// elements, 1e-4: 608 / 560), the line lies at 101 and 201 M elements.  Where nearly all symbols lie among 2048 entries the table
 // is only longer (64 x 256 x 56 x 56, 4096 bins with 4096 such entries 154 -> 164).
 constexpr uint32_t kEncPackWindow = 8192, kEncPackMinChunks = 512;
 static_assert((kEncTableMax + 1u) * 8u <= kEncPackWindow * 4u, "either kind of entries");

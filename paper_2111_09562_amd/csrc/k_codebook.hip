@@ -711,7 +711,8 @@ __device__ inline uint32_t count_le_wave(const uint32_t *w, uint32_t lo, uint32_
 // All rounds of a tree with the weights of m <= kBookLdsLeaves presorted leaves in LDS, by the whole workgroup: w[i] is the weight of
 // leaf i until it is merged, and w[k] that of node k from then on.  (Two items make a node, so node k is made after leaf k has been
 // merged: the nodes never need a place that a waiting leaf has.)  A round takes the items of weight <= t, or the first kRoundItems of
-// them in merged order: thread by thread the new nodes find their two items by a search along the diagonal of both queues, and
+// them in merged order: thread by thread the new nodes find their two items by a search along the diagonal of both queues (the
+// merge-path method of Odeh, Green, Mwassi, Shmueli and Birk, 2012), and
 // their weights are stored once everybody has read.  Weights of all leaves together: below 2^31.
 // Bound by the latency of the searches in LDS, about 1.5 us a round; 26 000 symbols take 26 rounds.  With the queues in global
 // memory (huffman_rounds_window) a round took 5 to 15 us: the queues' next items and the new nodes went through L2.
