@@ -41,12 +41,14 @@ __device__ inline uint64_t record_total(const RecordArgs &a, uint32_t kind, uint
 // kDeriveBuf of them per wavefront, the ring behind it), in bulk: stored one by one where they belong, a quarter of 51 M elements took
 // 160 us whatever the rest of the loop did.  64 x 256 x 56 x 56 with 21 % records 268 us -> 226 (row above loaded again, two
 // steps in flight, truth values), 411 M elements 2201 -> 1716.
-// IN: element type (0 fp32, 1 IEEE half, 2 bfloat16, -1 any).
-template <int IN, bool RING>
+// IN: element type (0 fp32, 1 IEEE half, 2 bfloat16, -1 any).  U: steps per batch of loads: four, or two in k_place_payload, which
+// then needs 60 registers instead of 78: eight wavefronts per SIMD instead of six, also where nothing is derived (five layers
+// on five streams with their code books given 1460 -> 1486 GB/s; 21 % records 254 us -> 257).
+template <int IN, bool RING, uint32_t U>
 __device__ __forceinline__ void derive_records(const RecordArgs &a, uint32_t run, uint32_t lane, uint32_t held, uint32_t last_key, uint32_t count,
                                       uint2 *dst, uint64_t room, uint2 *s_buf) {
     constexpr uint32_t V = 4, kStep = V * kWave;             // elements per lane and step
-    constexpr uint32_t U = RING ? 4 : 2, kBatch = U * kStep; // steps per batch of loads
+    constexpr uint32_t kBatch = U * kStep;
     typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
     typedef unsigned short u16x4 __attribute__((ext_vector_type(4), aligned(2)));
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
@@ -282,6 +284,7 @@ __device__ __forceinline__ void derive_records(const RecordArgs &a, uint32_t run
 }
 
 // The records of one run, by one wavefront (s_buf: record_lds(a.ring) bytes of LDS).
+template <uint32_t U>
 __device__ __forceinline__ void place_records(const RecordArgs &a, uint32_t run, uint32_t lane, uint2 *s_buf) {
     const uint32_t n_runs = a.n_wg * kQuantWaves;
     if (run >= n_runs) return;
@@ -298,10 +301,10 @@ __device__ __forceinline__ void place_records(const RecordArgs &a, uint32_t run,
         if (i < room) dst[i] = src[i];
     if (mine > held && room > held) {                        // (uniform)
         const uint32_t last_key = (uint32_t)__builtin_amdgcn_readfirstlane((int)src[held - 1u].x);
-        if (a.ring == 0u) derive_records<-1, false>(a, run, lane, held, last_key, mine, dst, room, s_buf);
-        else if (a.in_type == 0u) derive_records<0, true>(a, run, lane, held, last_key, mine, dst, room, s_buf);
-        else if (a.in_type == 1u) derive_records<1, true>(a, run, lane, held, last_key, mine, dst, room, s_buf);
-        else derive_records<2, true>(a, run, lane, held, last_key, mine, dst, room, s_buf);
+        if (a.ring == 0u) derive_records<-1, false, (U + 1u) / 2u>(a, run, lane, held, last_key, mine, dst, room, s_buf);
+        else if (a.in_type == 0u) derive_records<0, true, U>(a, run, lane, held, last_key, mine, dst, room, s_buf);
+        else if (a.in_type == 1u) derive_records<1, true, U>(a, run, lane, held, last_key, mine, dst, room, s_buf);
+        else derive_records<2, true, U>(a, run, lane, held, last_key, mine, dst, room, s_buf);
     }
     if (mine > room && lane == 0) atomicOr(&a.ctl->status, (uint32_t)ST_CAPACITY);
 }

@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(kBookBlock) void k_codebook(BookArgs a) {
         const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
         const uint32_t run_0 = (blockIdx.x - 1u) * a.rec_wg_runs;
         for (uint32_t r = w; r < a.rec_wg_runs; r += (uint32_t)(kBookBlock / kWave))
-            place_records(a.recs, run_0 + r, (uint32_t)lane_id(), reinterpret_cast<uint2 *>(s_book + w * record_lds(a.recs.ring)));
+            place_records<4>(a.recs, run_0 + r, (uint32_t)lane_id(), reinterpret_cast<uint2 *>(s_book + w * record_lds(a.recs.ring)));
         return;
     }
     // One workgroup on the critical path of its stream, often next to the streaming kernels of
@@ -1596,7 +1596,7 @@ __global__ __launch_bounds__(kGatherBlock) void k_gather_records(RecordArgs a, u
         const uint64_t total = record_total(a, wave, lane);
         if (lane == 0) *(wave == 0u ? &a.ctl->n_rec : (wave == 1u ? &a.ctl->nnz : &a.ctl->n_vrec)) = total;
     }
-    place_records(a, blockIdx.x * (uint32_t)(kGatherBlock / kWave) + wave, lane, reinterpret_cast<uint2 *>(s_book + wave * record_lds(a.ring)));
+    place_records<4>(a, blockIdx.x * (uint32_t)(kGatherBlock / kWave) + wave, lane, reinterpret_cast<uint2 *>(s_book + wave * record_lds(a.ring)));
 }
 
 }  // namespace comet

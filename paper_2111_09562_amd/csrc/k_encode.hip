@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place_payload(PlaceArgs a) {
     uint32_t *chunk_off = reinterpret_cast<uint32_t *>(a.container + h->off_chunk);
     const uint32_t c_lo = (uint32_t)(e_lo / a.chunk_syms), c_hi = (uint32_t)((e_hi + a.chunk_syms - 1u) / a.chunk_syms);
     for (uint32_t c = c_lo + lane; c < c_hi; c += kWave) chunk_off[c] = (uint32_t)(base + chunk_off[c]);
-    place_records(a.recs, run, lane, reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(s_dyn_enc) + wave * record_lds(a.recs.ring)));
+    place_records<2>(a.recs, run, lane, reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(s_dyn_enc) + wave * record_lds(a.recs.ring)));
 }
 
 #define COMET_INST_ENC(S)                                                  \
