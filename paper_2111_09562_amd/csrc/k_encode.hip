@@ -329,7 +329,7 @@ __global__ __launch_bounds__(NT) void k_encode_pack(EncodeArgs a) {
         flush(off0, wpos);
     }
     };
-    const bool whole = (uint64_t)c_hi * S <= a.n;              // every chunk of my segment has all its symbols
+    const bool whole = (uint64_t)c_lo * S + (uint64_t)steps * 256u <= a.n;     // every step of my segment has all its symbols
     auto sweep_with = [&](auto tbl) {
         if (whole) sweep(tbl, std::false_type{}); else sweep(tbl, std::true_type{});
     };

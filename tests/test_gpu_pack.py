@@ -108,3 +108,37 @@ def test_symbols_inside_and_outside_the_range(oracle, scale, lo, hi):
     assert ctx.comet_compress(torch.from_numpy(x).cuda(), eb, nbins, box) == want.size
     assert np.array_equal(box[:want.size].cpu().numpy(), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("nbins", [64, 1024, 16384])
+@pytest.mark.parametrize("chunk", [64, 128])
+def test_last_step_with_fewer_chunks(oracle, nbins, chunk):
+    """A step is 256 symbols: the last one of a tensor may have chunks of them missing, which take no words.  The payload's own size is
+    enough for it, and what lies behind a container stays as it was."""
+    from paper_2111_09562_amd import comet
+    rng = np.random.default_rng(nbins + chunk)
+    ctx = comet.Context(1 << 16, nbins)
+    ctx.comet_set_chunk_syms(chunk)
+    for n in (chunk, 2 * chunk, 3 * chunk, 5 * chunk, 256 + chunk, 40 * 256 - chunk, 40 * 256 + chunk, 16 * 1024 - 2 * chunk, 3 * chunk - 5):
+        x = rng.standard_normal((1, 1, 1, n) if n <= 512 else (1, 1, n // chunk, chunk)).astype(np.float32) if n % chunk == 0 else \
+            rng.standard_normal((1, 1, 1, n)).astype(np.float32)
+        x.reshape(-1)[:n:7] = 1e5                                 # (escapes: symbol 0 has a code word)
+        want = oracle.compress(x, 1e-2, nbins, chunk)
+        room = torch.full((want.size // 16 * 16 + 4096,), 77, dtype=torch.uint8, device="cuda")
+        assert ctx.comet_compress(torch.from_numpy(x).cuda(), 1e-2, nbins, room) == want.size, n
+        assert np.array_equal(room[:want.size].cpu().numpy(), want), n
+        assert bool((room[want.size:] == 77).all()), n
+        parts = oracle.parse_container(want)
+        codes = oracle.decode(parts["len"], parts["chunk_off"], parts["payload"], x.size, chunk)
+        hist = oracle.histogram(codes, nbins)
+        lens = torch.empty(nbins, dtype=torch.uint8, device="cuda")
+        off = torch.empty(parts["n_chunks"], dtype=torch.int32, device="cuda")
+        payload = torch.full((parts["payload_words"] + 64,), 7, dtype=torch.int32, device="cuda")
+        pw = torch.zeros(1, dtype=torch.int64, device="cuda")
+        ctx.comet_stage_codebook(torch.from_numpy(hist.astype(np.uint32).view(np.int32)).cuda(), nbins, lens)
+        ctx.comet_stage_encode(torch.from_numpy(codes.view(np.int16)).cuda(), x.size, nbins, chunk, off, payload[:parts["payload_words"]], pw)
+        ctx.comet_sync()                                          # (no error: the payload fits)
+        assert int(pw.item()) == parts["payload_words"]
+        assert np.array_equal(payload.cpu().numpy().view(np.uint32)[:parts["payload_words"]], parts["payload"]), n
+        assert bool((payload[parts["payload_words"]:] == 7).all()), n
+    ctx.close()
